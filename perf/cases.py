@@ -184,3 +184,29 @@ def tolerance(case):
     if case["op"] == "dequant":
         return "exact"
     return {"rel": 1.2e-3, "max": 6e-3}
+
+
+def exact(case, seed):
+    """The outputs in float64 from the definition, s * (q - z) with no rounding in between; a block of columns at a
+    time, so that the widest layer fits beside the inputs."""
+    state = prepare(dict(case, op="act_order" if case["op"] == "repacked" else case["op"], graph=False), seed)
+    return [_exact(c, case["group"]) for c in state["calls"]]
+
+
+def _exact(call, group):
+    rows = call["qweight"].shape[0] * 8
+    n = call["qweight"].shape[1]
+    nibble = torch.arange(0, 32, 4, dtype=torch.int32, device="cuda")
+    group_of = call.get("g_idx")
+    if group_of is None:
+        group_of = torch.arange(rows, device="cuda") // group
+    group_of = group_of.long()
+    x = call["x"].double() if "x" in call else None
+    parts = []
+    for lo in range(0, n, 8192):
+        hi = min(n, lo + 8192)
+        q = (call["qweight"][:, None, lo:hi] >> nibble[None, :, None] & 15).reshape(rows, hi - lo)
+        z = (call["qzeros"][:, lo // 8:hi // 8, None] >> nibble & 15).reshape(-1, hi - lo)
+        w = (q - z[group_of]).double().mul_(call["scales"][:, lo:hi].double()[group_of])
+        parts.append(w if x is None else x @ w)
+    return torch.cat(parts, dim=1)
