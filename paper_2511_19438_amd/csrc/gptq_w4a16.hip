@@ -167,6 +167,7 @@ bool mid_batch_by_default(const Problem &p)
 // What a call resolves to: the kernel and its decomposition, after the automatic choices.
 struct Resolved {
     int kernel;  // 1 vector, 2 big-tile MFMA, 3 small-batch MFMA, 4 mid-batch streaming MFMA
+    bool act;    // the act-order lookup variant of the small-batch kernel (plan in `skinny`) runs in its place
     DecodePlan decode;
     SkinnyPlan skinny;
     MidPlan mid;
@@ -177,6 +178,16 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
 {
     Resolved r = {};
     int kernel = plan ? plan->kernel : 0;
+    if (kernel == 0 && act_supported(p)) {
+        // act-order as stored: the lookup variant for every batch of two rows and more.  Reported under the ids of
+        // the kernels that serve an explicit request there (the vector kernel up to 16 rows, the big-tile kernel's
+        // general path above).
+        r.kernel = (p.M <= kDecodeMaxM) ? 1 : 2;
+        r.act = true;
+        r.skinny.split_k = plan ? plan->split_k : 0;
+        act_make_plan(p, r.skinny);
+        return r;
+    }
     if (kernel == 0) {
         if (p.M <= kVectorMaxM)
             kernel = 1;
@@ -224,6 +235,8 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
 
 size_t scratch_bytes(const Problem &p, const Resolved &r)
 {
+    if (r.act)
+        return act_workspace_bytes(p, r.skinny);
     if (r.kernel == 1)
         return decode_workspace_bytes(p, r.decode);
     if (r.kernel == 3)
@@ -236,7 +249,9 @@ size_t scratch_bytes(const Problem &p, const Resolved &r)
 int launch_resolved(const Problem &p, const Resolved &r, void *ws, hipStream_t stream)
 {
     hipError_t err;
-    if (r.kernel == 1)
+    if (r.act)
+        err = launch_act(p, r.skinny, ws, stream);
+    else if (r.kernel == 1)
         err = launch_decode(p, r.decode, ws, stream);
     else if (r.kernel == 3)
         err = launch_skinny(p, r.skinny, ws, stream);
@@ -247,17 +262,38 @@ int launch_resolved(const Problem &p, const Resolved &r, void *ws, hipStream_t s
     return err == hipSuccess ? GPTQ_OK : GPTQ_HIP_ERROR;
 }
 
+// An act-order call whose slices' scratch cannot be had (a workspace of the caller's that is too small, growth under
+// capture, the static block) must still run wherever it ran before it had slices.  From 17 rows on it needed no
+// scratch at all: it gives up its slices.  Up to 16 rows, and where the lookup variant cannot do without slices, it
+// takes the kernel of an explicit request, with that kernel's own needs.  False: nothing else to try.
+bool fall_back(const Problem &p, Resolved &r)
+{
+    if (!r.act)
+        return false;
+    if (r.kernel == 2 && r.skinny.split_k > 1) {
+        r.skinny.split_k = 1;
+        act_make_plan(p, r.skinny);
+        if (r.skinny.split_k == 1)
+            return true;
+    }
+    gptq_w4a16_plan_t plan = {};
+    plan.kernel = r.kernel;
+    r = resolve(p, &plan);
+    return true;
+}
+
 int run_gemm(const Problem &p, hipStream_t stream, const gptq_w4a16_plan_t *plan)
 {
-    const Resolved r = resolve(p, plan);
+    Resolved r = resolve(p, plan);
     void *ws = nullptr;
-    const size_t bytes = scratch_bytes(p, r);
-    if (bytes > 0) {
-        const int rc = acquire_workspace(bytes, stream, &ws);
-        if (rc != GPTQ_OK)
+    for (;;) {
+        const size_t bytes = scratch_bytes(p, r);
+        const int rc = bytes > 0 ? acquire_workspace(bytes, stream, &ws) : GPTQ_OK;
+        if (rc == GPTQ_OK)
+            return launch_resolved(p, r, ws, stream);
+        if (rc != GPTQ_WORKSPACE_TOO_SMALL || !fall_back(p, r))
             return rc;
     }
-    return launch_resolved(p, r, ws, stream);
 }
 
 size_t align256(size_t v)
@@ -334,9 +370,10 @@ int gptq_w4a16_gemm_static(const void *x, const void *qweight, const void *qzero
     const int rc = make_problem(x, qweight, qzeros, scales, g_idx, out, M, K, N, group_size, nullptr, p);
     if (rc != GPTQ_OK)
         return rc;
-    const Resolved r = resolve(p, nullptr);
-    if (scratch_bytes(p, r) > kStaticScratchBytes)
-        return GPTQ_STATIC_SCRATCH_EXCEEDED;
+    Resolved r = resolve(p, nullptr);
+    while (scratch_bytes(p, r) > kStaticScratchBytes)
+        if (!fall_back(p, r))
+            return GPTQ_STATIC_SCRATCH_EXCEEDED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     void *ws = nullptr;
     const int wrc = static_scratch_ptr(st, &ws);
@@ -373,7 +410,10 @@ int gptq_w4a16_plan_query(int M, int K, int N, int group_size, int act_order, co
     const Resolved r = resolve(p, request);
     gptq_w4a16_plan_t out = {};
     out.kernel = r.kernel;
-    if (r.kernel == 1) {
+    if (r.act) {
+        out.split_k = r.skinny.split_k;
+        out.tile = r.skinny.cols_per_wg;
+    } else if (r.kernel == 1) {
         out.split_k = r.decode.split_k;
         out.tile = r.decode.cols_per_wg;
         out.flags = r.decode.flags;
@@ -566,7 +606,7 @@ size_t gptq_w4a16_workspace_bytes(int M, int K, int N, int group_size)
     for (int act = 0; act < 2; ++act) {
         p.g_idx = act ? &dummy : nullptr;
         const Resolved r = resolve(p, nullptr);
-        if (r.kernel == 2 || r.kernel == 4) {
+        if (r.act || r.kernel == 2 || r.kernel == 4) {
             const size_t pf = scratch_bytes(p, r);
             if (pf > bytes)
                 bytes = pf;

@@ -73,6 +73,12 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan);
 size_t skinny_workspace_bytes(const Problem &p, const SkinnyPlan &plan);
 hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream);
 
+// ---- act-order checkpoints as stored, M >= 2: the small-batch kernel with per-k lookups (64 rows per workgroup) ----
+bool act_supported(const Problem &p);
+void act_make_plan(const Problem &p, SkinnyPlan &plan);  // honours plan.split_k
+size_t act_workspace_bytes(const Problem &p, const SkinnyPlan &plan);  // 0 without a split
+hipError_t launch_act(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream);
+
 // ---- mid batch: streaming MFMA kernel, every wavefront on its own share of the K slice, M <= 128 ----
 constexpr int kMidMaxM = 128;
 struct MidPlan {

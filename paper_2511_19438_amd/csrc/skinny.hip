@@ -37,21 +37,123 @@ int waves_of(int tiles_n, int split_k, int wn, int tm)
     return (wn == 1 && tm <= 2 && (long long)tiles_n * split_k <= 256) ? 8 : 4;
 }
 
-template <int TM, int WN, int WAVES, int GPU = 1>
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false>
 hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
 {
-    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU>;
+    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU, ACT>;
     if (lds > 48 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess)
             return err;
     }
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.tiles_n * a.split_k)), dim3(64 * WAVES), lds, stream, a);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.tiles_n * a.row_tiles * a.split_k)), dim3(64 * WAVES), lds, stream, a);
     return hipGetLastError();
 }
 
+// LDS that a workgroup of the act-order variant may use (the rest holds its static words).
+constexpr size_t kActLdsBytes = 160 * 1024 - 512;
+
+int act_row_blocks(int M)
+{
+    return M <= 16 ? 1 : M <= 32 ? 2 : 4;
+}
+
+size_t act_table_bytes(const Problem &p)
+{
+    return (size_t)(p.K / p.group_size) * skinny::kActTableRow;
+}
+
+// Units whose table offsets fit the LDS behind the table (0: not even one unit's do).
+int act_max_units(const Problem &p)
+{
+    const size_t table = act_table_bytes(p);
+    return table >= kActLdsBytes ? 0 : (int)((kActLdsBytes - table) / (skinny::kUnitK * sizeof(uint32_t)));
+}
+
 }  // namespace
+
+// K must be whole 128-k units; groups may be of any size, the table of all of them has to fit the LDS (up to 636
+// groups: K = 28672 with groups of 64 does, with groups of 32 does not and stays with the general path).
+bool act_supported(const Problem &p)
+{
+    if (p.g_idx == nullptr || p.M < 2 || p.N < 8 || p.K % skinny::kUnitK != 0)
+        return false;
+    const long long tiles = (long long)ceil_div(p.N, skinny::kCols) * ceil_div(p.M, skinny::kActRows);
+    return tiles <= kMaxColumnTiles && act_max_units(p) >= 4;
+}
+
+void act_make_plan(const Problem &p, SkinnyPlan &plan)
+{
+    const int total_units = p.K / skinny::kUnitK;
+    const int tm = act_row_blocks(p.M);
+    const int tiles = ceil_div(p.N, skinny::kCols) * ceil_div(p.M, skinny::kActRows);
+    plan.cols_per_wg = skinny::kCols;
+    int split = plan.split_k;
+    int quantum = 1;
+    if (split <= 0) {
+        // One workgroup per compute unit, as in the plain format: measured best of 1, 2, 3, 4, 6 and 8 slices on
+        // 4096x11008 (M = 8: 12.7 us unsplit, 15.4 in two), 11008x4096 (25.9 unsplit, 13.7 in four, 15.2 in eight)
+        // and 4096x4096 (12.1, 8.8 in four) for M = 2 ... 512.  Partial sums within half of the weight bytes
+        // (4096x4096 at M = 64: 18.0 us in four slices, 22.5 in two).
+        split = (256 + tiles / 2) / tiles;
+        const int max_split = p.K / (16 * (p.M < skinny::kActRows ? p.M : skinny::kActRows));
+        if (split > max_split)
+            split = max_split;
+        if (split < 1)
+            split = 1;
+        quantum = waves_of(tiles, split, 1, tm);
+    }
+    if (split > total_units)
+        split = total_units;
+    int ups = ceil_div(ceil_div(total_units, split), quantum) * quantum;
+    if (ups > act_max_units(p))
+        ups = act_max_units(p);
+    if (ups > total_units)
+        ups = total_units;
+    plan.units_per_slice = ups;
+    plan.split_k = ceil_div(total_units, ups);
+}
+
+size_t act_workspace_bytes(const Problem &p, const SkinnyPlan &plan)
+{
+    return plan.split_k > 1 ? kCounterBytes + (size_t)plan.split_k * p.M * p.N * sizeof(float) : 0;
+}
+
+hipError_t launch_act(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream)
+{
+    unsigned char *ws = static_cast<unsigned char *>(workspace);
+    const int tm = act_row_blocks(p.M);
+    skinny::Args a;
+    a.x = p.x;
+    a.qweight = p.qweight;
+    a.qzeros = p.qzeros;
+    a.scales = p.scales;
+    a.g_idx = p.g_idx;
+    a.out = p.out;
+    a.counters = reinterpret_cast<unsigned *>(ws);
+    a.partial = ws ? reinterpret_cast<float *>(ws + kCounterBytes) : nullptr;
+    a.M = p.M;
+    a.K = p.K;
+    a.N = p.N;
+    a.groups = p.K / p.group_size;
+    a.row_tiles = ceil_div(p.M, skinny::kActRows);
+    a.units_per_group = 1;
+    a.unit_group_shift = 0;
+    a.tiles_n = ceil_div(p.N, skinny::kCols);
+    a.split_k = plan.split_k;
+    a.units_per_slice = plan.units_per_slice;
+    a.total_units = p.K / skinny::kUnitK;
+    const int waves = waves_of(a.tiles_n * a.row_tiles, a.split_k, 1, tm);
+    const size_t table = act_table_bytes(p) + (size_t)plan.units_per_slice * skinny::kUnitK * sizeof(uint32_t);
+    const size_t red = (size_t)waves * 16 * tm * skinny::kCols * sizeof(float);
+    const size_t lds = table > red ? table : red;
+    if (tm == 1)
+        return waves == 8 ? launch_tm<1, 1, 8, 1, true>(a, lds, stream) : launch_tm<1, 1, 4, 1, true>(a, lds, stream);
+    if (tm == 2)
+        return waves == 8 ? launch_tm<2, 1, 8, 1, true>(a, lds, stream) : launch_tm<2, 1, 4, 1, true>(a, lds, stream);
+    return launch_tm<4, 1, 4, 1, true>(a, lds, stream);
+}
 
 bool skinny_supported(const Problem &p)
 {
@@ -152,6 +254,9 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
         a.qweight = p.qweight;
         a.qzeros = p.qzeros;
         a.scales = p.scales;
+        a.g_idx = nullptr;
+        a.groups = 0;
+        a.row_tiles = 1;
         a.out = p.out + (size_t)m0 * p.N;
         a.counters = reinterpret_cast<unsigned *>(ws);
         a.partial = reinterpret_cast<float *>(ws + kCounterBytes);

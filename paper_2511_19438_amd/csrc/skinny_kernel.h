@@ -35,10 +35,13 @@ struct Args {
     const uint32_t *qweight;
     const uint32_t *qzeros;
     const half_t *scales;
+    const int32_t *g_idx;  // ACT only: group of every k
     half_t *out;
     float *partial;      // [split_k, M, N] fp32, only if split_k > 1
-    unsigned *counters;  // [tiles_n], zero between launches
+    unsigned *counters;  // [row_tiles * tiles_n], zero between launches
     int M, K, N;
+    int groups;           // ACT only: K / group_size
+    int row_tiles;        // ACT only: blocks of kActRows rows in the grid (1: M fits one)
     int units_per_group;  // group_size / 128
     int unit_group_shift; // log2(units_per_group) if that is a power of two, else -1
     int tiles_n;
@@ -79,6 +82,11 @@ __device__ __forceinline__ float load_device_scope(const float *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Bytes of the act-order table: one (scale, -(1024 + z)) pair of halves per group and column of the tile.
+constexpr int kActTableRow = kCols * 4;
+// Rows of x that one workgroup of the act-order variant multiplies; larger batches are row tiles of one grid.
+constexpr int kActRows = 64;
+
 // Loads of one 128-k unit of one lane: 4 steps x 4 adjacent words, plus the unit's scales and zero word.
 template <int XROWS, int GPU>  // XROWS: 16-row blocks of activations that travel with the weights (0: they are in LDS)
 struct UnitRegs {                // GPU: quantisation groups per unit (1: groups of 128 k or more; 2: 64; 4: 32)
@@ -101,9 +109,23 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
 // GPU: quantisation groups per 128-k unit.  1 serves every group size that is a multiple of 128; 2 and 4 serve
 // groups of 64 and 32 k: a unit then carries two or four (scale, zero) rows, the exact q - z of a 32-k step is
 // formed with its own group's zero point and the MFMA chain is scaled and restarted at every group boundary.
-template <int TM, int WN, int WAVES, int GPU = 1>
-__global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
+//
+// ACT: act-order checkpoints as stored (row k of the weights belongs to group g_idx[k], any map).  The workgroup
+// first lays the scales and zero points of ALL groups for its 64 columns into LDS - (scale, -(1024 + z)) as two
+// halves, 4 bytes per column - and the table offset of every k of its slice behind it.  A lane then reads, for
+// each of the eight k of a packed row, one 16-byte table entry (its four columns; the 16 lanes of one packed row
+// read 256 contiguous bytes: no bank conflicts), so a word costs 4 + 4 permutes to pair the entries on top of the
+// masks, adds and multiplies: 24 vector operations and two 128-bit LDS reads per word WHATEVER M IS, where the
+// vector kernel paid for its lookups and for two operations per weight and row on top, and the big-tile kernel's
+// general path fetched every scale and zero point from global memory.  4096x11008, groups of 128: M = 8 40.8 us
+// (vector kernel) -> 12.7, M = 24 258 (general path) -> 15.1, M = 128 272 -> 48, M = 512 422 -> 138.  Bound by vector
+// issue (~30 instructions per word against 16 in the plain format) and, from 33 rows on, by the latency of the
+// activation loads.  More than 64 rows are row tiles of one grid.
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false>
+__global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
 {
+    static_assert(!ACT || (WN == 1 && GPU == 1), "act-order: 64-column workgroups");
+    Args a = args;
     static_assert(GPU == 1 || GPU == 2 || GPU == 4, "groups of >= 128, 64 or 32 k");
     static_assert(GPU == 1 || TM <= 2, "small groups: up to two row blocks");
     static_assert(WAVES == 4 || (WAVES == 8 && WN <= 2), "eight wavefronts only where they split the slice");
@@ -135,8 +157,20 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cq = lane & 15;  // column quad: columns n0 + 4*cq .. +3
     const int kg = lane >> 4;  // k group inside a 32-k step = packed row inside the step
-    const int tile = blockIdx.x % a.tiles_n;
-    const int slice = blockIdx.x / a.tiles_n;
+    int tile = blockIdx.x % a.tiles_n;
+    int slice = blockIdx.x / a.tiles_n;
+    int counter = tile;  // this output tile's arrival counter
+    size_t slice_values = (size_t)a.M * a.N;  // partial sums of one slice
+    if (ACT && a.row_tiles > 1) {  // grid: column tiles fastest, then row tiles, then slices
+        const int row_tile = slice % a.row_tiles;
+        slice = slice / a.row_tiles;
+        counter = row_tile * a.tiles_n + tile;
+        const int m0 = row_tile * kActRows;
+        a.x += (size_t)m0 * a.K;
+        a.out += (size_t)m0 * a.N;
+        a.partial += (size_t)m0 * a.N;
+        a.M = min(a.M - m0, kActRows);
+    }
     const int N = a.N;
     const int cb = wave / KW;  // this wavefront's 64-column block inside the tile
     const int kw = wave % KW;  // and its share of the slice
@@ -174,6 +208,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
         for (int s = 0; s < 4; ++s)
             r.w[s] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(wrow + (size_t)s * 4 * N) +
                                                       voff_w);
+        if (!ACT) {
         const int grp0 = GPU > 1 ? uc * GPU
                                  : (a.unit_group_shift >= 0 ? (uc >> a.unit_group_shift) : uc / a.units_per_group);
 #pragma unroll
@@ -183,6 +218,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
                 *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(a.scales + (size_t)grp * N) + voff_s);
             r.zb[h] = *reinterpret_cast<const uint32_t *>(
                 reinterpret_cast<const char *>(a.qzeros + (size_t)grp * (N >> 3)) + voff_z);
+        }
         }
         if (DIRECT && !XSTEP) {
             const half_t *xrow = a.x + (size_t)uc * kUnitK;
@@ -235,6 +271,34 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
         __syncthreads();
     }
 
+    // ---- act-order: the table of this tile's columns, then the table offset of every k of the slice ----
+    unsigned char *const act_table = smem;
+    uint32_t *const act_off = reinterpret_cast<uint32_t *>(smem + (size_t)(ACT ? a.groups : 0) * kActTableRow);
+    if (ACT) {
+        const int quads = a.groups * (kCols / 4);
+#pragma unroll 4
+        for (int i = tid; i < quads; i += kThreads) {
+            const int g = i / (kCols / 4);
+            const int n = min(tile * kCols + 4 * (i % (kCols / 4)), N - 4);
+            const uint2 sc = *reinterpret_cast<const uint2 *>(a.scales + (size_t)g * N + n);
+            const uint32_t z4 = a.qzeros[(size_t)g * (N >> 3) + (n >> 3)] >> ((n & 4) * 4);
+            const u32x4_t e = {(sc.x & 0xffffu) | 0xE4000000u | (z4 & 15u) << 16,
+                               (sc.x >> 16) | 0xE4000000u | (z4 >> 4 & 15u) << 16,
+                               (sc.y & 0xffffu) | 0xE4000000u | (z4 >> 8 & 15u) << 16,
+                               (sc.y >> 16) | 0xE4000000u | (z4 >> 12 & 15u) << 16};
+            *reinterpret_cast<u32x4_t *>(act_table + (size_t)i * 16) = e;
+        }
+#pragma unroll 2
+        for (int i = tid; i < Ls / 4; i += kThreads) {
+            const int4 g = *reinterpret_cast<const int4 *>(a.g_idx + kbeg + 4 * i);
+            const uint32_t top = (uint32_t)a.groups - 1u;  // entries outside the map stay inside the table
+            const u32x4_t o = {min((uint32_t)g.x, top) * kActTableRow, min((uint32_t)g.y, top) * kActTableRow,
+                               min((uint32_t)g.z, top) * kActTableRow, min((uint32_t)g.w, top) * kActTableRow};
+            *reinterpret_cast<u32x4_t *>(act_off + 4 * i) = o;
+        }
+        __syncthreads();
+    }
+
     float4_t acc[TM][4];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -256,7 +320,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
     // From four row blocks on (SCALE_B) the scale goes into the B operand instead (one more packed multiply per
     // pair: the fp16 weight itself, rounded once) and the MFMAs add straight into the running sums: scaling the
     // sums of 4 x 16 rows per group would cost as many operations and twice the accumulator registers.
-    constexpr bool SCALE_B = TM >= 4;
+    constexpr bool SCALE_B = ACT || TM >= 4;  // (act-order: every k has a scale of its own)
     auto consume = [&](int u, const Regs &r, auto refill) {
         constexpr bool REFILL = decltype(refill)::value;  // XSTEP: fetch the next unit's A operands step by step
         const int j = u - u0;
@@ -266,7 +330,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
         float4_t d[SCALE_B ? 1 : TM][4];
 #pragma unroll
         for (int st = 0; st < 4; ++st) {
-            if (st % SPG == 0) {  // a group begins: its zero points and scales
+            if (!ACT && st % SPG == 0) {  // a group begins: its zero points and scales
                 const int h = st / SPG;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
@@ -304,6 +368,34 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
             }
             if (XSTEP && REFILL)
                 issue_x(u + 1, st);
+            if (ACT) {
+                // the table entries of this packed row's eight k, four columns each
+                const uint32_t *off = act_off + (j * 4 + st) * 32 + kg * 8;
+                const u32x4_t o0 = *reinterpret_cast<const u32x4_t *>(off);
+                const u32x4_t o1 = *reinterpret_cast<const u32x4_t *>(off + 4);
+                u32x4_t e[8];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    e[k] = *reinterpret_cast<const u32x4_t *>(act_table + o0[k] + cq * 16);
+                    e[k + 4] = *reinterpret_cast<const u32x4_t *>(act_table + o1[k] + cq * 16);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    half8_t b;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {  // the pair (k, k + 4), each with its own scale and zero point
+                        const half2_t s = as_half2(__builtin_amdgcn_perm(e[k + 4][t], e[k][t], 0x05040100u));
+                        const half2_t nz = as_half2(__builtin_amdgcn_perm(e[k + 4][t], e[k][t], 0x07060302u));
+                        const half2_t v = (as_half2((w[t] >> (4 * k) & magic.mask_lo) | magic.bias_lo) + nz) * s;
+                        b[2 * k] = v[0];
+                        b[2 * k + 1] = v[1];
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+                        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[i], b, acc[i][t], 0, 0, 0);
+                }
+                continue;
+            }
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 const uint32_t w8 = w[t] >> 8;
@@ -406,7 +498,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
             if (a.split_k == 1)
                 a.out[(size_t)m * N + n] = (half_t)s;
             else
-                store_device_scope(a.partial + ((size_t)slice * a.M + m) * N + n, s);
+                store_device_scope(a.partial + slice * slice_values + (size_t)m * N + n, s);
         }
     }
 
@@ -415,7 +507,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
         __builtin_amdgcn_s_waitcnt(0);  // every partial store of this workgroup has been acknowledged (exchange.h)
         __syncthreads();
         if (tid == 0)
-            s_last = (slice_arrive(a.counters + tile) == (unsigned)(a.split_k - 1));
+            s_last = (slice_arrive(a.counters + counter) == (unsigned)(a.split_k - 1));
         __syncthreads();
         if (s_last) {
             slice_acquire();
@@ -444,7 +536,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
 #pragma unroll
                         for (int j = 0; j < 8; ++j) {
                             const int sl = min(sl0 + j, a.split_k - 1);
-                            v[o][j] = load_device_scope(a.partial + (size_t)sl * a.M * N + off[o]);
+                            v[o][j] = load_device_scope(a.partial + sl * slice_values + off[o]);
                         }
 #pragma unroll
                     for (int o = 0; o < OUTS; ++o)
@@ -463,7 +555,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args a)
             else
                 combine(std::integral_constant<int, 4>());
             if (tid == 0)
-                __hip_atomic_store(a.counters + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(a.counters + counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
