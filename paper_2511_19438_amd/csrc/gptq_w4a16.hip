@@ -144,6 +144,10 @@ int acquire_workspace(size_t bytes, hipStream_t stream, void **out)
 // behind it on 4096x4096 and on layers whose tiles make a second, partly filled round).
 constexpr int kVectorMaxM = 1;
 constexpr int kSmallBatchAutoMaxM = 32;
+// Formats that the small-batch kernel does not take (K no multiple of 128, groups of 96, ...): the vector kernel up to
+// eight rows, then the pipelined big-tile kernel with K slices (4128x4096, groups of 32: M = 8 16.0 us each, M = 16
+// 31.9 against 15.8; 2752x6888: M = 4 9.4 against 14.1, M = 16 33.1 against 14.0).
+constexpr int kVectorFallbackMaxM = 8;
 
 bool small_batch_by_default(const Problem &p)
 {
@@ -196,7 +200,7 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
         else if (small_batch_by_default(p))
             kernel = 3;
         else
-            kernel = (p.M <= kDecodeMaxM) ? 1 : 2;
+            kernel = (p.M <= kVectorFallbackMaxM || (p.M <= kDecodeMaxM && !prefill_pipelined(p))) ? 1 : 2;
     }
     if (kernel == 3 && !skinny_supported(p))
         kernel = (p.M <= kDecodeMaxM) ? 1 : 2;
@@ -262,12 +266,19 @@ int launch_resolved(const Problem &p, const Resolved &r, void *ws, hipStream_t s
     return err == hipSuccess ? GPTQ_OK : GPTQ_HIP_ERROR;
 }
 
-// An act-order call whose slices' scratch cannot be had (a workspace of the caller's that is too small, growth under
-// capture, the static block) must still run wherever it ran before it had slices.  From 17 rows on it needed no
-// scratch at all: it gives up its slices.  Up to 16 rows, and where the lookup variant cannot do without slices, it
-// takes the kernel of an explicit request, with that kernel's own needs.  False: nothing else to try.
+// Formats that need no scratch in their most general kernel (act-order from 17 rows on, groups or widths that only
+// the big-tile kernel's HALF variant pipelines) must not fail where the scratch of their K slices cannot be had - a
+// workspace of the caller's that is too small, growth under capture, the static block: they give up the slices.
+// Act-order up to 16 rows, and where the lookup variant cannot do without slices, takes the kernel of an explicit
+// request, with that kernel's own needs.  False: nothing else to try.
 bool fall_back(const Problem &p, Resolved &r)
 {
+    if (r.kernel == 2 && !r.act && r.prefill.split_k > 1 && prefill_slices_optional(p)) {
+        r.prefill.split_k = 1;
+        r.prefill.tile = 0;
+        prefill_make_plan(p, r.prefill);
+        return true;
+    }
     if (!r.act)
         return false;
     if (r.kernel == 2 && r.skinny.split_k > 1) {

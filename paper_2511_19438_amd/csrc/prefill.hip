@@ -115,11 +115,23 @@ int mode_of(const Problem &p)
     if (p.g_idx)
         return prefill::kActOrder;
     // the pipelined kernel moves 16-byte chunks of every operand row: rows of packed zero points (N/8 words)
-    // are 16-byte aligned only when N is a multiple of 32
-    return (p.group_size % 64 == 0 && p.N % 32 == 0) ? prefill::kGroupPerStage : prefill::kGroupPerRow;
+    // are 16-byte aligned only when N is a multiple of 32; its HALF variant moves them word by word
+    if (p.group_size % 64 == 0 && p.N % 32 == 0)
+        return prefill::kGroupPerStage;
+    return (p.group_size % 32 == 0 && p.K >= 64) ? prefill::kGroupPerHalf : prefill::kGroupPerRow;
 }
 
 }  // namespace
+
+bool prefill_pipelined(const Problem &p)
+{
+    return mode_of(p) == prefill::kGroupPerStage || mode_of(p) == prefill::kGroupPerHalf;
+}
+
+bool prefill_slices_optional(const Problem &p)
+{
+    return mode_of(p) == prefill::kGroupPerHalf;
+}
 
 bool prefill_supported(const Problem &p)
 {
@@ -133,8 +145,7 @@ bool prefill_tile_exists(int tile)
 
 void prefill_make_plan(const Problem &p, PrefillPlan &plan)
 {
-    const int mode = mode_of(p);
-    if (mode != prefill::kGroupPerStage) {
+    if (!prefill_pipelined(p)) {
         plan.tile = 3;  // the general modes exist for one tile shape only, without a K split
         plan.split_k = 1;
         return;

@@ -32,8 +32,11 @@
 //     neighbours in the (m fastest) tile order and share their weight panel and activations in
 //     that XCD's L2.
 //
+// Its HALF variant carries the scales and zero points of every 32-k half of a stage on their own, which serves group
+// sizes that are odd multiples of 32, a K that ends half-way through a stage, and an N that is no multiple of 32.
+//
 // prefill_general_kernel serves the remaining cases (g_idx, group sizes that are not a multiple of
-// 64, a k tail) with the same operand layout but plain register staging; it is about correctness.
+// 32) with the same operand layout but plain register staging; it is about correctness.
 #pragma once
 
 #include <type_traits>
@@ -47,9 +50,10 @@ namespace prefill {
 constexpr int kThreads = 256;
 
 enum Mode {
-    kGroupPerStage = 0,  // group_size % 64 == 0, no g_idx: pipelined kernel
+    kGroupPerStage = 0,  // group_size % 64 == 0, N % 32 == 0, no g_idx: pipelined kernel
     kGroupPerRow = 1,    // any group_size, no g_idx: looked up per packed row
-    kActOrder = 2        // g_idx: looked up per k
+    kActOrder = 2,       // g_idx: looked up per k
+    kGroupPerHalf = 3    // group_size % 32 == 0, K >= 64, no g_idx: pipelined kernel, HALF variant
 };
 
 struct Args {
@@ -254,11 +258,15 @@ __device__ __forceinline__ bool combine_slices(float (&v)[ACC], const Args &a, i
 // =====================================================================================================
 
 // LDS layout of one stage buffer of the pipelined kernel.
-template <int BM, int BN, int BK>
+template <int BM, int BN, int BK, bool HALF>
 struct StageLayout {
     static constexpr int A_BYTES = BM * BK * 2;        // [BM][BK] halves, 16-byte chunks swizzled
     static constexpr int B_BYTES = (BK / 8) * BN * 4;  // [BK/8][BN] packed words
-    static constexpr int SZ_BYTES = 1024;              // scales [BN] halves, then zero words [BN/8], then padding
+    // scales [BN] halves, then zero words [BN/8], then padding; HALF: scales [2][BN], then zero words [2][BN/8],
+    // padded to the 256 bytes of a wave-wide DMA of single words (any more padding and the 64x128 tile would fit a
+    // compute unit twice only, not three times)
+    static constexpr int SCALE_BYTES = 4 * BN;
+    static constexpr int SZ_BYTES = HALF ? SCALE_BYTES + 256 : 1024;
     static constexpr int BYTES = A_BYTES + B_BYTES + SZ_BYTES;
 };
 
@@ -267,13 +275,25 @@ struct StageLayout {
 template <int BM, int BN>
 constexpr int kWavesPerSimd = (BM * BN <= 128 * 256) ? 2 : 1;
 
-template <int BM, int BN, int WM, int WN, int BK, int NBUF>
+// HALF: each 32-k half of a stage brings its own row of scales and of zero points, and both rows travel in DMA pieces
+// that suit any N that is a multiple of 8: word by word (a row of zero points is only 4-byte aligned then), the
+// wavefronts sharing the scales.  One DMA instruction and a few vector operations per
+// stage more than the variant with one group per stage, which therefore stays where it applies (groups of 128 against
+// groups of 32: 2048x4096x11008 on the 128x256 tile 194 us against 205, 512x4096x4096 on the 64x128 tile 33 against
+// 39).  What it took over from the general path: 2048x4096x11008 582 -> 205 us, 333x2752x6888 116 -> 38 (groups of 32),
+// 512x4096x4104 (groups of 128, a width of 8 mod 32) 148 -> 44.
+// A K that ends half-way through a stage (K % 64 == 32): the last stage covers the last 64 k, the first half of which
+// the stage before has done already; its activations are cleared in LDS once they have landed, so nothing is read
+// past a row's or the matrix' end and what is repeated contributes exact zeros.
+template <int BM, int BN, int WM, int WN, int BK, int NBUF, bool HALF = false>
 __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pipelined_kernel(const Args a)
 {
+    static_assert(!HALF || BK == 64, "two 32-k halves");
     static_assert(WM * WN == 4, "four wavefronts per workgroup");
     static_assert(BK == 32 || BK == 64, "stage of 32 or 64 k");
     static_assert(NBUF >= 3, "ring of at least three stage buffers");
-    using L = StageLayout<BM, BN, BK>;
+    using L = StageLayout<BM, BN, BK, HALF>;
+    constexpr int GROUPS = HALF ? 2 : 1;  // rows of scales / zero points per stage
     constexpr int WAVE_M = BM / WM;
     constexpr int WAVE_N = BN / WN;
     constexpr int TM = WAVE_M / 32;
@@ -286,7 +306,7 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     constexpr int B_CHUNKS = (BK / 8) * BN / 4 / kThreads;  // ... for the packed weights
     static_assert(A_CHUNKS >= 1 && B_CHUNKS >= 1, "tile too small for 256 threads");
     static_assert(BN / 8 + BN / 32 <= 64, "scales and zero points of a stage must fit one wave-wide DMA");
-    constexpr int LOADS_PER_STAGE = A_CHUNKS + B_CHUNKS + 1;
+    constexpr int LOADS_PER_STAGE = A_CHUNKS + B_CHUNKS + (HALF ? 2 : 1);
     constexpr int MAX_IN_FLIGHT = (NBUF - 3) * LOADS_PER_STAGE;  // may stay outstanding when a stage is published
     static_assert(MAX_IN_FLIGHT < 64, "vmcnt is a 6-bit counter");
 
@@ -306,7 +326,8 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     const int m0 = tile_m * BM;
     const int n0 = tile_n * BN;
     const int N = a.N, K = a.K, M = a.M;
-    const int all_stages = K / BK;  // K is a multiple of the group size, which is a multiple of 64
+    // K is a multiple of the group size, which is a multiple of 64 (HALF: of 32, and K may end half-way)
+    const int all_stages = HALF ? (K + BK - 1) / BK : K / BK;
     const int first = slice * a.stages_per_slice;  // this workgroup's stages: [first, first + stages)
     const int stages = min(a.stages_per_slice, all_stages - first);
     const int last = first + stages - 1;
@@ -352,21 +373,39 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     const int sz_lane = min(lane, BN / 8 + BN / 32 - 1);
     const bool sz_is_scale = sz_lane < BN / 8;
     const int sz_col = sz_is_scale ? min(n0 + 8 * sz_lane, N - 8) : min(n0 + 32 * (sz_lane - BN / 8), N - 32);
-    const char *sz_src = sz_is_scale ? reinterpret_cast<const char *>(a.scales + sz_col)
-                                     : reinterpret_cast<const char *>(a.qzeros + (sz_col >> 3));
-    const uint32_t sz_stride = sz_is_scale ? (uint32_t)N * 2u : (uint32_t)(N >> 3) * 4u;  // bytes per group row
-    const int stages_per_group = a.group_size / BK;
+    const char *sz_src_plain = sz_is_scale ? reinterpret_cast<const char *>(a.scales + sz_col)
+                                           : reinterpret_cast<const char *>(a.qzeros + (sz_col >> 3));
+    // HALF, zero points: lane -> half lane / (BN/8) of the stage (lanes past the second one repeat it), one zero word
+    // each; scales: two per lane, 128 per wavefront - wavefront -> half and part of the half's row.
+    const int z_half = min(lane / (BN / 8), 1);
+    const char *z_src = reinterpret_cast<const char *>(a.qzeros + (min(n0 + 8 * (lane % (BN / 8)), N - 8) >> 3));
+    const uint32_t z_stride = (uint32_t)(N >> 3) * 4u;
+    constexpr int S_PARTS = BN / 128;  // wavefronts per half's row of scales
+    const int s_part = wave % (2 * S_PARTS);
+    const int s_half = s_part / S_PARTS;
+    const char *sz_src = HALF ? reinterpret_cast<const char *>(
+                                    a.scales + min(n0 + 128 * (s_part % S_PARTS) + 2 * lane, N - 2))
+                              : sz_src_plain;
+    const uint32_t sz_stride = HALF || sz_is_scale ? (uint32_t)N * 2u : (uint32_t)(N >> 3) * 4u;  // bytes per group row
+    const int stages_per_group = HALF ? a.group_size / 32 : a.group_size / BK;  // HALF: halves per group
+    // the position of a stage in 32-k halves: twice its number, one less for a last stage that K ends half-way through
+    const bool k_tail = HALF && (K & 32) != 0;
+    const int first_half = 2 * first - (k_tail && first == all_stages - 1 ? 1 : 0);
+    const int tail_stage = k_tail && last == all_stages - 1 ? stages - 1 : -2;  // within this workgroup's stages
 
     // The stage whose loads are issued next, as running source pointers (uniform for the activations and the
     // packed words, per lane for the scales / zero points) that advance by constants: no multiplication and no
     // division in the loop, and selects instead of branches - a branch would end the basic block, and the
     // dequantisation of a stage's last k step (pure arithmetic, first used in the next stage) would sink
     // across it, out of the MFMAs' shadow.
-    int ld_stage = first, ld_in_group = first % stages_per_group;
-    const char *a_cur = a_base + (size_t)first * BK * 2;
+    int ld_stage = first;
+    int ld_in_group = HALF ? (first_half + s_half) % stages_per_group : first % stages_per_group;
+    int z_in_group = HALF ? (first_half + z_half) % stages_per_group : 0;
+    const char *a_cur = a_base + (HALF ? (size_t)first_half * 64 : (size_t)first * BK * 2);
     const size_t b_step = (size_t)(BK / 8) * N * 4;  // bytes between the packed rows of consecutive stages
-    const char *b_cur = b_base + (size_t)first * b_step;
-    const char *sz_cur = sz_src + (size_t)(first / stages_per_group) * sz_stride;
+    const char *b_cur = b_base + (HALF ? (size_t)first_half * (b_step / 2) : (size_t)first * b_step);
+    const char *sz_cur = sz_src + (size_t)((HALF ? first_half + s_half : first) / stages_per_group) * sz_stride;
+    const char *z_cur = z_src + (size_t)((first_half + z_half) / stages_per_group) * z_stride;  // HALF
     auto stage_base = [&](int ring) { return smem + (size_t)ring * L::BYTES; };
     // piece `p` (0 .. LOADS_PER_STAGE-1) of the loads of stage `ld_stage` into ring slot `ring`
     auto issue_piece = [&](int p, int ring) {
@@ -379,6 +418,12 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
             __builtin_amdgcn_global_load_lds((global_ptr_t *)(b_cur + b_off[j]),
                                              (lds_ptr_t *)(base + L::A_BYTES + (size_t)(j * kThreads + wave * 64) * 16),
                                              16, 0, 0);
+        } else if (HALF && p == LOADS_PER_STAGE - 1) {
+            __builtin_amdgcn_global_load_lds((global_ptr_t *)z_cur,
+                                             (lds_ptr_t *)(base + L::A_BYTES + L::B_BYTES + L::SCALE_BYTES), 4, 0, 0);
+        } else if (HALF) {
+            __builtin_amdgcn_global_load_lds((global_ptr_t *)sz_cur,
+                                             (lds_ptr_t *)(base + L::A_BYTES + L::B_BYTES + s_part * 256), 4, 0, 0);
         } else {
             // all four waves write the same bytes: keeps the per-wave count of outstanding loads identical
             __builtin_amdgcn_global_load_lds((global_ptr_t *)sz_cur, (lds_ptr_t *)(base + L::A_BYTES + L::B_BYTES),
@@ -389,6 +434,24 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
         // past the end the last stage is refetched: uniform counts, no branch in the loads
         const int more = ld_stage < last ? 1 : 0;
         ld_stage += more;
+        if (HALF) {
+            // one half less into a last stage that K ends half-way through; a group may be a single half
+            const bool into_tail = k_tail && ld_stage == all_stages - 1;
+            a_cur += more ? (into_tail ? BK : BK * 2) : 0;
+            b_cur += more ? (into_tail ? b_step / 2 : b_step) : (size_t)0;
+            ld_in_group += more ? (into_tail ? 1 : 2) : 0;
+            z_in_group += more ? (into_tail ? 1 : 2) : 0;
+#pragma unroll
+            for (int w = 0; w < 2; ++w) {
+                const bool s_wrap = ld_in_group >= stages_per_group;
+                ld_in_group -= s_wrap ? stages_per_group : 0;
+                sz_cur += s_wrap ? sz_stride : 0u;
+                const bool z_wrap = z_in_group >= stages_per_group;
+                z_in_group -= z_wrap ? stages_per_group : 0;
+                z_cur += z_wrap ? z_stride : 0u;
+            }
+            return;
+        }
         a_cur += more ? BK * 2 : 0;
         b_cur += more ? b_step : (size_t)0;
         ld_in_group += more;
@@ -403,11 +466,25 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
         asm volatile("" ::: "memory");
     };
 
+    // Clears the activations of the first half of the last stage (see above) once the stage is in LDS; the barrier
+    // stands before any wavefront's first read of them.
+    auto clear_repeated_half = [&](int ring) {
+#pragma unroll
+        for (int j = 0; j < BM * 4 / kThreads; ++j) {
+            const int slot = tid + j * kThreads;
+            const int row = slot >> 2;
+            const int ch = (slot & 3) ^ ((row / RPB) & (CH - 1));
+            *reinterpret_cast<uint4 *>(smem + (size_t)ring * L::BYTES + (size_t)(row * CH + ch) * 16) =
+                make_uint4(0u, 0u, 0u, 0u);
+        }
+        __syncthreads();
+    };
+
     // ---- operand registers ----
     half8_t afr[2][TM];  // A operands of two consecutive k steps
     u32x4_t bfr[2][TN];  // B operands (bits of 4 half2 each)
     uint32_t w_cur[KSTEPS][TN], w_nxt[KSTEPS][TN];  // packed words of this lane: stage in use / the next one
-    uint32_t nz_cur[TN], ss_cur[TN], nz_nxt[TN], ss_nxt[TN];
+    uint32_t nz_cur[GROUPS][TN], ss_cur[GROUPS][TN], nz_nxt[GROUPS][TN], ss_nxt[GROUPS][TN];
     const PairMagic magic;
 
     // A operand of 32-row block i at k step kk: row wm*WAVE_M + 32 i + lj, chunk (2 kk + kh) ^ swizzle(row).
@@ -451,7 +528,8 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
 #undef GPTQ_WAIT_A
     };
     // this lane's packed words, scales and zero points of a whole stage
-    auto read_weights = [&](int ring, uint32_t (&w)[KSTEPS][TN], uint32_t (&nz)[TN], uint32_t (&ss)[TN]) {
+    auto read_weights = [&](int ring, uint32_t (&w)[KSTEPS][TN], uint32_t (&nz)[GROUPS][TN],
+                            uint32_t (&ss)[GROUPS][TN]) {
         const unsigned char *base = stage_base(ring) + L::A_BYTES;
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk) {
@@ -471,12 +549,17 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
             }
         }
         const unsigned char *sz = base + L::B_BYTES;
-        const uint32_t zword = *reinterpret_cast<const uint32_t *>(sz + BN * 2 + (col_local >> 3) * 4);
 #pragma unroll
-        for (int t = 0; t < TN; ++t) {
-            const uint32_t sb = *reinterpret_cast<const uint16_t *>(sz + (col_local + t) * 2);
-            ss[t] = sb | (sb << 16);
-            nz[t] = neg_bias((zword >> (4 * ((col_local + t) & 7))) & 15u);
+        for (int g = 0; g < GROUPS; ++g) {
+            const unsigned char *zw = HALF ? sz + L::SCALE_BYTES + (g * (BN / 8) + (col_local >> 3)) * 4
+                                           : sz + BN * 2 + (col_local >> 3) * 4;
+            const uint32_t zword = *reinterpret_cast<const uint32_t *>(zw);
+#pragma unroll
+            for (int t = 0; t < TN; ++t) {
+                const uint32_t sb = *reinterpret_cast<const uint16_t *>(sz + (g * BN + col_local + t) * 2);
+                ss[g][t] = sb | (sb << 16);
+                nz[g][t] = neg_bias((zword >> (4 * ((col_local + t) & 7))) & 15u);
+            }
         }
     };
 
@@ -552,16 +635,18 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
         advance_load_stage();
     }
     publish();
+    if (HALF && (tail_stage == 0 || tail_stage == 1))
+        clear_repeated_half(tail_stage);
     read_weights(0, w_cur, nz_cur, ss_cur);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
         read_afrag(0, 0, i, afr[0][i]);
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
-        bfr[0][t][0] = dequant_pair<0>(w_cur[0][t], magic, nz_cur[t], ss_cur[t]);
-        bfr[0][t][1] = dequant_pair<1>(w_cur[0][t], magic, nz_cur[t], ss_cur[t]);
-        bfr[0][t][2] = dequant_pair<2>(w_cur[0][t], magic, nz_cur[t], ss_cur[t]);
-        bfr[0][t][3] = dequant_pair<3>(w_cur[0][t], magic, nz_cur[t], ss_cur[t]);
+        bfr[0][t][0] = dequant_pair<0>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
+        bfr[0][t][1] = dequant_pair<1>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
+        bfr[0][t][2] = dequant_pair<2>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
+        bfr[0][t][3] = dequant_pair<3>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
     }
 
     // Invariant at the top of stage s: stages s and s+1 are in LDS and visible, every wave has left stage s-1,
@@ -584,17 +669,18 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
                 read_weights(ring_next, w_nxt, nz_nxt, ss_nxt);
         };
         if (KSTEPS == 4) {
-            kstep(P0{}, ring, 1, w_cur[1], nz_cur, ss_cur, issue_loads);
-            kstep(P1{}, ring, 2, w_cur[2 % KSTEPS], nz_cur, ss_cur, nothing);
-            kstep(P0{}, ring, 3, w_cur[3 % KSTEPS], nz_cur, ss_cur, fetch_next_weights);
-            kstep(P1{}, ring_next, 0, w_nxt[0], nz_nxt, ss_nxt, nothing);
+            constexpr int G2 = GROUPS - 1;  // the second half's row where the halves have their own
+            kstep(P0{}, ring, 1, w_cur[1], nz_cur[0], ss_cur[0], issue_loads);
+            kstep(P1{}, ring, 2, w_cur[2 % KSTEPS], nz_cur[G2], ss_cur[G2], nothing);
+            kstep(P0{}, ring, 3, w_cur[3 % KSTEPS], nz_cur[G2], ss_cur[G2], fetch_next_weights);
+            kstep(P1{}, ring_next, 0, w_nxt[0], nz_nxt[0], ss_nxt[0], nothing);
         } else {
             auto both = [&](int m) {
                 issue_loads(m);
                 fetch_next_weights(m);
             };
-            kstep(P0{}, ring, 1, w_cur[1], nz_cur, ss_cur, both);
-            kstep(P1{}, ring_next, 0, w_nxt[0], nz_nxt, ss_nxt, nothing);
+            kstep(P0{}, ring, 1, w_cur[1], nz_cur[0], ss_cur[0], both);
+            kstep(P1{}, ring_next, 0, w_nxt[0], nz_nxt[0], ss_nxt[0], nothing);
         }
         advance_load_stage();
 #pragma unroll
@@ -603,11 +689,15 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
             for (int t = 0; t < TN; ++t)
                 w_cur[kk][t] = w_nxt[kk][t];
 #pragma unroll
-        for (int t = 0; t < TN; ++t) {
-            nz_cur[t] = nz_nxt[t];
-            ss_cur[t] = ss_nxt[t];
-        }
+        for (int g = 0; g < GROUPS; ++g)
+#pragma unroll
+            for (int t = 0; t < TN; ++t) {
+                nz_cur[g][t] = nz_nxt[g][t];
+                ss_cur[g][t] = ss_nxt[g][t];
+            }
         publish();  // stage s+2 has landed; everyone is done with stage s
+        if (HALF && s + 2 == tail_stage)
+            clear_repeated_half(ring_next + 1 == NBUF ? 0 : ring_next + 1);
         ring = ring_next;
     }
     // nothing may still be writing this workgroup's LDS when it retires; the LDS wait retires the operand reads

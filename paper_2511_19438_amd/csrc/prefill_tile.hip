@@ -57,7 +57,10 @@ hipError_t launch_tile<GPTQ_PREFILL_TILE>(const Args &a, int mode, hipStream_t s
 {
     if (mode == kGroupPerStage)
         return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF>, a,
-                      (size_t)NBUF * StageLayout<BM, BN, BK>::BYTES, true, stream);
+                      (size_t)NBUF * StageLayout<BM, BN, BK, false>::BYTES, true, stream);
+    if (mode == kGroupPerHalf)
+        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, true>, a,
+                      (size_t)NBUF * StageLayout<BM, BN, BK, true>::BYTES, true, stream);
 #if GPTQ_PREFILL_TILE == 3
     const size_t lds = 2 * (size_t)BM * 64 * sizeof(half_t);
     if (mode == kGroupPerRow)

@@ -49,3 +49,51 @@ def test_act_order_runs_on_a_workspace_without_room_for_slices(B, M):
             check(B, case, group, "without slices")
     finally:
         B.gptq_w4a16_set_workspace(None)
+
+
+# ---- big-tile kernel with a row of scales and zero points per 32-k half stage: groups that are odd multiples of 32, a K
+#      that ends half-way through a stage, widths that are no multiple of 32; every tile, with and without K slices ----
+
+@pytest.mark.parametrize("tile", [1, 3, 5, 8])
+@pytest.mark.parametrize("M,K,N,group,split_k", [
+    (70, 64, 8, 32, 1),        # one stage
+    (130, 96, 40, 32, 1),      # K ends in the second stage, three groups of one half each
+    (65, 96, 264, 96, 2),      # a slice that is nothing but the half-repeated last stage
+    (257, 160, 520, 32, 1),    # ... in the third (cleared inside the loop)
+    (33, 672, 136, 96, 3),     # groups of three halves, slices that start inside a group
+    (300, 1056, 1032, 32, 4),
+    (96, 512, 264, 128, 2),    # groups of whole stages, width no multiple of 32
+])
+def test_big_tile_half_stage_groups(B, tile, M, K, N, group, split_k):
+    case = workloads.make_case(M, K, N, group, seed=M + K + N)
+    plan = B.Plan(kernel=2, tile=tile, split_k=split_k)
+    res = B.gptq_w4a16_plan_query(M, K, N, group, False, plan)
+    assert res.kernel == 2 and res.tile == tile
+    first = check(B, case, group, f"tile {tile} {M}x{K}x{N} group {group} split {split_k}", plan)
+    assert np.array_equal(first.view(np.uint16), run_gemm(B, case, group, plan).view(np.uint16))
+
+
+def test_half_stage_groups_repeat_nothing_of_a_row(B):
+    """The last 64 k of a K that ends half-way through a stage contain 32 that the stage before has multiplied already:
+    infinities among those activations must count once, like every other value."""
+    M, K, N, group = 40, 160, 64, 32
+    case = workloads.make_case(M, K, N, group, seed=3)
+    case["x"][5, 100] = np.float16(np.inf)  # k 96 ... 127 are read twice
+    out = run_gemm(B, case, group).astype(np.float64)
+    w = oracle.dequant(case["qweight"], case["qzeros"], case["scales"], None, group)[100].astype(np.float64)
+    assert np.array_equal(np.isnan(out[5]), w == 0) and np.all(out[5][w != 0] == np.sign(w[w != 0]) * np.inf)
+    case["x"][5, 100] = np.float16(0)
+    ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group)
+    rows = np.arange(M) != 5
+    assert_within_band(out[rows].astype(np.float16), ref[rows], "the other rows")
+
+
+def test_half_stage_groups_run_on_a_workspace_without_room_for_slices(B):
+    M, K, N, group = 40, 2048, 264, 32
+    case = workloads.make_case(M, K, N, group, seed=M)
+    assert B.gptq_w4a16_plan_query(M, K, N, group).split_k > 1
+    B.gptq_w4a16_set_workspace(torch.empty(1 << 18, dtype=torch.uint8, device="cuda"))  # the arrival counters alone
+    try:
+        check(B, case, group, "without slices")
+    finally:
+        B.gptq_w4a16_set_workspace(None)
