@@ -129,7 +129,8 @@ typedef struct gptq_w4a16_plan {
                         64 rows always use 64);
                         MFMA kernel: tile id = rows x columns per workgroup (wavefront grid):
                         1 256x256 (1x4), 3 128x128 (2x2), 5 64x128 (1x4), 8 128x256 (1x4, two workgroups
-                        per compute unit); 0 auto; any other id is GPTQ_INVALID_ARG */
+                        per compute unit, or two wavefront groups of one that split its K slice; 96 rows instead of
+                        128 where that pads the batch less); 0 auto; any other id is GPTQ_INVALID_ARG */
     int flags;       /* 0, or (vector kernel only: M <= 4, no g_idx, group_size % 32 == 0, 64-column tiles) a set
                         of ablation switches that take one of the paper's techniques out each, for measuring its
                         gain in isolation (Table 3's columns at kernel level):

@@ -95,6 +95,7 @@ hipError_t launch_mid(const Problem &p, const MidPlan &plan, void *workspace, hi
 struct PrefillPlan {
     int tile;     // tile configuration id (1-based), 0 = auto
     int split_k;  // K slices (pipelined kernel only), 0 = auto
+    int rows;     // filled in: rows of tile 8's workgroups, 96 or 128
 };
 bool prefill_supported(const Problem &p);
 // Whether the pipelined kernel (tiles, K slices) takes the problem; else the general path does.

@@ -7,11 +7,12 @@ namespace gptq {
 
 namespace prefill {
 template <int TILE>
-hipError_t launch_tile(const Args &a, int mode, hipStream_t stream);
-template <> hipError_t launch_tile<1>(const Args &, int, hipStream_t);
-template <> hipError_t launch_tile<3>(const Args &, int, hipStream_t);
-template <> hipError_t launch_tile<5>(const Args &, int, hipStream_t);
-template <> hipError_t launch_tile<8>(const Args &, int, hipStream_t);
+hipError_t launch_tile(const Args &a, int mode, int kw, hipStream_t stream);
+template <> hipError_t launch_tile<1>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<3>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<5>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<8>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<9>(const Args &, int, int, hipStream_t);
 }  // namespace prefill
 
 namespace {
@@ -32,7 +33,8 @@ struct TileShape {
     double scratch_tbps;
 };
 // by tile id (1, 3, 5, 8: see the plan documentation in the public header; the other ids up to 10 belonged to
-// layouts that measurement retired - 2x2 wavefront grids, 32-k stages, a 32-row tile - and are refused)
+// layouts that measurement retired - 2x2 wavefront grids, 32-k stages, a 32-row tile - and are refused; tile 8 runs
+// with 96 rows where that fits the batch better)
 constexpr TileShape kTiles[11] = {
     {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0},
     {256, 256, 64, 1.25, false, 0.0, 0, {0, 0, 0}, 0, 0},
@@ -55,15 +57,35 @@ int ceil_div_i(int a, int b)
     return (a + b - 1) / b;
 }
 
+// Workgroups of tile 8 (`rows` x 256) with `split` K slices (as many as whole stages make of them).
+int workgroups_of_tile8(const Problem &p, int rows, int split, int *stages_per_slice)
+{
+    const int stages = ceil_div_i(p.K, 64);
+    const int sps = ceil_div_i(stages, split < 1 ? 1 : split);
+    *stages_per_slice = sps;
+    return ceil_div_i(p.M, rows) * ceil_div_i(p.N, 256) * ceil_div_i(stages, sps);
+}
+
+// Wavefront groups that share a tile of 128x256, each with half of the K slice: two where that gives every compute
+// unit its two wavefronts per SIMD and otherwise it would have one (M = 512: 4096x12288 73.5 -> 58.0 us, 28672x8192
+// in two slices 266 -> 226; M = 128, 8192x57344 152 -> 126).  With more workgroups than compute units two of them
+// meet there anyway (4096x22016 at M = 512, 344 workgroups: 104 us with one group, 114 with two), and slices of a few
+// stages do not earn the sum through LDS (4096x4096 at M = 256, eight stages: 34.2, 35.3).
+int k_groups_of_tile8(const Problem &p, int rows, int split)
+{
+    int sps;
+    return workgroups_of_tile8(p, rows, split, &sps) <= kComputeUnits && sps > 8 ? 2 : 1;
+}
+
 // Estimated duration (microseconds) of the pipelined kernel with tile `t` and `split` K slices.  A workgroup
 // walks its stages at a pace set by instruction issue and latency, not by the matrix pipe or by HBM: alone on
 // a compute unit it leaves most of it idle, and co-resident workgroups slow each other down by less than their
 // number.  Big tiles: whole rounds (or waves of pairs) of workgroups.  Small tiles: workgroups per compute unit
 // -> pace, from sweeps of 6 Llama shapes x 8 batch sizes (48 ... 512) x 8 slice counts (picks within 1.1 % of
 // the best swept plan on average, 7 % at worst).
-double estimate_us(const Problem &p, int t, int split)
+double estimate_us(const Problem &p, int t, int rows, int split)
 {
-    const TileShape &ts = kTiles[t];
+    const TileShape &ts = kTiles[t];  // (rows: of tile 8, 96 or 128)
     const int tiles = ceil_div_i(p.M, ts.bm) * ceil_div_i(p.N, ts.bn);
     const int stages = ceil_div_i(p.K, 64);
     const int sps = ceil_div_i(stages, split);
@@ -84,26 +106,33 @@ double estimate_us(const Problem &p, int t, int split)
             us += 2.0 * wgs * ts.bm * ts.bn * sizeof(float) / (ts.scratch_tbps * 1e6);
         return us;
     }
-    if (ts.pair_us > 0.0 && slices > 1) {
-        // K slices of the 128x256 tile, for few tiles under a deep K (M = 512 ... 1024 on the narrow layers): only
-        // with one workgroup per compute unit at most.  A stage takes 0.8 of its usual time while a quarter of
-        // the chip idles (clock), the slices' fp32 tiles go through scratch once each way - written by all
-        // workgroups at about 4 TB/s, read back by the last arriver of each tile alone at about 60 GB/s.
-        // (up to 128 rows the 64x128 tile's slices measured 10 % faster: 4096x22016 at M = 128, 42 against 46 us)
-        if (wgs > kComputeUnits || p.M <= 128)
-            return 1e30;
-        const double stage = ts.stage_us * (wgs <= 192.0 ? 0.8 : 1.0);
-        const double tile_bytes = (double)ts.bm * ts.bn * sizeof(float);
-        return 3.5 + sps * stage + 1.5 + 4.0 + wgs * tile_bytes / 4e6 + slices * tile_bytes / 6e4;
-    }
     if (ts.pair_us > 0.0) {
+        // (96 rows: three quarters of the MFMAs and all of the dequantisation, 0.87 of the time measured)
+        const double rows_scale = rows == 96 ? 0.87 : 1.0;
+        const double tile_bytes = (double)rows * ts.bn * sizeof(float);
+        int sps8;
+        const int wgs8 = workgroups_of_tile8(p, rows, split, &sps8);
+        // K slices, for few tiles under a deep K: only with one workgroup per compute unit at most.  The slices' fp32
+        // tiles go through scratch once each way - written by all workgroups at about 4 TB/s, read back by the last
+        // arriver of each tile alone at about 60 GB/s.
+        if (slices > 1 && wgs8 > kComputeUnits)
+            return 1e30;
+        const double exchange = slices > 1 ? wgs8 * tile_bytes / 4e6 + slices * tile_bytes / 6e4 : 0.0;
+        if (k_groups_of_tile8(p, rows, split) == 2) {
+            // two groups per workgroup: a pair of stages takes 1.5 us with up to 160 workgroups on the chip, 1.85 with
+            // one on every compute unit (clock).  Within 7 % of sixteen plans measured on eight Llama shapes.
+            const double pace = wgs8 <= 160 ? 1.5 : 1.5 + (wgs8 - 160) * (0.35 / 96.0);
+            return 6.5 + ceil_div_i(sps8, 2) * pace * rows_scale + exchange;
+        }
+        if (slices > 1)
+            return 9.0 + sps8 * ts.stage_us * rows_scale * (wgs8 <= 192 ? 0.8 : 1.0) + exchange;
         // whole waves of two workgroups per compute unit, then the rest: alone if it fits one per unit
         const int per_wave = 2 * kComputeUnits;
-        const int waves = (int)wgs / per_wave;
-        const int rest = (int)wgs - waves * per_wave;
-        double us = 3.5 + waves * (sps * ts.pair_us + 1.5);
+        const int waves = wgs8 / per_wave;
+        const int rest = wgs8 - waves * per_wave;
+        double us = 3.5 + waves * (sps * ts.pair_us * rows_scale + 1.5);
         if (rest > 0)
-            us += sps * (rest > kComputeUnits ? ts.pair_us : ts.stage_us) + 1.5;
+            us += sps * (rest > kComputeUnits ? ts.pair_us : ts.stage_us) * rows_scale + 1.5;
         return us;
     }
     // one workgroup per compute unit: whole rounds, 1.5 us each to fill and drain the pipeline
@@ -148,6 +177,7 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     if (!prefill_pipelined(p)) {
         plan.tile = 3;  // the general modes exist for one tile shape only, without a K split
         plan.split_k = 1;
+        plan.rows = 0;
         return;
     }
     const bool tile_given = prefill_tile_exists(plan.tile);
@@ -155,7 +185,9 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     // Few output tiles and a deep K leave most of the chip idle and every workgroup walking all of K: K slices
     // (combined through scratch in slice order) shorten the walk.  Cheapest (tile, split) by the estimate.
     double best = 0.0;
-    int best_tile = 3, best_split = 1;
+    int best_tile = 3, best_split = 1, best_rows = 128;
+    // tile 8 with 96 rows is a candidate where it pads the batch less (65-96 rows, 129-192, ...)
+    const bool try96 = ceil_div_i(p.M, 96) * 96 < ceil_div_i(p.M, 128) * 128;
     const int stages = ceil_div_i(p.K, 64);
     for (int t = 1; t <= kNumTiles; ++t) {
         if (kTiles[t].stage_us <= 0.0 || (tile_given && t != plan.tile))
@@ -170,18 +202,23 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
             if (slices == last_slices)
                 continue;
             last_slices = slices;
-            const double us = estimate_us(p, t, split);
-            if (best == 0.0 || us < best - 1e-9) {
-                best = us;
-                best_tile = t;
-                best_split = slices;
+            for (int rows = 128; rows >= (t == 8 && try96 ? 96 : 128); rows -= 32) {
+                const double us = estimate_us(p, t, rows, split);
+                if (best == 0.0 || us < best - 1e-9) {
+                    best = us;
+                    best_tile = t;
+                    best_split = slices;
+                    best_rows = rows;
+                }
             }
         }
     }
     if (best == 0.0) {  // a requested split beyond what the loop offers
         best_tile = tile_given ? plan.tile : 3;
         best_split = split_given ? plan.split_k : 1;
+        best_rows = try96 ? 96 : 128;
     }
+    plan.rows = best_rows;
     plan.tile = best_tile;
     plan.split_k = best_split;
 }
@@ -191,6 +228,7 @@ size_t prefill_workspace_bytes(const Problem &p, const PrefillPlan &plan)
     if (plan.split_k <= 1 || !prefill_tile_exists(plan.tile))
         return 0;
     const TileShape &ts = kTiles[plan.tile];
+    // (tile 8 runs with 96 rows only where they cover no more rows in all)
     const size_t tiles = (size_t)ceil_div_i(p.M, ts.bm) * ceil_div_i(p.N, ts.bn);
     return kCounterBytes + (size_t)plan.split_k * tiles * ts.bm * ts.bn * sizeof(float);
 }
@@ -213,15 +251,19 @@ hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *works
     a.stages_per_slice = 0;
     a.counters = reinterpret_cast<unsigned *>(workspace);
     a.partial = workspace ? reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + kCounterBytes) : nullptr;
-    if (a.split_k > 1 && (size_t)ceil_div_i(p.M, kTiles[plan.tile].bm) * ceil_div_i(p.N, kTiles[plan.tile].bn) >
+    if (a.split_k > 1 && (size_t)ceil_div_i(p.M, plan.tile == 8 ? plan.rows : kTiles[plan.tile].bm) *
+                               ceil_div_i(p.N, kTiles[plan.tile].bn) >
                              kCounterBytes / sizeof(unsigned))
         a.split_k = 1;  // more tiles than arrival counters: such a problem needs no split anyway
     const int mode = mode_of(p);
     switch (plan.tile) {
-    case 1: return prefill::launch_tile<1>(a, mode, stream);
-    case 3: return prefill::launch_tile<3>(a, mode, stream);
-    case 5: return prefill::launch_tile<5>(a, mode, stream);
-    case 8: return prefill::launch_tile<8>(a, mode, stream);
+    case 1: return prefill::launch_tile<1>(a, mode, 1, stream);
+    case 3: return prefill::launch_tile<3>(a, mode, 1, stream);
+    case 5: return prefill::launch_tile<5>(a, mode, 1, stream);
+    case 8: {
+        const int kw = k_groups_of_tile8(p, plan.rows, plan.split_k);
+        return plan.rows == 96 ? prefill::launch_tile<9>(a, mode, kw, stream) : prefill::launch_tile<8>(a, mode, kw, stream);
+    }
     default: return hipErrorInvalidValue;
     }
 }

@@ -192,8 +192,11 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TM][TN], half_
 // one per slice.  Device-scope accesses and an arrival counter with release / acquire at agent scope (exchange.h).
 // Returns false in the workgroups that are not the last of their tile.  Partial layout:
 // [split_k][tiles][ACC / 2 pairs][256 threads] x 8 bytes.
+// `member`: whether this thread holds values (a workgroup of two K halves: only the first half's threads do; the
+// others only pass the barriers).
 template <int ACC>
-__device__ __forceinline__ bool combine_slices(float (&v)[ACC], const Args &a, int slice, int tile_id, int tid)
+__device__ __forceinline__ bool combine_slices(float (&v)[ACC], const Args &a, int slice, int tile_id, int tid,
+                                               bool member)
 {
     static_assert(ACC % 2 == 0, "values travel in pairs");
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -205,18 +208,20 @@ __device__ __forceinline__ bool combine_slices(float (&v)[ACC], const Args &a, i
     const size_t tiles = (size_t)a.tiles_m * a.tiles_n;
     unsigned long long *scratch = reinterpret_cast<unsigned long long *>(a.partial);
     unsigned long long *mine = scratch + ((size_t)slice * tiles + tile_id) * PAIRS * kThreads + tid;
+    if (member) {
 #pragma unroll
-    for (int p = 0; p < PAIRS; ++p) {
-        const f32x2_t pair = {v[2 * p], v[2 * p + 1]};
-        __hip_atomic_store(mine + (size_t)p * kThreads, __builtin_bit_cast(unsigned long long, pair), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        for (int p = 0; p < PAIRS; ++p) {
+            const f32x2_t pair = {v[2 * p], v[2 * p + 1]};
+            __hip_atomic_store(mine + (size_t)p * kThreads, __builtin_bit_cast(unsigned long long, pair),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     __builtin_amdgcn_s_waitcnt(0);  // every partial store of this workgroup has been acknowledged (exchange.h)
     __syncthreads();
-    if (tid == 0)
+    if (threadIdx.x == 0)
         s_last = (slice_arrive(a.counters + tile_id) == (unsigned)(a.split_k - 1));
     __syncthreads();
-    if (!s_last)
+    if (!s_last || !member)
         return false;
     slice_acquire();
 #pragma unroll
@@ -285,9 +290,17 @@ constexpr int kWavesPerSimd = (BM * BN <= 128 * 256) ? 2 : 1;
 // A K that ends half-way through a stage (K % 64 == 32): the last stage covers the last 64 k, the first half of which
 // the stage before has done already; its activations are cleared in LDS once they have landed, so nothing is read
 // past a row's or the matrix' end and what is repeated contributes exact zeros.
-template <int BM, int BN, int WM, int WN, int BK, int NBUF, bool HALF = false>
-__global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pipelined_kernel(const Args a)
+//
+// KW = 2: a workgroup of eight wavefronts, two per SIMD, in two groups of four that each walk half of the K slice for
+// the SAME tile, with a ring of their own; only the stage barriers and the sum through LDS at the end are shared.  Two
+// wavefronts per SIMD are what the matrix pipe needs to run under the other's dequantisation (128x256 tile: a 64-k
+// stage takes 0.99 us alone on a compute unit, 1.31 us when two run), and where the tiles give every compute unit one
+// workgroup at most, this is how they get there without partial sums in scratch. 
+// 4096x12288 at M = 512: 73.5 -> 58.0 us; 28672x8192 at M = 512, two slices: 266 -> 226.
+template <int BM, int BN, int WM, int WN, int BK, int NBUF, bool HALF = false, int KW = 1>
+__global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefill_pipelined_kernel(const Args a)
 {
+    static_assert(KW == 1 || (KW == 2 && BM * BN <= 128 * 256), "two wavefronts per SIMD have 256 registers each");
     static_assert(!HALF || BK == 64, "two 32-k halves");
     static_assert(WM * WN == 4, "four wavefronts per workgroup");
     static_assert(BK == 32 || BK == 64, "stage of 32 or 64 k");
@@ -310,9 +323,11 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     constexpr int MAX_IN_FLIGHT = (NBUF - 3) * LOADS_PER_STAGE;  // may stay outstanding when a stage is published
     static_assert(MAX_IN_FLIGHT < 64, "vmcnt is a 6-bit counter");
 
-    extern __shared__ __align__(16) unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem_all[];
 
-    const int tid = threadIdx.x;
+    const int kgroup = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / kThreads);
+    const int tid = threadIdx.x % kThreads;  // within the four wavefronts that share a ring
+    unsigned char *const smem = smem_all + (size_t)kgroup * NBUF * L::BYTES;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keep it in a scalar register
     const int wm = wave / WN;
@@ -328,9 +343,13 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     const int N = a.N, K = a.K, M = a.M;
     // K is a multiple of the group size, which is a multiple of 64 (HALF: of 32, and K may end half-way)
     const int all_stages = HALF ? (K + BK - 1) / BK : K / BK;
-    const int first = slice * a.stages_per_slice;  // this workgroup's stages: [first, first + stages)
-    const int stages = min(a.stages_per_slice, all_stages - first);
-    const int last = first + stages - 1;
+    // this workgroup's stages: [wg_first, wg_first + wg_stages); a group's: [first, first + stages), maybe none
+    const int wg_first = slice * a.stages_per_slice;
+    const int wg_stages = min(a.stages_per_slice, all_stages - wg_first);
+    const int lead = KW == 1 ? wg_stages : (wg_stages + 1) / 2;  // stages of the first group: no group has more
+    const int stages = kgroup == 0 ? lead : wg_stages - lead;
+    const int first = wg_first + (stages > 0 ? kgroup * lead : 0);
+    const int last = first + max(stages, 1) - 1;
     const int col_local = wn * WAVE_N + TN * lj;  // first of this lane's TN columns inside the tile
     const int col_raw = n0 + col_local;
     const bool col_ok = col_raw < N;
@@ -391,7 +410,10 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     // the position of a stage in 32-k halves: twice its number, one less for a last stage that K ends half-way through
     const bool k_tail = HALF && (K & 32) != 0;
     const int first_half = 2 * first - (k_tail && first == all_stages - 1 ? 1 : 0);
-    const int tail_stage = k_tail && last == all_stages - 1 ? stages - 1 : -2;  // within this workgroup's stages
+    // the last stage within its group's stages (the barrier that goes with clearing it is everybody's), or none
+    const bool wg_tail = k_tail && wg_first + wg_stages == all_stages;
+    const int tail_group = KW == 1 || wg_stages == 1 ? 0 : 1;
+    const int tail_stage = wg_tail ? (tail_group == 0 ? lead : wg_stages - lead) - 1 : -2;
 
     // The stage whose loads are issued next, as running source pointers (uniform for the activations and the
     // packed words, per lane for the scales / zero points) that advance by constants: no multiplication and no
@@ -469,9 +491,7 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     // Clears the activations of the first half of the last stage (see above) once the stage is in LDS; the barrier
     // stands before any wavefront's first read of them.
     auto clear_repeated_half = [&](int ring) {
-#pragma unroll
-        for (int j = 0; j < BM * 4 / kThreads; ++j) {
-            const int slot = tid + j * kThreads;
+        for (int slot = tid; slot < (kgroup == tail_group ? BM * 4 : 0); slot += kThreads) {
             const int row = slot >> 2;
             const int ch = (slot & 3) ^ ((row / RPB) & (CH - 1));
             *reinterpret_cast<uint4 *>(smem + (size_t)ring * L::BYTES + (size_t)(row * CH + ch) * 16) =
@@ -700,6 +720,8 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
             clear_repeated_half(ring_next + 1 == NBUF ? 0 : ring_next + 1);
         ring = ring_next;
     }
+    if (KW > 1 && stages < lead)
+        publish();  // the other group's last barrier
     // nothing may still be writing this workgroup's LDS when it retires; the LDS wait retires the operand reads
     // issued for the stage after the last one, whose destination registers stay reserved until here (named as
     // in/outs after the wait: the compiler knows nothing of the inline-asm reads in flight and could otherwise
@@ -709,6 +731,36 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
     for (int i = 0; i < TM; ++i)
         asm volatile("" : "+v"(afr[0][i]), "+v"(afr[1][i]));
 
+    if (KW > 1) {
+        // the second group's sums go to the first through LDS (the rings are done with: every DMA has landed),
+        // four values per access, [value / 4][thread]
+        static_assert(KW == 1 || TM * TN * 16 * kThreads * 4 <= KW * NBUF * L::BYTES, "the sums fit the rings");
+        __syncthreads();
+        float4_t *sums = reinterpret_cast<float4_t *>(smem_all) + tid;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (kgroup == 1)
+                        sums[((i * TN + t) * 4 + q) * kThreads] = float4_t{acc[i][t][4 * q], acc[i][t][4 * q + 1],
+                                                                          acc[i][t][4 * q + 2], acc[i][t][4 * q + 3]};
+        __syncthreads();
+        if (kgroup == 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4_t v = sums[((i * TN + t) * 4 + q) * kThreads];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            acc[i][t][4 * q + r] += v[r];
+                    }
+        }
+    }
     if (a.split_k > 1) {
         constexpr int ACC = TM * TN * 16;
         float flat[ACC];
@@ -719,7 +771,7 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     flat[(i * TN + t) * 16 + r] = acc[i][t][r];
-        if (!combine_slices<ACC>(flat, a, slice, tile_id, tid))
+        if (!combine_slices<ACC>(flat, a, slice, tile_id, tid, kgroup == 0))
             return;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -729,7 +781,8 @@ __global__ __launch_bounds__(kThreads, (kWavesPerSimd<BM, BN>)) void prefill_pip
                 for (int r = 0; r < 16; ++r)
                     acc[i][t][r] = flat[(i * TN + t) * 16 + r];
     }
-    store_tile<TM, TN>(acc, a.out, m0 + wm * WAVE_M, col_raw, col_ok, kh, M, N);
+    if (kgroup == 0)
+        store_tile<TM, TN>(acc, a.out, m0 + wm * WAVE_M, col_raw, col_ok, kh, M, N);
 }
 
 // =====================================================================================================

@@ -3,14 +3,14 @@
 #include "prefill_kernel.h"
 
 #ifndef GPTQ_PREFILL_TILE
-#error "compile with -DGPTQ_PREFILL_TILE=<1|3|5|8>"
+#error "compile with -DGPTQ_PREFILL_TILE=<1|3|5|8|9>"
 #endif
 
 namespace gptq {
 namespace prefill {
 
 template <int TILE>
-hipError_t launch_tile(const Args &a, int mode, hipStream_t stream);
+hipError_t launch_tile(const Args &a, int mode, int kw, hipStream_t stream);
 
 namespace {
 
@@ -23,12 +23,14 @@ constexpr int BM = 128, BN = 128, WM = 2, WN = 2, BK = 64, NBUF = 3;
 constexpr int BM = 64, BN = 128, WM = 1, WN = 4, BK = 64, NBUF = 4;
 #elif GPTQ_PREFILL_TILE == 8
 constexpr int BM = 128, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3;
+#elif GPTQ_PREFILL_TILE == 9  // tile 8 where 96 rows fit the batch better
+constexpr int BM = 96, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3;
 #else
 #error "unknown tile id"
 #endif
 
 template <typename Kernel>
-hipError_t launch(Kernel kernel, Args a, size_t lds, bool may_split, hipStream_t stream)
+hipError_t launch(Kernel kernel, Args a, size_t lds, bool may_split, hipStream_t stream, int kw = 1)
 {
     a.tiles_m = (a.M + BM - 1) / BM;
     a.tiles_n = (a.N + BN - 1) / BN;
@@ -46,15 +48,25 @@ hipError_t launch(Kernel kernel, Args a, size_t lds, bool may_split, hipStream_t
         if (err != hipSuccess)
             return err;
     }
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, stream, a);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads * kw), lds, stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
 template <>
-hipError_t launch_tile<GPTQ_PREFILL_TILE>(const Args &a, int mode, hipStream_t stream)
+hipError_t launch_tile<GPTQ_PREFILL_TILE>(const Args &a, int mode, int kw, hipStream_t stream)
 {
+#if GPTQ_PREFILL_TILE >= 8
+    if (kw == 2 && mode == kGroupPerStage)
+        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, false, 2>, a,
+                      2 * (size_t)NBUF * StageLayout<BM, BN, BK, false>::BYTES, true, stream, 2);
+    if (kw == 2 && mode == kGroupPerHalf)
+        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, true, 2>, a,
+                      2 * (size_t)NBUF * StageLayout<BM, BN, BK, true>::BYTES, true, stream, 2);
+#endif
+    if (kw != 1)
+        return hipErrorInvalidValue;
     if (mode == kGroupPerStage)
         return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF>, a,
                       (size_t)NBUF * StageLayout<BM, BN, BK, false>::BYTES, true, stream);

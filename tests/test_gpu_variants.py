@@ -73,6 +73,24 @@ def test_big_tile_half_stage_groups(B, tile, M, K, N, group, split_k):
     assert np.array_equal(first.view(np.uint16), run_gemm(B, case, group, plan).view(np.uint16))
 
 
+# ---- 128x256 tile: 96 rows where they fit the batch better, two wavefront groups per workgroup that halve its K slice ----
+
+@pytest.mark.parametrize("M", [70, 96, 128, 130, 192])  # 96 rows; 96; 128; two tiles of 96, ragged and full
+@pytest.mark.parametrize("K,N,group,split_k", [
+    (512, 264, 128, 1),    # eight stages: one group
+    (576, 264, 64, 1),     # nine: five and four
+    (1280, 520, 128, 2),   # two slices of ten stages
+    (608, 136, 32, 1),     # ends half-way through a stage, in the second group
+    (1888, 40, 32, 3),     # slices of ten, ten and ten stages (the last one ends half-way)
+    (1184, 72, 32, 2),     # slices of ten and nine stages: five and four, the last one half
+])
+def test_tile_of_two_wavefront_groups(B, M, K, N, group, split_k):
+    case = workloads.make_case(M, K, N, group, seed=M + K + N)
+    plan = B.Plan(kernel=2, tile=8, split_k=split_k)
+    first = check(B, case, group, f"128x256 tile {M}x{K}x{N} group {group} split {split_k}", plan)
+    assert np.array_equal(first.view(np.uint16), run_gemm(B, case, group, plan).view(np.uint16))
+
+
 def test_half_stage_groups_repeat_nothing_of_a_row(B):
     """The last 64 k of a K that ends half-way through a stage contain 32 that the stage before has multiplied already:
     infinities among those activations must count once, like every other value."""
