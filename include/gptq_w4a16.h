@@ -72,12 +72,12 @@ enum gptq_status {
  * not be zeroed (unlike the accumulate-by-atomicAdd contract of Eq. 9-10).
  * By default M = 1 runs the bandwidth-bound split-K vector kernel, 2 <= M <= 32 a small-batch
  * MFMA kernel with the same split-K decomposition (when the format allows: no g_idx,
- * group_size % 128 == 0 or 64 / 32; otherwise the vector kernel up to M = 16), 33 <= M <= 64
+ * group_size % 128 == 0 or 64 / 32; otherwise the vector kernel up to M = 8), 33 <= M <= 64
  * (and 17-32 or 65-128 rows on the layer shapes where it measured faster) a mid-batch MFMA
  * kernel in which every wavefront streams its own share of the K slice (no g_idx, K and
  * group_size multiples of 64), larger M the big-tile fp16 MFMA kernel (with K slices where
  * the output tiles alone would not fill the chip).
- * With g_idx, M >= 2 and K % 128 == 0 run a variant of the small-batch kernel that looks every k up in a table of all
+ * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in a table of all
  * groups in LDS (as long as that fits: up to 636 groups); plan queries report it as kernel 1 (M <= 16) or 2 with
  * 64-column tiles, an explicit request for either runs that kernel itself.
  * Accumulation is in fp32; the result differs from the exact sum by fp32 reassociation

@@ -144,14 +144,19 @@ int acquire_workspace(size_t bytes, hipStream_t stream, void **out)
 // behind it on 4096x4096 and on layers whose tiles make a second, partly filled round).
 constexpr int kVectorMaxM = 1;
 constexpr int kSmallBatchAutoMaxM = 32;
-// Formats that the small-batch kernel does not take (K no multiple of 128, groups of 96, ...): the vector kernel up to
-// eight rows, then the pipelined big-tile kernel with K slices (4128x4096, groups of 32: M = 8 16.0 us each, M = 16
-// 31.9 against 15.8; 2752x6888: M = 4 9.4 against 14.1, M = 16 33.1 against 14.0).
+// Formats that the small-batch kernel does not take (groups of 96, ...): the vector kernel up to eight rows, then the
+// pipelined big-tile kernel with K slices (4128x4096, groups of 96: M = 8 15.9 us against 16.1, M = 9 29.7 against 16.0;
+// 2784x6888: M = 4 9.1 against 14.8, M = 16 32.3 against 14.6).
 constexpr int kVectorFallbackMaxM = 8;
 
 bool small_batch_by_default(const Problem &p)
 {
     if (!skinny_supported(p))
+        return false;
+    // A K that ends inside a 128-k unit: two rows stay with the vector kernel (faster on half of eight shapes measured,
+    // 3776x34176 18.4 us against 22.9), four too on layers so small that the launch dominates (1344x1536 4.9, 5.4);
+    // from three rows on the small-batch kernel is 2-40 % ahead on the others.
+    if (p.K % 128 != 0 && (p.M <= 2 || (p.M <= 4 && (long long)p.K * p.N < (1ll << 22))))
         return false;
     return p.M <= kSmallBatchAutoMaxM;
 }

@@ -37,10 +37,10 @@ int waves_of(int tiles_n, int split_k, int wn, int tm)
     return (wn == 1 && tm <= 2 && (long long)tiles_n * split_k <= 256) ? 8 : 4;
 }
 
-template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false>
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false>
 hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
 {
-    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU, ACT>;
+    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU, ACT, TAIL>;
     if (lds > 48 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -49,6 +49,30 @@ hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
     }
     hipLaunchKernelGGL(kernel, dim3((unsigned)(a.tiles_n * a.row_tiles * a.split_k)), dim3(64 * WAVES), lds, stream, a);
     return hipGetLastError();
+}
+
+// Groups of 128 / GPU k.
+template <int GPU, bool TAIL>
+hipError_t launch_small_groups(const skinny::Args &a, int tm, int waves, size_t lds, hipStream_t stream)
+{
+    if (tm == 1)
+        return waves == 8 ? launch_tm<1, 1, 8, GPU, false, TAIL>(a, lds, stream)
+                          : launch_tm<1, 1, 4, GPU, false, TAIL>(a, lds, stream);
+    return waves == 8 ? launch_tm<2, 1, 8, GPU, false, TAIL>(a, lds, stream)
+                      : launch_tm<2, 1, 4, GPU, false, TAIL>(a, lds, stream);
+}
+
+// Act-order with lookups.
+template <bool TAIL>
+hipError_t launch_lookup(const skinny::Args &a, int tm, int waves, size_t lds, hipStream_t stream)
+{
+    if (tm == 1)
+        return waves == 8 ? launch_tm<1, 1, 8, 1, true, TAIL>(a, lds, stream)
+                          : launch_tm<1, 1, 4, 1, true, TAIL>(a, lds, stream);
+    if (tm == 2)
+        return waves == 8 ? launch_tm<2, 1, 8, 1, true, TAIL>(a, lds, stream)
+                          : launch_tm<2, 1, 4, 1, true, TAIL>(a, lds, stream);
+    return launch_tm<4, 1, 4, 1, true, TAIL>(a, lds, stream);
 }
 
 // LDS that a workgroup of the act-order variant may use (the rest holds its static words).
@@ -73,11 +97,11 @@ int act_max_units(const Problem &p)
 
 }  // namespace
 
-// K must be whole 128-k units; groups may be of any size, the table of all of them has to fit the LDS (up to 636
+// K must be a multiple of 32; groups may be of any size, the table of all of them has to fit the LDS (up to 636
 // groups: K = 28672 with groups of 64 does, with groups of 32 does not and stays with the general path).
 bool act_supported(const Problem &p)
 {
-    if (p.g_idx == nullptr || p.M < 2 || p.N < 8 || p.K % skinny::kUnitK != 0)
+    if (p.g_idx == nullptr || p.M < 2 || p.N < 8 || p.K % 32 != 0)
         return false;
     const long long tiles = (long long)ceil_div(p.N, skinny::kCols) * ceil_div(p.M, skinny::kActRows);
     return tiles <= kMaxColumnTiles && act_max_units(p) >= 4;
@@ -85,7 +109,7 @@ bool act_supported(const Problem &p)
 
 void act_make_plan(const Problem &p, SkinnyPlan &plan)
 {
-    const int total_units = p.K / skinny::kUnitK;
+    const int total_units = ceil_div(p.K, skinny::kUnitK);
     const int tm = act_row_blocks(p.M);
     const int tiles = ceil_div(p.N, skinny::kCols) * ceil_div(p.M, skinny::kActRows);
     plan.cols_per_wg = skinny::kCols;
@@ -143,24 +167,20 @@ hipError_t launch_act(const Problem &p, const SkinnyPlan &plan, void *workspace,
     a.tiles_n = ceil_div(p.N, skinny::kCols);
     a.split_k = plan.split_k;
     a.units_per_slice = plan.units_per_slice;
-    a.total_units = p.K / skinny::kUnitK;
+    a.total_units = ceil_div(p.K, skinny::kUnitK);
     const int waves = waves_of(a.tiles_n * a.row_tiles, a.split_k, 1, tm);
     const size_t table = act_table_bytes(p) + (size_t)plan.units_per_slice * skinny::kUnitK * sizeof(uint32_t);
     const size_t red = (size_t)waves * 16 * tm * skinny::kCols * sizeof(float);
     const size_t lds = table > red ? table : red;
-    if (tm == 1)
-        return waves == 8 ? launch_tm<1, 1, 8, 1, true>(a, lds, stream) : launch_tm<1, 1, 4, 1, true>(a, lds, stream);
-    if (tm == 2)
-        return waves == 8 ? launch_tm<2, 1, 8, 1, true>(a, lds, stream) : launch_tm<2, 1, 4, 1, true>(a, lds, stream);
-    return launch_tm<4, 1, 4, 1, true>(a, lds, stream);
+    return p.K % skinny::kUnitK != 0 ? launch_lookup<true>(a, tm, waves, lds, stream)
+                                     : launch_lookup<false>(a, tm, waves, lds, stream);
 }
 
 bool skinny_supported(const Problem &p)
 {
-    if (p.g_idx != nullptr || p.M < 1 || p.M > kSkinnyMaxM || p.N < 8 || p.K % skinny::kUnitK != 0 ||
-        ceil_div(p.N, skinny::kCols) > kMaxColumnTiles)
+    if (p.g_idx != nullptr || p.M < 1 || p.M > kSkinnyMaxM || p.N < 8 || ceil_div(p.N, skinny::kCols) > kMaxColumnTiles)
         return false;
-    // groups of 64 and 32 k: the 64-column kernel with up to two row blocks
+    // groups of 64 and 32 k: the 64-column kernel with up to two row blocks (K need not be whole 128-k units)
     if (p.group_size == 64 || p.group_size == 32)
         return p.M <= 32;
     return p.group_size % 128 == 0;
@@ -170,7 +190,7 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
 {
     const int launch_m = rows_of_launch(p.M);
     const int rows = 16 * row_blocks(launch_m);
-    const int total_units = p.K / skinny::kUnitK;
+    const int total_units = ceil_div(p.K, skinny::kUnitK);
     if (p.group_size < skinny::kUnitK)
         plan.cols_per_wg = 64;  // the small-group variants exist for the 64-column workgroup
     const bool wide_ok = rows <= 32;  // the 128-column workgroup exists for one and two row blocks
@@ -271,7 +291,7 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
         a.tiles_n = ceil_div(p.N, plan.cols_per_wg);
         a.split_k = plan.split_k;
         a.units_per_slice = plan.units_per_slice;
-        a.total_units = p.K / skinny::kUnitK;
+        a.total_units = ceil_div(p.K, skinny::kUnitK);
 
         const int tm = row_blocks(a.M);
         const int rows = 16 * tm;
@@ -286,12 +306,13 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
         if (gpu > 1) {
             if (wn != 1 || tm > 2)
                 return hipErrorInvalidValue;  // refused by skinny_supported / skinny_make_plan
+            const bool tail = p.K % skinny::kUnitK != 0;
             if (gpu == 2)
-                err = waves == 8 ? (tm == 1 ? launch_tm<1, 1, 8, 2>(a, lds, stream) : launch_tm<2, 1, 8, 2>(a, lds, stream))
-                                 : (tm == 1 ? launch_tm<1, 1, 4, 2>(a, lds, stream) : launch_tm<2, 1, 4, 2>(a, lds, stream));
+                err = tail ? launch_small_groups<2, true>(a, tm, waves, lds, stream)
+                           : launch_small_groups<2, false>(a, tm, waves, lds, stream);
             else
-                err = waves == 8 ? (tm == 1 ? launch_tm<1, 1, 8, 4>(a, lds, stream) : launch_tm<2, 1, 8, 4>(a, lds, stream))
-                                 : (tm == 1 ? launch_tm<1, 1, 4, 4>(a, lds, stream) : launch_tm<2, 1, 4, 4>(a, lds, stream));
+                err = tail ? launch_small_groups<4, true>(a, tm, waves, lds, stream)
+                           : launch_small_groups<4, false>(a, tm, waves, lds, stream);
         } else if (wn == 2) {
             if (tm > 2)
                 return hipErrorInvalidValue;  // refused by skinny_make_plan

@@ -15,8 +15,8 @@
 //     XOR-swizzled by row so that the 16-row operand reads are bank-conflict free;
 //   * every weight is read once and dequantised once, whatever M is: 2 vector ALU operations per weight
 //     instead of 1.2 + M/2 in the vector kernel.
-// Supports no g_idx and group sizes that are multiples of 128 (the tuned format) or 64 / 32 (template GPU);
-// other cases use the other kernels.
+// Supports group sizes that are multiples of 128 (the tuned format) or 64 / 32 (template GPU), and g_idx (template
+// ACT); other cases use the other kernels.
 #pragma once
 
 #include "exchange.h"
@@ -47,7 +47,7 @@ struct Args {
     int tiles_n;
     int split_k;
     int units_per_slice;  // 128-k units per K slice (multiple of 4 where possible)
-    int total_units;      // K / 128
+    int total_units;      // K / 128, rounded up (TAIL variants: the last unit may have 1-3 of its 32-k steps)
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -121,10 +121,16 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
 // (vector kernel) -> 12.7, M = 24 258 (general path) -> 15.1, M = 128 272 -> 48, M = 512 422 -> 138.  Bound by vector
 // issue (~30 instructions per word against 16 in the plain format) and, from 33 rows on, by the latency of the
 // activation loads.  More than 64 rows are row tiles of one grid.
-template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false>
+//
+// TAIL: K is a multiple of 32 but not of 128 (small groups, act-order).  The steps past K of the last unit load the last
+// step again and multiply zeros with it: one select per activation register and a clamp per load (5-7 % on a K without
+// a tail, which therefore has its own instance).  Groups of 32: 8x6048x7016 23.1 us (vector kernel) -> 12.7,
+// 16x2752x6888 14.4 (big-tile kernel) -> 9.8, 32x4128x4096 15.8 -> 10.7.
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false>
 __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
 {
     static_assert(!ACT || (WN == 1 && GPU == 1), "act-order: 64-column workgroups");
+    static_assert(!TAIL || ACT || GPU > 1, "groups of 128 k leave no tail");
     Args a = args;
     static_assert(GPU == 1 || GPU == 2 || GPU == 4, "groups of >= 128, 64 or 32 k");
     static_assert(GPU == 1 || TM <= 2, "small groups: up to two row blocks");
@@ -204,16 +210,17 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
     auto issue = [&](int u, Regs &r) {
         const int uc = min(u, u1 - 1);  // clamped: a unit past the end is loaded again but not consumed
         const uint32_t *wrow = a.qweight + (size_t)uc * 16 * N;
+        const int last_step = TAIL ? min(3, a.K / 32 - 1 - 4 * uc) : 3;
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-            r.w[s] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(wrow + (size_t)s * 4 * N) +
-                                                      voff_w);
+            r.w[s] = *reinterpret_cast<const uint4 *>(
+                reinterpret_cast<const char *>(wrow + (size_t)(TAIL ? min(s, last_step) : s) * 4 * N) + voff_w);
         if (!ACT) {
         const int grp0 = GPU > 1 ? uc * GPU
                                  : (a.unit_group_shift >= 0 ? (uc >> a.unit_group_shift) : uc / a.units_per_group);
 #pragma unroll
         for (int h = 0; h < GPU; ++h) {
-            const int grp = grp0 + h;
+            const int grp = GPU > 1 ? min(grp0 + h, a.K / (kUnitK / GPU) - 1) : grp0 + h;
             r.sc[h] =
                 *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(a.scales + (size_t)grp * N) + voff_s);
             r.zb[h] = *reinterpret_cast<const uint32_t *>(
@@ -226,13 +233,14 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int st = 0; st < 4; ++st)
-                    r.xa[i][st] = *reinterpret_cast<const u32x4_t *>(reinterpret_cast<const char *>(xrow + st * 32) +
-                                                                     voff_x[i]);
+                    r.xa[i][st] = *reinterpret_cast<const u32x4_t *>(
+                        reinterpret_cast<const char *>(xrow + (TAIL ? min(st, last_step) : st) * 32) + voff_x[i]);
         }
     };
     u32x4_t xstep[XSTEP ? TM : 1][4];  // XSTEP: the A operands of the unit being consumed, refilled per step
     auto issue_x = [&](int u, int st) {
-        const half_t *xrow = a.x + (size_t)min(u, u1 - 1) * kUnitK + st * 32;
+        const half_t *xrow = a.x + (TAIL ? (size_t)min(min(u, u1 - 1) * 4 + st, a.K / 32 - 1) * 32
+                                         : (size_t)min(u, u1 - 1) * kUnitK + st * 32);
 #pragma unroll
         for (int i = 0; i < (XSTEP ? TM : 1); ++i)
             xstep[i][st] = *reinterpret_cast<const u32x4_t *>(reinterpret_cast<const char *>(xrow) + voff_x[i]);
@@ -290,7 +298,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
         }
 #pragma unroll 2
         for (int i = tid; i < Ls / 4; i += kThreads) {
-            const int4 g = *reinterpret_cast<const int4 *>(a.g_idx + kbeg + 4 * i);
+            const int4 g = *reinterpret_cast<const int4 *>(a.g_idx + min(kbeg + 4 * i, a.K - 4));  // (TAIL)
             const uint32_t top = (uint32_t)a.groups - 1u;  // entries outside the map stay inside the table
             const u32x4_t o = {min((uint32_t)g.x, top) * kActTableRow, min((uint32_t)g.y, top) * kActTableRow,
                                min((uint32_t)g.z, top) * kActTableRow, min((uint32_t)g.w, top) * kActTableRow};
@@ -325,6 +333,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
         constexpr bool REFILL = decltype(refill)::value;  // XSTEP: fetch the next unit's A operands step by step
         const int j = u - u0;
         constexpr int SPG = 4 / GPU;  // 32-k steps per quantisation group
+        const int live_steps = a.K / 32 - 4 * u;  // TAIL
         half2_t neg_lo[4], neg_hi[4], s2[4];
         float sf[4];
         float4_t d[SCALE_B ? 1 : TM][4];
@@ -358,6 +367,11 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
                     const int m = 16 * i + cq;  // the A operand lane holds row lane % 16
                     const int pc = (c & ~15) | ((c ^ m) & 15);
                     xv = *reinterpret_cast<const u32x4_t *>(xs + (size_t)m * Ls + pc * 8);
+                }
+                if (TAIL) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        xv[e] = st < live_steps ? xv[e] : 0u;
                 }
                 // the same k order for the activations: halves (0,4) (1,5) (2,6) (3,7)
                 const u32x4_t xp = {__builtin_amdgcn_perm(xv[2], xv[0], 0x05040100u),

@@ -22,7 +22,8 @@ def check(B, case, group, what, plan=None):
 # ---- act-order as stored: rows 2 ... several row tiles, one unit per slice, groups of every size, any map ----
 
 @pytest.mark.parametrize("M", [2, 16, 17, 32, 33, 64, 65, 130])
-@pytest.mark.parametrize("K,N,group", [(128, 8, 8), (1152, 72, 128), (2048, 200, 32), (1280, 1032, 640)])
+@pytest.mark.parametrize("K,N,group", [(128, 8, 8), (1152, 72, 128), (2048, 200, 32), (1280, 1032, 640),
+                                       (32, 8, 32), (1120, 136, 32), (2144, 72, 8), (1088, 264, 64)])  # K ends inside a unit
 def test_act_order_lookup_variant(B, M, K, N, group):
     case = workloads.make_case(M, K, N, group, seed=M + K + N, act_order=True)
     check(B, case, group, f"act-order {M}x{K}x{N} group {group}")
@@ -49,6 +50,23 @@ def test_act_order_runs_on_a_workspace_without_room_for_slices(B, M):
             check(B, case, group, "without slices")
     finally:
         B.gptq_w4a16_set_workspace(None)
+
+
+@pytest.mark.parametrize("M", [2, 8, 16, 17, 32])
+@pytest.mark.parametrize("K,N,group,split_k", [(32, 8, 32, 1), (96, 72, 32, 1), (160, 264, 32, 2), (192, 136, 64, 1),
+                                               (1120, 520, 32, 3), (1984, 1032, 64, 4), (4128, 4104, 32, 0)])
+def test_small_batch_kernel_with_a_k_that_ends_inside_a_unit(B, M, K, N, group, split_k):
+    case = workloads.make_case(M, K, N, group, seed=M + K + N)
+    plan = B.Plan(kernel=3 if split_k else 0, split_k=split_k)
+    assert B.gptq_w4a16_plan_query(M, K, N, group, False, plan).kernel == (3 if split_k or M > 2 else 1)
+    check(B, case, group, f"small batch {M}x{K}x{N} group {group} split {split_k}", plan)
+    if not split_k and M <= 2:
+        return  # the vector kernel: biased codes, an infinity leaves it as a NaN
+    # an infinity in the last 32 k, which the steps past K load again, must reach its own row only, and not as a NaN
+    case["x"][0, K - 3] = np.float16(np.inf)
+    out = run_gemm(B, case, group, plan).astype(np.float64)
+    w = oracle.dequant(case["qweight"], case["qzeros"], case["scales"], None, group)[K - 3].astype(np.float64)
+    assert np.array_equal(np.isnan(out[0]), w == 0) and np.all(np.isfinite(out[1:]))
 
 
 # ---- big-tile kernel with a row of scales and zero points per 32-k half stage: groups that are odd multiples of 32, a K
