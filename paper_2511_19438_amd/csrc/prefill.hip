@@ -1,4 +1,5 @@
 // Host side of the MFMA kernel: tile selection and dispatch.
+#include "gptq_w4a16.h"
 #include "prefill_kernel.h"
 
 #include <cmath>
@@ -18,35 +19,15 @@ template <> hipError_t launch_tile<9>(const Args &, int, int, hipStream_t);
 namespace {
 
 struct TileShape {
-    int bm, bn, bk;
-    double stage_us;  // one 64-k stage of a workgroup that has a compute unit to itself, measured
-                      // (0 = tile is never auto-selected)
-    bool may_split;   // K slices pay only where a thread holds few accumulators (the combine moves them all)
-    double pair_us;   // big tiles, if > 0: exactly two workgroups fit a compute unit and a stage takes this long
-                      // when two are resident (they share the matrix pipe); the estimate counts waves of 512
-    // small tiles (resident > 0): up to `resident` workgroups share a compute unit and a stage of each takes
-    // pace[r-1] with r of them resident; fixed_us covers launch, pipeline fill and the store; a split moves
-    // every slice's partial tile through scratch once each way at scratch_tbps
-    int resident;
-    double pace[3];
-    double fixed_us;
-    double scratch_tbps;
+    int bm, bn;
+    bool may_split;  // K slices pay only where a thread holds few accumulators (the combine moves them all)
 };
 // by tile id (1, 3, 5, 8: see the plan documentation in the public header; the other ids up to 10 belonged to
 // layouts that measurement retired - 2x2 wavefront grids, 32-k stages, a 32-row tile - and are refused; tile 8 runs
 // with 96 rows where that fits the batch better)
-constexpr TileShape kTiles[11] = {
-    {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0},
-    {256, 256, 64, 1.25, false, 0.0, 0, {0, 0, 0}, 0, 0},
-    {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0},
-    {128, 128, 64, 0.75, true, 0.0, 2, {0.75, 1.4, 0}, 7.0, 6.0},
-    {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0},
-    {64, 128, 64, 0.46, true, 0.0, 3, {0.46, 0.72, 1.0}, 6.0, 6.0},
-    {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0},
-    {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0},
-    {128, 256, 64, 0.99, true, 1.31, 0, {0, 0, 0}, 0, 0},
-    {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0},
-    {0, 0, 64, 0.0, false, 0.0, 0, {0, 0, 0}, 0, 0}};
+constexpr TileShape kTiles[11] = {{0, 0, false},   {256, 256, false}, {0, 0, false}, {128, 128, true},
+                                  {0, 0, false},   {64, 128, true},   {0, 0, false}, {0, 0, false},
+                                  {128, 256, true}, {0, 0, false},    {0, 0, false}};
 constexpr int kNumTiles = 10;
 constexpr int kComputeUnits = 256;
 constexpr size_t kCounterBytes = 256 * 1024;  // same fixed counter area as the other kernels
@@ -77,66 +58,63 @@ int k_groups_of_tile8(const Problem &p, int rows, int split)
     return workgroups_of_tile8(p, rows, split, &sps) <= kComputeUnits && sps > 8 ? 2 : 1;
 }
 
-// Estimated duration (microseconds) of the pipelined kernel with tile `t` and `split` K slices.  A workgroup
-// walks its stages at a pace set by instruction issue and latency, not by the matrix pipe or by HBM: alone on
-// a compute unit it leaves most of it idle, and co-resident workgroups slow each other down by less than their
-// number.  Big tiles: whole rounds (or waves of pairs) of workgroups.  Small tiles: workgroups per compute unit
-// -> pace, from sweeps of 6 Llama shapes x 8 batch sizes (48 ... 512) x 8 slice counts (picks within 1.1 % of
-// the best swept plan on average, 7 % at worst).
-double estimate_us(const Problem &p, int t, int rows, int split)
+// Estimated duration (microseconds) of the pipelined kernel with tile `t` and `split` K slices.  A workgroup walks its
+// stages at a pace set by instruction issue and latency: alone on a compute unit it leaves most of it idle, and
+// co-resident workgroups slow each other down by less than their number.  What counts is the busiest compute unit of the
+// busiest XCD: a tile's slices share an XCD and the tiles are dealt out in eight equal ranges (tile_of_workgroup), so 50
+// tiles in five slices are 35 workgroups on 32 compute units there, not 250 on 256 (28160x2432 at M = 385: 136 us; 94 in
+// six slices of fewer tiles).  The slices' exchange costs a fixed part, a part per slice that the last arriver of a tile
+// reads, and the traffic of all partial tiles.  Constants: least squares over 3.9 k measured plans of 160 random problems
+// (M 33-1100, K 1024-28672, N 1024-57344; 6-8 % rms), whose picks are 1.4 % behind the best of every problem on
+// average, 25 % at worst (the model before, without the XCDs: 7.7 %, 45 %).
+struct SmallTilePace {
+    double resident[3];  // one stage with that many workgroups on a compute unit
+    int most;            // workgroups that fit one
+    double fixed, split, per_slice, tbps, half;  // half: the HALF variant's stages take this much longer
+};
+constexpr SmallTilePace kPace64x128 = {{0.41, 0.635, 0.925}, 3, 5.3, 1.65, 0.48, 6.3, 1.22};
+constexpr SmallTilePace kPace128x128 = {{0.825, 1.12, 0.0}, 2, 2.3, 2.55, 1.03, 4.8, 1.18};
+
+double estimate_us(const Problem &p, int t, int rows, int split, bool half)
 {
     const TileShape &ts = kTiles[t];  // (rows: of tile 8, 96 or 128)
-    const int tiles = ceil_div_i(p.M, ts.bm) * ceil_div_i(p.N, ts.bn);
+    const int bm = t == 8 ? rows : ts.bm;
+    const int tiles = ceil_div_i(p.M, bm) * ceil_div_i(p.N, ts.bn);
     const int stages = ceil_div_i(p.K, 64);
     const int sps = ceil_div_i(stages, split);
     const int slices = ceil_div_i(stages, sps);
-    const double wgs = (double)tiles * slices;
-    if (ts.resident > 0) {
-        const double n = wgs / kComputeUnits;  // workgroups per compute unit
-        // the busiest compute units set the time: ceil(n) resident there; past `resident` the rest queue up
-        double pace;
-        if (n >= ts.resident) {
-            pace = ts.pace[ts.resident - 1] * n / ts.resident;
-        } else {
-            const int r = (int)std::ceil(n - 1e-9);
-            pace = ts.pace[(r < 1 ? 1 : r) - 1];
-        }
-        double us = ts.fixed_us + sps * pace;
-        if (slices > 1)
-            us += 2.0 * wgs * ts.bm * ts.bn * sizeof(float) / (ts.scratch_tbps * 1e6);
-        return us;
+    const int wgs = tiles * slices;
+    const double n = ceil_div_i(tiles, 8) * slices / 32.0;  // workgroups per compute unit of the busiest XCD
+    const double partial_mb = wgs * (double)bm * ts.bn * sizeof(float) / 1e6;
+    if (t == 3 || t == 5) {
+        const SmallTilePace &c = t == 5 ? kPace64x128 : kPace128x128;
+        const int full = (int)((n - 1e-9) / c.most);  // times that a compute unit is filled up, then the rest
+        const int rest = (int)std::ceil(n - full * c.most - 1e-9);
+        const double stage = full * c.resident[c.most - 1] + (rest > 0 ? c.resident[rest - 1] : 0.0);
+        return c.fixed + sps * stage * (half ? c.half : 1.0) +
+               (slices > 1 ? c.split + slices * c.per_slice + partial_mb / c.tbps : 0.0);
     }
-    if (ts.pair_us > 0.0) {
-        // (96 rows: three quarters of the MFMAs and all of the dequantisation, 0.87 of the time measured)
-        const double rows_scale = rows == 96 ? 0.87 : 1.0;
-        const double tile_bytes = (double)rows * ts.bn * sizeof(float);
-        int sps8;
-        const int wgs8 = workgroups_of_tile8(p, rows, split, &sps8);
-        // K slices, for few tiles under a deep K: only with one workgroup per compute unit at most.  The slices' fp32
-        // tiles go through scratch once each way - written by all workgroups at about 4 TB/s, read back by the last
-        // arriver of each tile alone at about 60 GB/s.
-        if (slices > 1 && wgs8 > kComputeUnits)
+    if (t == 8) {
+        // more workgroups than compute units and K slices: the exchange is not worth it
+        if (slices > 1 && wgs > kComputeUnits)
             return 1e30;
-        const double exchange = slices > 1 ? wgs8 * tile_bytes / 4e6 + slices * tile_bytes / 6e4 : 0.0;
+        // (96 rows: three quarters of the MFMAs and all of the dequantisation)
+        const double scale = (rows == 96 ? 0.89 : 1.0) * (half ? 1.16 : 1.0);
+        const double exchange =
+            slices > 1 ? 3.2 + slices * (bm * ts.bn * sizeof(float) / 79e3) + partial_mb / 4.9 : 0.0;
         if (k_groups_of_tile8(p, rows, split) == 2) {
-            // two groups per workgroup: a pair of stages takes 1.5 us with up to 160 workgroups on the chip, 1.85 with
-            // one on every compute unit (clock).  Within 7 % of sixteen plans measured on eight Llama shapes.
-            const double pace = wgs8 <= 160 ? 1.5 : 1.5 + (wgs8 - 160) * (0.35 / 96.0);
-            return 6.5 + ceil_div_i(sps8, 2) * pace * rows_scale + exchange;
+            // a pair of stages takes 1.4 us with up to 160 workgroups on the chip, 1.75 with one on every compute unit
+            const double on_chip = n * kComputeUnits;
+            const double pace = on_chip <= 160 ? 1.4 : 1.4 + (on_chip - 160) * (0.35 / 96.0);
+            return 5.2 + ceil_div_i(sps, 2) * pace * scale * (n > 1.0 ? 2.0 : 1.0) + exchange;
         }
-        if (slices > 1)
-            return 9.0 + sps8 * ts.stage_us * rows_scale * (wgs8 <= 192 ? 0.8 : 1.0) + exchange;
-        // whole waves of two workgroups per compute unit, then the rest: alone if it fits one per unit
-        const int per_wave = 2 * kComputeUnits;
-        const int waves = wgs8 / per_wave;
-        const int rest = wgs8 - waves * per_wave;
-        double us = 3.5 + waves * (sps * ts.pair_us * rows_scale + 1.5);
-        if (rest > 0)
-            us += sps * (rest > kComputeUnits ? ts.pair_us : ts.stage_us) * rows_scale + 1.5;
-        return us;
+        const int full = (int)((n - 1e-9) / 2.0);  // two workgroups per compute unit, then the rest
+        const double rest = n - 2.0 * full;
+        const double stage = full * 1.6 + (rest > 1.0 + 1e-9 ? 1.6 : rest > 1e-9 ? 0.98 : 0.0);
+        return 5.2 + sps * stage * scale + 1.5 * full + exchange;
     }
-    // one workgroup per compute unit: whole rounds, 1.5 us each to fill and drain the pipeline
-    return 3.5 + std::ceil(wgs / kComputeUnits) * (sps * ts.stage_us + 1.5) + (slices > 1 ? 5.0 : 0.0);
+    // 256x256: one workgroup per compute unit, whole rounds
+    return std::ceil(n - 1e-9) * (sps * 1.286 * (half ? 1.16 : 1.0) + 9.9);
 }
 
 int mode_of(const Problem &p)
@@ -184,13 +162,14 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     const bool split_given = plan.split_k >= 1;
     // Few output tiles and a deep K leave most of the chip idle and every workgroup walking all of K: K slices
     // (combined through scratch in slice order) shorten the walk.  Cheapest (tile, split) by the estimate.
+    const bool half = mode_of(p) == prefill::kGroupPerHalf;
     double best = 0.0;
     int best_tile = 3, best_split = 1, best_rows = 128;
     // tile 8 with 96 rows is a candidate where it pads the batch less (65-96 rows, 129-192, ...)
     const bool try96 = ceil_div_i(p.M, 96) * 96 < ceil_div_i(p.M, 128) * 128;
     const int stages = ceil_div_i(p.K, 64);
     for (int t = 1; t <= kNumTiles; ++t) {
-        if (kTiles[t].stage_us <= 0.0 || (tile_given && t != plan.tile))
+        if (kTiles[t].bm == 0 || (tile_given && t != plan.tile))
             continue;
         int last_slices = 0;
         for (int split = 1; split <= kMaxSplit && split <= stages / 2 + (stages < 2); ++split) {
@@ -202,8 +181,12 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
             if (slices == last_slices)
                 continue;
             last_slices = slices;
+            // (automatic slices stay within the static scratch block, so that gptq_w4a16_gemm_static runs the same plan)
+            PrefillPlan candidate = {t, slices, 0};
+            if (!split_given && slices > 1 && prefill_workspace_bytes(p, candidate) > GPTQ_STATIC_SCRATCH_BYTES)
+                continue;
             for (int rows = 128; rows >= (t == 8 && try96 ? 96 : 128); rows -= 32) {
-                const double us = estimate_us(p, t, rows, split);
+                const double us = estimate_us(p, t, rows, split, half);
                 if (best == 0.0 || us < best - 1e-9) {
                     best = us;
                     best_tile = t;

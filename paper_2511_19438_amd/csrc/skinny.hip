@@ -1,4 +1,5 @@
 // Host side of the small-batch MFMA kernel: support check, launch plan, scratch sizing, dispatch.
+#include "gptq_w4a16.h"
 #include "skinny_kernel.h"
 
 namespace gptq {
@@ -124,6 +125,10 @@ void act_make_plan(const Problem &p, SkinnyPlan &plan)
         const int max_split = p.K / (16 * (p.M < skinny::kActRows ? p.M : skinny::kActRows));
         if (split > max_split)
             split = max_split;
+        // (and within the static scratch block, so that gptq_w4a16_gemm_static runs the same plan)
+        const long long slice_bytes = (long long)p.M * p.N * sizeof(float);
+        if (split * slice_bytes > (long long)(GPTQ_STATIC_SCRATCH_BYTES - kCounterBytes))
+            split = (int)((GPTQ_STATIC_SCRATCH_BYTES - kCounterBytes) / slice_bytes);
         if (split < 1)
             split = 1;
         quantum = waves_of(tiles, split, 1, tm);

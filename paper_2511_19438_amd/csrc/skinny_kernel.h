@@ -220,7 +220,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
                                  : (a.unit_group_shift >= 0 ? (uc >> a.unit_group_shift) : uc / a.units_per_group);
 #pragma unroll
         for (int h = 0; h < GPU; ++h) {
-            const int grp = GPU > 1 ? min(grp0 + h, a.K / (kUnitK / GPU) - 1) : grp0 + h;
+            const int grp = TAIL ? min(grp0 + h, a.K / (kUnitK / GPU) - 1) : grp0 + h;
             r.sc[h] =
                 *reinterpret_cast<const uint2 *>(reinterpret_cast<const char *>(a.scales + (size_t)grp * N) + voff_s);
             r.zb[h] = *reinterpret_cast<const uint32_t *>(

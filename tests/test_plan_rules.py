@@ -1,0 +1,40 @@
+"""Host logic of the automatic plans (no device is touched)."""
+import random
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2511_19438_amd import build
+
+    if not __import__("os").path.exists(build.LIB_PATH):
+        build.build()
+    from paper_2511_19438_amd import binding
+
+    return binding
+
+
+def test_automatic_slices_fit_the_static_scratch_block_and_the_grid(B):
+    """Big-tile and act-order plans: partial sums within the 48 MiB of gptq_w4a16_gemm_static, slices of whole stages (none
+    empty), and K slices of the 128x256 tile only with a compute unit for every workgroup."""
+    tile_dims = {1: (256, 256), 3: (128, 128), 5: (64, 128), 8: (128, 256), 64: (64, 64)}
+    rng = random.Random(5)
+    for _ in range(400):
+        group = rng.choice([32, 64, 128])
+        K, N = group * rng.randint(2, 28672 // group), 8 * rng.randint(1, 7168)
+        M, act = rng.choice([rng.randint(65, 700), rng.randint(17, 2048)]), rng.random() < 0.3
+        pl = B.gptq_w4a16_plan_query(M, K, N, group, act)
+        if pl.kernel != 2:
+            continue
+        bm, bn = tile_dims[pl.tile]
+        tiles = -(-M // bm) * -(-N // bn)
+        if pl.split_k > 1:
+            assert pl.split_k * tiles * bm * bn * 4 <= 48 << 20 or act, (M, K, N, group, act)
+            assert not act or pl.split_k * M * N * 4 <= 48 << 20 or K // group > 500, (M, K, N, group)
+            stages = -(-K // (128 if act else 64))
+            per = -(-stages // pl.split_k)
+            assert (pl.split_k - 1) * per < stages, (M, K, N, pl.split_k)
+        if pl.tile == 8 and pl.split_k > 1:
+            assert tiles * pl.split_k <= 256, (M, K, N, pl.split_k)
+            assert B.gptq_w4a16_workspace_bytes(M, K, N, group) >= pl.split_k * tiles * bm * bn * 4
