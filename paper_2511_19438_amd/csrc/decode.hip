@@ -294,7 +294,7 @@ hipError_t launch_decode(const Problem &p, const DecodePlan &plan, void *workspa
                                 p.group_size % 128 == 0 && plan.split_k == 1 &&
                                 plan.chunks_per_slice % (4 * row_lanes) == 0;
         const int flags = plan.flags | (p.x_perm ? decode::kGatherX : 0) | (waves == 8 ? decode::kEightWaves : 0) |
-                          (group_corr ? decode::kGroupCorr : 0);
+                          (group_corr ? decode::kGroupCorr : 0) | (stream_weights(p) ? decode::kStreamWeights : 0);
         hipError_t err;
         switch (mb) {
         case 1: err = decode::launch_mb<1>(a, d.lpr, plan.chunk_rows, act, flags, lds, stream); break;

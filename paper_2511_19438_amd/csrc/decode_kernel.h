@@ -157,6 +157,7 @@ constexpr int kEightWaves = 32;
 // per column are paid once per 64 packed words instead of once per 16.  Single row, plain format, group sizes
 // that are multiples of 128, slices of whole groups.
 constexpr int kGroupCorr = 64;
+constexpr int kStreamWeights = 128;  // non-temporal weight loads (stream_weights)
 
 template <int MB, int LPR, int R, bool ACT, int ABL = 0>
 __global__ __launch_bounds__((ABL & kEightWaves) ? 512 : 256) void decode_kernel(const Args a)
@@ -235,7 +236,7 @@ __global__ __launch_bounds__((ABL & kEightWaves) ? 512 : 256) void decode_kernel
             const uint32_t woff = (__umul24(ul * R, N) + n0c) * 4u;
 #pragma unroll
             for (int rr = 0; rr < R; ++rr)
-                r.wq[j][rr] = *reinterpret_cast<const uint4 *>(
+                r.wq[j][rr] = load_words<(ABL & kStreamWeights) != 0>(
                     reinterpret_cast<const char *>(wslice + (size_t)rr * N) + woff);
             if (!ACT && !(GC && (ODD || j > 0))) {
                 const int u = c0 + ul;

@@ -40,6 +40,20 @@ hipError_t launch_lpr(const Args &a, int lpr, size_t lds_bytes, hipStream_t stre
     }
 }
 
+// ABL with streamed weights: single row, tiles of whole 256-byte pieces of a packed row
+template <int MB, int ABL>
+hipError_t launch_streamed(const Args &a, int lpr, bool eight_waves, size_t lds_bytes, hipStream_t stream)
+{
+    constexpr int V = ABL | kStreamWeights;
+    if (eight_waves)
+        return lpr == 16   ? launch_one<MB, 16, 4, false, V | kEightWaves>(a, lds_bytes, stream)
+               : lpr == 32 ? launch_one<MB, 32, 4, false, V | kEightWaves>(a, lds_bytes, stream)
+                           : launch_one<MB, 64, 4, false, V | kEightWaves>(a, lds_bytes, stream);
+    return lpr == 16   ? launch_one<MB, 16, 4, false, V>(a, lds_bytes, stream)
+           : lpr == 32 ? launch_one<MB, 32, 4, false, V>(a, lds_bytes, stream)
+                       : launch_one<MB, 64, 4, false, V>(a, lds_bytes, stream);
+}
+
 // ABL, or ABL with eight wavefronts (single-row kernel only)
 template <int MB, int ABL>
 hipError_t launch_lpr_waves(const Args &a, int lpr, bool eight_waves, size_t lds_bytes, hipStream_t stream)
@@ -106,6 +120,10 @@ hipError_t dispatch(const Args &a, int lpr, int chunk_rows, bool act, int varian
         // Up to four batch rows the inner loop contracts on the matrix unit (kMatrixDot): measured 3-6 % faster
         // than v_dot2_f32_f16 at M = 1, which stays as a comparison switch and for the larger batches.
         if constexpr (MB == 1) {
+            if (!vector_dot && (variant & kStreamWeights) && lpr >= 16)
+                return (variant & kGroupCorr)
+                           ? launch_streamed<MB, kMatrixDot | kGroupCorr>(a, lpr, eight_waves, lds_bytes, stream)
+                           : launch_streamed<MB, kMatrixDot>(a, lpr, eight_waves, lds_bytes, stream);
             if (!vector_dot && (variant & kGroupCorr))
                 return launch_lpr_waves<MB, kMatrixDot | kGroupCorr>(a, lpr, eight_waves, lds_bytes, stream);
         }

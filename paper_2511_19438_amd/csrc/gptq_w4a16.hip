@@ -154,9 +154,9 @@ bool small_batch_by_default(const Problem &p)
     if (!skinny_supported(p))
         return false;
     // A K that ends inside a 128-k unit: two rows stay with the vector kernel (faster on half of eight shapes measured,
-    // 3776x34176 18.4 us against 22.9), four too on layers so small that the launch dominates (1344x1536 4.9, 5.4);
-    // from three rows on the small-batch kernel is 2-40 % ahead on the others.
-    if (p.K % 128 != 0 && (p.M <= 2 || (p.M <= 4 && (long long)p.K * p.N < (1ll << 22))))
+    // 3776x34176 18.4 us against 22.9), four too on layers so small that the launch dominates (1344x1536 4.9, 5.4) and
+    // on very wide ones (8256x38256 45, 53); from three rows on the small-batch kernel is 2-40 % ahead on the others.
+    if (p.K % 128 != 0 && (p.M <= 2 || (p.M <= 4 && ((long long)p.K * p.N < (1ll << 22) || p.N > 32768))))
         return false;
     return p.M <= kSmallBatchAutoMaxM;
 }

@@ -25,6 +25,28 @@ struct Problem {
     int M, K, N, group_size;
 };
 
+// Whether the HBM-bound kernels (up to 32 rows) read a call's packed weights with non-temporal loads.  Two matrices of
+// 128 MB or more do not fit the 256 MB memory-side cache: they come from HBM on every call and the streaming hint is
+// worth 3-9 % (8192x57344: M = 1 43.0 -> 39.5 us, M = 8 52.1 -> 48.9, M = 16 56.9 -> 53.8).  Smaller matrices that a program calls again and again are found in that cache and lose 5-8 % with the
+// hint (weights that do not fit gain 2-5 %); which of the two a call belongs to is not known here.  Rows have to be whole cache lines: neighbouring tiles share the line at their border otherwise, and the
+// hint drops it before the neighbour comes (17664x9896 at M = 32: 32 us without the hint, 45 with it).
+inline bool stream_weights(const Problem &p)
+{
+    return p.N % 32 == 0 && (long long)p.K * p.N / 2 >= 128000000ll;
+}
+
+#ifdef __HIPCC__
+template <bool STREAM>
+__device__ __forceinline__ uint4 load_words(const void *p)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    if (!STREAM)
+        return *reinterpret_cast<const uint4 *>(p);
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+#endif
+
 // ---- unpack / dequant (standalone, HBM-bound) ----
 hipError_t launch_unpack(const uint32_t *qweight, uint8_t *q_out, const uint32_t *qzeros, uint8_t *z_out, int K,
                          int N, int group_size, hipStream_t stream);

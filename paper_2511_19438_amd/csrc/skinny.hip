@@ -38,10 +38,10 @@ int waves_of(int tiles_n, int split_k, int wn, int tm)
     return (wn == 1 && tm <= 2 && (long long)tiles_n * split_k <= 256) ? 8 : 4;
 }
 
-template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false>
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false, bool STREAM = false>
 hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
 {
-    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU, ACT, TAIL>;
+    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU, ACT, TAIL, STREAM>;
     if (lds > 48 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -50,6 +50,14 @@ hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
     }
     hipLaunchKernelGGL(kernel, dim3((unsigned)(a.tiles_n * a.row_tiles * a.split_k)), dim3(64 * WAVES), lds, stream, a);
     return hipGetLastError();
+}
+
+// One and two row blocks with streamed weights.
+template <int WN, int WAVES>
+hipError_t launch_streamed(const skinny::Args &a, int tm, size_t lds, hipStream_t stream)
+{
+    return tm == 1 ? launch_tm<1, WN, WAVES, 1, false, false, true>(a, lds, stream)
+                   : launch_tm<2, WN, WAVES, 1, false, false, true>(a, lds, stream);
 }
 
 // Groups of 128 / GPU k.
@@ -318,6 +326,10 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
             else
                 err = tail ? launch_small_groups<4, true>(a, tm, waves, lds, stream)
                            : launch_small_groups<4, false>(a, tm, waves, lds, stream);
+        } else if (tm <= 2 && stream_weights(p)) {
+            err = wn == 2   ? launch_streamed<2, 8>(a, tm, lds, stream)
+                  : wn == 4 ? launch_streamed<4, 4>(a, tm, lds, stream)
+                  : waves == 8 ? launch_streamed<1, 8>(a, tm, lds, stream) : launch_streamed<1, 4>(a, tm, lds, stream);
         } else if (wn == 2) {
             if (tm > 2)
                 return hipErrorInvalidValue;  // refused by skinny_make_plan

@@ -35,19 +35,20 @@ struct Args {
     const uint32_t *qweight;
     const uint32_t *qzeros;
     const half_t *scales;
-    const int32_t *g_idx;  // ACT only: group of every k
     half_t *out;
     float *partial;      // [split_k, M, N] fp32, only if split_k > 1
     unsigned *counters;  // [row_tiles * tiles_n], zero between launches
     int M, K, N;
-    int groups;           // ACT only: K / group_size
-    int row_tiles;        // ACT only: blocks of kActRows rows in the grid (1: M fits one)
     int units_per_group;  // group_size / 128
     int unit_group_shift; // log2(units_per_group) if that is a power of two, else -1
     int tiles_n;
     int split_k;
     int units_per_slice;  // 128-k units per K slice (multiple of 4 where possible)
     int total_units;      // K / 128, rounded up (TAIL variants: the last unit may have 1-3 of its 32-k steps)
+    // ACT only (at the end: the other instances' argument loads stay as short as they were)
+    const int32_t *g_idx;  // group of every k
+    int groups;            // K / group_size
+    int row_tiles;         // blocks of kActRows rows in the grid (1: M fits one)
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -126,7 +127,9 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
 // step again and multiply zeros with it: one select per activation register and a clamp per load (5-7 % on a K without
 // a tail, which therefore has its own instance).  Groups of 32: 8x6048x7016 23.1 us (vector kernel) -> 12.7,
 // 16x2752x6888 14.4 (big-tile kernel) -> 9.8, 32x4128x4096 15.8 -> 10.7.
-template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false>
+//
+// STREAM: non-temporal weight loads (stream_weights in kernels.h).
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false, bool STREAM = false>
 __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
 {
     static_assert(!ACT || (WN == 1 && GPU == 1), "act-order: 64-column workgroups");
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
         const int last_step = TAIL ? min(3, a.K / 32 - 1 - 4 * uc) : 3;
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-            r.w[s] = *reinterpret_cast<const uint4 *>(
+            r.w[s] = load_words<STREAM>(
                 reinterpret_cast<const char *>(wrow + (size_t)(TAIL ? min(s, last_step) : s) * 4 * N) + voff_w);
         if (!ACT) {
         const int grp0 = GPU > 1 ? uc * GPU
