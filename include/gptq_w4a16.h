@@ -78,7 +78,7 @@ enum gptq_status {
  * group_size multiples of 64), larger M the big-tile fp16 MFMA kernel (with K slices where
  * the output tiles alone would not fill the chip).
  * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in a table of all
- * groups in LDS (as long as that fits: up to 636 groups); plan queries report it as kernel 1 (M <= 16) or 2 with
+ * groups in LDS (as long as that fits: up to 606 groups); plan queries report it as kernel 1 (M <= 16) or 2 with
  * 64-column tiles, an explicit request for either runs that kernel itself.
  * Accumulation is in fp32; the result differs from the exact sum by fp32 reassociation
  * and the final fp16 rounding only.  The same inputs give bit-identical outputs on every

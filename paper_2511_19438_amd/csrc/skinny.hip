@@ -106,14 +106,15 @@ int act_max_units(const Problem &p)
 
 }  // namespace
 
-// K must be a multiple of 32; groups may be of any size, the table of all of them has to fit the LDS (up to 636
-// groups: K = 28672 with groups of 64 does, with groups of 32 does not and stays with the general path).
+// K must be a multiple of 32; groups may be of any size, the table of all of them has to fit the LDS beside
+// the offsets of a slice (up to 606 groups: K = 28672 with groups of 64 does, with groups of 32 does not and stays with
+// the kernels of an explicit request).
 bool act_supported(const Problem &p)
 {
     if (p.g_idx == nullptr || p.M < 2 || p.N < 8 || p.K % 32 != 0)
         return false;
     const long long tiles = (long long)ceil_div(p.N, skinny::kCols) * ceil_div(p.M, skinny::kActRows);
-    return tiles <= kMaxColumnTiles && act_max_units(p) >= 4;
+    return tiles <= kMaxColumnTiles && act_max_units(p) >= 16;  // (fewer: the table would be laid out again for every few units)
 }
 
 void act_make_plan(const Problem &p, SkinnyPlan &plan)

@@ -33,6 +33,13 @@ def test_act_order_lookup_variant(B, M, K, N, group):
     assert np.array_equal(first.view(np.uint16), run_gemm(B, case, group).view(np.uint16))
 
 
+@pytest.mark.parametrize("M,K,group", [(2, 28672, 64), (17, 19392, 32), (40, 19392, 32)])  # 448 and 606 groups
+def test_act_order_lookup_variant_with_tables_as_large_as_the_lds(B, M, K, group):
+    case = workloads.make_case(M, K, 72, group, seed=M, act_order=True)
+    assert B.gptq_w4a16_plan_query(M, K, 72, group, True).tile == 64
+    check(B, case, group, f"{K // group} groups, M={M}")
+
+
 @pytest.mark.parametrize("M", [8, 40])
 def test_act_order_runs_on_a_workspace_without_room_for_slices(B, M):
     """Scratch that holds no partial sums: from 17 rows on the call gives up its slices, below it is refused as before."""
