@@ -428,13 +428,13 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
                     }
 #pragma unroll
                     for (int j = 0; j < 8; ++j) {
-                        const float keep = sl0 + j < a.split_k ? 1.f : 0.f;
+                        const bool keep = sl0 + j < a.split_k;  // (a select: 0 * infinity would be a NaN)
                         const f32x2_t lo = __builtin_bit_cast(f32x2_t, v[j][0]);
                         const f32x2_t hi = __builtin_bit_cast(f32x2_t, v[j][1]);
-                        s[0] += keep * lo[0];
-                        s[1] += keep * lo[1];
-                        s[2] += keep * hi[0];
-                        s[3] += keep * hi[1];
+                        s[0] += keep ? lo[0] : 0.f;
+                        s[1] += keep ? lo[1] : 0.f;
+                        s[2] += keep ? hi[0] : 0.f;
+                        s[3] += keep ? hi[1] : 0.f;
                     }
                 }
                 const half4_t o = {(half_t)s[0], (half_t)s[1], (half_t)s[2], (half_t)s[3]};

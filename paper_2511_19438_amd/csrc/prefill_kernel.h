@@ -243,12 +243,12 @@ __device__ __forceinline__ bool combine_slices(float (&v)[ACC], const Args &a, i
             }
 #pragma unroll
             for (int u = 0; u < G; ++u) {
-                const float keep = sl0 + u < a.split_k ? 1.f : 0.f;
+                const bool keep = sl0 + u < a.split_k;  // (a select: zero times an infinite sum would be a NaN)
 #pragma unroll
                 for (int p = 0; p < CH; ++p) {
                     const f32x2_t pair = __builtin_bit_cast(f32x2_t, part[u][p]);
-                    v[2 * (c0 + p)] += keep * pair[0];
-                    v[2 * (c0 + p) + 1] += keep * pair[1];
+                    v[2 * (c0 + p)] += keep ? pair[0] : 0.f;
+                    v[2 * (c0 + p) + 1] += keep ? pair[1] : 0.f;
                 }
             }
         }

@@ -140,3 +140,28 @@ def test_half_stage_groups_run_on_a_workspace_without_room_for_slices(B):
         check(B, case, group, "without slices")
     finally:
         B.gptq_w4a16_set_workspace(None)
+
+
+# ---- an infinity among the activations: its row is infinite where the weight is not zero, whatever the number of slices
+#      (a slice count that the batches of the exchange do not divide must not turn it into a NaN) ----
+
+@pytest.mark.parametrize("kernel,tile,M,group,split_k", [
+    (2, 5, 70, 128, 3), (2, 5, 70, 32, 5), (2, 3, 70, 128, 3), (2, 3, 130, 32, 3), (2, 8, 130, 32, 3),
+    (4, 64, 40, 128, 3), (4, 64, 90, 64, 3), (3, 64, 24, 32, 3), (0, 0, 40, 32, 0)])
+def test_an_infinity_survives_the_exchange_of_k_slices(B, kernel, tile, M, group, split_k):
+    K, N = 1536, 136  # (24 stages: every wavefront of the mid-batch kernel has whole stages of its own)
+    case = workloads.make_case(M, K, N, group, seed=M + split_k)
+    plan = B.Plan(kernel=kernel, tile=tile, split_k=split_k)
+    resolved = B.gptq_w4a16_plan_query(M, K, N, group, False, plan)
+    assert resolved.split_k > 1 and kernel in (0, resolved.kernel)
+    w = oracle.dequant(case["qweight"], case["qzeros"], case["scales"], None, group).astype(np.float64)
+    ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group)
+    for k in (5, K - 7):  # in the first slice and in the last
+        x = case["x"].copy()
+        x[3, k] = np.float16(np.inf)
+        out = run_gemm(B, dict(case, x=x), group, plan)
+        assert np.array_equal(np.isnan(out[3]), w[k] == 0), f"infinity at k = {k}"
+        hit = w[k] != 0
+        assert np.array_equal(out[3][hit], (np.sign(w[k][hit]) * np.inf).astype(np.float16))
+        rows = np.arange(M) != 3
+        assert_within_band(out[rows], ref[rows], "the other rows")
