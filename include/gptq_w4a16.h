@@ -79,7 +79,8 @@ enum gptq_status {
  * the output tiles alone would not fill the chip).
  * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in a table of all
  * groups in LDS (as long as that fits: up to 606 groups); plan queries report it as kernel 1 (M <= 16) or 2 with
- * 64-column tiles, an explicit request for either runs that kernel itself.
+ * 64-column tiles and the flag GPTQ_ACT_LOOKUP, and such a plan given back runs it again.  An explicit request for
+ * either kernel without the flag runs that kernel itself.
  * Accumulation is in fp32; the result differs from the exact sum by fp32 reassociation
  * and the final fp16 rounding only.  The same inputs give bit-identical outputs on every
  * call (no floating point atomics are used).
@@ -115,6 +116,7 @@ GPTQ_API int gptq_w4a16_gemm_static(const void *x, const void *qweight, const vo
 #define GPTQ_ABLATE_VML 2
 #define GPTQ_ABLATE_ILA 4
 #define GPTQ_VECTOR_DOT 8
+#define GPTQ_ACT_LOOKUP 16
 
 typedef struct gptq_w4a16_plan {
     int kernel;      /* 0 auto, 1 vector split-K kernel (any M, processed 16 rows at a time), 2 big-tile MFMA kernel,
@@ -131,7 +133,8 @@ typedef struct gptq_w4a16_plan {
                         MFMA kernel: tile id = rows x columns per workgroup (wavefront grid):
                         1 256x256 (1x4), 3 128x128 (2x2), 5 64x128 (1x4), 8 128x256 (1x4, two workgroups
                         per compute unit, or two wavefront groups of one that split its K slice; 96 rows instead of
-                        128 where that pads the batch less); 0 auto; any other id is GPTQ_INVALID_ARG */
+                        128 where that pads the batch less); 0 auto; any other id is GPTQ_INVALID_ARG;
+                        with GPTQ_ACT_LOOKUP: 0 or 64 */
     int flags;       /* 0, or (vector kernel only: M <= 4, no g_idx, group_size % 32 == 0, 64-column tiles) a set
                         of ablation switches that take one of the paper's techniques out each, for measuring its
                         gain in isolation (Table 3's columns at kernel level):
@@ -143,7 +146,11 @@ typedef struct gptq_w4a16_plan {
                                            half arithmetic (Section 3.3);
                         and one comparison switch without restrictions on the problem:
                         8 GPTQ_VECTOR_DOT  contract the packed codes with v_dot2_f32_f16 on the vector ALU instead
-                                           of 4x4x4 MFMAs (the default up to four rows) */
+                                           of 4x4x4 MFMAs (the default up to four rows);
+                        or, alone and with kernel 1 or 2:
+                       16 GPTQ_ACT_LOOKUP  the small-batch kernel's act-order variant with lookups in LDS (g_idx,
+                                           M >= 2, K % 32 == 0, at most 606 groups; GPTQ_UNSUPPORTED_SHAPE
+                                           otherwise, without g_idx GPTQ_INVALID_ARG) */
     int reserved[4]; /* must be zero */
 } gptq_w4a16_plan_t;
 
@@ -183,8 +190,9 @@ GPTQ_API int gptq_w4a16_gemm_prepared(const void *x, const void *qweight_sorted,
  * Host-only: what gptq_w4a16_gemm_plan(..., request) would run for a problem of this shape.
  * `act_order` non-zero means a g_idx array would be passed; `request` may be NULL (automatic).
  * On success *resolved holds the kernel id (1 to 4, never 0), its number of K slices and its tile
- * (vector, small-batch and mid-batch kernels: columns per workgroup; big-tile MFMA kernel: tile id).  Touches no
- * device.  Errors as for gptq_w4a16_gemm_plan's shape and plan checks.
+ * (vector, small-batch and mid-batch kernels: columns per workgroup; big-tile MFMA kernel: tile id) and its flags.
+ * The plan of an automatic call, given back as a request, names the same kernel, variant, tile and number of slices.
+ * Touches no device.  Errors as for gptq_w4a16_gemm_plan's shape and plan checks.
  */
 GPTQ_API int gptq_w4a16_plan_query(int M, int K, int N, int group_size, int act_order,
                                    const gptq_w4a16_plan_t *request, gptq_w4a16_plan_t *resolved);

@@ -191,11 +191,12 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
 {
     Resolved r = {};
     int kernel = plan ? plan->kernel : 0;
-    if (kernel == 0 && act_supported(p)) {
+    const bool lookup = plan && (plan->flags & GPTQ_ACT_LOOKUP) != 0;  // (check_flags: the problem has the variant)
+    if (lookup || (kernel == 0 && act_supported(p))) {
         // act-order as stored: the lookup variant for every batch of two rows and more.  Reported under the ids of
         // the kernels that serve an explicit request there (the vector kernel up to 16 rows, the big-tile kernel's
-        // general path above).
-        r.kernel = (p.M <= kDecodeMaxM) ? 1 : 2;
+        // general path above), with a flag that tells it from them.
+        r.kernel = lookup ? kernel : (p.M <= kDecodeMaxM) ? 1 : 2;
         r.act = true;
         r.skinny.split_k = plan ? plan->split_k : 0;
         act_make_plan(p, r.skinny);
@@ -327,15 +328,28 @@ int check_plan(const gptq_w4a16_plan_t *plan)
         return GPTQ_OK;
     if (plan->kernel < 0 || plan->kernel > 4 || plan->split_k < 0 || plan->tile < 0)
         return GPTQ_INVALID_ARG;
+    for (int i = 0; i < 4; ++i)
+        if (plan->reserved[i] != 0)
+            return GPTQ_INVALID_ARG;
+    if (plan->flags == GPTQ_ACT_LOOKUP)
+        return (plan->kernel == 1 || plan->kernel == 2) && (plan->tile == 0 || plan->tile == 64) ? GPTQ_OK
+                                                                                                  : GPTQ_INVALID_ARG;
     // the ablation switches belong to the vector kernel
     if (plan->flags < 0 || plan->flags > 15 || (plan->flags != 0 && plan->kernel != 1))
         return GPTQ_INVALID_ARG;
     if (plan->kernel == 2 && plan->tile != 0 && !prefill_tile_exists(plan->tile))
         return GPTQ_INVALID_ARG;
-    for (int i = 0; i < 4; ++i)
-        if (plan->reserved[i] != 0)
-            return GPTQ_INVALID_ARG;
     return GPTQ_OK;
+}
+
+// Whether the problem has the variants that a plan's flags ask for.
+int check_flags(const Problem &p, const gptq_w4a16_plan_t *plan)
+{
+    if (!plan)
+        return GPTQ_OK;
+    if (plan->flags == GPTQ_ACT_LOOKUP)
+        return !p.g_idx ? GPTQ_INVALID_ARG : act_supported(p) ? GPTQ_OK : GPTQ_UNSUPPORTED_SHAPE;
+    return (plan->flags & 7) != 0 && !decode_ablation_supported(p) ? GPTQ_UNSUPPORTED_SHAPE : GPTQ_OK;
 }
 
 // Validates the arguments of a GEMM call and fills `p`.
@@ -362,9 +376,7 @@ int make_problem(const void *x, const void *qweight, const void *qzeros, const v
     p.K = K;
     p.N = N;
     p.group_size = group_size;
-    if (plan && (plan->flags & 7) != 0 && !decode_ablation_supported(p))
-        return GPTQ_UNSUPPORTED_SHAPE;
-    return GPTQ_OK;
+    return check_flags(p, plan);
 }
 
 }  // namespace
@@ -425,14 +437,16 @@ int gptq_w4a16_plan_query(int M, int K, int N, int group_size, int act_order, co
     p.K = K;
     p.N = N;
     p.group_size = group_size;
-    if (request && (request->flags & 7) != 0 && !decode_ablation_supported(p))
-        return GPTQ_UNSUPPORTED_SHAPE;
+    const int frc = check_flags(p, request);
+    if (frc != GPTQ_OK)
+        return frc;
     const Resolved r = resolve(p, request);
     gptq_w4a16_plan_t out = {};
     out.kernel = r.kernel;
     if (r.act) {
         out.split_k = r.skinny.split_k;
         out.tile = r.skinny.cols_per_wg;
+        out.flags = GPTQ_ACT_LOOKUP;
     } else if (r.kernel == 1) {
         out.split_k = r.decode.split_k;
         out.tile = r.decode.cols_per_wg;

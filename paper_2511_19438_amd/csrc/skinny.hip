@@ -125,6 +125,16 @@ void act_make_plan(const Problem &p, SkinnyPlan &plan)
     plan.cols_per_wg = skinny::kCols;
     int split = plan.split_k;
     int quantum = 1;
+    if (split > 0) {
+        // a request for the automatic plan's slices (a queried plan given back) is the automatic plan: its slices are
+        // whole multiples of a quantum, which the number of slices alone does not tell
+        SkinnyPlan automatic = {};
+        act_make_plan(p, automatic);
+        if (automatic.split_k == split) {
+            plan = automatic;
+            return;
+        }
+    }
     if (split <= 0) {
         // One workgroup per compute unit, as in the plain format: measured best of 1, 2, 3, 4, 6 and 8 slices on
         // 4096x11008 (M = 8: 12.7 us unsplit, 15.4 in two), 11008x4096 (25.9 unsplit, 13.7 in four, 15.2 in eight)

@@ -40,6 +40,16 @@ def test_act_order_lookup_variant_with_tables_as_large_as_the_lds(B, M, K, group
     check(B, case, group, f"{K // group} groups, M={M}")
 
 
+@pytest.mark.parametrize("M,K,N,group", [(2, 1280, 264, 128), (8, 4096, 1032, 128), (16, 1376, 4104, 32), (40, 2048, 264, 64),
+                                         (130, 4096, 520, 128)])
+def test_a_queried_act_order_plan_runs_the_automatic_call_again(B, M, K, N, group):
+    case = workloads.make_case(M, K, N, group, seed=M, act_order=True)
+    plan = B.gptq_w4a16_plan_query(M, K, N, group, True)
+    assert plan.flags == 16
+    assert np.array_equal(run_gemm(B, case, group, plan).view(np.uint16), run_gemm(B, case, group).view(np.uint16))
+    check(B, case, group, "three slices", B.Plan(kernel=plan.kernel, split_k=3, flags=16))
+
+
 @pytest.mark.parametrize("M", [8, 40])
 def test_act_order_runs_on_a_workspace_without_room_for_slices(B, M):
     """Scratch that holds no partial sums: from 17 rows on the call gives up its slices, below it is refused as before."""

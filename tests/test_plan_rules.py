@@ -39,3 +39,43 @@ def test_automatic_slices_fit_the_static_scratch_block_and_the_grid(B):
         if pl.tile == 8 and pl.split_k > 1:
             assert tiles * pl.split_k <= 256, (M, K, N, pl.split_k)
             assert B.gptq_w4a16_workspace_bytes(M, K, N, group) >= pl.split_k * tiles * bm * bn * 4
+
+
+def fields(plan):
+    return plan.kernel, plan.split_k, plan.tile, plan.flags
+
+
+def test_a_queried_plan_given_back_resolves_to_itself(B):
+    """Every automatic plan is a valid request for itself, act-order lookups (flag 16) among them."""
+    rng = random.Random(11)
+    lookups = 0
+    for _ in range(2000):
+        group = rng.choice([8, 16, 32, 64, 96, 128, 256])
+        K, N = group * rng.randint(1, 28672 // group), 8 * rng.randint(1, 4000)
+        M, act = int(2 ** rng.uniform(0, 11)), rng.random() < 0.5
+        auto = B.gptq_w4a16_plan_query(M, K, N, group, act)
+        again = B.gptq_w4a16_plan_query(M, K, N, group, act, auto)
+        assert fields(again) == fields(auto), (M, K, N, group, act, fields(auto), fields(again))
+        lookups += auto.flags == 16
+        assert auto.flags == 0 or act
+    assert lookups > 300
+
+
+def test_the_act_order_lookup_flag_is_refused_where_there_is_no_such_variant(B):
+    def code(plan, M=8, K=1024, act=True, group=128):
+        try:
+            B.gptq_w4a16_plan_query(M, K, 264, group, act, plan)
+        except B.GptqError as e:
+            return e.code
+        return 0
+
+    assert [code(B.Plan(kernel=k, flags=16)) for k in (0, 1, 2, 3, 4)] == [-1, 0, 0, -1, -1]
+    assert [code(B.Plan(kernel=2, tile=t, flags=16)) for t in (0, 3, 64, 128)] == [0, -1, 0, -1]
+    assert code(B.Plan(kernel=2, tile=64)) == -1 and code(B.Plan(kernel=1, flags=17)) == -1
+    assert code(B.Plan(kernel=1, flags=16), act=False) == -1
+    assert code(B.Plan(kernel=1, flags=16), M=1) == -2
+    assert code(B.Plan(kernel=2, flags=16), K=1032, group=8) == -2   # K % 32
+    assert code(B.Plan(kernel=2, flags=16), K=28672, group=32) == -2  # 896 groups do not fit the LDS
+    # without the flag the named kernels themselves
+    assert fields(B.gptq_w4a16_plan_query(8, 4096, 4096, 128, True, B.Plan(kernel=1)))[3] == 0
+    assert fields(B.gptq_w4a16_plan_query(40, 4096, 4096, 128, True, B.Plan(kernel=2)))[2:] == (3, 0)
