@@ -280,9 +280,12 @@ int launch_resolved(const Problem &p, const Resolved &r, void *ws, hipStream_t s
 // the big-tile kernel's HALF variant pipelines) must not fail where the scratch of their K slices cannot be had - a
 // workspace of the caller's that is too small, growth under capture, the static block: they give up the slices.
 // Act-order up to 16 rows, and where the lookup variant cannot do without slices, takes the kernel of an explicit
-// request, with that kernel's own needs.  False: nothing else to try.
-bool fall_back(const Problem &p, Resolved &r)
+// request, with that kernel's own needs.  A number of slices that the caller asked for is never given up.  False:
+// nothing else to try.
+bool fall_back(const Problem &p, const gptq_w4a16_plan_t *request, Resolved &r)
 {
+    if (request && request->split_k > 0)
+        return false;
     if (r.kernel == 2 && !r.act && r.prefill.split_k > 1 && prefill_slices_optional(p)) {
         r.prefill.split_k = 1;
         r.prefill.tile = 0;
@@ -312,7 +315,7 @@ int run_gemm(const Problem &p, hipStream_t stream, const gptq_w4a16_plan_t *plan
         const int rc = bytes > 0 ? acquire_workspace(bytes, stream, &ws) : GPTQ_OK;
         if (rc == GPTQ_OK)
             return launch_resolved(p, r, ws, stream);
-        if (rc != GPTQ_WORKSPACE_TOO_SMALL || !fall_back(p, r))
+        if (rc != GPTQ_WORKSPACE_TOO_SMALL || !fall_back(p, plan, r))
             return rc;
     }
 }
@@ -404,7 +407,7 @@ int gptq_w4a16_gemm_static(const void *x, const void *qweight, const void *qzero
         return rc;
     Resolved r = resolve(p, nullptr);
     while (scratch_bytes(p, r) > kStaticScratchBytes)
-        if (!fall_back(p, r))
+        if (!fall_back(p, nullptr, r))
             return GPTQ_STATIC_SCRATCH_EXCEEDED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     void *ws = nullptr;
