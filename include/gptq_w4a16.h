@@ -83,7 +83,7 @@ enum gptq_status {
  * either kernel without the flag runs that kernel itself.
  * Accumulation is in fp32; the result differs from the exact sum by fp32 reassociation
  * and the final fp16 rounding only.  The same inputs give bit-identical outputs on every
- * call (no floating point atomics are used).
+ * call (no floating point atomics are used), whatever scratch the call finds.
  */
 GPTQ_API int gptq_w4a16_gemm(const void *x, const void *qweight, const void *qzeros, const void *scales,
                     const void *g_idx, void *out, int M, int K, int N, int group_size,
@@ -95,7 +95,8 @@ GPTQ_API int gptq_w4a16_gemm(const void *x, const void *qweight, const void *qze
  * results as gptq_w4a16_gemm, but the split-K scratch (partial sums and arrival counters) is a fixed block of
  * GPTQ_STATIC_SCRATCH_BYTES inside the library's device image: every GPU the library runs on holds it until the
  * process ends, and the call makes no hipMalloc / hipFree and ignores gptq_w4a16_set_workspace().  A problem
- * whose plan needs more scratch returns GPTQ_STATIC_SCRATCH_EXCEEDED and enqueues nothing (needs are
+ * whose plan needs more scratch (and cannot do without, see gptq_w4a16_workspace_bytes) returns
+ * GPTQ_STATIC_SCRATCH_EXCEEDED and enqueues nothing (needs are
  * 256 KiB + 4 * slices * M * N bytes where the plan splits K, which it does only while the output is small; the
  * largest need among the Llama-7B/70B layer shapes for M up to 2048 is 32.3 MiB, at 1024 x 11008 x 4096; the slices of
  * the big-tile kernel and of act-order problems are chosen to fit the block).  The first call on a
@@ -231,7 +232,13 @@ GPTQ_API int gptq_w4a16_unpack(const void *qweight, void *q_out, const void *qze
  * launches in flight and HIP graphs captured earlier keep working on it, so later growth never invalidates a
  * captured graph.  Growth is refused (GPTQ_WORKSPACE_TOO_SMALL, nothing enqueued) while `stream` is being
  * captured, since it allocates and clears memory: make one eager call of every problem a graph will hold
- * before capturing it, or use gptq_w4a16_gemm_static.  A graph replay and an eager call that use different
+ * before capturing it, or use gptq_w4a16_gemm_static.
+ * Some automatic plans can do without the scratch of their slices: act-order problems, and the big-tile kernel on
+ * groups or widths that are no multiples of 64 and 32.  Where it cannot be had, as above or on a workspace that
+ * is too small, every workgroup walks the slices itself, one after the other, and adds them in the same order: the
+ * result is the same, the call is slower by up to as many times as it has slices, and a graph that captured it
+ * stays so.  Such a call needs no scratch from 17 rows on, and up to 16 rows what the vector kernel takes for the
+ * problem.  A number of slices that an explicit plan names is never given up.  A graph replay and an eager call that use different
  * blocks do not share arrival counters; two pieces of work that share one block must not overlap in time.
  * gptq_w4a16_set_workspace() hands over caller-owned device memory (256-byte aligned, at least
  * gptq_w4a16_workspace_bytes() of the problems it will serve) instead; it synchronises the device, frees

@@ -185,6 +185,7 @@ struct Resolved {
     SkinnyPlan skinny;
     MidPlan mid;
     PrefillPlan prefill;
+    size_t least;  // bytes of scratch that are asked for even if the launch needs less
 };
 
 Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
@@ -249,15 +250,18 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
 
 size_t scratch_bytes(const Problem &p, const Resolved &r)
 {
+    size_t bytes;
     if (r.act)
-        return act_workspace_bytes(p, r.skinny);
-    if (r.kernel == 1)
-        return decode_workspace_bytes(p, r.decode);
-    if (r.kernel == 3)
-        return skinny_workspace_bytes(p, r.skinny);
-    if (r.kernel == 4)
-        return mid_workspace_bytes(p, r.mid);
-    return prefill_workspace_bytes(p, r.prefill);  // 0 unless K is split
+        bytes = act_workspace_bytes(p, r.skinny);
+    else if (r.kernel == 1)
+        bytes = decode_workspace_bytes(p, r.decode);
+    else if (r.kernel == 3)
+        bytes = skinny_workspace_bytes(p, r.skinny);
+    else if (r.kernel == 4)
+        bytes = mid_workspace_bytes(p, r.mid);
+    else
+        bytes = prefill_workspace_bytes(p, r.prefill);  // 0 unless K is split
+    return bytes > r.least ? bytes : r.least;
 }
 
 int launch_resolved(const Problem &p, const Resolved &r, void *ws, hipStream_t stream)
@@ -276,33 +280,33 @@ int launch_resolved(const Problem &p, const Resolved &r, void *ws, hipStream_t s
     return err == hipSuccess ? GPTQ_OK : GPTQ_HIP_ERROR;
 }
 
-// Formats that need no scratch in their most general kernel (act-order from 17 rows on, groups or widths that only
-// the big-tile kernel's HALF variant pipelines) must not fail where the scratch of their K slices cannot be had - a
-// workspace of the caller's that is too small, growth under capture, the static block: they give up the slices.
-// Act-order up to 16 rows, and where the lookup variant cannot do without slices, takes the kernel of an explicit
-// request, with that kernel's own needs.  A number of slices that the caller asked for is never given up.  False:
-// nothing else to try.
+// Scratch that a call may rely on the caller for, whatever its plan would like: what the vector kernel takes for up to 16
+// rows, nothing above and nothing for the big-tile kernel.
+size_t required_scratch(const Problem &p, const gptq_w4a16_plan_t *request)
+{
+    if (p.M > kDecodeMaxM || (request && request->kernel == 2))
+        return 0;
+    gptq_w4a16_plan_t vector = {};
+    vector.kernel = 1;
+    return scratch_bytes(p, resolve(p, &vector));
+}
+
+// Formats that run without scratch in their most general kernel (act-order, groups or widths that only the big-tile
+// kernel's HALF variant pipelines) must not fail where the scratch of their K slices cannot be had - a workspace of the
+// caller's that is too small, growth under capture, the static block: every workgroup then walks the slices itself, in
+// the same order, so that the result does not depend on the scratch.  A number of slices that the caller asked for is
+// never given up.  False: the call needs what it needs.
 bool fall_back(const Problem &p, const gptq_w4a16_plan_t *request, Resolved &r)
 {
-    if (request && request->split_k > 0)
+    if (r.skinny.serial || r.prefill.serial || (request && request->split_k > 0))
         return false;
-    if (r.kernel == 2 && !r.act && r.prefill.split_k > 1 && prefill_slices_optional(p)) {
-        r.prefill.split_k = 1;
-        r.prefill.tile = 0;
-        prefill_make_plan(p, r.prefill);
-        return true;
-    }
-    if (!r.act)
+    if (r.act)
+        r.skinny.serial = true;
+    else if (r.kernel == 2 && r.prefill.split_k > 1 && prefill_slices_optional(p))
+        r.prefill.serial = true;
+    else
         return false;
-    if (r.kernel == 2 && r.skinny.split_k > 1) {
-        r.skinny.split_k = 1;
-        act_make_plan(p, r.skinny);
-        if (r.skinny.split_k == 1)
-            return true;
-    }
-    gptq_w4a16_plan_t plan = {};
-    plan.kernel = r.kernel;
-    r = resolve(p, &plan);
+    r.least = required_scratch(p, request);
     return true;
 }
 

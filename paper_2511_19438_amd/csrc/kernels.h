@@ -89,6 +89,7 @@ struct SkinnyPlan {
                           // or 256 (four wavefronts side by side); 0 = choose
     int split_k;          // number of K slices (0 = choose)
     int units_per_slice;  // 128-k units per slice
+    bool serial;          // every workgroup walks all slices one after the other: no scratch, the same bits
 };
 bool skinny_supported(const Problem &p);
 void skinny_make_plan(const Problem &p, SkinnyPlan &plan);
@@ -118,6 +119,7 @@ struct PrefillPlan {
     int tile;     // tile configuration id (1-based), 0 = auto
     int split_k;  // K slices (pipelined kernel only), 0 = auto
     int rows;     // filled in: rows of tile 8's workgroups, 96 or 128
+    bool serial;  // every workgroup walks all slices one after the other: no scratch, the same bits (tile 5 in any case)
 };
 bool prefill_supported(const Problem &p);
 // Whether the pipelined kernel (tiles, K slices) takes the problem; else the general path does.

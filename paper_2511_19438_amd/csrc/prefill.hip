@@ -182,7 +182,7 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
                 continue;
             last_slices = slices;
             // (automatic slices stay within the static scratch block, so that gptq_w4a16_gemm_static runs the same plan)
-            PrefillPlan candidate = {t, slices, 0};
+            PrefillPlan candidate = {t, slices, 0, false};
             if (!split_given && slices > 1 && prefill_workspace_bytes(p, candidate) > GPTQ_STATIC_SCRATCH_BYTES)
                 continue;
             for (int rows = 128; rows >= (t == 8 && try96 ? 96 : 128); rows -= 32) {
@@ -208,7 +208,7 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
 
 size_t prefill_workspace_bytes(const Problem &p, const PrefillPlan &plan)
 {
-    if (plan.split_k <= 1 || !prefill_tile_exists(plan.tile))
+    if (plan.split_k <= 1 || plan.serial || !prefill_tile_exists(plan.tile))
         return 0;
     const TileShape &ts = kTiles[plan.tile];
     // (tile 8 runs with 96 rows only where they cover no more rows in all)
@@ -232,6 +232,8 @@ hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *works
     a.tiles_m = a.tiles_n = 0;
     a.split_k = (workspace && plan.split_k > 1) ? plan.split_k : 1;
     a.stages_per_slice = 0;
+    a.serial_slices = 0;
+    a.serial_kw = 1;
     a.counters = reinterpret_cast<unsigned *>(workspace);
     a.partial = workspace ? reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + kCounterBytes) : nullptr;
     if (a.split_k > 1 && (size_t)ceil_div_i(p.M, plan.tile == 8 ? plan.rows : kTiles[plan.tile].bm) *
@@ -239,6 +241,12 @@ hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *works
                              kCounterBytes / sizeof(unsigned))
         a.split_k = 1;  // more tiles than arrival counters: such a problem needs no split anyway
     const int mode = mode_of(p);
+    if (plan.serial) {
+        a.split_k = 1;
+        a.serial_slices = plan.split_k;
+        a.serial_kw = plan.tile == 8 ? k_groups_of_tile8(p, plan.rows, plan.split_k) : 1;
+        return prefill::launch_tile<5>(a, mode, 1, stream);
+    }
     switch (plan.tile) {
     case 1: return prefill::launch_tile<1>(a, mode, 1, stream);
     case 3: return prefill::launch_tile<3>(a, mode, 1, stream);

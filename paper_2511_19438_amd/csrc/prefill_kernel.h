@@ -71,6 +71,8 @@ struct Args {
     int stages_per_slice;
     float *partial;         // [split_k][tiles][accumulators per thread][256 threads] fp32 (see combine_slices)
     unsigned *counters;     // [tiles], zero between launches
+    // SERIAL only: the slices that a workgroup walks (split_k is 1), and the wavefront groups that would have shared each
+    int serial_slices, serial_kw;
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -297,11 +299,17 @@ constexpr int kWavesPerSimd = (BM * BN <= 128 * 256) ? 2 : 1;
 // stage takes 0.99 us alone on a compute unit, 1.31 us when two run), and where the tiles give every compute unit one
 // workgroup at most, this is how they get there without partial sums in scratch. 
 // 4096x12288 at M = 512: 73.5 -> 58.0 us; 28672x8192 at M = 512, two slices: 266 -> 226.
-template <int BM, int BN, int WM, int WN, int BK, int NBUF, bool HALF = false, int KW = 1>
+//
+// SERIAL: no scratch for the K slices.  A workgroup walks all slices of its tile one after the other - the halves of a
+// slice that two wavefront groups would have shared, too - and adds their sums in the order of the sliced launch, so the
+// bits are those of that launch whatever its tile was.  For the 64x128 tile only, whose accumulators leave room for
+// the sums.  Slower than slices in parallel, and never chosen where scratch can be had.
+template <int BM, int BN, int WM, int WN, int BK, int NBUF, bool HALF = false, int KW = 1, bool SERIAL = false>
 __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefill_pipelined_kernel(const Args a)
 {
     static_assert(KW == 1 || (KW == 2 && BM * BN <= 128 * 256), "two wavefronts per SIMD have 256 registers each");
     static_assert(!HALF || BK == 64, "two 32-k halves");
+    static_assert(!SERIAL || (KW == 1 && BM * BN <= 64 * 128), "32 accumulators, their sum and a half's");
     static_assert(WM * WN == 4, "four wavefronts per workgroup");
     static_assert(BK == 32 || BK == 64, "stage of 32 or 64 k");
     static_assert(NBUF >= 3, "ring of at least three stage buffers");
@@ -343,18 +351,31 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     const int N = a.N, K = a.K, M = a.M;
     // K is a multiple of the group size, which is a multiple of 64 (HALF: of 32, and K may end half-way)
     const int all_stages = HALF ? (K + BK - 1) / BK : K / BK;
-    // this workgroup's stages: [wg_first, wg_first + wg_stages); a group's: [first, first + stages), maybe none
-    const int wg_first = slice * a.stages_per_slice;
-    const int wg_stages = min(a.stages_per_slice, all_stages - wg_first);
-    const int lead = KW == 1 ? wg_stages : (wg_stages + 1) / 2;  // stages of the first group: no group has more
-    const int stages = kgroup == 0 ? lead : wg_stages - lead;
-    const int first = wg_first + (stages > 0 ? kgroup * lead : 0);
-    const int last = first + max(stages, 1) - 1;
     const int col_local = wn * WAVE_N + TN * lj;  // first of this lane's TN columns inside the tile
     const int col_raw = n0 + col_local;
     const bool col_ok = col_raw < N;
-
     float16_t acc[TM][TN];
+    const int groups = SERIAL ? a.serial_kw : KW;
+    float16_t total[SERIAL ? TM : 1][SERIAL ? TN : 1], half_sum[SERIAL ? TM : 1][SERIAL ? TN : 1];
+    if (SERIAL) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    total[i][t][r] = half_sum[i][t][r] = 0.f;
+    }
+    int group = kgroup;  // SERIAL: the groups of every slice, one after the other
+    for (;;) {           // (a single pass unless SERIAL; the body, up to the sums, is not indented)
+    // this workgroup's stages: [wg_first, wg_first + wg_stages); a group's: [first, first + stages), maybe none
+    const int wg_first = slice * a.stages_per_slice;
+    const int wg_stages = min(a.stages_per_slice, all_stages - wg_first);
+    const int lead = groups == 1 ? wg_stages : (wg_stages + 1) / 2;  // stages of the first group: no group has more
+    const int stages = group == 0 ? lead : wg_stages - lead;
+    const int first = wg_first + (stages > 0 ? group * lead : 0);
+    const int last = first + max(stages, 1) - 1;
+
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -412,7 +433,7 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     const int first_half = 2 * first - (k_tail && first == all_stages - 1 ? 1 : 0);
     // the last stage within its group's stages (the barrier that goes with clearing it is everybody's), or none
     const bool wg_tail = k_tail && wg_first + wg_stages == all_stages;
-    const int tail_group = KW == 1 || wg_stages == 1 ? 0 : 1;
+    const int tail_group = groups == 1 || wg_stages == 1 ? 0 : 1;
     const int tail_stage = wg_tail ? (tail_group == 0 ? lead : wg_stages - lead) - 1 : -2;
 
     // The stage whose loads are issued next, as running source pointers (uniform for the activations and the
@@ -491,7 +512,7 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     // Clears the activations of the first half of the last stage (see above) once the stage is in LDS; the barrier
     // stands before any wavefront's first read of them.
     auto clear_repeated_half = [&](int ring) {
-        for (int slot = tid; slot < (kgroup == tail_group ? BM * 4 : 0); slot += kThreads) {
+        for (int slot = tid; slot < (group == tail_group ? BM * 4 : 0); slot += kThreads) {
             const int row = slot >> 2;
             const int ch = (slot & 3) ^ ((row / RPB) & (CH - 1));
             *reinterpret_cast<uint4 *>(smem + (size_t)ring * L::BYTES + (size_t)(row * CH + ch) * 16) =
@@ -731,6 +752,37 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     for (int i = 0; i < TM; ++i)
         asm volatile("" : "+v"(afr[0][i]), "+v"(afr[1][i]));
 
+    if (SERIAL) {
+        if (group + 1 < groups) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+                    half_sum[i][t] = acc[i][t];
+            ++group;
+        } else {
+            // (as the sliced launch: two halves to a slice, and the slices to zero)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+                    total[i][t] += groups > 1 ? half_sum[i][t] + acc[i][t] : acc[i][t];
+            group = 0;
+            ++slice;
+        }
+        if (slice < a.serial_slices) {
+            __syncthreads();  // every wavefront has its operands: the next loads may overwrite the ring
+            continue;
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+                acc[i][t] = total[i][t];
+    }
+    break;
+    }
+
     if (KW > 1) {
         // the second group's sums go to the first through LDS (the rings are done with: every DMA has landed),
         // four values per access, [value / 4][thread]
@@ -761,7 +813,7 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
                     }
         }
     }
-    if (a.split_k > 1) {
+    if (!SERIAL && a.split_k > 1) {
         constexpr int ACC = TM * TN * 16;
         float flat[ACC];
 #pragma unroll

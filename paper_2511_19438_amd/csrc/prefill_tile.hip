@@ -41,6 +41,8 @@ hipError_t launch(Kernel kernel, Args a, size_t lds, bool may_split, hipStream_t
     a.stages_per_slice = (all_stages + split - 1) / split;
     split = (all_stages + a.stages_per_slice - 1) / a.stages_per_slice;
     a.split_k = split;
+    if (a.serial_slices > 1)
+        a.stages_per_slice = (all_stages + a.serial_slices - 1) / a.serial_slices;  // of the workgroup's own slices
     const unsigned grid = 8u * (unsigned)((total + 7) / 8) * (unsigned)split;
     if (lds > 48 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
@@ -66,6 +68,13 @@ hipError_t launch_tile<GPTQ_PREFILL_TILE>(const Args &a, int mode, int kw, hipSt
                       2 * (size_t)NBUF * StageLayout<BM, BN, BK, true>::BYTES, true, stream, 2);
 #endif
     if (kw != 1)
+        return hipErrorInvalidValue;
+#if GPTQ_PREFILL_TILE == 5
+    if (a.serial_slices > 1 && mode == kGroupPerHalf)
+        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, true, 1, true>, a,
+                      (size_t)NBUF * StageLayout<BM, BN, BK, true>::BYTES, false, stream);
+#endif
+    if (a.serial_slices > 1)
         return hipErrorInvalidValue;
     if (mode == kGroupPerStage)
         return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF>, a,

@@ -38,17 +38,19 @@ int waves_of(int tiles_n, int split_k, int wn, int tm)
     return (wn == 1 && tm <= 2 && (long long)tiles_n * split_k <= 256) ? 8 : 4;
 }
 
-template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false, bool STREAM = false>
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false, bool STREAM = false,
+          bool SERIAL = false>
 hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
 {
-    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU, ACT, TAIL, STREAM>;
+    auto kernel = skinny::skinny_kernel<TM, WN, WAVES, GPU, ACT, TAIL, STREAM, SERIAL>;
     if (lds > 48 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess)
             return err;
     }
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.tiles_n * a.row_tiles * a.split_k)), dim3(64 * WAVES), lds, stream, a);
+    const unsigned grid = (unsigned)(a.tiles_n * a.row_tiles * (SERIAL ? 1 : a.split_k));
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * WAVES), lds, stream, a);
     return hipGetLastError();
 }
 
@@ -72,16 +74,16 @@ hipError_t launch_small_groups(const skinny::Args &a, int tm, int waves, size_t 
 }
 
 // Act-order with lookups.
-template <bool TAIL>
+template <bool TAIL, bool SERIAL>
 hipError_t launch_lookup(const skinny::Args &a, int tm, int waves, size_t lds, hipStream_t stream)
 {
     if (tm == 1)
-        return waves == 8 ? launch_tm<1, 1, 8, 1, true, TAIL>(a, lds, stream)
-                          : launch_tm<1, 1, 4, 1, true, TAIL>(a, lds, stream);
+        return waves == 8 ? launch_tm<1, 1, 8, 1, true, TAIL, false, SERIAL>(a, lds, stream)
+                          : launch_tm<1, 1, 4, 1, true, TAIL, false, SERIAL>(a, lds, stream);
     if (tm == 2)
-        return waves == 8 ? launch_tm<2, 1, 8, 1, true, TAIL>(a, lds, stream)
-                          : launch_tm<2, 1, 4, 1, true, TAIL>(a, lds, stream);
-    return launch_tm<4, 1, 4, 1, true, TAIL>(a, lds, stream);
+        return waves == 8 ? launch_tm<2, 1, 8, 1, true, TAIL, false, SERIAL>(a, lds, stream)
+                          : launch_tm<2, 1, 4, 1, true, TAIL, false, SERIAL>(a, lds, stream);
+    return launch_tm<4, 1, 4, 1, true, TAIL, false, SERIAL>(a, lds, stream);
 }
 
 // LDS that a workgroup of the act-order variant may use (the rest holds its static words).
@@ -165,7 +167,7 @@ void act_make_plan(const Problem &p, SkinnyPlan &plan)
 
 size_t act_workspace_bytes(const Problem &p, const SkinnyPlan &plan)
 {
-    return plan.split_k > 1 ? kCounterBytes + (size_t)plan.split_k * p.M * p.N * sizeof(float) : 0;
+    return plan.split_k > 1 && !plan.serial ? kCounterBytes + (size_t)plan.split_k * p.M * p.N * sizeof(float) : 0;
 }
 
 hipError_t launch_act(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream)
@@ -196,8 +198,11 @@ hipError_t launch_act(const Problem &p, const SkinnyPlan &plan, void *workspace,
     const size_t table = act_table_bytes(p) + (size_t)plan.units_per_slice * skinny::kUnitK * sizeof(uint32_t);
     const size_t red = (size_t)waves * 16 * tm * skinny::kCols * sizeof(float);
     const size_t lds = table > red ? table : red;
-    return p.K % skinny::kUnitK != 0 ? launch_lookup<true>(a, tm, waves, lds, stream)
-                                     : launch_lookup<false>(a, tm, waves, lds, stream);
+    if (plan.serial)
+        return p.K % skinny::kUnitK != 0 ? launch_lookup<true, true>(a, tm, waves, lds, stream)
+                                         : launch_lookup<false, true>(a, tm, waves, lds, stream);
+    return p.K % skinny::kUnitK != 0 ? launch_lookup<true, false>(a, tm, waves, lds, stream)
+                                     : launch_lookup<false, false>(a, tm, waves, lds, stream);
 }
 
 bool skinny_supported(const Problem &p)

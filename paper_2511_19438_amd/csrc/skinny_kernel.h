@@ -129,11 +129,16 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
 // 16x2752x6888 14.4 (big-tile kernel) -> 9.8, 32x4128x4096 15.8 -> 10.7.
 //
 // STREAM: non-temporal weight loads (stream_weights in kernels.h).
-template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false, bool STREAM = false>
+//
+// SERIAL: no scratch for the K slices.  A workgroup walks all slices of its tile one after the other and adds their sums
+// in registers, in slice order: the bits of the sliced launch, in about as many times its duration as it has slices.
+template <int TM, int WN, int WAVES, int GPU = 1, bool ACT = false, bool TAIL = false, bool STREAM = false,
+          bool SERIAL = false>
 __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
 {
     static_assert(!ACT || (WN == 1 && GPU == 1), "act-order: 64-column workgroups");
     static_assert(!TAIL || ACT || GPU > 1, "groups of 128 k leave no tail");
+    static_assert(!SERIAL || WN == 1, "64-column workgroups");
     Args a = args;
     static_assert(GPU == 1 || GPU == 2 || GPU == 4, "groups of >= 128, 64 or 32 k");
     static_assert(GPU == 1 || TM <= 2, "small groups: up to two row blocks");
@@ -186,6 +191,12 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
     const int n0 = tile * COLS + cb * kCols + 4 * cq;
     const int nc = min(n0, N - 4);  // clamped for loads; columns past N are never stored
 
+    constexpr int OUTS = SERIAL ? ROWS * COLS / kThreads : 1;
+    float total[OUTS];  // SERIAL: output tid + j * kThreads of the tile, over the slices so far
+#pragma unroll
+    for (int j = 0; j < OUTS; ++j)
+        total[j] = 0.f;
+    for (;;) {  // (a single pass unless SERIAL; the body, up to the sum over the wavefronts, is not indented)
     const int u0 = slice * a.units_per_slice;
     const int u1 = min(u0 + a.units_per_slice, a.total_units);
     const int nunits = u1 - u0;
@@ -503,20 +514,48 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
             *reinterpret_cast<float4_t *>(red + ((size_t)kw * ROWS + row) * COLS + cb * kCols + 4 * cq) = v;
         }
     __syncthreads();
-    for (int i = tid; i < a.M * COLS; i += kThreads) {
-        const int m = i / COLS;
-        const int col = i - m * COLS;
-        const int n = tile * COLS + col;
+    auto sum_of_wavefronts = [&](int m, int col) {
         float s = red[(size_t)m * COLS + col];
 #pragma unroll
         for (int w = 1; w < KW; ++w)
             s += red[((size_t)w * ROWS + m) * COLS + col];
+        return s;
+    };
+    if (SERIAL) {
+#pragma unroll
+        for (int j = 0; j < OUTS; ++j) {
+            const int i = tid + j * kThreads;
+            const float s = sum_of_wavefronts(i / COLS, i % COLS);
+            total[j] = a.split_k == 1 ? s : total[j] + s;  // (the sliced launch adds to zero, the unsplit one does not)
+        }
+        if (++slice < a.split_k) {
+            __syncthreads();  // the sums have been read: the next slice's table may take their place
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < OUTS; ++j) {
+            const int i = tid + j * kThreads;
+            const int m = i / COLS;
+            const int n = tile * COLS + i % COLS;
+            if (m < a.M && n < N)
+                a.out[(size_t)m * N + n] = (half_t)total[j];
+        }
+        return;
+    }
+    for (int i = tid; i < a.M * COLS; i += kThreads) {
+        const int m = i / COLS;
+        const int col = i - m * COLS;
+        const int n = tile * COLS + col;
+        const float s = sum_of_wavefronts(m, col);
         if (n < N) {
             if (a.split_k == 1)
                 a.out[(size_t)m * N + n] = (half_t)s;
             else
                 store_device_scope(a.partial + slice * slice_values + (size_t)m * N + n, s);
         }
+    }
+
+    break;
     }
 
     // ---- combine the K slices: the last workgroup of this column tile adds them in slice order ----

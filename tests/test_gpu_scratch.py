@@ -42,3 +42,64 @@ def test_an_explicit_number_of_slices_is_refused_without_their_scratch(B, M, gro
         with pytest.raises(B.GptqError) as e:
             run_gemm(B, case, group, plan)
         assert e.value.code == -5
+
+
+def vector_scratch(B, M, K, N, group, act):
+    """What the vector kernel takes for a batch of up to 16 rows (the least that an automatic call of so few asks for)."""
+    plan = B.gptq_w4a16_plan_query(M, K, N, group, act, B.Plan(kernel=1))
+    return COUNTERS + (plan.split_k * M * N * 4 if plan.kernel == 1 and plan.split_k > 1 else 0)
+
+
+# small groups or a width of 8 mod 32 on every tile, with and without two wavefront groups, a K that ends half-way through
+# a stage, 96 and 128 rows; act-order from two rows to several row tiles, with a K that ends inside a unit
+@pytest.mark.parametrize("M,K,N,group,act,tile", [
+    (100, 2304, 8, 128, False, 0), (108, 1056, 32, 96, False, 0), (143, 928, 16, 32, False, 0),
+    (359, 640, 8, 128, False, 3), (40, 4256, 136, 32, False, 3), (40, 4256, 136, 32, False, 5),
+    (52, 1408, 104, 128, False, 8), (100, 2304, 264, 96, False, 8), (206, 1440, 16, 160, False, 8),
+    (45, 3072, 264, 32, False, 8), (70, 4256, 40, 32, False, 8), (286, 7296, 1032, 128, False, 0),
+    (12, 2112, 1032, 96, False, 0), (2, 768, 8704, 128, True, 0), (11, 704, 10416, 32, True, 0),
+    (24, 2048, 264, 128, True, 0), (40, 2208, 520, 96, True, 0), (130, 2144, 72, 8, True, 0), (300, 4096, 264, 128, True, 0)])
+def test_the_result_does_not_depend_on_the_scratch(B, M, K, N, group, act, tile):
+    case = workloads.make_case(M, K, N, group, seed=M + N, act_order=act)
+    plan = B.Plan(kernel=2, tile=tile) if tile else None
+    resolved = B.gptq_w4a16_plan_query(M, K, N, group, act, plan)
+    assert resolved.split_k > 1 and (resolved.kernel == 2 or act)
+    sliced = run_gemm(B, case, group, plan)
+    ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], case["g_idx"], group)
+    assert_within_band(sliced, ref, "slices in parallel")
+    with workspace(B, vector_scratch(B, M, K, N, group, act) if M <= 16 else COUNTERS):
+        assert np.array_equal(bits(run_gemm(B, case, group, plan)), bits(sliced))
+
+
+@pytest.mark.parametrize("M,K,N,group,act", [(40, 4256, 136, 32, False), (300, 2016, 264, 96, False), (40, 2048, 264, 128, True)])
+def test_a_call_captured_before_there_is_scratch_gives_the_same_bits(B, M, K, N, group, act):
+    case = workloads.make_case(M, K, N, group, seed=M, act_order=act)
+    assert B.gptq_w4a16_plan_query(M, K, N, group, act).split_k > 1
+    eager = run_gemm(B, case, group)
+    x, qw, qz, sc, gi = (dev(case[k]) for k in ("x", "qweight", "qzeros", "scales", "g_idx"))
+    out = torch.zeros((M, N), dtype=torch.float16, device="cuda")
+    torch.cuda.synchronize()
+    B.gptq_w4a16_set_workspace(None)  # the library owns no scratch
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            B.gptq_w4a16_gemm(x, qw, qz, sc, gi, out, group)
+        for rep in range(3):
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert np.array_equal(bits(out.cpu().numpy()), bits(eager)), f"replay {rep}"
+            assert np.array_equal(bits(run_gemm(B, case, group)), bits(eager))  # eagerly, on scratch of its own
+
+
+def test_static_act_order_beyond_its_block_gives_the_bits_of_the_regular_call(B):
+    """606 groups leave the LDS no room for longer slices: ten of them, whose partial sums exceed the static block."""
+    M, K, N, group = 320, 19392, 4096, 32
+    plan = B.gptq_w4a16_plan_query(M, K, N, group, True)
+    assert plan.split_k * M * N * 4 > 48 << 20
+    case = workloads.make_case(M, K, N, group, seed=6, act_order=True)
+    x, qw, qz, sc, gi = (dev(case[k]) for k in ("x", "qweight", "qzeros", "scales", "g_idx"))
+    out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    B.gptq_w4a16_gemm_static(x, qw, qz, sc, gi, out, group)
+    assert np.array_equal(bits(out.cpu().numpy()), bits(run_gemm(B, case, group)))
