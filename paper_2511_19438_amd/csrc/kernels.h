@@ -93,6 +93,8 @@ struct SkinnyPlan {
 };
 bool skinny_supported(const Problem &p);
 void skinny_make_plan(const Problem &p, SkinnyPlan &plan);
+// Problems that have to be served where there is no scratch, with plan.serial: a K that ends inside a 128-k unit.
+bool skinny_scratch_optional(const Problem &p);
 size_t skinny_workspace_bytes(const Problem &p, const SkinnyPlan &plan);
 hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream);
 

@@ -63,14 +63,14 @@ hipError_t launch_streamed(const skinny::Args &a, int tm, size_t lds, hipStream_
 }
 
 // Groups of 128 / GPU k.
-template <int GPU, bool TAIL>
+template <int GPU, bool TAIL, bool SERIAL>
 hipError_t launch_small_groups(const skinny::Args &a, int tm, int waves, size_t lds, hipStream_t stream)
 {
     if (tm == 1)
-        return waves == 8 ? launch_tm<1, 1, 8, GPU, false, TAIL>(a, lds, stream)
-                          : launch_tm<1, 1, 4, GPU, false, TAIL>(a, lds, stream);
-    return waves == 8 ? launch_tm<2, 1, 8, GPU, false, TAIL>(a, lds, stream)
-                      : launch_tm<2, 1, 4, GPU, false, TAIL>(a, lds, stream);
+        return waves == 8 ? launch_tm<1, 1, 8, GPU, false, TAIL, false, SERIAL>(a, lds, stream)
+                          : launch_tm<1, 1, 4, GPU, false, TAIL, false, SERIAL>(a, lds, stream);
+    return waves == 8 ? launch_tm<2, 1, 8, GPU, false, TAIL, false, SERIAL>(a, lds, stream)
+                      : launch_tm<2, 1, 4, GPU, false, TAIL, false, SERIAL>(a, lds, stream);
 }
 
 // Act-order with lookups.
@@ -285,8 +285,15 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
     plan.split_k = ceil_div(total_units, ups);
 }
 
+bool skinny_scratch_optional(const Problem &p)
+{
+    return p.group_size < skinny::kUnitK && p.K % skinny::kUnitK != 0;
+}
+
 size_t skinny_workspace_bytes(const Problem &p, const SkinnyPlan &plan)
 {
+    if (plan.serial)
+        return 0;
     size_t bytes = kCounterBytes;
     if (plan.split_k > 1)
         bytes += (size_t)plan.split_k * rows_of_launch(p.M) * p.N * sizeof(float);
@@ -308,7 +315,7 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
         a.row_tiles = 1;
         a.out = p.out + (size_t)m0 * p.N;
         a.counters = reinterpret_cast<unsigned *>(ws);
-        a.partial = reinterpret_cast<float *>(ws + kCounterBytes);
+        a.partial = ws ? reinterpret_cast<float *>(ws + kCounterBytes) : nullptr;
         a.M = (p.M - m0) < kRowsPerLaunch ? (p.M - m0) : kRowsPerLaunch;
         a.K = p.K;
         a.N = p.N;
@@ -336,12 +343,15 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
             if (wn != 1 || tm > 2)
                 return hipErrorInvalidValue;  // refused by skinny_supported / skinny_make_plan
             const bool tail = p.K % skinny::kUnitK != 0;
-            if (gpu == 2)
-                err = tail ? launch_small_groups<2, true>(a, tm, waves, lds, stream)
-                           : launch_small_groups<2, false>(a, tm, waves, lds, stream);
+            if (plan.serial && tail)
+                err = gpu == 2 ? launch_small_groups<2, true, true>(a, tm, waves, lds, stream)
+                               : launch_small_groups<4, true, true>(a, tm, waves, lds, stream);
+            else if (gpu == 2)
+                err = tail ? launch_small_groups<2, true, false>(a, tm, waves, lds, stream)
+                           : launch_small_groups<2, false, false>(a, tm, waves, lds, stream);
             else
-                err = tail ? launch_small_groups<4, true>(a, tm, waves, lds, stream)
-                           : launch_small_groups<4, false>(a, tm, waves, lds, stream);
+                err = tail ? launch_small_groups<4, true, false>(a, tm, waves, lds, stream)
+                           : launch_small_groups<4, false, false>(a, tm, waves, lds, stream);
         } else if (tm <= 2 && stream_weights(p)) {
             err = wn == 2   ? launch_streamed<2, 8>(a, tm, lds, stream)
                   : wn == 4 ? launch_streamed<4, 4>(a, tm, lds, stream)
