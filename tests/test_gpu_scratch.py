@@ -18,9 +18,10 @@ COUNTERS = 1 << 18  # the arrival counters alone
 
 @contextlib.contextmanager
 def workspace(B, nbytes):
-    B.gptq_w4a16_set_workspace(torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+    buf = torch.empty(nbytes, dtype=torch.uint8, device="cuda")  # (borrowed by the library: it has to live as long)
+    B.gptq_w4a16_set_workspace(buf)
     try:
-        yield
+        yield buf
     finally:
         B.gptq_w4a16_set_workspace(None)
 
