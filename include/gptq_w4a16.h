@@ -181,7 +181,8 @@ GPTQ_API int gptq_w4a16_act_order_prepare(const void *qweight, const void *g_idx
  * g_idx.  At M = 1 the vector kernel gathers x through perm while it stages it (one launch; perm
  * entries outside [0, K) read x[K-1]); for larger M x is first gathered into scratch (M*K fp16) and
  * the kernels of the plain format run on it; otherwise the contract of gptq_w4a16_gemm.  A caller-owned workspace must hold
- * gptq_w4a16_workspace_bytes(M, K, N, group_size) + 256 + 2*M*K bytes.
+ * gptq_w4a16_workspace_bytes(M, K, N, group_size) + 256 + 2*M*K bytes; plans that can do without the scratch of their
+ * slices (see there) make do with 256 KiB + 2*M*K from 17 rows on.
  */
 GPTQ_API int gptq_w4a16_gemm_prepared(const void *x, const void *qweight_sorted, const void *qzeros,
                                       const void *scales, const void *perm, void *out, int M, int K, int N,

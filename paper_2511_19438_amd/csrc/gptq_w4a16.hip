@@ -530,7 +530,7 @@ int gptq_w4a16_gemm_prepared(const void *x, const void *qweight_sorted, const vo
     p.K = K;
     p.N = N;
     p.group_size = group_size;
-    const Resolved r = resolve(p, nullptr);
+    Resolved r = resolve(p, nullptr);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (r.kernel == 1 && M == 1 && r.decode.chunk_rows == 4 && r.decode.flags == 0) {
         // the vector kernel gathers the activations itself while it stages them: one launch
@@ -547,13 +547,18 @@ int gptq_w4a16_gemm_prepared(const void *x, const void *qweight_sorted, const vo
     }
     // scratch: what the kernel needs, then the gathered activations
     // (the counter area at the front stays reserved even if this launch needs none: it must remain zero)
-    size_t kernel_bytes = align256(scratch_bytes(p, r));
-    if (kernel_bytes < decode_counter_bytes(N))
-        kernel_bytes = decode_counter_bytes(N);
+    size_t kernel_bytes;
     void *ws = nullptr;
-    const int wrc = acquire_workspace(kernel_bytes + (size_t)M * K * sizeof(half_t), st, &ws);
-    if (wrc != GPTQ_OK)
-        return wrc;
+    for (;;) {
+        kernel_bytes = align256(scratch_bytes(p, r));
+        if (kernel_bytes < decode_counter_bytes(N))
+            kernel_bytes = decode_counter_bytes(N);
+        const int wrc = acquire_workspace(kernel_bytes + (size_t)M * K * sizeof(half_t), st, &ws);
+        if (wrc == GPTQ_OK)
+            break;
+        if (wrc != GPTQ_WORKSPACE_TOO_SMALL || !fall_back(p, nullptr, r))
+            return wrc;
+    }
     half_t *xp = reinterpret_cast<half_t *>(static_cast<unsigned char *>(ws) + kernel_bytes);
     if (launch_gather_activations(static_cast<const half_t *>(x), static_cast<const int32_t *>(perm), xp, M, K, st) !=
         hipSuccess)

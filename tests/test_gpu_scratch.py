@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
 from paper_2511_19438_amd import workloads  # noqa: E402
-from test_gpu_parity import B, assert_within_band, dev, run_gemm  # noqa: E402,F401
+from test_gpu_parity import B, _repack, assert_within_band, dev, run_gemm  # noqa: E402,F401
 
 COUNTERS = 1 << 18  # the arrival counters alone
 
@@ -109,3 +109,28 @@ def test_static_act_order_beyond_its_block_gives_the_bits_of_the_regular_call(B)
     out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
     B.gptq_w4a16_gemm_static(x, qw, qz, sc, gi, out, group)
     assert np.array_equal(bits(out.cpu().numpy()), bits(run_gemm(B, case, group)))
+
+
+@pytest.mark.parametrize("M,K,N,group", [(40, 4256, 136, 32), (333, 2752, 1032, 32), (24, 2752, 1032, 32), (100, 2304, 264, 96),
+                                         (3, 3552, 6960, 32), (12, 2112, 1032, 96)])
+def test_a_repacked_checkpoint_runs_without_the_scratch_of_its_slices(B, M, K, N, group):
+    """A workspace that holds the counters and the gathered activations (up to 16 rows: and what the vector kernel takes)."""
+    case = workloads.make_case(M, K, N, group, seed=M, act_order=True)
+    assert B.gptq_w4a16_plan_query(M, K, N, group).split_k > 1
+    qs, perm = _repack(B, case, group)
+    x, qz, sc = (dev(case[k]) for k in ("x", "qzeros", "scales"))
+
+    def run():
+        out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+        return B.gptq_w4a16_gemm_prepared(x, qs, qz, sc, perm, out, group).cpu().numpy()
+
+    sliced = run()
+    ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], case["g_idx"], group)
+    assert_within_band(sliced, ref, "slices in parallel")
+    least = vector_scratch(B, M, K, N, group, False) if M <= 16 else COUNTERS
+    with workspace(B, (least + 255) // 256 * 256 + 2 * M * K):
+        assert np.array_equal(bits(run()), bits(sliced))
+    with workspace(B, least + 2 * M * K - 256):
+        with pytest.raises(B.GptqError) as e:
+            run()
+        assert e.value.code == -5
