@@ -291,18 +291,18 @@ size_t required_scratch(const Problem &p, const gptq_w4a16_plan_t *request)
     return scratch_bytes(p, resolve(p, &vector));
 }
 
-// Formats that run without scratch in their most general kernel (act-order, groups or widths that only the big-tile
-// kernel's HALF variant pipelines, a K that ends inside a unit of the small-batch kernel) must not fail where the scratch of their K slices cannot be had - a workspace of the
-// caller's that is too small, growth under capture, the static block: every workgroup then walks the slices itself, in
-// the same order, so that the result does not depend on the scratch.  A number of slices that the caller asked for is
-// never given up.  False: the call needs what it needs.
+// Act-order problems, the big-tile kernel and the small-batch kernel where K ends inside a unit do not fail where the
+// scratch of their K slices cannot be had - a workspace of the caller's that is too small, growth under capture, the
+// static block: every workgroup then walks the slices itself, in the same order, so that the result does not depend on
+// the scratch.  (How many slices pay is a matter of measurement and may change; which calls a workspace serves may
+// not.)  A number of slices that the caller asked for is never given up.  False: the call needs what it needs.
 bool fall_back(const Problem &p, const gptq_w4a16_plan_t *request, Resolved &r)
 {
     if (r.skinny.serial || r.prefill.serial || (request && request->split_k > 0))
         return false;
     if (r.act || (r.kernel == 3 && skinny_scratch_optional(p)))
         r.skinny.serial = true;
-    else if (r.kernel == 2 && r.prefill.split_k > 1 && prefill_slices_optional(p))
+    else if (r.kernel == 2 && r.prefill.split_k > 1)
         r.prefill.serial = true;
     else
         return false;

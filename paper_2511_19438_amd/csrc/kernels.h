@@ -126,8 +126,6 @@ struct PrefillPlan {
 bool prefill_supported(const Problem &p);
 // Whether the pipelined kernel (tiles, K slices) takes the problem; else the general path does.
 bool prefill_pipelined(const Problem &p);
-// Problems that a launch without K slices has to serve where there is no scratch for them (gptq_w4a16.hip).
-bool prefill_slices_optional(const Problem &p);
 bool prefill_tile_exists(int tile);  // the tile ids a plan may name
 void prefill_make_plan(const Problem &p, PrefillPlan &plan);
 // Scratch of a plan with split_k > 1 (counter area first, as for the other kernels); 0 without a split.

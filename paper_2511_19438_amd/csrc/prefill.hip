@@ -135,11 +135,6 @@ bool prefill_pipelined(const Problem &p)
     return mode_of(p) == prefill::kGroupPerStage || mode_of(p) == prefill::kGroupPerHalf;
 }
 
-bool prefill_slices_optional(const Problem &p)
-{
-    return mode_of(p) == prefill::kGroupPerHalf;
-}
-
 bool prefill_supported(const Problem &p)
 {
     return p.M >= 1 && p.K % 8 == 0 && p.N % 8 == 0;

@@ -70,6 +70,9 @@ hipError_t launch_tile<GPTQ_PREFILL_TILE>(const Args &a, int mode, int kw, hipSt
     if (kw != 1)
         return hipErrorInvalidValue;
 #if GPTQ_PREFILL_TILE == 5
+    if (a.serial_slices > 1 && mode == kGroupPerStage)
+        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, false, 1, true>, a,
+                      (size_t)NBUF * StageLayout<BM, BN, BK, false>::BYTES, false, stream);
     if (a.serial_slices > 1 && mode == kGroupPerHalf)
         return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, true, 1, true>, a,
                       (size_t)NBUF * StageLayout<BM, BN, BK, true>::BYTES, false, stream);

@@ -54,6 +54,7 @@ def vector_scratch(B, M, K, N, group, act):
 # small groups or a width of 8 mod 32 on every tile, with and without two wavefront groups, a K that ends half-way through
 # a stage, 96 and 128 rows; act-order from two rows to several row tiles, with a K that ends inside a unit
 @pytest.mark.parametrize("M,K,N,group,act,tile", [
+    (300, 4096, 1024, 128, False, 0), (200, 2048, 544, 64, False, 3), (150, 2560, 512, 128, False, 8), (77, 4096, 512, 128, False, 8),
     (100, 2304, 8, 128, False, 0), (108, 1056, 32, 96, False, 0), (143, 928, 16, 32, False, 0),
     (359, 640, 8, 128, False, 3), (40, 4256, 136, 32, False, 3), (40, 4256, 136, 32, False, 5),
     (52, 1408, 104, 128, False, 8), (100, 2304, 264, 96, False, 8), (206, 1440, 16, 160, False, 8),
@@ -134,3 +135,21 @@ def test_a_repacked_checkpoint_runs_without_the_scratch_of_its_slices(B, M, K, N
         with pytest.raises(B.GptqError) as e:
             run()
         assert e.value.code == -5
+
+
+def test_a_deep_layer_runs_on_the_workspace_that_served_it_with_fewer_slices(B):
+    """The mid-batch kernel's slices took 15 MB here, the big-tile kernel's take 34."""
+    M, K, N, group = 77, 28672, 8192, 128
+    mid = B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(kernel=4))
+    assert mid.kernel == 4
+    case = workloads.make_case(M, K, N, group, seed=1)
+    x, qw, qz, sc = (dev(case[k]) for k in ("x", "qweight", "qzeros", "scales"))
+    want, got = (torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    B.gptq_w4a16_gemm(x, qw, qz, sc, None, want, group)
+    with workspace(B, COUNTERS + mid.split_k * M * N * 4):
+        B.gptq_w4a16_gemm(x, qw, qz, sc, None, got, group)
+        torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    mi, ni = workloads.sample_positions(M, N, 128, 2)
+    ref = oracle.gemm_ref_sampled(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group, mi, ni)
+    assert_within_band(want.cpu().numpy()[mi, ni], ref, "77 rows of a deep layer")
