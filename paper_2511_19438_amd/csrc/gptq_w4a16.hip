@@ -149,14 +149,42 @@ constexpr int kSmallBatchAutoMaxM = 32;
 // 2784x6888: M = 4 9.1 against 14.8, M = 16 32.3 against 14.6).
 constexpr int kVectorFallbackMaxM = 8;
 
+// Small groups with a K that ends inside a 128-k unit, up to four rows: whether the vector kernel is the better one.  At
+// two rows it is on half of the shapes (3776x34176 18.4 us against 22.9).  At three and four the small-batch kernel is
+// ahead (2-90 %) where its 64-column workgroups fill whole rounds of the chip, and behind where a deep K meets a last
+// round that is half empty, because the vector kernel has wider tiles to choose from.  Sweep of 17 widths and 6 depths,
+// groups of 32 and 64, vector against small-batch at three rows:
+//   a round less than four fifths full, K from 6144, 50 M weights:  12320x18432 29.5 us, 46.4; 8224x9216 14.5, 17.8
+//     (groups of 64 13.8, 15.9); in smaller matrices the small-batch kernel stays ahead (8224x2056 10.3, 8.4), and below
+//     that depth, too (4128x12288 11.8, 10.7);
+//   beyond 16384 columns a round less than 70 % full, whatever the depth (4128x20480 15.0, 19.5);
+//   groups of 32, K from 8192, N from 14336: level at best (28704x28672 89.6, 107.6; 16416x16384 33.9, 33.9).
+// Layers so small that the launch dominates (1344x1536 4.9, 5.4) and very wide ones (8256x38256 41, 51; 2112x57344 17, 22;
+// but 4160x45056 36, 29) stay with the vector kernel as well.
+bool tail_prefers_vector(const Problem &p)
+{
+    if (p.M <= 2)
+        return true;
+    if (p.M > 4)
+        return false;
+    if ((long long)p.K * p.N < (1ll << 22) || p.N > 32768)
+        return true;
+    SkinnyPlan plan = {};
+    skinny_make_plan(p, plan);
+    const int workgroups = (p.N + 63) / 64 * plan.split_k;
+    const double full = workgroups / (256.0 * ((workgroups + 255) / 256));
+    if (full < 0.8 && p.K >= 6144 && (long long)p.K * p.N >= (3ll << 24))
+        return true;
+    if (full < 0.7 && p.N > 16384)
+        return true;
+    return p.group_size == 32 && p.K >= 8192 && p.N >= 14336;
+}
+
 bool small_batch_by_default(const Problem &p)
 {
     if (!skinny_supported(p))
         return false;
-    // A K that ends inside a 128-k unit: two rows stay with the vector kernel (faster on half of eight shapes measured,
-    // 3776x34176 18.4 us against 22.9), four too on layers so small that the launch dominates (1344x1536 4.9, 5.4) and
-    // on very wide ones (8256x38256 45, 53); from three rows on the small-batch kernel is 2-40 % ahead on the others.
-    if (p.K % 128 != 0 && (p.M <= 2 || (p.M <= 4 && ((long long)p.K * p.N < (1ll << 22) || p.N > 32768))))
+    if (p.K % 128 != 0 && tail_prefers_vector(p))
         return false;
     return p.M <= kSmallBatchAutoMaxM;
 }
