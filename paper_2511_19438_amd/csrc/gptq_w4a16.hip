@@ -198,9 +198,13 @@ bool mid_batch_by_default(const Problem &p)
         return tiles64 >= 160 || (long long)p.K * p.N >= (1ll << 27);
     if (p.M <= 64)
         return true;
-    // (up to 96 rows of a very deep layer: eight slices of the big-tile kernel's 96x256 tile, 28672x8192 at M = 77
-    // 69.9 us against 77.9)
-    if (p.M <= 96 && p.K >= 16384)
+    // Up to 96 rows of a deep and wide layer: K slices of the big-tile kernel's 96x256 tile, which pads the batch less
+    // and has two wavefronts per SIMD.  Mid-batch against big-tile at 65, 80 and 96 rows over K 12288-28672 and N
+    // 2048-16384: from 128 column tiles and K = 16384 on level at worst and up to 51 % ahead (16384x8192 48.6 us, 48.4;
+    // 20480x12288 87.1, 64.9; 28672x8192 78.5, 66.4), from 96 tiles on at K = 20480 (20480x6144 49.4, 48.3; 28672x7168
+    // 73.1, 64.4).  Narrower layers lose with it, their tiles being too few (28672x4096 43.3, 51.6; 16384x2048 19.9, 24.8;
+    // 24576x5120 45.0, 53.5).
+    if (p.M <= 96 && ((tiles64 >= 128 && p.K >= 16384) || (tiles64 >= 96 && p.K >= 20480)))
         return false;
     return tiles64 <= 256 && (tiles64 >= 128 || p.K >= 8192);
 }

@@ -91,3 +91,13 @@ def test_three_and_four_rows_on_a_k_that_ends_inside_a_unit(B):
         assert [s for s in vector if B.gptq_w4a16_plan_query(M, s[0], s[1], s[2]).kernel != 1] == []
         assert [s for s in small if B.gptq_w4a16_plan_query(M, s[0], s[1], s[2]).kernel != 3] == []
     assert all(B.gptq_w4a16_plan_query(5, *s).kernel == 3 for s in vector + small)
+
+
+def test_deep_layers_at_65_to_96_rows(B):
+    """The big-tile kernel (2) only where the layer is wide enough for its tiles; sizes where both measured 5 % and more apart."""
+    mid = [(16384, 2048), (16384, 4096), (20480, 5120), (24576, 2048), (24576, 5120), (28672, 4096), (12288, 4096)]
+    big = [(18432, 8192), (20480, 12288), (28672, 8192), (24576, 7168), (28672, 6144), (16384, 10240), (28672, 16384)]
+    for M in (65, 77, 96):
+        assert [s for s in mid if B.gptq_w4a16_plan_query(M, *s, 128).kernel != 4] == []
+        assert [s for s in big if B.gptq_w4a16_plan_query(M, *s, 128).kernel != 2] == []
+    assert B.gptq_w4a16_plan_query(97, 28672, 8192, 128).kernel == 4
