@@ -47,16 +47,28 @@ __global__ __launch_bounds__(kThreads) void unpack_qzeros_kernel(const uint32_t 
     *reinterpret_cast<uint2 *>(z_out + 8 * idx) = bytes;
 }
 
+constexpr long long kMemorySideCacheBytes = 256000000;
+
 // w_out[k, n] = fp16( scales[r(k), n] * (q[k, n] - z[r(k), n]) ): exact integer difference, one fp16 multiply.
 //
 // Bound by HBM (2.5 bytes per weight, four fifths of them written), so what counts is how the rows are written: a thread
 // owns EIGHT adjacent columns of one packed row (two 128-bit loads, one whole zero word), which makes every store 128
 // bits and a wavefront's part of a row 1 KB contiguous.  The difference comes from the mantissa of 1024.0: (1024 + q) -
-// (1024 + z) in packed halves is exact (and +0 for q = z, as the conversion of an integer 0 is).  The stores are
-// non-temporal: the written rows are 80 % of the traffic and nothing here reads them again.  11008x4096: 23.8 us with
-// four columns per thread, 23.1 with eight, 18.1 with non-temporal stores on top (6.3 TB/s; act-order 31.8, 30.0, 18.2);
-// ahead at every size from 8 MB of output (4.2 -> 3.7 us) to 134 MB (34.7 -> 27.6), level on 8192x57344 (194 us).
-template <bool ACT_ORDER>
+// (1024 + z) in packed halves is exact (and +0 for q = z, as the conversion of an integer 0 is).
+//
+// The written rows are 80 % of the traffic, and what counts next is whether their reader finds them in the memory-side
+// cache (256 MB).  BYPASS, for outputs that do not fit it: non-temporal stores, past all caches.  Otherwise write-through
+// stores (sc1): nothing is left dirty in the L2, and the rows stay in the memory-side cache.  Non-temporal stores would
+// make the dequantisation itself shorter there, too, but a product that follows longer by more.  The weights alone, and
+// with a product of 16 rows behind them, us with plain / non-temporal / write-through stores (the first three over a set of
+// layers that exceeds the cache):
+//   4096x4096    9.8 /  7.5 /  8.8    25.8 /  30.4 /  24.8
+//   11008x4096  23.1 / 17.8 / 22.4    71.5 /  87.8 /  70.9
+//   8192x12288  47.0 / 43.8 / 45.6    89.9 /  94.5 /  88.1
+//   8192x16384  61.9 / 48.9 / 57.8   112.1 / 108.2 / 112.9   (268 MB)
+//   8192x28672 102.5 / 86.4 / 101.4  230.6 / 205.3 / 230.6
+// (11008x4096 with four columns per thread and plain 64-bit stores: 24.0 alone.)
+template <bool ACT_ORDER, bool BYPASS>
 __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint32_t *__restrict__ qweight,
                                                            const uint32_t *__restrict__ qzeros,
                                                            const half_t *__restrict__ scales,
@@ -64,6 +76,10 @@ __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint32_t *__res
                                                            half_t *__restrict__ w_out, int rows, int N,
                                                            int group_size)
 {
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    constexpr int kWriteThrough = 16;  // cache policy of a buffer store: sc1
+    // (write-through: the whole output is under 4 GB)
+    const auto out_rsrc = __builtin_amdgcn_make_buffer_rsrc(w_out, 0, (uint32_t)rows * 16u * (uint32_t)N, 0x00020000);
     const int octs = N >> 3;
     const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
     if (idx >= (long long)rows * octs)
@@ -95,7 +111,11 @@ __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint32_t *__res
         for (int c = 0; c < 8; ++c)
             o[c] = __builtin_bit_cast(half_t, (uint16_t)(0x6400u | ((w[c] >> (4 * j)) & 15u)));
         o = (o + nz) * s;
-        __builtin_nontemporal_store(o, reinterpret_cast<half8_t *>(w_out + (size_t)k * N + n0));
+        if (BYPASS)
+            __builtin_nontemporal_store(o, reinterpret_cast<half8_t *>(w_out + (size_t)k * N + n0));
+        else
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), out_rsrc,
+                                                   ((uint32_t)k * (uint32_t)N + (uint32_t)n0) * 2u, 0, kWriteThrough);
     }
 }
 
@@ -152,12 +172,11 @@ hipError_t launch_dequant(const uint32_t *qweight, const uint32_t *qzeros, const
 {
     const int rows = K / 8;
     const long long items = (long long)rows * (N / 8);
-    if (g_idx)
-        hipLaunchKernelGGL(dequant_kernel<true>, dim3(blocks_for(items)), dim3(kThreads), 0, stream, qweight, qzeros,
-                           scales, g_idx, w_out, rows, N, group_size);
-    else
-        hipLaunchKernelGGL(dequant_kernel<false>, dim3(blocks_for(items)), dim3(kThreads), 0, stream, qweight,
-                           qzeros, scales, g_idx, w_out, rows, N, group_size);
+    const bool bypass = 2ll * K * N > kMemorySideCacheBytes;
+    auto kernel = g_idx ? (bypass ? dequant_kernel<true, true> : dequant_kernel<true, false>)
+                        : (bypass ? dequant_kernel<false, true> : dequant_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3(blocks_for(items)), dim3(kThreads), 0, stream, qweight, qzeros, scales, g_idx,
+                       w_out, rows, N, group_size);
     return hipGetLastError();
 }
 

@@ -175,3 +175,23 @@ def test_an_infinity_survives_the_exchange_of_k_slices(B, kernel, tile, M, group
         assert np.array_equal(out[3][hit], (np.sign(w[k][hit]) * np.inf).astype(np.float16))
         rows = np.arange(M) != 3
         assert_within_band(out[rows], ref[rows], "the other rows")
+
+
+# ---- dequantisation: write-through stores for outputs that fit the memory-side cache, past the caches beyond ----
+
+@pytest.mark.parametrize("K,N,group,act", [(8192, 15624, 128, False), (8192, 15632, 128, False), (8192, 15624, 64, True),
+                                           (8192, 15632, 64, True)])  # 255.98 and 256.1 MB of output
+def test_dequant_on_both_sides_of_the_cache_size_is_bit_exact(B, K, N, group, act):
+    w = workloads.make_weights(K, N, group, seed=K + N, act_order=act)
+    qw, qz, sc, gi = (dev(w[k]) for k in ("qweight", "qzeros", "scales", "g_idx"))
+    guard = torch.full((K + 2, N), 7.0, dtype=torch.float16, device="cuda")  # a row on either side stays as it is
+    B.gptq_w4a16_dequant(qw, qz, sc, gi, guard[1:-1], group)
+    shift = torch.arange(0, 32, 4, dtype=torch.int32, device="cuda")
+    z = (qz[:, :, None] >> shift & 15).reshape(K // group, N)
+    group_of = gi.long() if act else torch.arange(K, device="cuda") // group
+    for lo in range(0, K, 1024):
+        q = (qw[lo // 8:lo // 8 + 128, None, :] >> shift[None, :, None] & 15).reshape(1024, N)
+        rows = group_of[lo:lo + 1024]
+        want = (q - z[rows]).half() * sc[rows]  # exact difference, one fp16 multiplication
+        assert torch.equal(guard[1 + lo:1 + lo + 1024].view(torch.int16), want.view(torch.int16)), lo
+    assert bool((guard[0] == 7).all()) and bool((guard[-1] == 7).all())
