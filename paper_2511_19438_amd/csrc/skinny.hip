@@ -127,17 +127,18 @@ void act_make_plan(const Problem &p, SkinnyPlan &plan)
     plan.cols_per_wg = skinny::kCols;
     int split = plan.split_k;
     int quantum = 1;
-    if (split > 0) {
+    const bool automatic = split <= 0;
+    if (!automatic) {
         // a request for the automatic plan's slices (a queried plan given back) is the automatic plan: its slices are
         // whole multiples of a quantum, which the number of slices alone does not tell
-        SkinnyPlan automatic = {};
-        act_make_plan(p, automatic);
-        if (automatic.split_k == split) {
-            plan = automatic;
+        SkinnyPlan own = {};
+        act_make_plan(p, own);
+        if (own.split_k == split) {
+            plan = own;
             return;
         }
     }
-    if (split <= 0) {
+    if (automatic) {
         // One workgroup per compute unit, as in the plain format: measured best of 1, 2, 3, 4, 6 and 8 slices on
         // 4096x11008 (M = 8: 12.7 us unsplit, 15.4 in two), 11008x4096 (25.9 unsplit, 13.7 in four, 15.2 in eight)
         // and 4096x4096 (12.1, 8.8 in four) for M = 2 ... 512.  Partial sums within half of the weight bytes
@@ -163,6 +164,10 @@ void act_make_plan(const Problem &p, SkinnyPlan &plan)
         ups = total_units;
     plan.units_per_slice = ups;
     plan.split_k = ceil_div(total_units, ups);
+    // Slices that only the room for their offsets calls for, with partial sums beyond the static block: the tiles alone fill
+    // the chip then, and the workgroups walk the slices themselves (606 groups, ten slices: 2048x19392x8192 4485 us with
+    // 671 MB of partial sums, 2929 without; 200x19392x8192 518, 356; 320x19392x4096 329, 340).
+    plan.serial = plan.serial || (automatic && act_workspace_bytes(p, plan) > GPTQ_STATIC_SCRATCH_BYTES);
 }
 
 size_t act_workspace_bytes(const Problem &p, const SkinnyPlan &plan)

@@ -101,3 +101,11 @@ def test_deep_layers_at_65_to_96_rows(B):
         assert [s for s in mid if B.gptq_w4a16_plan_query(M, *s, 128).kernel != 4] == []
         assert [s for s in big if B.gptq_w4a16_plan_query(M, *s, 128).kernel != 2] == []
     assert B.gptq_w4a16_plan_query(97, 28672, 8192, 128).kernel == 4
+
+
+def test_scratch_of_act_order_slices_is_bounded(B):
+    """Slices that the LDS calls for (606 groups: ten of them) ask for no scratch beyond the static block."""
+    for M in (64, 200, 512, 2048, 8192):
+        for N in (4096, 8192, 28672):
+            assert B.gptq_w4a16_plan_query(M, 19392, N, 32, True).split_k == 10
+            assert B.gptq_w4a16_workspace_bytes(M, 19392, N, 32) <= 48 << 20, (M, N)
