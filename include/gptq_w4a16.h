@@ -79,7 +79,7 @@ enum gptq_status {
  * group_size multiples of 64), larger M the big-tile fp16 MFMA kernel (with K slices where
  * the output tiles alone would not fill the chip).
  * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in a table of all
- * groups in LDS (as long as that fits: up to 606 groups); plan queries report it as kernel 1 (M <= 16) or 2 with
+ * groups in LDS (as long as that fits: up to 606 groups, 630 at up to 384 rows); plan queries report it as kernel 1 (M <= 16) or 2 with
  * 64-column tiles and the flag GPTQ_ACT_LOOKUP, and such a plan given back runs it again.  An explicit request for
  * either kernel without the flag runs that kernel itself.
  * Accumulation is in fp32; the result differs from the exact sum by fp32 reassociation
@@ -151,7 +151,7 @@ typedef struct gptq_w4a16_plan {
                                            of 4x4x4 MFMAs (the default up to four rows);
                         or, alone and with kernel 1 or 2:
                        16 GPTQ_ACT_LOOKUP  the small-batch kernel's act-order variant with lookups in LDS (g_idx,
-                                           M >= 2, K % 32 == 0, at most 606 groups; GPTQ_UNSUPPORTED_SHAPE
+                                           M >= 2, K % 32 == 0, at most 606 or 630 groups; GPTQ_UNSUPPORTED_SHAPE
                                            otherwise, without g_idx GPTQ_INVALID_ARG) */
     int reserved[4]; /* must be zero */
 } gptq_w4a16_plan_t;

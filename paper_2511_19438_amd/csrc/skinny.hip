@@ -109,14 +109,16 @@ int act_max_units(const Problem &p)
 }  // namespace
 
 // K must be a multiple of 32; groups may be of any size, the table of all of them has to fit the LDS beside
-// the offsets of a slice (up to 606 groups: K = 28672 with groups of 64 does, with groups of 32 does not and stays with
-// the kernels of an explicit request).
+// the offsets of a slice (K = 28672 with groups of 64 does, with groups of 32 does not and stays with the kernels of an
+// explicit request).  Up to 606 groups slices have sixteen units or more; up to 630 they have four or more, and the
+// table is laid out again for every few units: still faster than the general path up to 384 rows (20096x8192, 628 groups:
+// M = 2 187 us against 1311, M = 256 686, 1372; 630 groups: M = 384 1186, 1401), but not at 512 and more (1581, 1440).
 bool act_supported(const Problem &p)
 {
     if (p.g_idx == nullptr || p.M < 2 || p.N < 8 || p.K % 32 != 0)
         return false;
     const long long tiles = (long long)ceil_div(p.N, skinny::kCols) * ceil_div(p.M, skinny::kActRows);
-    return tiles <= kMaxColumnTiles && act_max_units(p) >= 16;  // (fewer: the table would be laid out again for every few units)
+    return tiles <= kMaxColumnTiles && act_max_units(p) >= (p.M <= 384 ? 4 : 16);
 }
 
 void act_make_plan(const Problem &p, SkinnyPlan &plan)

@@ -195,3 +195,12 @@ def test_dequant_on_both_sides_of_the_cache_size_is_bit_exact(B, K, N, group, ac
         want = (q - z[rows]).half() * sc[rows]  # exact difference, one fp16 multiplication
         assert torch.equal(guard[1 + lo:1 + lo + 1024].view(torch.int16), want.view(torch.int16)), lo
     assert bool((guard[0] == 7).all()) and bool((guard[-1] == 7).all())
+
+
+@pytest.mark.parametrize("M", [2, 17, 130, 384])
+def test_act_order_lookups_with_four_units_per_slice(B, M):
+    K, N, group = 20160, 72, 32  # 630 groups: 40 slices
+    case = workloads.make_case(M, K, N, group, seed=M, act_order=True)
+    plan = B.gptq_w4a16_plan_query(M, K, N, group, True)
+    assert (plan.flags, plan.split_k) == (16, 40)
+    check(B, case, group, f"630 groups, M={M}")

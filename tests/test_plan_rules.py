@@ -109,3 +109,10 @@ def test_scratch_of_act_order_slices_is_bounded(B):
         for N in (4096, 8192, 28672):
             assert B.gptq_w4a16_plan_query(M, 19392, N, 32, True).split_k == 10
             assert B.gptq_w4a16_workspace_bytes(M, 19392, N, 32) <= 48 << 20, (M, N)
+
+
+def test_act_order_lookups_serve_as_many_groups_as_the_lds_holds(B):
+    flags = lambda M, groups: B.gptq_w4a16_plan_query(M, 32 * groups, 4096, 32, True).flags
+    assert [flags(M, 606) for M in (2, 16, 384, 385, 2048)] == [16] * 5
+    assert [flags(M, 630) for M in (2, 16, 17, 384, 385)] == [16, 16, 16, 16, 0]
+    assert [flags(M, 631) for M in (2, 17, 384)] == [0, 0, 0]
