@@ -25,11 +25,16 @@ struct Problem {
     int M, K, N, group_size;
 };
 
-// Whether the HBM-bound kernels (up to 32 rows) read a call's packed weights with non-temporal loads.  Two matrices of
-// 128 MB or more do not fit the 256 MB memory-side cache: they come from HBM on every call and the streaming hint is
-// worth 3-9 % (8192x57344: M = 1 43.0 -> 39.5 us, M = 8 52.1 -> 48.9, M = 16 56.9 -> 53.8).  Smaller matrices that a program calls again and again are found in that cache and lose 5-8 % with the
-// hint (weights that do not fit gain 2-5 %); which of the two a call belongs to is not known here.  Rows have to be whole cache lines: neighbouring tiles share the line at their border otherwise, and the
-// hint drops it before the neighbour comes (17664x9896 at M = 32: 32 us without the hint, 45 with it).
+// Whether the HBM-bound kernels - the vector kernel at one row, the small-batch kernel up to 16 - read a call's packed
+// weights with non-temporal loads.  Matrices of 128 MB and more that a program goes through in turn, as a model does, come
+// from HBM on every call (two of them hardly fit the 256 MB memory-side cache), and the streaming hint is worth 3-9 %
+// (five of 8192x57344: M = 1 40.2 -> 37.6 us, M = 8 50.1 -> 48.0; five of 16384x16384: 27.0 -> 25.7, 28.2 -> 26.0).  The
+// price: ONE such matrix called again and again is found in that cache without the hint and, from two rows on, loses
+// 5-28 % with it (8192x57344: M = 1 35.6, 35.4; M = 8 41.9, 47.6; 28672x9216: M = 8 29.7, 37.9) - until the matrix alone
+// exceeds the cache (16384x49152, 403 MB: 4-8 % gained either way).  Smaller matrices lose 5-8 % where they are found in
+// the cache and gain 2-5 % where not; which of the two a call belongs to is not known here, so they go without.
+// Rows have to be whole cache lines: neighbouring tiles share the line at their border otherwise, and the hint drops it
+// before the neighbour comes (17664x9896 at M = 32: 32 us without the hint, 45 with it).
 inline bool stream_weights(const Problem &p)
 {
     return p.N % 32 == 0 && (long long)p.K * p.N / 2 >= 128000000ll;

@@ -54,12 +54,11 @@ hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
     return hipGetLastError();
 }
 
-// One and two row blocks with streamed weights.
+// Streamed weights: one row block (matrices of that size run on the mid-batch kernel from 17 rows on).
 template <int WN, int WAVES>
-hipError_t launch_streamed(const skinny::Args &a, int tm, size_t lds, hipStream_t stream)
+hipError_t launch_streamed(const skinny::Args &a, size_t lds, hipStream_t stream)
 {
-    return tm == 1 ? launch_tm<1, WN, WAVES, 1, false, false, true>(a, lds, stream)
-                   : launch_tm<2, WN, WAVES, 1, false, false, true>(a, lds, stream);
+    return launch_tm<1, WN, WAVES, 1, false, false, true>(a, lds, stream);
 }
 
 // Groups of 128 / GPU k.
@@ -359,10 +358,10 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
             else
                 err = tail ? launch_small_groups<4, true, false>(a, tm, waves, lds, stream)
                            : launch_small_groups<4, false, false>(a, tm, waves, lds, stream);
-        } else if (tm <= 2 && stream_weights(p)) {
-            err = wn == 2   ? launch_streamed<2, 8>(a, tm, lds, stream)
-                  : wn == 4 ? launch_streamed<4, 4>(a, tm, lds, stream)
-                  : waves == 8 ? launch_streamed<1, 8>(a, tm, lds, stream) : launch_streamed<1, 4>(a, tm, lds, stream);
+        } else if (tm == 1 && stream_weights(p)) {
+            err = wn == 2   ? launch_streamed<2, 8>(a, lds, stream)
+                  : wn == 4 ? launch_streamed<4, 4>(a, lds, stream)
+                  : waves == 8 ? launch_streamed<1, 8>(a, lds, stream) : launch_streamed<1, 4>(a, lds, stream);
         } else if (wn == 2) {
             if (tm > 2)
                 return hipErrorInvalidValue;  // refused by skinny_make_plan

@@ -204,3 +204,29 @@ def test_act_order_lookups_with_four_units_per_slice(B, M):
     plan = B.gptq_w4a16_plan_query(M, K, N, group, True)
     assert (plan.flags, plan.split_k) == (16, 40)
     check(B, case, group, f"630 groups, M={M}")
+
+
+# ---- non-temporal weight loads (matrices of 128 MB and more, rows of whole cache lines): every tile of both kernels ----
+
+@pytest.fixture(scope="module", params=[(8192, 31264), (16384, 16384)], ids=str)  # 64-column tiles: four wavefronts, eight
+def large(request, B):
+    K, N, group = *request.param, 128
+    assert N % 32 == 0 and K * N // 2 >= 128000000
+    case = workloads.make_case(16, K, N, group, seed=N)
+    qw, qz, sc, x = (dev(case[k]) for k in ("qweight", "qzeros", "scales", "x"))
+    w = torch.empty((K, N), dtype=torch.float16, device="cuda")
+    B.gptq_w4a16_dequant(qw, qz, sc, None, w, group)  # bit-exact by its own tests
+    ref = torch.cat([x.float() @ w[:, lo:lo + 4096].float() for lo in range(0, N, 4096)], dim=1).cpu().numpy()
+    return x, qw, qz, sc, ref, group
+
+
+@pytest.mark.parametrize("kernel,tile,split_k,batches", [
+    (1, 64, 1, (1,)), (1, 64, 3, (1,)), (1, 128, 1, (1,)), (1, 128, 5, (1,)), (1, 256, 1, (1,)), (1, 256, 7, (1,)),
+    (3, 64, 1, (2, 16)), (3, 64, 3, (2, 16)), (3, 128, 1, (2, 16)), (3, 128, 3, (2, 16)), (3, 256, 1, (2, 16)),
+    (3, 256, 8, (2, 16)), (0, 0, 0, (1, 2, 7, 16))])
+def test_streamed_weights(B, large, kernel, tile, split_k, batches):
+    x, qw, qz, sc, ref, group = large
+    for M in batches:
+        out = torch.full((M, qw.shape[1]), float("nan"), dtype=torch.float16, device="cuda")
+        B.gptq_w4a16_gemm(x[:M], qw, qz, sc, None, out, group, B.Plan(kernel=kernel, tile=tile, split_k=split_k))
+        assert_within_band(out.cpu().numpy(), ref[:M], f"kernel {kernel} tile {tile} slices {split_k} M={M}")
