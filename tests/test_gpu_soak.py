@@ -16,7 +16,7 @@ torch = pytest.importorskip("torch")
 
 from paper_2511_19438_amd import workloads  # noqa: E402
 
-# (M, K, N, act_order, plan fields): every plan has K slices
+# (M, K, N, act_order, plan fields[, group, 128 if not given]): every plan has K slices
 CASES = [
     (1, 4096, 1024, False, dict(kernel=1, tile=64, split_k=4)),
     (4, 2048, 520, False, dict(kernel=1, tile=32, split_k=7)),
@@ -31,6 +31,12 @@ CASES = [
     (120, 2048, 544, False, dict(kernel=4, split_k=3)),
     (100, 2048, 544, False, dict(kernel=2, tile=3, split_k=2)),
     (64, 4096, 4096, False, dict()),                              # mid-batch kernel, automatic plan with K slices
+    (8, 4096, 1024, True, dict()),                                # act-order lookups: one row tile
+    (200, 4096, 520, True, dict()),                               # several: a counter per row and column tile
+    (120, 2560, 520, False, dict(kernel=2, tile=8, split_k=2)),   # two wavefront groups, half of the threads exchange
+    (96, 2560, 520, False, dict(kernel=2, tile=8, split_k=2)),    # the same on 96 rows
+    (40, 4256, 136, False, dict(), 32),                           # big-tile kernel with a group row per half stage
+    (70, 4256, 520, False, dict(kernel=2, tile=8, split_k=3), 32),
 ]
 ROUNDS = 1500
 BUDGET_S = 25.0
@@ -42,9 +48,9 @@ def test_k_split_exchange_soak():
     from paper_2511_19438_amd import binding as B
 
     B.load()
-    group = 128
     prepared = []
-    for i, (M, K, N, act, plan_args) in enumerate(CASES):
+    for i, (M, K, N, act, plan_args, *rest) in enumerate(CASES):
+        group = rest[0] if rest else 128
         plan = B.Plan(**plan_args) if plan_args else None
         resolved = B.gptq_w4a16_plan_query(M, K, N, group, act, plan)
         assert resolved.split_k > 1, f"case {i} is meant to exchange partial sums"
@@ -53,12 +59,12 @@ def test_k_split_exchange_soak():
         out = torch.zeros((M, N), dtype=torch.float16, device="cuda")
         B.gptq_w4a16_gemm(dev["x"], dev["qweight"], dev["qzeros"], dev["scales"], dev["g_idx"], out, group, plan)
         torch.cuda.synchronize()
-        prepared.append((dev, plan, out, out.clone().view(torch.int16)))
+        prepared.append((dev, plan, group, out, out.clone().view(torch.int16)))
     bad = torch.zeros(len(CASES), dtype=torch.int32, device="cuda")
     t0 = time.perf_counter()
     launches = 0
     for rnd in range(ROUNDS):
-        for i, (dev, plan, out, first) in enumerate(prepared):
+        for i, (dev, plan, group, out, first) in enumerate(prepared):
             out.fill_(float("nan"))
             B.gptq_w4a16_gemm(dev["x"], dev["qweight"], dev["qzeros"], dev["scales"], dev["g_idx"], out, group, plan)
             bad[i] += (out.view(torch.int16) != first).any().to(torch.int32)
