@@ -182,9 +182,9 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
     const int per_wave = (s1 - s0 + WAVES - 1) / WAVES;
     const int ws0 = min(s0 + wave * per_wave, s1);
     const int ws1 = min(ws0 + per_wave, s1);
-    // every wavefront runs `per_wave` stage bodies (three per loop iteration - the register sets rotate by
-    // unrolling - and one or two after the loop); a body past the wavefront's own share loads its last stage
-    // again and contributes zeros
+    // a wavefront runs one body per stage of its own share, maybe none (three per loop iteration - the register sets
+    // rotate by unrolling - and one or two after the loop; nothing in the loop is shared between wavefronts)
+    const int share = ws1 - ws0;
 
     unsigned char *ring = smem + (size_t)wave * LW;
 
@@ -242,8 +242,7 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
     const PairMagic magic;
 
     // One stage: 64 k of this lane's NB columns against all batch rows.
-    auto consume = [&](int st, const StageRegs<NB> &r, int buf) {
-        const bool live = st < ws1;
+    auto consume = [&](const StageRegs<NB> &r, int buf) {
         uint32_t nz[NB], ss[NB];
 #pragma unroll
         for (int t = 0; t < NB; ++t) {
@@ -251,7 +250,7 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
             nz[t] = 0xD400E400u | z | (z << 20);  // (-(1024 + z), -(64 + z))
             const uint32_t pair = scale_pair(r.sc, t);
             const uint32_t sb = (t & 1) ? (pair >> 16) : (pair & 0xffffu);
-            ss[t] = live ? (sb | (sb << 16)) : 0u;
+            ss[t] = sb | (sb << 16);
         }
         const unsigned char *xs = ring + (size_t)buf * XBUF;
         // The A operands of a step are read from LDS while the MFMAs of the step before run (two register sets):
@@ -288,7 +287,7 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
         asm volatile("" ::: "memory");
         issue_w(st + 2, nxt2);
         arrived(cur, std::integral_constant<int, NX + 2 * NWL>());
-        consume(st, cur, buf);
+        consume(cur, buf);
         // the next body's DMA overwrites the buffer this one has just read: the reads are complete (their values
         // fed the MFMAs above), this keeps the compiler from moving them
         asm volatile("" ::: "memory");
@@ -302,14 +301,14 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
     {
         int st = ws0;
         int buf = 0;
-        for (int b = 3; b <= per_wave; b += 3) {
+        for (int b = 3; b <= share; b += 3) {
             body(st, r0, r2, buf);
             body(st + 1, r1, r0, buf ^ 1);
             body(st + 2, r2, r1, buf);
             st += 3;
             buf ^= 1;
         }
-        const int rest = per_wave % 3;  // the same for every wavefront of the grid
+        const int rest = share % 3;
         if (rest >= 1)
             body(st, r0, r2, buf);
         if (rest == 2)

@@ -177,6 +177,23 @@ def test_an_infinity_survives_the_exchange_of_k_slices(B, kernel, tile, M, group
         assert_within_band(out[rows], ref[rows], "the other rows")
 
 
+@pytest.mark.parametrize("M,K,tile,split_k", [(40, 1280, 64, 3), (24, 1280, 128, 1), (64, 704, 64, 1), (90, 1344, 64, 2), (48, 2048, 0, 0)])
+def test_an_infinity_counts_once_where_wavefronts_have_uneven_shares(B, M, K, tile, split_k):
+    """Mid-batch kernel: a wavefront with fewer stages than the others goes through its last bodies without a stage."""
+    N, group = 136, 64
+    case = workloads.make_case(M, K, N, group, seed=M)
+    plan = B.Plan(kernel=4, tile=tile, split_k=split_k)
+    resolved = B.gptq_w4a16_plan_query(M, K, N, group, False, plan)
+    slices = [K // 64 // resolved.split_k * i for i in range(resolved.split_k + 1)]
+    w = oracle.dequant(case["qweight"], case["qzeros"], case["scales"], None, group).astype(np.float64)
+    for k in sorted({K - 1, K - 64, 64 * slices[1] - 3, 5}):
+        x = case["x"].copy()
+        x[M - 1, k] = np.float16(-np.inf)
+        out = run_gemm(B, dict(case, x=x), group, plan)
+        assert np.array_equal(np.isnan(out[M - 1]), w[k] == 0), f"k = {k}"
+        assert np.all(np.isfinite(out[:M - 1]))
+
+
 # ---- dequantisation: write-through stores for outputs that fit the memory-side cache, past the caches beyond ----
 
 @pytest.mark.parametrize("K,N,group,act", [(8192, 15624, 128, False), (8192, 15632, 128, False), (8192, 15624, 64, True),
