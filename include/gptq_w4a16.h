@@ -61,7 +61,7 @@ enum gptq_status {
     GPTQ_UNSUPPORTED_SHAPE = -2,   /* divisibility rules above violated */
     GPTQ_MISALIGNED = -3,          /* a base pointer is not 16-byte aligned */
     GPTQ_HIP_ERROR = -4,           /* a HIP call or a kernel launch failed */
-    GPTQ_WORKSPACE_TOO_SMALL = -5, /* caller-set workspace smaller than gptq_w4a16_workspace_bytes() */
+    GPTQ_WORKSPACE_TOO_SMALL = -5, /* caller-set workspace too small for the plan, or growth under capture */
     GPTQ_STATIC_SCRATCH_EXCEEDED = -6 /* gptq_w4a16_gemm_static: the problem needs more than the static scratch */
 };
 
@@ -78,10 +78,11 @@ enum gptq_status {
  * kernel in which every wavefront streams its own share of the K slice (no g_idx, K and
  * group_size multiples of 64), larger M the big-tile fp16 MFMA kernel (with K slices where
  * the output tiles alone would not fill the chip).
- * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in a table of all
- * groups in LDS (as long as that fits: up to 606 groups, 630 at up to 384 rows); plan queries report it as kernel 1 (M <= 16) or 2 with
- * 64-column tiles and the flag GPTQ_ACT_LOOKUP, and such a plan given back runs it again.  An explicit request for
- * either kernel without the flag runs that kernel itself.
+ * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in
+ * a table of all groups in LDS (as long as that fits: up to 606 groups, 630 at up to 384 rows); plan
+ * queries report it as kernel 1 (M <= 16) or 2 with 64-column tiles and the flag GPTQ_ACT_LOOKUP, and such
+ * a plan given back runs it again.  An explicit request for either kernel without the flag runs that
+ * kernel itself.
  * Accumulation is in fp32; the result differs from the exact sum by fp32 reassociation
  * and the final fp16 rounding only.  The same inputs give bit-identical outputs on every
  * call (no floating point atomics are used), whatever scratch the call finds.
@@ -123,7 +124,7 @@ GPTQ_API int gptq_w4a16_gemm_static(const void *x, const void *qweight, const vo
 typedef struct gptq_w4a16_plan {
     int kernel;      /* 0 auto, 1 vector split-K kernel (any M, processed 16 rows at a time), 2 big-tile MFMA kernel,
                         3 small-batch MFMA kernel (M <= 128, processed 64 rows at a time; no g_idx,
-                        group_size % 128 == 0; else falls back),
+                        group_size % 128 == 0, or 64 or 32 with M <= 32; else falls back),
                         4 mid-batch streaming MFMA kernel (M <= 128; no g_idx, K % 64 == 0, group_size % 64 == 0;
                         else falls back) */
     int split_k;     /* number of K slices (all four kernels; the big-tile kernel splits by itself on every tile

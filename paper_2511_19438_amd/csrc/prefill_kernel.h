@@ -284,11 +284,11 @@ constexpr int kWavesPerSimd = (BM * BN <= 128 * 256) ? 2 : 1;
 
 // HALF: each 32-k half of a stage brings its own row of scales and of zero points, and both rows travel in DMA pieces
 // that suit any N that is a multiple of 8: word by word (a row of zero points is only 4-byte aligned then), the
-// wavefronts sharing the scales.  One DMA instruction and a few vector operations per
-// stage more than the variant with one group per stage, which therefore stays where it applies (groups of 128 against
-// groups of 32: 2048x4096x11008 on the 128x256 tile 194 us against 205, 512x4096x4096 on the 64x128 tile 33 against
-// 39).  What it took over from the general path: 2048x4096x11008 582 -> 205 us, 333x2752x6888 116 -> 38 (groups of 32),
-// 512x4096x4104 (groups of 128, a width of 8 mod 32) 148 -> 44.
+// wavefronts sharing the scales.  One DMA instruction and a few vector operations per stage more than the variant with
+// one group per stage, which therefore stays where it applies (groups of 128 against groups of 32: 2048x4096x11008 on the
+// 128x256 tile 194 us against 205, 512x4096x4096 on the 64x128 tile 33 against 39).  What it took over from the general
+// path: 2048x4096x11008 582 -> 205 us, 333x2752x6888 107 -> 31 (groups of 32), 512x4096x4104 (groups of 128, a width of 8
+// mod 32) 148 -> 44.
 // A K that ends half-way through a stage (K % 64 == 32): the last stage covers the last 64 k, the first half of which
 // the stage before has done already; its activations are cleared in LDS once they have landed, so nothing is read
 // past a row's or the matrix' end and what is repeated contributes exact zeros.
@@ -297,7 +297,7 @@ constexpr int kWavesPerSimd = (BM * BN <= 128 * 256) ? 2 : 1;
 // the SAME tile, with a ring of their own; only the stage barriers and the sum through LDS at the end are shared.  Two
 // wavefronts per SIMD are what the matrix pipe needs to run under the other's dequantisation (128x256 tile: a 64-k
 // stage takes 0.99 us alone on a compute unit, 1.31 us when two run), and where the tiles give every compute unit one
-// workgroup at most, this is how they get there without partial sums in scratch. 
+// workgroup at most, this is how they get there without partial sums in scratch.
 // 4096x12288 at M = 512: 73.5 -> 58.0 us; 28672x8192 at M = 512, two slices: 266 -> 226.
 //
 // SERIAL: no scratch for the K slices.  A workgroup walks all slices of its tile one after the other - the halves of a

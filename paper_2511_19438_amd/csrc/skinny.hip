@@ -88,11 +88,6 @@ hipError_t launch_lookup(const skinny::Args &a, int tm, int waves, size_t lds, h
 // LDS that a workgroup of the act-order variant may use (the rest holds its static words).
 constexpr size_t kActLdsBytes = 160 * 1024 - 512;
 
-int act_row_blocks(int M)
-{
-    return M <= 16 ? 1 : M <= 32 ? 2 : 4;
-}
-
 size_t act_table_bytes(const Problem &p)
 {
     return (size_t)(p.K / p.group_size) * skinny::kActTableRow;
@@ -123,7 +118,7 @@ bool act_supported(const Problem &p)
 void act_make_plan(const Problem &p, SkinnyPlan &plan)
 {
     const int total_units = ceil_div(p.K, skinny::kUnitK);
-    const int tm = act_row_blocks(p.M);
+    const int tm = row_blocks(p.M);
     const int tiles = ceil_div(p.N, skinny::kCols) * ceil_div(p.M, skinny::kActRows);
     plan.cols_per_wg = skinny::kCols;
     int split = plan.split_k;
@@ -142,8 +137,9 @@ void act_make_plan(const Problem &p, SkinnyPlan &plan)
     if (automatic) {
         // One workgroup per compute unit, as in the plain format: measured best of 1, 2, 3, 4, 6 and 8 slices on
         // 4096x11008 (M = 8: 12.7 us unsplit, 15.4 in two), 11008x4096 (25.9 unsplit, 13.7 in four, 15.2 in eight)
-        // and 4096x4096 (12.1, 8.8 in four) for M = 2 ... 512.  Partial sums within half of the weight bytes
-        // (4096x4096 at M = 64: 18.0 us in four slices, 22.5 in two).
+        // and 4096x4096 (12.1, 8.8 in four) for M = 2 ... 512.  Up to 64 rows the partial sums, written and read, stay
+        // within the weight bytes (8 * split * M * N <= K * N / 2; 4096x4096 at M = 64, at that limit: 18.0 us in four
+        // slices, 22.5 in two); above, their row tiles leave room for few slices anyway (at most K / 1024).
         split = (256 + tiles / 2) / tiles;
         const int max_split = p.K / (16 * (p.M < skinny::kActRows ? p.M : skinny::kActRows));
         if (split > max_split)
@@ -179,7 +175,7 @@ size_t act_workspace_bytes(const Problem &p, const SkinnyPlan &plan)
 hipError_t launch_act(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream)
 {
     unsigned char *ws = static_cast<unsigned char *>(workspace);
-    const int tm = act_row_blocks(p.M);
+    const int tm = row_blocks(p.M);
     skinny::Args a;
     a.x = p.x;
     a.qweight = p.qweight;

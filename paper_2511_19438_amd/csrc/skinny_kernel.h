@@ -118,8 +118,8 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
 // read 256 contiguous bytes: no bank conflicts), so a word costs 4 + 4 permutes to pair the entries on top of the
 // masks, adds and multiplies: 24 vector operations and two 128-bit LDS reads per word WHATEVER M IS, where the
 // vector kernel paid for its lookups and for two operations per weight and row on top, and the big-tile kernel's
-// general path fetched every scale and zero point from global memory.  4096x11008, groups of 128: M = 8 40.8 us
-// (vector kernel) -> 12.7, M = 24 258 (general path) -> 15.1, M = 128 272 -> 48, M = 512 422 -> 138.  Bound by vector
+// general path fetched every scale and zero point from global memory.  4096x11008, groups of 128: M = 8 40.5 us
+// (vector kernel) -> 12.0, M = 24 258 (general path) -> 15.1, M = 128 272 -> 48, M = 512 422 -> 138.  Bound by vector
 // issue (~30 instructions per word against 16 in the plain format) and, from 33 rows on, by the latency of the
 // activation loads.  More than 64 rows are row tiles of one grid.
 //
