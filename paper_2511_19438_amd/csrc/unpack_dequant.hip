@@ -47,7 +47,13 @@ __global__ __launch_bounds__(kThreads) void unpack_qzeros_kernel(const uint32_t 
     *reinterpret_cast<uint2 *>(z_out + 8 * idx) = bytes;
 }
 
-constexpr long long kMemorySideCacheBytes = 256000000;
+// How the dequantised rows are stored.
+enum StorePolicy {
+    kPlain = 0,         // through the L2
+    kWriteThrough = 1,  // sc1: nothing is left dirty in the L2, the rows stay in the memory-side cache
+    kBypass = 2         // non-temporal: past all caches
+};
+constexpr long long kBypassBytes = 224000000;
 
 // w_out[k, n] = fp16( scales[r(k), n] * (q[k, n] - z[r(k), n]) ): exact integer difference, one fp16 multiply.
 //
@@ -57,18 +63,20 @@ constexpr long long kMemorySideCacheBytes = 256000000;
 // (1024 + z) in packed halves is exact (and +0 for q = z, as the conversion of an integer 0 is).
 //
 // The written rows are 80 % of the traffic, and what counts next is whether their reader finds them in the memory-side
-// cache (256 MB).  BYPASS, for outputs that do not fit it: non-temporal stores, past all caches.  Otherwise write-through
-// stores (sc1): nothing is left dirty in the L2, and the rows stay in the memory-side cache.  Non-temporal stores would
-// make the dequantisation itself shorter there, too, but a product that follows longer by more.  The weights alone, and
-// with a product of 16 rows behind them, us with plain / non-temporal / write-through stores (the first three over a set of
-// layers that exceeds the cache):
-//   4096x4096    9.8 /  7.5 /  8.8    25.8 /  30.4 /  24.8
-//   11008x4096  23.1 / 17.8 / 22.4    71.5 /  87.8 /  70.9
-//   8192x12288  47.0 / 43.8 / 45.6    89.9 /  94.5 /  88.1
-//   8192x16384  61.9 / 48.9 / 57.8   112.1 / 108.2 / 112.9   (268 MB)
-//   8192x28672 102.5 / 86.4 / 101.4  230.6 / 205.3 / 230.6
+// cache (256 MB).  Outputs that hardly fit it go past all caches.  Smaller ones stay in it: bypassing it would make the
+// dequantisation itself shorter there, too, but a product that follows longer by more.  Rows that are no whole pieces of
+// 64 bytes (N % 32) share lines at their borders, which both other policies write twice: plain stores.  The weights
+// alone, and with a product of 16 rows behind them, over a set of layers that exceeds the cache, us with plain /
+// non-temporal / write-through stores:
+//   4096x4096             9.8 /  7.5 /  8.8    25.8 /  30.4 /  24.8
+//   11008x4096           23.1 / 17.8 / 22.4    71.5 /  87.8 /  70.9
+//   8192x13312  218 MB   49.9 / 42.2 / 47.9    93.1 /  99.0 /  90.8
+//   10368x11200 232 MB   53.0 / 45.0 / 52.0   107.0 / 106.8 / 107.0
+//   8192x28672  470 MB  101.5 / 98.6 / 100.5  227.8 / 205.0 / 226.9
+//   4096x4528            11.3 / 10.1 / 14.2    28.8 /  34.3 /  29.0
+//   8192x28680          111.9 / 122.7 / 130.8 237.4 / 230.4 / 240.5
 // (11008x4096 with four columns per thread and plain 64-bit stores: 24.0 alone.)
-template <bool ACT_ORDER, bool BYPASS>
+template <bool ACT_ORDER, int POLICY>
 __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint32_t *__restrict__ qweight,
                                                            const uint32_t *__restrict__ qzeros,
                                                            const half_t *__restrict__ scales,
@@ -77,8 +85,8 @@ __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint32_t *__res
                                                            int group_size)
 {
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-    constexpr int kWriteThrough = 16;  // cache policy of a buffer store: sc1
-    // (write-through: the whole output is under 4 GB)
+    constexpr int kSc1 = 16;  // cache policy of a buffer store
+    // (kWriteThrough: the whole output is under 4 GB)
     const auto out_rsrc = __builtin_amdgcn_make_buffer_rsrc(w_out, 0, (uint32_t)rows * 16u * (uint32_t)N, 0x00020000);
     const int octs = N >> 3;
     const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
@@ -111,11 +119,13 @@ __global__ __launch_bounds__(kThreads) void dequant_kernel(const uint32_t *__res
         for (int c = 0; c < 8; ++c)
             o[c] = __builtin_bit_cast(half_t, (uint16_t)(0x6400u | ((w[c] >> (4 * j)) & 15u)));
         o = (o + nz) * s;
-        if (BYPASS)
+        if (POLICY == kPlain)
+            *reinterpret_cast<half8_t *>(w_out + (size_t)k * N + n0) = o;
+        else if (POLICY == kBypass)
             __builtin_nontemporal_store(o, reinterpret_cast<half8_t *>(w_out + (size_t)k * N + n0));
         else
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, o), out_rsrc,
-                                                   ((uint32_t)k * (uint32_t)N + (uint32_t)n0) * 2u, 0, kWriteThrough);
+                                                   ((uint32_t)k * (uint32_t)N + (uint32_t)n0) * 2u, 0, kSc1);
     }
 }
 
@@ -172,9 +182,10 @@ hipError_t launch_dequant(const uint32_t *qweight, const uint32_t *qzeros, const
 {
     const int rows = K / 8;
     const long long items = (long long)rows * (N / 8);
-    const bool bypass = 2ll * K * N > kMemorySideCacheBytes;
-    auto kernel = g_idx ? (bypass ? dequant_kernel<true, true> : dequant_kernel<true, false>)
-                        : (bypass ? dequant_kernel<false, true> : dequant_kernel<false, false>);
+    const int policy = N % 32 != 0 ? kPlain : 2ll * K * N > kBypassBytes ? kBypass : kWriteThrough;
+    auto kernel = policy == kPlain    ? (g_idx ? dequant_kernel<true, kPlain> : dequant_kernel<false, kPlain>)
+                  : policy == kBypass ? (g_idx ? dequant_kernel<true, kBypass> : dequant_kernel<false, kBypass>)
+                                      : (g_idx ? dequant_kernel<true, kWriteThrough> : dequant_kernel<false, kWriteThrough>);
     hipLaunchKernelGGL(kernel, dim3(blocks_for(items)), dim3(kThreads), 0, stream, qweight, qzeros, scales, g_idx,
                        w_out, rows, N, group_size);
     return hipGetLastError();
