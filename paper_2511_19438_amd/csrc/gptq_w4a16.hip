@@ -157,7 +157,8 @@ constexpr int kVectorFallbackMaxM = 8;
 //   a round less than four fifths full, K from 6144, 50 M weights:  12320x18432 29.5 us, 46.4; 8224x9216 14.5, 17.8
 //     (groups of 64 13.8, 15.9); in smaller matrices the small-batch kernel stays ahead (8224x2056 10.3, 8.4), and below
 //     that depth, too (4128x12288 11.8, 10.7);
-//   beyond 16384 columns a round less than 70 % full, whatever the depth (4128x20480 15.0, 19.5);
+//   beyond 16384 columns a round less than 70 % full, K from 2048 (groups of 64: 3072):  4128x20480 15.0, 19.5; 2080x18432
+//     10.4, 11.4 (1120x18432 8.7, 8.0); groups of 64 3136x18432 10.7, 12.2 (2112x18432 10.1, 9.6);
 //   groups of 32, K from 8192, N from 14336: level at best (28704x28672 89.6, 107.6; 16416x16384 33.9, 33.9).
 // Layers so small that the launch dominates (1344x1536 4.9, 5.4) and very wide ones (8256x38256 41, 51; 2112x57344 17, 22;
 // but 4160x45056 36, 29) stay with the vector kernel as well.
@@ -175,7 +176,7 @@ bool tail_prefers_vector(const Problem &p)
     const double full = workgroups / (256.0 * ((workgroups + 255) / 256));
     if (full < 0.8 && p.K >= 6144 && (long long)p.K * p.N >= (3ll << 24))
         return true;
-    if (full < 0.7 && p.N > 16384)
+    if (full < 0.7 && p.N > 16384 && p.K >= (p.group_size == 32 ? 2048 : 3072))
         return true;
     return p.group_size == 32 && p.K >= 8192 && p.N >= 14336;
 }

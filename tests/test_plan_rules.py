@@ -84,9 +84,9 @@ def test_the_act_order_lookup_flag_is_refused_where_there_is_no_such_variant(B):
 def test_three_and_four_rows_on_a_k_that_ends_inside_a_unit(B):
     """The faster of the vector kernel (1) and the small-batch kernel (3) at sizes where they measured 10 % and more apart."""
     vector = [(12320, 18432, 32), (8224, 9216, 32), (8224, 16392, 32), (16416, 24576, 32), (28704, 6400, 32), (4128, 20480, 32),
-              (28704, 28672, 32), (12352, 18432, 64), (16448, 9216, 64), (28736, 4168, 64), (8256, 24576, 64), (2112, 57344, 32)]
+              (28704, 28672, 32), (12352, 18432, 64), (16448, 9216, 64), (28736, 4168, 64), (8256, 24576, 64), (2112, 57344, 32), (2592, 18432, 32), (3136, 17408, 64)]
     small = [(8224, 2056, 32), (28704, 3072, 32), (4128, 4168, 32), (4128, 12288, 32), (6176, 5120, 32), (8224, 6912, 32),
-             (4160, 24576, 64), (8256, 4168, 64), (28736, 5120, 64), (2112, 16384, 64), (6208, 28672, 64), (12352, 2304, 64)]
+             (4160, 24576, 64), (8256, 4168, 64), (28736, 5120, 64), (2112, 16384, 64), (6208, 28672, 64), (12352, 2304, 64), (704, 21504, 64), (1120, 18432, 32), (1088, 20480, 64)]
     for M in (3, 4):
         assert [s for s in vector if B.gptq_w4a16_plan_query(M, s[0], s[1], s[2]).kernel != 1] == []
         assert [s for s in small if B.gptq_w4a16_plan_query(M, s[0], s[1], s[2]).kernel != 3] == []
