@@ -204,8 +204,10 @@ bool mid_batch_by_default(const Problem &p)
     // 2048-16384: from 128 column tiles and K = 16384 on level at worst and up to 51 % ahead (16384x8192 48.6 us, 48.4;
     // 20480x12288 87.1, 64.9; 28672x8192 78.5, 66.4), from 96 tiles on at K = 20480 (20480x6144 49.4, 48.3; 28672x7168
     // 73.1, 64.4).  Narrower layers lose with it, their tiles being too few (28672x4096 43.3, 51.6; 16384x2048 19.9, 24.8;
-    // 24576x5120 45.0, 53.5).
-    if (p.M <= 96 && ((tiles64 >= 128 && p.K >= 16384) || (tiles64 >= 96 && p.K >= 20480)))
+    // 24576x5120 45.0, 53.5) - down to a few hundred columns, where the mid-batch kernel has to make more slices than its
+    // exchange is worth (16384x512 25.1, 21.2; 96 rows of 20480x896 26.9, 24.1, but 65 rows 23.7, 24.1).
+    if (p.M <= 96 && p.K >= 16384 &&
+        (tiles64 >= 128 || (tiles64 >= 96 && p.K >= 20480) || tiles64 <= 8 || (tiles64 <= 14 && p.M > 80)))
         return false;
     return tiles64 <= 256 && (tiles64 >= 128 || p.K >= 8192);
 }

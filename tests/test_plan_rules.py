@@ -101,6 +101,8 @@ def test_deep_layers_at_65_to_96_rows(B):
         assert [s for s in mid if B.gptq_w4a16_plan_query(M, *s, 128).kernel != 4] == []
         assert [s for s in big if B.gptq_w4a16_plan_query(M, *s, 128).kernel != 2] == []
     assert B.gptq_w4a16_plan_query(97, 28672, 8192, 128).kernel == 4
+    assert [B.gptq_w4a16_plan_query(M, 20480, 512, 128).kernel for M in (65, 96, 97)] == [2, 2, 4]
+    assert [B.gptq_w4a16_plan_query(M, 20480, 640, 128).kernel for M in (65, 80, 81, 96)] == [4, 4, 2, 2]
 
 
 def test_scratch_of_act_order_slices_is_bounded(B):
