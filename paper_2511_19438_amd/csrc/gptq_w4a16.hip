@@ -147,7 +147,17 @@ constexpr int kSmallBatchAutoMaxM = 32;
 // Formats that the small-batch kernel does not take (groups of 96, ...): the vector kernel up to eight rows, then the
 // pipelined big-tile kernel with K slices (4128x4096, groups of 96: M = 8 15.9 us against 16.1, M = 9 29.7 against 16.0;
 // 2784x6888: M = 4 9.1 against 14.8, M = 16 32.3 against 14.6).
+// Up to 16 rows deep narrow layers stay with the vector kernel, too: the big-tile kernel has few tiles there and many slices
+// (groups of 96, M = 9 and 16: 8064x512 15.9 us against 18.8, 16.1, 18.6; 16128x256 16.4, 22.5; 8064x1024 16.9, 19.1; but
+// 8064x1536 20.0, 19.8 and 12096x768 21.6, 20.1, 25.7, 20.1; 4032x512 15.2, 13.9).
 constexpr int kVectorFallbackMaxM = 8;
+
+bool vector_fallback(const Problem &p)
+{
+    if (p.M <= kVectorFallbackMaxM)
+        return true;
+    return p.M <= kDecodeMaxM && (!prefill_pipelined(p) || (p.K >= 6144 && (long long)p.K * p.N < (1ll << 23)));
+}
 
 // Small groups with a K that ends inside a 128-k unit, up to four rows: whether the vector kernel is the better one.  At
 // two rows it is on half of the shapes (3776x34176 18.4 us against 22.9).  At three and four the small-batch kernel is
@@ -246,7 +256,7 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
         else if (small_batch_by_default(p))
             kernel = 3;
         else
-            kernel = (p.M <= kVectorFallbackMaxM || (p.M <= kDecodeMaxM && !prefill_pipelined(p))) ? 1 : 2;
+            kernel = vector_fallback(p) ? 1 : 2;
     }
     if (kernel == 3 && !skinny_supported(p))
         kernel = (p.M <= kDecodeMaxM) ? 1 : 2;

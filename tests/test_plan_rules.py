@@ -118,3 +118,11 @@ def test_act_order_lookups_serve_as_many_groups_as_the_lds_holds(B):
     assert [flags(M, 606) for M in (2, 16, 384, 385, 2048)] == [16] * 5
     assert [flags(M, 630) for M in (2, 16, 17, 384, 385)] == [16, 16, 16, 16, 0]
     assert [flags(M, 631) for M in (2, 17, 384)] == [0, 0, 0]
+
+
+def test_nine_to_sixteen_rows_of_formats_without_a_small_batch_kernel(B):
+    """The vector kernel (1) on deep narrow layers, the big-tile kernel (2) elsewhere; sizes measured 8 % and more apart."""
+    for M in (9, 11, 16):
+        assert {B.gptq_w4a16_plan_query(M, *s, 96).kernel for s in [(8064, 256), (8064, 1024), (12096, 512), (16128, 512), (24192, 256)]} == {1}
+        assert {B.gptq_w4a16_plan_query(M, *s, 96).kernel for s in [(4032, 512), (2016, 4096), (8064, 3072), (12096, 1536), (24192, 1024)]} == {2}
+    assert B.gptq_w4a16_plan_query(17, 8064, 256, 96).kernel == 2
