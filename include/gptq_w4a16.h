@@ -72,8 +72,9 @@ enum gptq_status {
  * not be zeroed (unlike the accumulate-by-atomicAdd contract of Eq. 9-10).
  * By default M = 1 runs the bandwidth-bound split-K vector kernel, 2 <= M <= 32 a small-batch
  * MFMA kernel with the same split-K decomposition (when the format allows: no g_idx,
- * group_size % 128 == 0 or 64 / 32; otherwise the vector kernel up to M = 8, which also
- * keeps up to four rows where it measured faster with a K that is no multiple of 128), 33 <= M <= 64
+ * group_size % 128 == 0 or 64 / 32; otherwise the vector kernel up to M = 8, or 16 on deep
+ * narrow layers, which also keeps up to four rows where it measured faster with a K that is
+ * no multiple of 128), 33 <= M <= 64
  * (and 17-32 or 65-128 rows on the layer shapes where it measured faster) a mid-batch MFMA
  * kernel in which every wavefront streams its own share of the K slice (no g_idx, K and
  * group_size multiples of 64), larger M the big-tile fp16 MFMA kernel (with K slices where
