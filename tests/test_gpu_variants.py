@@ -52,7 +52,7 @@ def test_a_queried_act_order_plan_runs_the_automatic_call_again(B, M, K, N, grou
 
 @pytest.mark.parametrize("M", [8, 40])
 def test_act_order_runs_on_a_workspace_without_room_for_slices(B, M):
-    """Scratch that holds no partial sums: from 17 rows on the call gives up its slices, below it is refused as before."""
+    """Scratch that holds no partial sums: from 17 rows on the workgroups walk the slices themselves, below the call is refused."""
     K, N, group = 2048, 264, 128
     case = workloads.make_case(M, K, N, group, seed=M, act_order=True)
     assert B.gptq_w4a16_plan_query(M, K, N, group, True).split_k > 1
