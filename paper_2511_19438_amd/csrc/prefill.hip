@@ -113,8 +113,12 @@ double estimate_us(const Problem &p, int t, int rows, int split, bool half)
         const double stage = full * 1.6 + (rest > 1.0 + 1e-9 ? 1.6 : rest > 1e-9 ? 0.98 : 0.0);
         return 5.2 + sps * stage * scale + 1.5 * full + exchange;
     }
-    // 256x256: one workgroup per compute unit, whole rounds
-    return std::ceil(n - 1e-9) * (sps * 1.286 * (half ? 1.16 : 1.0) + 9.9);
+    // 256x256: one workgroup per compute unit, whole rounds.  The pace is that of a full chip under sustained load: a
+    // stage takes 1.22 us with half of the units busy, 1.38 with one round of all, 1.43-1.55 over several rounds, and the
+    // tile is a candidate where they are busy (1.9 k random problems with M 129-2048, against the fitted 1.286: picks 0.7 %
+    // behind the best tile instead of 1.1, 19 % at worst instead of 34; 777x8192x57344 814 -> 744 us, 129x8192x57344
+    // 210 -> 187, 777x4096x12288 95 -> 87).
+    return std::ceil(n - 1e-9) * (sps * 1.39 * (half ? 1.16 : 1.0) + 9.9);
 }
 
 int mode_of(const Problem &p)

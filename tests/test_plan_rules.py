@@ -126,3 +126,11 @@ def test_nine_to_sixteen_rows_of_formats_without_a_small_batch_kernel(B):
         assert {B.gptq_w4a16_plan_query(M, *s, 96).kernel for s in [(8064, 256), (8064, 1024), (12096, 512), (16128, 512), (24192, 256)]} == {1}
         assert {B.gptq_w4a16_plan_query(M, *s, 96).kernel for s in [(4032, 512), (2016, 4096), (8064, 3072), (12096, 1536), (24192, 1024)]} == {2}
     assert B.gptq_w4a16_plan_query(17, 8064, 256, 96).kernel == 2
+
+
+def test_the_largest_tile_only_where_it_is_the_fastest(B):
+    """256x256 (1) or 128x256 (8), sizes where they measured 2 % and more apart."""
+    tile = lambda *q: B.gptq_w4a16_plan_query(*q, 128).tile
+    assert [tile(*q) for q in [(777, 4096, 12288), (777, 8192, 10240), (129, 8192, 57344), (777, 8192, 57344), (1024, 8192, 57344),
+                               (1396, 6656, 26112), (4096, 8192, 10240)]] == [8] * 7
+    assert [tile(*q) for q in [(2048, 8192, 57344), (512, 4096, 22016), (2048, 4096, 22016)]] == [1] * 3
