@@ -247,7 +247,7 @@ GPTQ_API int gptq_w4a16_unpack(const void *qweight, void *q_out, const void *qze
  * gptq_w4a16_set_workspace() hands over caller-owned device memory (256-byte aligned, at least
  * gptq_w4a16_workspace_bytes() of the problems it will serve) instead; it synchronises the device, frees
  * every library-owned block (current and retired: graphs captured on them must not be replayed afterwards)
- * and clears the new memory with a synchronous hipMemset.  Passing NULL returns to library-owned scratch.
+ * and clears the new memory before it returns.  Passing NULL returns to library-owned scratch.
  * There is one workspace per device (the current one when the call is made): calls that overlap in time on
  * different streams of one device race on it.
  */

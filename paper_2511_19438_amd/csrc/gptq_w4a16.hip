@@ -87,6 +87,13 @@ int check_shape(int K, int N, int group_size)
     return GPTQ_OK;
 }
 
+// Clears device memory and returns when that has happened: a memset of device memory may return before it is done, and
+// the streams that use the memory next need not wait for the null stream it runs on (hipStreamNonBlocking).
+bool clear_now(void *p, size_t bytes)
+{
+    return hipMemset(p, 0, bytes) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess;
+}
+
 // Makes sure the current device has scratch of at least `bytes`; returns it in *out.
 //
 // Library-owned scratch only ever grows, and a block that has been handed to a launch is never freed while the
@@ -121,7 +128,7 @@ int acquire_workspace(size_t bytes, hipStream_t stream, void **out)
     if (hipMalloc(&p, want) != hipSuccess)
         return GPTQ_HIP_ERROR;
     // the arrival counters live at the front and must start at zero; clear everything once
-    if (hipMemset(p, 0, want) != hipSuccess) {
+    if (!clear_now(p, want)) {
         (void)hipFree(p);
         return GPTQ_HIP_ERROR;
     }
@@ -731,7 +738,7 @@ int gptq_w4a16_set_workspace(void *dev_ptr, size_t bytes)
     if (dev_ptr) {
         if (hipDeviceSynchronize() != hipSuccess)
             return GPTQ_HIP_ERROR;
-        if (hipMemset(dev_ptr, 0, bytes) != hipSuccess)
+        if (!clear_now(dev_ptr, bytes))
             return GPTQ_HIP_ERROR;
         ws.ptr = dev_ptr;
         ws.bytes = bytes;

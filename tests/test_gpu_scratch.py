@@ -157,3 +157,33 @@ def test_a_deep_layer_runs_on_the_workspace_that_served_it_with_fewer_slices(B):
     mi, ni = workloads.sample_positions(M, N, 128, 2)
     ref = oracle.gemm_ref_sampled(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group, mi, ni)
     assert_within_band(want.cpu().numpy()[mi, ni], ref, "77 rows of a deep layer")
+
+
+@pytest.mark.parametrize("owned", [True, False])
+def test_new_scratch_is_clear_before_another_stream_uses_it(B, owned):
+    """The null stream, on which the memory is cleared, is busy; the stream of the call does not wait for it."""
+    M, K, N, group = 8, 4096, 1024, 128
+    case = workloads.make_case(M, K, N, group, seed=2)
+    assert B.gptq_w4a16_plan_query(M, K, N, group).split_k > 1
+    want = run_gemm(B, case, group)
+    x, qw, qz, sc = (dev(case[k]) for k in ("x", "qweight", "qzeros", "scales"))
+    out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    a = torch.randn(8192, 8192, device="cuda").half()
+    dirty = torch.full((64 << 20,), 0x5a, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    try:
+        for _ in range(5):
+            B.gptq_w4a16_set_workspace(None)
+            out.fill_(float("nan"))
+            dirty.fill_(0x5a)
+            torch.cuda.synchronize()
+            for _ in range(10):
+                a @ a  # about 10 ms on the default (null) stream
+            if not owned:
+                B.gptq_w4a16_set_workspace(dirty)
+            with torch.cuda.stream(torch.cuda.Stream()):
+                B.gptq_w4a16_gemm(x, qw, qz, sc, None, out, group)
+            torch.cuda.synchronize()
+            assert np.array_equal(bits(out.cpu().numpy()), bits(want))
+    finally:
+        B.gptq_w4a16_set_workspace(None)
