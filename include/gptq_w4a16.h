@@ -80,7 +80,7 @@ enum gptq_status {
  * group_size multiples of 64), larger M the big-tile fp16 MFMA kernel (with K slices where
  * the output tiles alone would not fill the chip).
  * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in
- * a table of all groups in LDS (as long as that fits: up to 606 groups, 630 at up to 384 rows); plan
+ * a table of all groups in LDS (as long as that fits: up to 606 groups, 630 at up to 384 rows; not large batches of a K under 640); plan
  * queries report it as kernel 1 (M <= 16) or 2 with 64-column tiles and the flag GPTQ_ACT_LOOKUP, and such
  * a plan given back runs it again.  An explicit request for either kernel without the flag runs that
  * kernel itself.

@@ -229,6 +229,18 @@ bool mid_batch_by_default(const Problem &p)
     return tiles64 <= 256 && (tiles64 >= 128 || p.K >= 8192);
 }
 
+// Act-order as stored: whether the lookup variant (64x64 tiles, each with its own table) is the better one against the
+// kernels without it.  It is everywhere but where a shallow K leaves many tiles little to do, against the big-tile kernel's
+// general path: 256x256x4096 9 us against 20, 512x256x4096 15, 20, but 1024x256x4096 26, 21 and 2048x256x40960 458, 272;
+// 512x544x4096 18, 39, but 2048x544x40960 614, 568.  From K = 768 on it is ahead at every size (2048x768x16384 278, 318).
+bool act_by_default(const Problem &p)
+{
+    if (!act_supported(p))
+        return false;
+    const long long tiles = (long long)((p.N + 63) / 64) * ((p.M + 63) / 64);
+    return !(p.M > 64 && p.K < 384 && tiles > 640) && !(p.M > 256 && p.K < 640 && tiles > 2048);
+}
+
 // What a call resolves to: the kernel and its decomposition, after the automatic choices.
 struct Resolved {
     int kernel;  // 1 vector, 2 big-tile MFMA, 3 small-batch MFMA, 4 mid-batch streaming MFMA
@@ -245,7 +257,7 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
     Resolved r = {};
     int kernel = plan ? plan->kernel : 0;
     const bool lookup = plan && (plan->flags & GPTQ_ACT_LOOKUP) != 0;  // (check_flags: the problem has the variant)
-    if (lookup || (kernel == 0 && act_supported(p))) {
+    if (lookup || (kernel == 0 && act_by_default(p))) {
         // act-order as stored: the lookup variant for every batch of two rows and more.  Reported under the ids of
         // the kernels that serve an explicit request there (the vector kernel up to 16 rows, the big-tile kernel's
         // general path above), with a flag that tells it from them.

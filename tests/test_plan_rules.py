@@ -134,3 +134,12 @@ def test_the_largest_tile_only_where_it_is_the_fastest(B):
     assert [tile(*q) for q in [(777, 4096, 12288), (777, 8192, 10240), (129, 8192, 57344), (777, 8192, 57344), (1024, 8192, 57344),
                                (1396, 6656, 26112), (4096, 8192, 10240)]] == [8] * 7
     assert [tile(*q) for q in [(2048, 8192, 57344), (512, 4096, 22016), (2048, 4096, 22016)]] == [1] * 3
+
+
+def test_act_order_on_a_shallow_k(B):
+    """Lookups (flag 16) or the general path; sizes measured 8 % and more apart."""
+    flags = lambda M, K, N: B.gptq_w4a16_plan_query(M, K, N, 32, True).flags
+    assert [flags(*s) for s in [(64, 256, 40960), (256, 256, 4096), (512, 256, 4096), (512, 544, 4096), (256, 544, 40960),
+                                (2048, 768, 16384), (8, 256, 57344)]] == [16] * 7
+    assert [flags(*s) for s in [(1024, 256, 4096), (256, 256, 16384), (2048, 256, 40960), (1024, 544, 16384), (2048, 544, 40960)]] == [0] * 5
+    assert B.gptq_w4a16_plan_query(2048, 256, 40960, 32, True, B.Plan(kernel=2, flags=16)).flags == 16  # still on request
