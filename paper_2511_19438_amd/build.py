@@ -29,6 +29,7 @@ COMMON = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc"
 
 DECODE_BATCHES = (1, 2, 4, 8, 16)
 PREFILL_TILES = (1, 3, 5, 8, 9)
+RING_GROUPS = (1, 2, 4)
 
 
 def units():
@@ -43,6 +44,8 @@ def units():
            ("probe.hip", "probe.o", [])]
     for mb in DECODE_BATCHES:
         out.append(("decode_mb.hip", f"decode_mb{mb}.o", [f"-DGPTQ_DECODE_MB={mb}"]))
+    for g in RING_GROUPS:
+        out.append(("ring.hip", f"ring{g}.o", [f"-DGPTQ_RING_GPU={g}"]))
     for t in PREFILL_TILES:
         out.append(("prefill_tile.hip", f"prefill_tile{t}.o", [f"-DGPTQ_PREFILL_TILE={t}"]))
     return out

@@ -17,8 +17,15 @@ constexpr int kDecodeMaxM = 16;
 
 struct Workspace {
     void *ptr = nullptr;
-    size_t bytes = 0;
+    size_t bytes = 0;  // without the slots
     bool owned = false;
+};
+
+// Scratch of a launch: the block, and the slots of two-slice exchanges (exchange.h) behind it where the library owns it.
+// A caller's workspace has none: the same launches then exchange through partial sums, with the same result.
+struct Scratch {
+    void *ws = nullptr;
+    void *slots = nullptr;
 };
 
 std::mutex g_mutex;
@@ -33,7 +40,7 @@ void *g_static_ptr[kMaxDevices] = {};
 
 }  // namespace
 
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kSlotBytes];
 
 namespace {
 
@@ -44,10 +51,10 @@ __global__ void clear_words_kernel(unsigned *p, unsigned n)
         p[i] = 0u;
 }
 
-// Device address of the current device's static scratch.  The first call on a device looks the address up and
-// clears the arrival counters at its front with a small kernel on `stream` (a kernel, not a memset: the call
-// may be under stream capture).  No allocation.
-int static_scratch_ptr(hipStream_t stream, void **out)
+// The current device's static scratch.  The first call on a device looks the address up and clears the arrival counters
+// at its front and the slots at its end with small kernels on `stream` (kernels, not memsets: the call may be under stream
+// capture).  No allocation.
+int static_scratch_ptr(hipStream_t stream, Scratch *out)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
@@ -60,11 +67,15 @@ int static_scratch_ptr(hipStream_t stream, void **out)
         const unsigned words = (unsigned)(decode_counter_bytes(0) / sizeof(unsigned));
         hipLaunchKernelGGL(clear_words_kernel, dim3((words + 255) / 256), dim3(256), 0, stream,
                            static_cast<unsigned *>(ptr), words);
+        const unsigned slot_words = (unsigned)(kSlotBytes / sizeof(unsigned));
+        hipLaunchKernelGGL(clear_words_kernel, dim3((slot_words + 255) / 256), dim3(256), 0, stream,
+                           reinterpret_cast<unsigned *>(static_cast<unsigned char *>(ptr) + kStaticScratchBytes), slot_words);
         if (hipGetLastError() != hipSuccess)
             return GPTQ_HIP_ERROR;
         g_static_ptr[dev] = ptr;
     }
-    *out = g_static_ptr[dev];
+    out->ws = g_static_ptr[dev];
+    out->slots = static_cast<unsigned char *>(g_static_ptr[dev]) + kStaticScratchBytes;
     return GPTQ_OK;
 }
 
@@ -101,7 +112,7 @@ bool clear_now(void *p, size_t bytes)
 // sums, arrival counters, gathered activations).  A block that became too small is retired instead and stays
 // valid; retired blocks are released by gptq_w4a16_set_workspace().  Growth allocates and clears memory, which is
 // not allowed while `stream` is being captured: such a call is refused.
-int acquire_workspace(size_t bytes, hipStream_t stream, void **out)
+int acquire_workspace(size_t bytes, hipStream_t stream, Scratch *out)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
@@ -109,7 +120,8 @@ int acquire_workspace(size_t bytes, hipStream_t stream, void **out)
     std::lock_guard<std::mutex> lock(g_mutex);
     Workspace &ws = g_ws[dev];
     if (ws.ptr && ws.bytes >= bytes) {
-        *out = ws.ptr;
+        out->ws = ws.ptr;
+        out->slots = ws.owned ? static_cast<unsigned char *>(ws.ptr) + ws.bytes : nullptr;
         return GPTQ_OK;
     }
     if (ws.ptr && !ws.owned)
@@ -124,11 +136,12 @@ int acquire_workspace(size_t bytes, hipStream_t stream, void **out)
     size_t want = bytes + bytes / 2;
     if (want < (size_t)(8u << 20))
         want = (size_t)(8u << 20);
+    want = (want + 255) & ~(size_t)255;
     void *p = nullptr;
-    if (hipMalloc(&p, want) != hipSuccess)
+    if (hipMalloc(&p, want + kSlotBytes) != hipSuccess)
         return GPTQ_HIP_ERROR;
-    // the arrival counters live at the front and must start at zero; clear everything once
-    if (!clear_now(p, want)) {
+    // the arrival counters at the front and the slots at the end must start at zero; clear everything once
+    if (!clear_now(p, want + kSlotBytes)) {
         (void)hipFree(p);
         return GPTQ_HIP_ERROR;
     }
@@ -137,7 +150,8 @@ int acquire_workspace(size_t bytes, hipStream_t stream, void **out)
     ws.ptr = p;
     ws.bytes = want;
     ws.owned = true;
-    *out = p;
+    out->ws = p;
+    out->slots = static_cast<unsigned char *>(p) + want;
     return GPTQ_OK;
 }
 
@@ -245,6 +259,7 @@ bool act_by_default(const Problem &p)
 struct Resolved {
     int kernel;  // 1 vector, 2 big-tile MFMA, 3 small-batch MFMA, 4 mid-batch streaming MFMA
     bool act;    // the act-order lookup variant of the small-batch kernel (plan in `skinny`) runs in its place
+    bool ring;   // the small-batch kernel (plan in `skinny`) runs in the mid-batch kernel's place
     DecodePlan decode;
     SkinnyPlan skinny;
     MidPlan mid;
@@ -304,6 +319,17 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
         r.mid.cols_per_wg = plan ? plan->tile : 0;
         r.mid.split_k = plan ? plan->split_k : 0;
         mid_make_plan(p, r.mid);
+        // Up to 32 rows the small-batch kernel on its ring of LDS slots has overtaken the mid-batch kernel and runs in its
+        // place (170 random layers at 17-32 rows: 1-35 % faster, 2 % slower on one; 4096x22016 at M = 32 19.6 us -> 15.7,
+        // 28672x8192 40.5 -> 34.1), with widths and slices of its own unless a plan says kernel 4.
+        if (ring_supported(p)) {
+            r.ring = true;
+            if (plan && plan->kernel == 4) {
+                r.skinny.cols_per_wg = plan->tile == 32 || plan->tile == 96 ? plan->tile : r.mid.cols_per_wg;
+                r.skinny.split_k = r.mid.split_k;
+            }
+            skinny_make_plan(p, r.skinny);
+        }
     } else {
         r.prefill.tile = plan ? plan->tile : 0;
         r.prefill.split_k = plan ? plan->split_k : 0;
@@ -319,7 +345,7 @@ size_t scratch_bytes(const Problem &p, const Resolved &r)
         bytes = act_workspace_bytes(p, r.skinny);
     else if (r.kernel == 1)
         bytes = decode_workspace_bytes(p, r.decode);
-    else if (r.kernel == 3)
+    else if (r.kernel == 3 || r.ring)
         bytes = skinny_workspace_bytes(p, r.skinny);
     else if (r.kernel == 4)
         bytes = mid_workspace_bytes(p, r.mid);
@@ -328,15 +354,16 @@ size_t scratch_bytes(const Problem &p, const Resolved &r)
     return bytes > r.least ? bytes : r.least;
 }
 
-int launch_resolved(const Problem &p, const Resolved &r, void *ws, hipStream_t stream)
+int launch_resolved(const Problem &p, const Resolved &r, const Scratch &scratch, hipStream_t stream)
 {
     hipError_t err;
+    void *const ws = scratch.ws;
     if (r.act)
         err = launch_act(p, r.skinny, ws, stream);
     else if (r.kernel == 1)
         err = launch_decode(p, r.decode, ws, stream);
-    else if (r.kernel == 3)
-        err = launch_skinny(p, r.skinny, ws, stream);
+    else if (r.kernel == 3 || r.ring)
+        err = launch_skinny(p, r.skinny, ws, scratch.slots, stream);
     else if (r.kernel == 4)
         err = launch_mid(p, r.mid, ws, stream);
     else
@@ -364,7 +391,7 @@ bool fall_back(const Problem &p, const gptq_w4a16_plan_t *request, Resolved &r)
 {
     if (r.skinny.serial || r.prefill.serial || (request && request->split_k > 0))
         return false;
-    if (r.act || (r.kernel == 3 && skinny_scratch_optional(p)))
+    if (r.act || ((r.kernel == 3 || r.ring) && skinny_scratch_optional(p, r.skinny)))
         r.skinny.serial = true;
     else if (r.kernel == 2 && r.prefill.split_k > 1)
         r.prefill.serial = true;
@@ -377,12 +404,12 @@ bool fall_back(const Problem &p, const gptq_w4a16_plan_t *request, Resolved &r)
 int run_gemm(const Problem &p, hipStream_t stream, const gptq_w4a16_plan_t *plan)
 {
     Resolved r = resolve(p, plan);
-    void *ws = nullptr;
+    Scratch scratch;
     for (;;) {
         const size_t bytes = scratch_bytes(p, r);
-        const int rc = bytes > 0 ? acquire_workspace(bytes, stream, &ws) : GPTQ_OK;
+        const int rc = bytes > 0 ? acquire_workspace(bytes, stream, &scratch) : GPTQ_OK;
         if (rc == GPTQ_OK)
-            return launch_resolved(p, r, ws, stream);
+            return launch_resolved(p, r, scratch, stream);
         if (rc != GPTQ_WORKSPACE_TOO_SMALL || !fall_back(p, plan, r))
             return rc;
     }
@@ -478,11 +505,11 @@ int gptq_w4a16_gemm_static(const void *x, const void *qweight, const void *qzero
         if (!fall_back(p, nullptr, r))
             return GPTQ_STATIC_SCRATCH_EXCEEDED;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    void *ws = nullptr;
-    const int wrc = static_scratch_ptr(st, &ws);
+    Scratch scratch;
+    const int wrc = static_scratch_ptr(st, &scratch);
     if (wrc != GPTQ_OK)
         return wrc;
-    return launch_resolved(p, r, ws, st);
+    return launch_resolved(p, r, scratch, st);
 }
 
 int gptq_w4a16_gemm(const void *x, const void *qweight, const void *qzeros, const void *scales,
@@ -522,7 +549,7 @@ int gptq_w4a16_plan_query(int M, int K, int N, int group_size, int act_order, co
         out.split_k = r.decode.split_k;
         out.tile = r.decode.cols_per_wg;
         out.flags = r.decode.flags;
-    } else if (r.kernel == 3) {
+    } else if (r.kernel == 3 || r.ring) {
         out.split_k = r.skinny.split_k;
         out.tile = r.skinny.cols_per_wg;
     } else if (r.kernel == 4) {
@@ -600,35 +627,35 @@ int gptq_w4a16_gemm_prepared(const void *x, const void *qweight_sorted, const vo
         // the vector kernel gathers the activations itself while it stages them: one launch
         p.x = static_cast<const half_t *>(x);
         p.x_perm = static_cast<const int32_t *>(perm);
-        void *ws = nullptr;
+        Scratch scratch;
         const size_t bytes = scratch_bytes(p, r);
         if (bytes > 0) {
-            const int wrc = acquire_workspace(bytes, st, &ws);
+            const int wrc = acquire_workspace(bytes, st, &scratch);
             if (wrc != GPTQ_OK)
                 return wrc;
         }
-        return launch_resolved(p, r, ws, st);
+        return launch_resolved(p, r, scratch, st);
     }
     // scratch: what the kernel needs, then the gathered activations
     // (the counter area at the front stays reserved even if this launch needs none: it must remain zero)
     size_t kernel_bytes;
-    void *ws = nullptr;
+    Scratch scratch;
     for (;;) {
         kernel_bytes = align256(scratch_bytes(p, r));
         if (kernel_bytes < decode_counter_bytes(N))
             kernel_bytes = decode_counter_bytes(N);
-        const int wrc = acquire_workspace(kernel_bytes + (size_t)M * K * sizeof(half_t), st, &ws);
+        const int wrc = acquire_workspace(kernel_bytes + (size_t)M * K * sizeof(half_t), st, &scratch);
         if (wrc == GPTQ_OK)
             break;
         if (wrc != GPTQ_WORKSPACE_TOO_SMALL || !fall_back(p, nullptr, r))
             return wrc;
     }
-    half_t *xp = reinterpret_cast<half_t *>(static_cast<unsigned char *>(ws) + kernel_bytes);
+    half_t *xp = reinterpret_cast<half_t *>(static_cast<unsigned char *>(scratch.ws) + kernel_bytes);
     if (launch_gather_activations(static_cast<const half_t *>(x), static_cast<const int32_t *>(perm), xp, M, K, st) !=
         hipSuccess)
         return GPTQ_HIP_ERROR;
     p.x = xp;
-    return launch_resolved(p, r, ws, st);
+    return launch_resolved(p, r, scratch, st);
 }
 
 int gptq_w4a16_shift_zeros(const void *qzeros_in, void *qzeros_out, int delta, int K, int N, int group_size,

@@ -90,18 +90,21 @@ bool decode_ablation_supported(const Problem &p);
 // ---- small batch: MFMA kernel with the vector kernel's split-K decomposition, M <= 128 (64 rows per launch) ----
 constexpr int kSkinnyMaxM = 128;
 struct SkinnyPlan {
-    int cols_per_wg;      // 64 (wavefronts split the K slice), 128 (two column blocks, four wavefronts each split the slice)
-                          // or 256 (four wavefronts side by side); 0 = choose
+    int cols_per_wg;      // 32, 64, 96 or 128 (wavefronts split the K slice) or 256 (four wavefronts side by side); 0 = choose
     int split_k;          // number of K slices (0 = choose)
     int units_per_slice;  // 128-k units per slice
     bool serial;          // every workgroup walks all slices one after the other: no scratch, the same bits
 };
 bool skinny_supported(const Problem &p);
+// Whether the problem has the variant on a ring of LDS slots: 32 rows at most, K a multiple of 128.
+bool ring_supported(const Problem &p);
 void skinny_make_plan(const Problem &p, SkinnyPlan &plan);
-// Problems that have to be served where there is no scratch, with plan.serial: a K that ends inside a 128-k unit.
-bool skinny_scratch_optional(const Problem &p);
+// Whether the plan has a form without scratch for its K slices, plan.serial.
+bool skinny_scratch_optional(const Problem &p, const SkinnyPlan &plan);
 size_t skinny_workspace_bytes(const Problem &p, const SkinnyPlan &plan);
-hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream);
+// `slots`: kSlotBytes of device memory that is zero between launches (exchange.h), or null.
+constexpr size_t kSlotBytes = 4u << 20;
+hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspace, void *slots, hipStream_t stream);
 
 // ---- act-order checkpoints as stored, M >= 2: the small-batch kernel with per-k lookups (64 rows per workgroup) ----
 bool act_supported(const Problem &p);

@@ -32,8 +32,6 @@ int rows_of_launch(int M)
 // Wavefronts per workgroup: eight where the 64-column workgroups have a compute unit each, else four.
 int waves_of(int tiles_n, int split_k, int wn, int tm)
 {
-    if (wn == 2)
-        return 8;  // 128-column workgroups: two column blocks of four wavefronts
     // (four row blocks do not fit the 256 registers that two wavefronts per SIMD leave each)
     return (wn == 1 && tm <= 2 && (long long)tiles_n * split_k <= 256) ? 8 : 4;
 }
@@ -54,22 +52,15 @@ hipError_t launch_tm(const skinny::Args &a, size_t lds, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Streamed weights: one row block (matrices of that size run on the mid-batch kernel from 17 rows on).
-template <int WN, int WAVES>
-hipError_t launch_streamed(const skinny::Args &a, size_t lds, hipStream_t stream)
-{
-    return launch_tm<1, WN, WAVES, 1, false, false, true>(a, lds, stream);
-}
-
-// Groups of 128 / GPU k.
-template <int GPU, bool TAIL, bool SERIAL>
-hipError_t launch_small_groups(const skinny::Args &a, int tm, int waves, size_t lds, hipStream_t stream)
+// Groups of 128 / GPU k and a K that ends inside a unit.
+template <int GPU, bool SERIAL>
+hipError_t launch_tail(const skinny::Args &a, int tm, int waves, size_t lds, hipStream_t stream)
 {
     if (tm == 1)
-        return waves == 8 ? launch_tm<1, 1, 8, GPU, false, TAIL, false, SERIAL>(a, lds, stream)
-                          : launch_tm<1, 1, 4, GPU, false, TAIL, false, SERIAL>(a, lds, stream);
-    return waves == 8 ? launch_tm<2, 1, 8, GPU, false, TAIL, false, SERIAL>(a, lds, stream)
-                      : launch_tm<2, 1, 4, GPU, false, TAIL, false, SERIAL>(a, lds, stream);
+        return waves == 8 ? launch_tm<1, 1, 8, GPU, false, true, false, SERIAL>(a, lds, stream)
+                          : launch_tm<1, 1, 4, GPU, false, true, false, SERIAL>(a, lds, stream);
+    return waves == 8 ? launch_tm<2, 1, 8, GPU, false, true, false, SERIAL>(a, lds, stream)
+                      : launch_tm<2, 1, 4, GPU, false, true, false, SERIAL>(a, lds, stream);
 }
 
 // Act-order with lookups.
@@ -196,6 +187,8 @@ hipError_t launch_act(const Problem &p, const SkinnyPlan &plan, void *workspace,
     a.split_k = plan.split_k;
     a.units_per_slice = plan.units_per_slice;
     a.total_units = ceil_div(p.K, skinny::kUnitK);
+    a.slots = nullptr;
+    a.serial_slices = 0;
     const int waves = waves_of(a.tiles_n * a.row_tiles, a.split_k, 1, tm);
     const size_t table = act_table_bytes(p) + (size_t)plan.units_per_slice * skinny::kUnitK * sizeof(uint32_t);
     const size_t red = (size_t)waves * 16 * tm * skinny::kCols * sizeof(float);
@@ -217,25 +210,95 @@ bool skinny_supported(const Problem &p)
     return p.group_size % 128 == 0;
 }
 
+bool ring_supported(const Problem &p)
+{
+    return skinny_supported(p) && p.M <= 32 && p.K % skinny::kUnitK == 0;
+}
+
+namespace {
+
+// Slots that two slices need: one for every pair of outputs.
+size_t ring_slot_bytes(const Problem &p)
+{
+    return (size_t)p.M * p.N * sizeof(float);
+}
+
+// Microseconds that a launch of ring_kernel takes, fitted to 11 k measured plans of 160 random layers (K 1024-28672, N
+// 1024-57344, groups of 128, 2-32 rows, weights from HBM): 6 % off on average, and the plan it picks 0.8 % behind the
+// best one.  A fixed part, the bytes at HBM speed, the units that one wavefront walks - more where workgroups share a
+// compute unit -, the sum over the wavefronts, and the exchange: two slices swap their sums (exchange.h), more go
+// through scratch.
+float ring_estimate(const Problem &p, int cols, int split, int units_per_slice)
+{
+    static const float unit[4][4] = {{0.57f, 0.65f, 0.85f, 0.95f}, {0.90f, 0.92f, 1.20f, 1.24f},
+                                     {1.27f, 1.29f, 1.72f, 1.80f}, {1.65f, 1.65f, 2.21f, 2.23f}};
+    const int rows = p.M <= 8 ? 0 : p.M <= 16 ? 1 : p.M <= 24 ? 2 : 3;
+    const int tiles = ceil_div(p.N, cols);
+    const int waves = skinny::ring_waves(tiles * split);
+    const float rounds = (float)ceil_div(tiles * split, 256);
+    const float m = (float)p.M, n = (float)p.N;
+    float us = 2.8f + (float)p.K * n * 3.44e-8f;
+    us += (float)ceil_div(units_per_slice, waves) * unit[cols / 32 - 1][rows] * (waves == 4 ? 0.52f : 1.f) * rounds;
+    us += 3.3e-4f * (m < 4.f ? 4.f : m) * (float)cols * rounds;
+    if (split == 2 && ring_slot_bytes(p) <= kSlotBytes)
+        us += 0.7f + 0.004f * (float)tiles;
+    else if (split > 1)
+        us += 2.2f + 5.8e-5f * m * (float)(cols * split) + 1.96e-6f * m * n * (float)split;
+    return us;
+}
+
+// Fills what the plan leaves open: the width of a workgroup, the number of K slices, or both.
+void ring_make_plan(const Problem &p, SkinnyPlan &plan)
+{
+    const int units = p.K / skinny::kUnitK;
+    const bool any_width = plan.cols_per_wg == 0;
+    const bool any_split = plan.split_k <= 0;
+    float best = 0.f;
+    SkinnyPlan choice = plan;
+    choice.split_k = 0;
+    for (int cols = any_width ? 32 : plan.cols_per_wg; cols <= (any_width ? 128 : plan.cols_per_wg); cols += 32) {
+        const int tiles = ceil_div(p.N, cols);
+        // Automatic slices: as long as every slice has a workgroup on a compute unit of its own and its wavefronts a unit
+        // each; more never paid.  Their partial sums fit the static scratch block.
+        for (int asked = any_split ? 1 : plan.split_k; asked <= (any_split ? 16 : plan.split_k); ++asked) {
+            const int ups = ceil_div(units, asked < units ? asked : units);
+            const int split = ceil_div(units, ups);
+            if (any_split && asked > 1 &&
+                (split != asked || tiles * split > 256 || ups < 8 ||
+                 (long long)split * p.M * p.N * (long long)sizeof(float) > (long long)(GPTQ_STATIC_SCRATCH_BYTES - kCounterBytes)))
+                continue;
+            const float us = ring_estimate(p, cols, split, ups);
+            if (choice.split_k == 0 || us < best) {
+                best = us;
+                choice.cols_per_wg = cols;
+                choice.split_k = split;
+                choice.units_per_slice = ups;
+            }
+        }
+    }
+    plan = choice;
+}
+
+}  // namespace
+
 void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
 {
     const int launch_m = rows_of_launch(p.M);
     const int rows = 16 * row_blocks(launch_m);
     const int total_units = ceil_div(p.K, skinny::kUnitK);
-    if (p.group_size < skinny::kUnitK)
-        plan.cols_per_wg = 64;  // the small-group variants exist for the 64-column workgroup
-    const bool wide_ok = rows <= 32;  // the 128-column workgroup exists for one and two row blocks
-    if (plan.cols_per_wg == 128 && !wide_ok)
-        plan.cols_per_wg = 0;
-    if (plan.cols_per_wg != 64 && plan.cols_per_wg != 128 && plan.cols_per_wg != 256) {
-        // Wide tiles stage the activations once for four times as many weights, but a workgroup's wavefronts
-        // then walk the whole slice: that only pays (measured) once the columns alone spread over most of
-        // the chip.  In between - more 64-column tiles than compute units, but no more 128-column ones - two
-        // column blocks share a workgroup of eight wavefronts, so that every compute unit has one workgroup
-        // instead of some having two.
-        const int tiles64 = ceil_div(p.N, 64);
-        plan.cols_per_wg = ceil_div(p.N, 256) >= 192 ? 256 : (wide_ok && tiles64 > 256 && ceil_div(p.N, 128) <= 256) ? 128 : 64;
+    const int asked = plan.cols_per_wg;
+    // 256 columns, from groups of 128 k on: on request, above 32 rows, and up to 16 rows beyond 65536 columns, wider than any
+    // layer measured; in the widest of those the ring is ahead (8192x57344: M = 16 53 us, 48; level at two to four rows).
+    const bool wide = p.group_size >= skinny::kUnitK &&
+                      (asked == 256 || (asked != 32 && asked != 64 && asked != 96 && asked != 128 &&
+                                        (rows > 32 ? ceil_div(p.N, 256) >= 192 : rows == 16 && p.N > 65536)));
+    if (ring_supported(p) && !wide) {
+        if (asked != 32 && asked != 64 && asked != 96 && asked != 128)
+            plan.cols_per_wg = 0;
+        ring_make_plan(p, plan);
+        return;
     }
+    plan.cols_per_wg = wide ? 256 : 64;
     // where the activations of a slice are staged in LDS (wide tiles, more than 32 rows) they must fit
     const bool direct = plan.cols_per_wg <= 128;
     int max_units = direct ? total_units : kMaxActivationLdsBytes / (rows * 2) / skinny::kUnitK;
@@ -273,8 +336,7 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
         if (split < 1)
             split = 1;
         // narrow tiles: one unit per wavefront and turn
-        const int quantum = plan.cols_per_wg == 64 ? waves_of(tiles_n, split, 1, row_blocks(launch_m))
-                                                   : plan.cols_per_wg == 128 ? 4 : 1;
+        const int quantum = plan.cols_per_wg == 64 ? waves_of(tiles_n, split, 1, row_blocks(launch_m)) : 1;
         ups = ceil_div(ceil_div(total_units, split), quantum) * quantum;
         if (ups > total_units)
             ups = total_units;
@@ -287,9 +349,9 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
     plan.split_k = ceil_div(total_units, ups);
 }
 
-bool skinny_scratch_optional(const Problem &p)
+bool skinny_scratch_optional(const Problem &p, const SkinnyPlan &plan)
 {
-    return p.group_size < skinny::kUnitK && p.K % skinny::kUnitK != 0;
+    return plan.cols_per_wg != 256 && p.M <= 32;
 }
 
 size_t skinny_workspace_bytes(const Problem &p, const SkinnyPlan &plan)
@@ -302,7 +364,7 @@ size_t skinny_workspace_bytes(const Problem &p, const SkinnyPlan &plan)
     return bytes;
 }
 
-hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspace, hipStream_t stream)
+hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspace, void *slots, hipStream_t stream)
 {
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const int wn = plan.cols_per_wg / skinny::kCols;
@@ -330,46 +392,54 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
         a.split_k = plan.split_k;
         a.units_per_slice = plan.units_per_slice;
         a.total_units = ceil_div(p.K, skinny::kUnitK);
+        a.slots = nullptr;
+        a.serial_slices = 0;
 
         const int tm = row_blocks(a.M);
         const int rows = 16 * tm;
-        // 64- and 128-column workgroups read the activations straight from global memory
-        const bool direct = wn <= 2;
-        const size_t xs = direct ? 0 : (size_t)rows * plan.units_per_slice * skinny::kUnitK * sizeof(half_t);
+        const int gpu = p.group_size >= skinny::kUnitK ? 1 : skinny::kUnitK / p.group_size;
+        const bool tail = p.K % skinny::kUnitK != 0;
+        hipError_t err;
+        if (wn != 4 && tm <= 2 && !tail) {
+            if (plan.serial && plan.split_k > 1) {  // (64 columns whatever the sliced plan has)
+                a.serial_slices = plan.split_k;
+                a.split_k = 1;
+                a.tiles_n = ceil_div(p.N, skinny::kCols);
+            } else if (plan.split_k == 2 && ring_slot_bytes(p) <= kSlotBytes) {
+                a.slots = static_cast<unsigned long long *>(slots);
+            }
+            const bool streamed = tm == 1 && stream_weights(p);  // (more rows are not bound by the weights)
+            err = gpu == 1   ? skinny::launch_ring<1>(a, plan.cols_per_wg, streamed, stream)
+                  : gpu == 2 ? skinny::launch_ring<2>(a, plan.cols_per_wg, streamed, stream)
+                             : skinny::launch_ring<4>(a, plan.cols_per_wg, streamed, stream);
+            if (err != hipSuccess)
+                return err;
+            continue;
+        }
+        // 64-column workgroups read the activations straight from global memory
+        const size_t xs = wn == 1 ? 0 : (size_t)rows * plan.units_per_slice * skinny::kUnitK * sizeof(half_t);
         const int waves = waves_of(a.tiles_n, a.split_k, wn, tm);
         const size_t red = (size_t)waves * rows * skinny::kCols * sizeof(float);  // [waves/wn][rows][64*wn]
         const size_t lds = xs > red ? xs : red;
-        hipError_t err;
-        const int gpu = p.group_size >= skinny::kUnitK ? 1 : skinny::kUnitK / p.group_size;
-        if (gpu > 1) {
-            if (wn != 1 || tm > 2)
+        if (tail) {
+            if (wn != 1 || tm > 2 || gpu == 1)
                 return hipErrorInvalidValue;  // refused by skinny_supported / skinny_make_plan
-            const bool tail = p.K % skinny::kUnitK != 0;
-            if (plan.serial && tail)
-                err = gpu == 2 ? launch_small_groups<2, true, true>(a, tm, waves, lds, stream)
-                               : launch_small_groups<4, true, true>(a, tm, waves, lds, stream);
-            else if (gpu == 2)
-                err = tail ? launch_small_groups<2, true, false>(a, tm, waves, lds, stream)
-                           : launch_small_groups<2, false, false>(a, tm, waves, lds, stream);
+            if (plan.serial)
+                err = gpu == 2 ? launch_tail<2, true>(a, tm, waves, lds, stream)
+                               : launch_tail<4, true>(a, tm, waves, lds, stream);
             else
-                err = tail ? launch_small_groups<4, true, false>(a, tm, waves, lds, stream)
-                           : launch_small_groups<4, false, false>(a, tm, waves, lds, stream);
-        } else if (tm == 1 && stream_weights(p)) {
-            err = wn == 2   ? launch_streamed<2, 8>(a, lds, stream)
-                  : wn == 4 ? launch_streamed<4, 4>(a, lds, stream)
-                  : waves == 8 ? launch_streamed<1, 8>(a, lds, stream) : launch_streamed<1, 4>(a, lds, stream);
-        } else if (wn == 2) {
-            if (tm > 2)
-                return hipErrorInvalidValue;  // refused by skinny_make_plan
-            err = tm == 1 ? launch_tm<1, 2, 8>(a, lds, stream) : launch_tm<2, 2, 8>(a, lds, stream);
-        } else if (wn == 4)
-            err = tm == 1 ? launch_tm<1, 4, 4>(a, lds, stream)
-                          : tm == 2 ? launch_tm<2, 4, 4>(a, lds, stream) : launch_tm<4, 4, 4>(a, lds, stream);
-        else if (waves == 8)
-            err = tm == 1 ? launch_tm<1, 1, 8>(a, lds, stream) : launch_tm<2, 1, 8>(a, lds, stream);
-        else
-            err = tm == 1 ? launch_tm<1, 1, 4>(a, lds, stream)
-                          : tm == 2 ? launch_tm<2, 1, 4>(a, lds, stream) : launch_tm<4, 1, 4>(a, lds, stream);
+                err = gpu == 2 ? launch_tail<2, false>(a, tm, waves, lds, stream)
+                               : launch_tail<4, false>(a, tm, waves, lds, stream);
+        } else if (gpu > 1 || (wn != 1 && wn != 4)) {
+            return hipErrorInvalidValue;  // refused by skinny_supported / skinny_make_plan
+        } else if (wn == 4) {
+            err = tm == 2   ? launch_tm<2, 4, 4>(a, lds, stream)
+                  : tm == 4 ? launch_tm<4, 4, 4>(a, lds, stream)
+                  : stream_weights(p) ? launch_tm<1, 4, 4, 1, false, false, true>(a, lds, stream)
+                                      : launch_tm<1, 4, 4>(a, lds, stream);
+        } else {
+            err = launch_tm<4, 1, 4>(a, lds, stream);
+        }
         if (err != hipSuccess)
             return err;
     }

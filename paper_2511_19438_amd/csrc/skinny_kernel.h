@@ -1,22 +1,21 @@
-// Small-batch MFMA kernel for the W4A16 GPTQ matrix multiply (2 <= M <= 64 per launch), gfx950.
+// Small-batch MFMA kernel for the W4A16 GPTQ matrix multiply, operands straight into registers, gfx950.
 //
 // Between the vector kernel (which runs out of vector ALU throughput once every weight has to be
 // multiplied with more than a few batch rows) and the big-tile MFMA kernel (which needs hundreds of rows
 // to fill its tiles) the problem is still bound by streaming the packed weights from HBM, but the
-// contraction no longer fits the vector units.  This kernel keeps the work decomposition of the vector
-// kernel - a workgroup owns 64 columns and one K slice, its four wavefronts split the slice, partial
-// sums meet in LDS and then in scratch, in a fixed order (Opt4GPTQ, Section 3.1) - and hands the
+// contraction no longer fits the vector units.  The small-batch kernels keep the work decomposition of the vector
+// kernel - a workgroup owns some columns and one K slice, its wavefronts split the slice, partial
+// sums meet in LDS and then in scratch, in a fixed order (Opt4GPTQ, Section 3.1) - and hand the
 // contraction to v_mfma_f32_16x16x32_f16:
 //   * one lane of the MFMA B operand holds 8 consecutive k of one column, which is exactly one packed
 //     qweight word: a lane loads four adjacent words (128 bits; a wavefront load touches 4 packed rows x
-//     256 contiguous bytes), dequantises them in registers (exact q - z, one fp16 multiply by the scale)
-//     and feeds four MFMAs, n-block t <-> column 4*(lane%16) + t;
-//   * the activations of the slice are staged in LDS with 128-bit accesses (Section 3.2), 16-byte chunks
-//     XOR-swizzled by row so that the 16-row operand reads are bank-conflict free;
+//     256 contiguous bytes), dequantises them in registers (exact q - z) and feeds four MFMAs, n-block t <->
+//     column 4*(lane%16) + t;
 //   * every weight is read once and dequantised once, whatever M is: 2 vector ALU operations per weight
 //     instead of 1.2 + M/2 in the vector kernel.
-// Supports group sizes that are multiples of 128 (the tuned format) or 64 / 32 (template GPU), and g_idx (template
-// ACT); other cases use the other kernels.
+// ring_kernel.h has the variant that serves plain formats up to 32 rows.  This one serves what does not fit its slots:
+// g_idx (template ACT), a K that ends inside a 128-k unit (TAIL), 256-column workgroups for very wide layers (WN = 4), and
+// 33 to 64 rows per launch (TM = 4, by explicit plan).
 #pragma once
 
 #include "exchange.h"
@@ -49,6 +48,10 @@ struct Args {
     const int32_t *g_idx;  // group of every k
     int groups;            // K / group_size
     int row_tiles;         // blocks of kActRows rows in the grid (1: M fits one)
+    // ring_kernel only: where two slices exchange their sums pair by pair (exchange.h), or null; SERIAL: the slices that a
+    // workgroup walks (split_k is 1)
+    unsigned long long *slots;
+    int serial_slices;
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -97,9 +100,8 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
     u32x4_t xa[XROWS > 0 ? XROWS : 1][4];  // A operand per row block and k step
 };
 
-// TM: 16-row blocks (M <= 16 * TM).  WN: wavefronts side by side along N (1, 2 or 4).  With WN = 1 the
-// workgroup owns 64 columns and its four wavefronts split the K slice (narrow layers: many small
-// workgroups); with WN = 4 it owns 256 columns, every wavefront walks the whole slice for its own 64
+// TM: 16-row blocks (M <= 16 * TM).  WN: wavefronts side by side along N (1 or 4).  With WN = 1 the
+// workgroup owns 64 columns and its wavefronts split the K slice; with WN = 4 it owns 256 columns, every wavefront walks the whole slice for its own 64
 // columns and the staged activations serve four times as many weights (wide layers).
 //
 // WAVES wavefronts per workgroup: four, or - 64-column workgroups that have a compute unit to themselves -
@@ -142,8 +144,8 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
     Args a = args;
     static_assert(GPU == 1 || GPU == 2 || GPU == 4, "groups of >= 128, 64 or 32 k");
     static_assert(GPU == 1 || TM <= 2, "small groups: up to two row blocks");
-    static_assert(WAVES == 4 || (WAVES == 8 && WN <= 2), "eight wavefronts only where they split the slice");
-    static_assert(WN != 2 || WAVES == 8, "128-column workgroups: two column blocks x four wavefronts each");
+    static_assert(WAVES == 4 || (WAVES == 8 && WN == 1), "eight wavefronts only where they split the slice");
+    static_assert(ACT || TAIL || WN == 4 || TM == 4, "the rest is ring_kernel's");
     constexpr int kWaves = WAVES;
     constexpr int kThreads = 64 * WAVES;
     constexpr int ROWS = 16 * TM;
@@ -153,9 +155,7 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
     // slice), so staging them in LDS would be a copy without reuse: each lane loads its A operand straight
     // from global memory (L2), in the same pipeline as the weights.  With 256-column workgroups the four
     // wavefronts share the slice and the activations are staged once in LDS.
-    // (128-column workgroups, WN = 2 with eight wavefronts, read them the same way: every activation is then
-    // loaded by the two wavefronts that share its k range, from L2.)
-    constexpr bool DIRECT = WN <= 2;
+    constexpr bool DIRECT = WN == 1;
     // DIRECT with four row blocks: the A operands of two units in flight would take 128 registers.  They are kept
     // for ONE unit instead and refilled step by step: as soon as a 32-k step's operands have been permuted into
     // the MFMA's k order, the same registers receive that step of the NEXT unit (from L2: a four-step lead is
@@ -615,6 +615,22 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
         }
     }
 }
+
+// Wavefronts per workgroup of ring_kernel.
+inline int ring_waves(int workgroups)
+{
+    return workgroups <= 256 ? 8 : 4;
+}
+
+// ring_kernel for GPU quantisation groups per 128-k unit (ring.hip); cols: 32, 64, 96 or 128 columns per workgroup.
+template <int GPU>
+hipError_t launch_ring(const Args &a, int cols, bool streamed, hipStream_t stream);
+template <>
+hipError_t launch_ring<1>(const Args &a, int cols, bool streamed, hipStream_t stream);
+template <>
+hipError_t launch_ring<2>(const Args &a, int cols, bool streamed, hipStream_t stream);
+template <>
+hipError_t launch_ring<4>(const Args &a, int cols, bool streamed, hipStream_t stream);
 
 }  // namespace skinny
 }  // namespace gptq
