@@ -9,6 +9,7 @@ fails loudly.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -16,8 +17,11 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libgptq_w4a16.so")
+NATIVE_CALL_PATH = os.path.join(_HERE, "lib", "_native_call.so")
 
 _lib = None
+_native_gemm = None  # csrc/native_call.cpp: tensors to the C ABI in one call
+_addresses = {}      # of the entry points that it calls
 
 
 class GptqError(RuntimeError):
@@ -41,13 +45,14 @@ EXPORTS = ("gptq_w4a16_gemm", "gptq_w4a16_gemm_static", "gptq_w4a16_gemm_plan", 
 
 def load() -> ctypes.CDLL:
     """Load the built library.  Raises if it is missing: build it with ``python -m paper_2511_19438_amd.build``."""
-    global _lib
+    global _lib, _native_gemm
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise FileNotFoundError(
-            f"{LIB_PATH} is missing: the HIP library must be built first "
-            "(python -m paper_2511_19438_amd.build); there is no CPU fallback")
+    for path in (LIB_PATH, NATIVE_CALL_PATH):
+        if not os.path.exists(path):
+            raise FileNotFoundError(
+                f"{path} is missing: the HIP library must be built first "
+                "(python -m paper_2511_19438_amd.build); there is no CPU fallback")
     lib = ctypes.CDLL(LIB_PATH)
     vp, ci = ctypes.c_void_p, ctypes.c_int
     lib.gptq_w4a16_gemm.argtypes = [vp, vp, vp, vp, vp, vp, ci, ci, ci, ci, vp]
@@ -82,6 +87,12 @@ def load() -> ctypes.CDLL:
     lib.gptq_w4a16_issue_probe.restype = ci
     lib.gptq_w4a16_version.argtypes = []
     lib.gptq_w4a16_version.restype = ci
+    spec = importlib.util.spec_from_file_location("_native_call", NATIVE_CALL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    for name in ("gptq_w4a16_gemm", "gptq_w4a16_gemm_static", "gptq_w4a16_gemm_prepared"):
+        _addresses[name] = ctypes.cast(getattr(lib, name), vp).value
+    _native_gemm = module.gemm
     _lib = lib
     return lib
 
@@ -106,9 +117,7 @@ def _ptr(t: Optional[torch.Tensor], dtype, name: str):
     return t.data_ptr()  # (an integer: the argument types of load() make it a pointer)
 
 
-# A single-row GEMM takes about 5 us on the GPU and 3.4 us of library and launch on the host, so the marshalling around
-# it decides whether a stream of small calls is bound by Python.  torch.cuda.current_stream() builds a Stream object
-# (2.8 us); the raw handle of the same stream takes 0.15 us.  Call of 1x1024x256 as a whole: 9.3 -> 6.3 us.
+# torch.cuda.current_stream() builds a Stream object (2.8 us); the raw handle of the same stream takes 0.15 us.
 _raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else None
 
 
@@ -142,6 +151,15 @@ def gptq_w4a16_gemm_static(x, qweight, qzeros, scales, g_idx, out, group_size: i
 def gptq_w4a16_gemm(x, qweight, qzeros, scales, g_idx, out, group_size: int, plan: Optional[Plan] = None,
                     _static: bool = False):
     """out[M, N] = x[M, K] @ W (see the header).  Shapes are taken from the tensors; `out` is overwritten."""
+    lib = _lib or load()
+    if plan is None:
+        name = "gptq_w4a16_gemm_static" if _static else "gptq_w4a16_gemm"
+        rc = _native_gemm(_addresses[name], x, qweight, qzeros, scales, g_idx, out, group_size)
+        if rc == 0:
+            return out
+        if rc is not None:
+            raise GptqError(rc, name)
+        # not a plain call: what follows says what is wrong with it, or serves it
     K, N = _shapes(qweight, qzeros, scales, g_idx, group_size)
     shape = x.shape
     if len(shape) != 2 or shape[1] != K:
@@ -149,7 +167,6 @@ def gptq_w4a16_gemm(x, qweight, qzeros, scales, g_idx, out, group_size: int, pla
     M = shape[0]
     if out.shape != (M, N):
         raise ValueError(f"out must be [{M}, {N}], got {tuple(out.shape)}")
-    lib = _lib or load()
     args = (_ptr(x, torch.float16, "x"), _ptr(qweight, torch.int32, "qweight"), _ptr(qzeros, torch.int32, "qzeros"),
             _ptr(scales, torch.float16, "scales"), _ptr(g_idx, torch.int32, "g_idx"), _ptr(out, torch.float16, "out"),
             M, K, N, int(group_size), _stream())
@@ -181,13 +198,20 @@ def gptq_w4a16_act_order_prepare(qweight, g_idx, qweight_sorted, perm, group_siz
 
 def gptq_w4a16_gemm_prepared(x, qweight_sorted, qzeros, scales, perm, out, group_size: int):
     """The act-order GEMM on a repacked checkpoint: out = x[:, perm] @ W_sorted."""
+    lib = _lib or load()
+    if perm is not None:
+        rc = _native_gemm(_addresses["gptq_w4a16_gemm_prepared"], x, qweight_sorted, qzeros, scales, perm, out, group_size)
+        if rc == 0:
+            return out
+        if rc is not None:
+            raise GptqError(rc, "gptq_w4a16_gemm_prepared")
     K, N = _shapes(qweight_sorted, qzeros, scales, perm, group_size)
     if x.dim() != 2 or x.shape[1] != K:
         raise ValueError(f"x must be [M, {K}], got {tuple(x.shape)}")
     M = x.shape[0]
     if tuple(out.shape) != (M, N):
         raise ValueError(f"out must be [{M}, {N}], got {tuple(out.shape)}")
-    rc = load().gptq_w4a16_gemm_prepared(
+    rc = lib.gptq_w4a16_gemm_prepared(
         _ptr(x, torch.float16, "x"), _ptr(qweight_sorted, torch.int32, "qweight_sorted"),
         _ptr(qzeros, torch.int32, "qzeros"), _ptr(scales, torch.float16, "scales"), _ptr(perm, torch.int32, "perm"),
         _ptr(out, torch.float16, "out"), M, K, N, int(group_size), _stream())

@@ -19,6 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libgptq_w4a16.so")
+NATIVE_CALL_PATH = os.path.join(LIB_DIR, "_native_call.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -58,6 +59,28 @@ def _compile(unit, extra_flags):
     return unit, proc
 
 
+def build_native_call() -> str:
+    """Compile the binding's CPython extension module (host code, against the installed torch).  Returns its path."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    rocm = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include")]
+    for path in cpp_extension.include_paths():
+        cmd += ["-isystem", path]
+    cmd += [os.path.join(CSRC, "native_call.cpp"), "-o", NATIVE_CALL_PATH,
+            "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    proc = subprocess.run(cmd, capture_output=True, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("native_call.cpp: " + (proc.stdout + proc.stderr)[-4000:])
+    return NATIVE_CALL_PATH
+
+
 def build(verbose: bool = False, jobs: int = 8, extra_flags=()) -> str:
     """Compile every translation unit and link the shared library.  Returns its path."""
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -79,6 +102,7 @@ def build(verbose: bool = False, jobs: int = 8, extra_flags=()) -> str:
     objs = [os.path.join(OBJ_DIR, u[1]) for u in todo]
     link = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-fno-gpu-rdc", "-fvisibility=hidden", "-o", LIB_PATH, *objs]
     subprocess.run(link, check=True)
+    build_native_call()
     return LIB_PATH
 
 
