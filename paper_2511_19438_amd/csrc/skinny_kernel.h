@@ -86,7 +86,7 @@ __device__ __forceinline__ float load_device_scope(const float *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Bytes of the act-order table: one (scale, -(1024 + z)) pair of halves per group and column of the tile.
+// Bytes of the act-order table: a scale and a -(1024 + z) as halves per group and column of the tile.
 constexpr int kActTableRow = kCols * 4;
 // Rows of x that one workgroup of the act-order variant multiplies; larger batches are row tiles of one grid.
 constexpr int kActRows = 64;
@@ -114,16 +114,17 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
 // formed with its own group's zero point and the MFMA chain is scaled and restarted at every group boundary.
 //
 // ACT: act-order checkpoints as stored (row k of the weights belongs to group g_idx[k], any map).  The workgroup
-// first lays the scales and zero points of ALL groups for its 64 columns into LDS - (scale, -(1024 + z)) as two
-// halves, 4 bytes per column - and the table offset of every k of its slice behind it.  A lane then reads, for
-// each of the eight k of a packed row, one 16-byte table entry (its four columns; the 16 lanes of one packed row
-// read 256 contiguous bytes: no bank conflicts), so a word costs 4 + 4 permutes to pair the entries on top of the
-// masks, adds and multiplies: 24 vector operations and two 128-bit LDS reads per word WHATEVER M IS, where the
-// vector kernel paid for its lookups and for two operations per weight and row on top, and the big-tile kernel's
-// general path fetched every scale and zero point from global memory.  4096x11008, groups of 128: M = 8 40.5 us
-// (vector kernel) -> 12.0, M = 24 258 (general path) -> 15.1, M = 128 272 -> 48, M = 512 422 -> 138.  Bound by vector
-// issue (~30 instructions per word against 16 in the plain format) and, from 33 rows on, by the latency of the
-// activation loads.  More than 64 rows are row tiles of one grid.
+// first lays the scales and zero points of ALL groups for its 64 columns into LDS - per column two halves, the scale and
+// -(1024 + z) - and the table offset of every k of its slice behind it.  A lane then reads, for each of the eight k of a
+// packed row, one 16-byte table entry (its four columns; the 16 lanes of one packed row read 256 contiguous bytes:
+// no bank conflicts).  An entry holds pairs of ADJACENT COLUMNS, scales (0,1) (2,3) then zero points, and the weights are
+// paired alike - one byte permute takes k and k + 1 of two columns - so the arithmetic needs no permutes of the entries;
+// the products go back to pairs of one column's k with one permute each.  20 vector operations per word WHATEVER M IS, and
+// the activations in their natural order (entries of one column: 24, and four permutes per activation operand; 4096x11008
+// at M = 8 13.2 us -> 12.0, 28672x2048 with groups of 64 at M = 64 42.9 -> 33.0), where the vector kernel paid for its
+// lookups and for two operations per weight and row on top (40.5 us), and the big-tile kernel's general path fetched
+// every scale and zero point from global memory (M = 512 422 us, here 135).  Bound by vector issue, two 128-bit LDS reads
+// per word and, from 33 rows on, the latency of the activation loads.  More than 64 rows are row tiles of one grid.
 //
 // TAIL: K is a multiple of 32 but not of 128 (small groups, act-order).  The steps past K of the last unit load the last
 // step again and multiply zeros with it: one select per activation register and a clamp per load (5-7 % on a K without
@@ -304,10 +305,8 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
             const int n = min(tile * kCols + 4 * (i % (kCols / 4)), N - 4);
             const uint2 sc = *reinterpret_cast<const uint2 *>(a.scales + (size_t)g * N + n);
             const uint32_t z4 = a.qzeros[(size_t)g * (N >> 3) + (n >> 3)] >> ((n & 4) * 4);
-            const u32x4_t e = {(sc.x & 0xffffu) | 0xE4000000u | (z4 & 15u) << 16,
-                               (sc.x >> 16) | 0xE4000000u | (z4 >> 4 & 15u) << 16,
-                               (sc.y & 0xffffu) | 0xE4000000u | (z4 >> 8 & 15u) << 16,
-                               (sc.y >> 16) | 0xE4000000u | (z4 >> 12 & 15u) << 16};
+            const u32x4_t e = {sc.x, sc.y, 0xE400E400u | (z4 & 15u) | (z4 >> 4 & 15u) << 16,
+                               0xE400E400u | (z4 >> 8 & 15u) | (z4 >> 12 & 15u) << 16};
             *reinterpret_cast<u32x4_t *>(act_table + (size_t)i * 16) = e;
         }
 #pragma unroll 2
@@ -387,6 +386,10 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
                     for (int e = 0; e < 4; ++e)
                         xv[e] = st < live_steps ? xv[e] : 0u;
                 }
+                if (ACT) {
+                    av[i] = __builtin_bit_cast(half8_t, xv);
+                    continue;
+                }
                 // the same k order for the activations: halves (0,4) (1,5) (2,6) (3,7)
                 const u32x4_t xp = {__builtin_amdgcn_perm(xv[2], xv[0], 0x05040100u),
                                     __builtin_amdgcn_perm(xv[2], xv[0], 0x07060302u),
@@ -408,19 +411,29 @@ __global__ __launch_bounds__(64 * WAVES) void skinny_kernel(const Args args)
                     e[k + 4] = *reinterpret_cast<const u32x4_t *>(act_table + o1[k] + cq * 16);
                 }
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    half8_t b;
+                for (int p = 0; p < 2; ++p) {  // columns 2p and 2p + 1: every k's scales and zero points are a pair already
+                    half2_t v[8];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {  // the pair (k, k + 4), each with its own scale and zero point
-                        const half2_t s = as_half2(__builtin_amdgcn_perm(e[k + 4][t], e[k][t], 0x05040100u));
-                        const half2_t nz = as_half2(__builtin_amdgcn_perm(e[k + 4][t], e[k][t], 0x07060302u));
-                        const half2_t v = (as_half2((w[t] >> (4 * k) & magic.mask_lo) | magic.bias_lo) + nz) * s;
-                        b[2 * k] = v[0];
-                        b[2 * k + 1] = v[1];
+                    for (int k = 0; k < 8; k += 2) {  // byte k / 2 of both words: k and k + 1
+                        const uint32_t both =
+                            __builtin_amdgcn_perm(w[2 * p + 1], w[2 * p], 0x0c040c00u + (uint32_t)(k / 2) * 0x00010001u);
+                        v[k] = (as_half2((both & magic.mask_lo) | magic.bias_lo) + as_half2(e[k][2 + p])) * as_half2(e[k][p]);
+                        v[k + 1] = (as_half2((both >> 4 & magic.mask_lo) | magic.bias_lo) + as_half2(e[k + 1][2 + p])) *
+                                   as_half2(e[k + 1][p]);
                     }
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-                        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av[i], b, acc[i][t], 0, 0, 0);
+                    for (int t = 0; t < 2; ++t) {  // a column's eight k, in order
+                        const uint32_t sel = t == 0 ? 0x05040100u : 0x07060302u;
+                        u32x4_t b;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            b[j] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, v[2 * j + 1]),
+                                                         __builtin_bit_cast(uint32_t, v[2 * j]), sel);
+#pragma unroll
+                        for (int i = 0; i < TM; ++i)
+                            acc[i][2 * p + t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                                av[i], __builtin_bit_cast(half8_t, b), acc[i][2 * p + t], 0, 0, 0);
+                    }
                 }
                 continue;
             }
