@@ -13,9 +13,10 @@ int ceil_div(int a, int b)
     return (a + b - 1) / b;
 }
 
+// 32-row blocks of a workgroup's tile.
 int row_blocks(int M)
 {
-    return M <= 32 ? 1 : M <= 64 ? 2 : 4;
+    return M <= 32 ? 1 : M <= 64 ? 2 : M <= 96 ? 3 : 4;
 }
 
 // Wavefronts per workgroup: eight (two per SIMD) where their activation rings fit the LDS, else four.
@@ -24,11 +25,11 @@ int waves_of(int tmb)
     return tmb <= 2 ? 8 : 4;
 }
 
-template <int TMB, int NB, int WAVES>
+template <int TMB, int NB, int WAVES, int DEPTH = 2>
 hipError_t launch_one(const mid::Args &a, hipStream_t stream)
 {
-    auto kernel = mid::mid_kernel<TMB, NB, WAVES>;
-    const size_t lds = (size_t)WAVES * 2 * (32 * TMB) * 128;
+    auto kernel = mid::mid_kernel<TMB, NB, WAVES, DEPTH>;
+    const size_t lds = (size_t)WAVES * DEPTH * (32 * TMB) * 128;
     if (lds > 48 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -56,8 +57,9 @@ void mid_make_plan(const Problem &p, MidPlan &plan)
     const int tmb = row_blocks(p.M);
     const int waves = waves_of(tmb);
     const int total = p.K / mid::kStageK;
-    // four row blocks leave registers for two n-blocks only
-    if (tmb == 4)
+    // four row blocks leave registers for two n-blocks only; three have room for four, which gained on layers of 160-256
+    // such tiles only (4096x22016 at M = 77 29.4 us; 34.6 with two, 33.7 on the big-tile kernel) and lost 40 % elsewhere
+    if (tmb >= 3)
         plan.cols_per_wg = 64;
     if (plan.cols_per_wg != 64 && plan.cols_per_wg != 128) {
         // 128-column tiles where they alone give most compute units a workgroup, or where K is so deep that the
@@ -126,6 +128,10 @@ hipError_t launch_mid(const Problem &p, const MidPlan &plan, void *workspace, hi
         return launch_one<1, 2, 8>(a, stream);
     if (tmb == 2)
         return launch_one<2, 2, 8>(a, stream);
+    // 65-96 rows: three row blocks leave LDS for a third stage of activations.  With four blocks as above 96 rows:
+    // 8192x10240 at M = 77 39.3 us -> 31.0, 8192x8192 31.3 -> 25.0.
+    if (tmb == 3)
+        return launch_one<3, 2, 4, 3>(a, stream);
     return launch_one<4, 2, 4>(a, stream);
 }
 

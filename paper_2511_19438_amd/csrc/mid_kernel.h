@@ -151,7 +151,10 @@ __device__ __forceinline__ uint32_t scale_pair(const uint32_t &sc, int)
 
 // TMB: 32-row blocks (M <= 32 * TMB).  NB: 32-column n-blocks per wavefront (2 or 4; n-block t <-> column
 // NB * (lane % 32) + t of the tile).  WAVES: wavefronts per workgroup, each with its own share of the K slice.
-template <int TMB, int NB, int WAVES>
+// DEPTH: stages in a wavefront's ring of activations: two, or three in the pinned loop of one wavefront per SIMD, which
+// 65-96 rows run.  There the MFMAs of 24 a stage take 0.49 us with all loads taken out and 0.7-0.8 with them (8192x10240:
+// 20.7 us without loads, 23.4 without activations' DMA, 30.6 in full): the latency of loads one and a half stages old.
+template <int TMB, int NB, int WAVES, int DEPTH>
 __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
 {
     static_assert(NB == 2 || NB == 4, "64- or 128-bit weight loads");
@@ -161,7 +164,9 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
     constexpr int XBUF = ROWS * 128;  // bytes of one stage of activations
     constexpr int NX = ROWS / 8;      // DMA instructions per stage: 8 rows x 128 bytes each
     constexpr int NWL = 6;            // vector memory instructions of one stage of weights (4 + scales + zeros)
-    constexpr int LW = 2 * XBUF;      // LDS bytes of one wavefront: a ring of two stages
+    constexpr int LW = DEPTH * XBUF;  // LDS bytes of one wavefront: its ring
+    static_assert(DEPTH == 2 || DEPTH == 3, "the loop's buffer indices");
+    static_assert(2 * NX + 2 * NWL < 64, "vmcnt counts to 63");
 
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_last;
@@ -278,27 +283,28 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
         }
     };
 
-    // ---- the loop: x(i+1) and w(i+2) are issued, in that order, before stage i is consumed.  The vector memory
-    //      counter retires in order, so waiting until only NX + 2*NWL instructions are outstanding leaves exactly
-    //      w(i+1), x(i+1), w(i+2) in flight: x(i) and w(i) have arrived.  Compiler barriers keep the issue order. ----
     StageRegs<NB> r0, r1, r2;
-    auto body = [&](int st, StageRegs<NB> &cur, StageRegs<NB> &nxt2, int buf) {
-        issue_x(st + 1, buf ^ 1);
+    if constexpr (DEPTH == 2) {
+        // ---- the loop: x(i+1) and w(i+2) are issued, in that order, before stage i is consumed.  The vector memory
+        //      counter retires in order, so waiting until only NX + 2*NWL instructions are outstanding leaves exactly
+        //      w(i+1), x(i+1), w(i+2) in flight: x(i) and w(i) have arrived.  Compiler barriers keep the issue
+        //      order. ----
+        auto body = [&](int st, StageRegs<NB> &cur, StageRegs<NB> &nxt2, int buf) {
+            issue_x(st + 1, buf ^ 1);
+            asm volatile("" ::: "memory");
+            issue_w(st + 2, nxt2);
+            arrived(cur, std::integral_constant<int, NX + 2 * NWL>());
+            consume(cur, buf);
+            // the next body's DMA overwrites the buffer this one has just read: the reads are complete (their values
+            // fed the MFMAs above), this keeps the compiler from moving them
+            asm volatile("" ::: "memory");
+        };
+        issue_w(ws0, r0);
         asm volatile("" ::: "memory");
-        issue_w(st + 2, nxt2);
-        arrived(cur, std::integral_constant<int, NX + 2 * NWL>());
-        consume(cur, buf);
-        // the next body's DMA overwrites the buffer this one has just read: the reads are complete (their values
-        // fed the MFMAs above), this keeps the compiler from moving them
+        issue_x(ws0, 0);
         asm volatile("" ::: "memory");
-    };
-    issue_w(ws0, r0);
-    asm volatile("" ::: "memory");
-    issue_x(ws0, 0);
-    asm volatile("" ::: "memory");
-    issue_w(ws0 + 1, r1);
-    asm volatile("" ::: "memory");
-    {
+        issue_w(ws0 + 1, r1);
+        asm volatile("" ::: "memory");
         int st = ws0;
         int buf = 0;
         for (int b = 3; b <= share; b += 3) {
@@ -313,6 +319,118 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
             body(st, r0, r2, buf);
         if (rest == 2)
             body(st + 1, r1, r0, buf ^ 1);
+    } else {
+        // ---- one wavefront per SIMD: nobody else's MFMAs run while this one issues loads, waits or dequantises.  The
+        //      order is pinned instead: every MFMA is followed by a share of what the ones after it need - a load of
+        //      stage i+2 (first half of a stage), a piece of the next word's dequantisation, the next step's LDS reads.
+        //      Before its last step a stage waits for the next one: only x(i+2) and w(i+2) stay in flight, and the
+        //      last step prepares the first operands of stage i+1.  Buffer and registers of stage i+2 are those of
+        //      stage i-1, whose last read fed MFMAs above. ----
+        half8_t av[2][TMB];
+        uint32_t nz[NB], ss[NB];
+        half8_t b;
+        auto group = [&](const StageRegs<NB> &r, int t) {
+            const uint32_t z = (r.zb >> (zshift + 4 * t)) & 15u;
+            nz[t] = 0xD400E400u | z | (z << 20);
+            const uint32_t pair = scale_pair(r.sc, t);
+            ss[t] = __builtin_amdgcn_perm(0u, pair, (t & 1) ? 0x03020302u : 0x01000100u);
+        };
+        auto read_a = [&](int buf, int s, int i) {
+            av[s & 1][i] = *reinterpret_cast<const half8_t *>(ring + (size_t)buf * XBUF + (aoff ^ (uint32_t)(s << 5)) + i * 4096);
+        };
+        auto body = [&](int st, const StageRegs<NB> &cur, StageRegs<NB> &nxt, StageRegs<NB> &nxt2, int buf) {
+            const int bufn = (buf + 1) % 3, bufn2 = (buf + 2) % 3;
+            const int sc = min(st + 2, s1 - 1);
+            const char *xb = reinterpret_cast<const char *>(a.x + (size_t)sc * kStageK);
+            const uint32_t *wrow = a.qweight + (size_t)sc * 8 * N;
+            const uint32_t grp = __umulhi((uint32_t)sc, a.group_mul) + (uint32_t)sc * a.group_one;
+            const half_t *srow = a.scales + (size_t)grp * N;
+            const uint32_t *zrow = a.qzeros + (size_t)grp * (N >> 3);
+            constexpr int HALF = 2 * NB * TMB;              // MFMAs of the first two steps
+            constexpr int PER = (NX + NWL + HALF - 1) / HALF;  // loads behind each of them
+            auto load = [&](int q) {
+                if (q < NX)
+                    __builtin_amdgcn_global_load_lds((global_ptr_t *)(xb + at_use(voff_x[q < NX ? q : 0])),
+                                                     (lds_ptr_t *)(ring + (size_t)bufn2 * XBUF + q * 1024), 16, 0, 0);
+                else if (q < NX + 4)
+                    load_global(nxt2.w[(q - NX) & 3], voff_w, wrow + (size_t)(2 * (q - NX)) * N);
+                else if (q == NX + 4)
+                    load_global(nxt2.sc, voff_s, srow);
+                else if (q == NX + 5)
+                    load_global(nxt2.zb, voff_z, zrow);
+            };
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (s == 3)
+                    arrived(nxt, std::integral_constant<int, NX + NWL>());
+#pragma unroll
+                for (int t = 0; t < NB; ++t) {
+                    const int s2 = t + 1 < NB ? s : (s + 1) & 3, t2 = t + 1 < NB ? t + 1 : 0;
+                    if (s2 == 0 && t2 == 0)
+                        group(nxt, 0);
+                    const uint32_t w = (s2 == 0 && t2 == 0) ? nxt.w[0][0] : cur.w[s2][t2];
+                    uint32_t p[4];
+#pragma unroll
+                    for (int i = 0; i < TMB; ++i) {
+                        acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[s & 1][i], b, acc[i][t], 0, 0, 0);
+                        const int m = (s * NB + t) * TMB + i;
+#pragma unroll
+                        for (int e = 0; e < PER; ++e)
+                            if (s < 2)
+                                load(m * PER + e);
+                        if (t == 0)
+                            read_a(s == 3 ? bufn : buf, (s + 1) & 3, i);
+                        // sixteen operations of the next word, in an order that keeps dependent ones apart
+#pragma unroll
+                        for (int o = 0; o < 16; ++o) {
+                            if (o * TMB / 16 != i)
+                                continue;
+                            const int e = o & 3;
+                            if (o < 4)
+                                p[e] = __builtin_amdgcn_perm(0u, w, 0x0c000c00u | e | (e << 16));
+                            else if (o < 8)
+                                p[e] = (p[e] & magic.mask) | magic.bias;
+                            else if (o < 12)
+                                p[e] = __builtin_bit_cast(uint32_t, as_half2(p[e]) + as_half2(nz[t2]));
+                            else
+                                p[e] = __builtin_bit_cast(uint32_t, as_half2(p[e]) * as_half2(ss[t2]));
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (s == 3 && t > 0)
+                        group(nxt, t);  // (this word's zero point and scale have served their last word)
+                    const u32x4_t v = {p[0], p[1], p[2], p[3]};
+                    b = __builtin_bit_cast(half8_t, v);
+                }
+            }
+        };
+        issue_w(ws0, r0);
+        asm volatile("" ::: "memory");
+        issue_x(ws0, 0);
+        asm volatile("" ::: "memory");
+        issue_x(ws0 + 1, 1);
+        asm volatile("" ::: "memory");
+        issue_w(ws0 + 1, r1);
+        arrived(r0, std::integral_constant<int, NX + NWL>());
+#pragma unroll
+        for (int i = 0; i < TMB; ++i)
+            read_a(0, 0, i);
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+            group(r0, t);
+        b = dequant_word(r0.w[0][0], magic, nz[0], ss[0]);
+        int st = ws0;
+        for (int i = 3; i <= share; i += 3) {
+            body(st, r0, r1, r2, 0);
+            body(st + 1, r1, r2, r0, 1);
+            body(st + 2, r2, r0, r1, 2);
+            st += 3;
+        }
+        const int rest = share % 3;
+        if (rest >= 1)
+            body(st, r0, r1, r2, 0);
+        if (rest == 2)
+            body(st + 1, r1, r2, r0, 1);
     }
 
     // ---- wavefronts meet in LDS (the rings are reused: every DMA has landed first), fixed order ----

@@ -1,0 +1,32 @@
+"""The mid-batch kernel's three-row-block form (65-96 rows): the edges of its rows, and every remainder of its pipeline."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_19438_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2511_19438_amd import binding
+    binding.load()
+    return binding
+
+
+# four wavefronts share K / 64 stages: none, one, two, three (a whole turn of the ring) to eight each, uneven shares
+@pytest.mark.parametrize("M,K,N,group,split", [(65, 64, 8, 64, 1), (96, 256, 72, 64, 1), (66, 576, 136, 192, 1), (95, 768, 64, 128, 1),
+                                               (80, 1088, 200, 64, 1), (77, 1920, 264, 128, 1), (96, 2048, 520, 256, 3)])
+def test_three_row_blocks_match_the_oracle(B, M, K, N, group, split):
+    case = workloads.make_case(M, K, N, group, seed=K + M)
+    dev = {k: torch.from_numpy(case[k]).cuda() for k in ("x", "qweight", "qzeros", "scales")}
+    # an infinite activation reaches its own row alone, and only through the stage that holds it
+    dev["x"][M - 1, K - 1] = float("inf")
+    out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+    B.gptq_w4a16_gemm(dev["x"], dev["qweight"], dev["qzeros"], dev["scales"], None, out, group, B.Plan(kernel=4, split_k=split))
+    got = out.cpu().numpy().astype(np.float64)[:M - 1]
+    ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group)[:M - 1]
+    assert np.all(np.abs(got - ref) <= 2e-2 * np.maximum(1.0, np.abs(ref)))
+    assert not np.isfinite(out[M - 1].float().cpu().numpy()).any()
