@@ -58,6 +58,24 @@ int k_groups_of_tile8(const Problem &p, int rows, int split)
     return workgroups_of_tile8(p, rows, split, &sps) <= kComputeUnits && sps > 8 ? 2 : 1;
 }
 
+// The same for the 128x128 and 64x128 tiles, where no compute unit of the busiest XCD has more than one workgroup (the
+// rings of two groups fill its LDS) and a slice has enough stages.  With one group against two: 64x128 tile, 4096x4096 at
+// M = 512 32.9 -> 28.0 us, at M = 100 29.3 -> 24.9 (in four slices of 16 stages 16.1 -> 15.3), 28672x4096 at M = 100
+// 183 -> 138; 128x128 tile, 4096x12288 at M = 256 61.2 -> 43.4, 11008x4096 at M = 512 147 -> 99.  Two groups fill the chip
+// without the partial sums of two slices in scratch: 4096x4096 at M = 256 20.7 us in four slices -> 19.5 in two.
+int k_groups_of_small_tile(const Problem &p, int t, int split)
+{
+    const int tiles = ceil_div_i(p.M, kTiles[t].bm) * ceil_div_i(p.N, kTiles[t].bn);
+    const int stages = ceil_div_i(p.K, 64);
+    const int sps = ceil_div_i(stages, split < 1 ? 1 : split);
+    return ceil_div_i(tiles, 8) * ceil_div_i(stages, sps) <= kComputeUnits / 8 && sps >= 16 ? 2 : 1;
+}
+
+int k_groups(const Problem &p, int t, int rows, int split)
+{
+    return t == 8 ? k_groups_of_tile8(p, rows, split) : t == 3 || t == 5 ? k_groups_of_small_tile(p, t, split) : 1;
+}
+
 // Estimated duration (microseconds) of the pipelined kernel with tile `t` and `split` K slices.  A workgroup walks its
 // stages at a pace set by instruction issue and latency: alone on a compute unit it leaves most of it idle, and
 // co-resident workgroups slow each other down by less than their number.  What counts is the busiest compute unit of the
@@ -71,9 +89,13 @@ struct SmallTilePace {
     double resident[3];  // one stage with that many workgroups on a compute unit
     int most;            // workgroups that fit one
     double fixed, split, per_slice, tbps, half;  // half: the HALF variant's stages take this much longer
+    // Two wavefront groups: a pair of stages with up to half of the compute units busy, what it takes longer with all of
+    // them, and the sum of the groups' results.  (64x128 tile, 28672x4096 unsplit: 138 us on 64 and 128 units, 166 on 256;
+    // 128x128: 237 and 241 on 32 and 128 units, 1.22-1.28 a pair on 256.)
+    double pair, pair_full, pair_fixed;
 };
-constexpr SmallTilePace kPace64x128 = {{0.41, 0.635, 0.925}, 3, 5.3, 1.65, 0.48, 6.3, 1.22};
-constexpr SmallTilePace kPace128x128 = {{0.825, 1.12, 0.0}, 2, 2.3, 2.55, 1.03, 4.8, 1.18};
+constexpr SmallTilePace kPace64x128 = {{0.41, 0.635, 0.925}, 3, 5.3, 1.65, 0.48, 6.3, 1.22, 0.59, 0.13, 0.5};
+constexpr SmallTilePace kPace128x128 = {{0.825, 1.12, 0.0}, 2, 2.3, 2.55, 1.03, 4.8, 1.18, 1.05, 0.2, 3.0};
 
 double estimate_us(const Problem &p, int t, int rows, int split, bool half)
 {
@@ -88,6 +110,9 @@ double estimate_us(const Problem &p, int t, int rows, int split, bool half)
     const double partial_mb = wgs * (double)bm * ts.bn * sizeof(float) / 1e6;
     if (t == 3 || t == 5) {
         const SmallTilePace &c = t == 5 ? kPace64x128 : kPace128x128;
+        if (k_groups_of_small_tile(p, t, split) == 2)
+            return c.fixed + c.pair_fixed + ceil_div_i(sps, 2) * (c.pair + c.pair_full * (n > 0.5 ? 2.0 * n - 1.0 : 0.0)) * (half ? c.half : 1.0) +
+                   (slices > 1 ? c.split + slices * c.per_slice + partial_mb / c.tbps : 0.0);
         const int full = (int)((n - 1e-9) / c.most);  // times that a compute unit is filled up, then the rest
         const int rest = (int)std::ceil(n - full * c.most - 1e-9);
         const double stage = full * c.resident[c.most - 1] + (rest > 0 ? c.resident[rest - 1] : 0.0);
@@ -243,17 +268,16 @@ hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *works
     if (plan.serial) {
         a.split_k = 1;
         a.serial_slices = plan.split_k;
-        a.serial_kw = plan.tile == 8 ? k_groups_of_tile8(p, plan.rows, plan.split_k) : 1;
+        a.serial_kw = k_groups(p, plan.tile, plan.rows, plan.split_k);
         return prefill::launch_tile<5>(a, mode, 1, stream);
     }
+    const bool pipelined = mode == prefill::kGroupPerStage || mode == prefill::kGroupPerHalf;
+    const int kw = pipelined ? k_groups(p, plan.tile, plan.rows, plan.split_k) : 1;
     switch (plan.tile) {
     case 1: return prefill::launch_tile<1>(a, mode, 1, stream);
-    case 3: return prefill::launch_tile<3>(a, mode, 1, stream);
-    case 5: return prefill::launch_tile<5>(a, mode, 1, stream);
-    case 8: {
-        const int kw = k_groups_of_tile8(p, plan.rows, plan.split_k);
-        return plan.rows == 96 ? prefill::launch_tile<9>(a, mode, kw, stream) : prefill::launch_tile<8>(a, mode, kw, stream);
-    }
+    case 3: return prefill::launch_tile<3>(a, mode, kw, stream);
+    case 5: return prefill::launch_tile<5>(a, mode, kw, stream);
+    case 8: return plan.rows == 96 ? prefill::launch_tile<9>(a, mode, kw, stream) : prefill::launch_tile<8>(a, mode, kw, stream);
     default: return hipErrorInvalidValue;
     }
 }

@@ -59,7 +59,7 @@ hipError_t launch(Kernel kernel, Args a, size_t lds, bool may_split, hipStream_t
 template <>
 hipError_t launch_tile<GPTQ_PREFILL_TILE>(const Args &a, int mode, int kw, hipStream_t stream)
 {
-#if GPTQ_PREFILL_TILE >= 8
+#if GPTQ_PREFILL_TILE != 1
     if (kw == 2 && mode == kGroupPerStage)
         return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, false, 2>, a,
                       2 * (size_t)NBUF * StageLayout<BM, BN, BK, false>::BYTES, true, stream, 2);

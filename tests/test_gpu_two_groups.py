@@ -1,0 +1,26 @@
+"""The 64x128 and 128x128 tiles with two wavefront groups to a workgroup, which few tiles of sixteen stages and more run."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_19438_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+# stages: 16 (the fewest), 17 (the groups' shares differ), 33 of which two slices get 17 and 16, a last half stage, a short last slice
+@pytest.mark.parametrize("tile", [3, 5])
+@pytest.mark.parametrize("M,K,N,group,split", [(65, 1024, 8, 128, 1), (128, 1088, 160, 64, 1), (129, 2112, 288, 64, 2), (200, 1056, 264, 32, 1),
+                                               (100, 2080, 136, 32, 2), (257, 3200, 128, 128, 3), (70, 1120, 1032, 160, 1)])
+def test_two_groups_match_the_oracle(tile, M, K, N, group, split):
+    from paper_2511_19438_amd import binding as B
+
+    case = workloads.make_case(M, K, N, group, seed=K + M)
+    dev = {k: torch.from_numpy(case[k]).cuda() for k in ("x", "qweight", "qzeros", "scales")}
+    out, again = (torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    for o in (out, again):
+        B.gptq_w4a16_gemm(dev["x"], dev["qweight"], dev["qzeros"], dev["scales"], None, o, group, B.Plan(kernel=2, tile=tile, split_k=split))
+    ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group)
+    assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - ref) <= 2e-2 * np.maximum(1.0, np.abs(ref)))
+    assert torch.equal(out.view(torch.int16), again.view(torch.int16))
