@@ -92,10 +92,12 @@ struct SmallTilePace {
     // Two wavefront groups: a pair of stages with up to half of the compute units busy, what it takes longer with all of
     // them, and the sum of the groups' results.  (64x128 tile, 28672x4096 unsplit: 138 us on 64 and 128 units, 166 on 256;
     // 128x128: 237 and 241 on 32 and 128 units, 1.22-1.28 a pair on 256.)
-    double pair, pair_full, pair_fixed;
+    // pair_half: `half` of such stages (333x2752x6888, groups of 32, 128x128 tile: 31.6 us in one slice, 31.0 in three of
+    // single groups).
+    double pair, pair_full, pair_fixed, pair_half;
 };
-constexpr SmallTilePace kPace64x128 = {{0.41, 0.635, 0.925}, 3, 5.3, 1.65, 0.48, 6.3, 1.22, 0.59, 0.13, 0.5};
-constexpr SmallTilePace kPace128x128 = {{0.825, 1.12, 0.0}, 2, 2.3, 2.55, 1.03, 4.8, 1.18, 1.05, 0.2, 3.0};
+constexpr SmallTilePace kPace64x128 = {{0.41, 0.635, 0.925}, 3, 5.3, 1.65, 0.48, 6.3, 1.22, 0.59, 0.13, 0.5, 1.22};
+constexpr SmallTilePace kPace128x128 = {{0.825, 1.12, 0.0}, 2, 2.3, 2.55, 1.03, 4.8, 1.18, 1.05, 0.2, 3.0, 1.25};
 
 double estimate_us(const Problem &p, int t, int rows, int split, bool half)
 {
@@ -111,7 +113,7 @@ double estimate_us(const Problem &p, int t, int rows, int split, bool half)
     if (t == 3 || t == 5) {
         const SmallTilePace &c = t == 5 ? kPace64x128 : kPace128x128;
         if (k_groups_of_small_tile(p, t, split) == 2)
-            return c.fixed + c.pair_fixed + ceil_div_i(sps, 2) * (c.pair + c.pair_full * (n > 0.5 ? 2.0 * n - 1.0 : 0.0)) * (half ? c.half : 1.0) +
+            return c.fixed + c.pair_fixed + ceil_div_i(sps, 2) * (c.pair + c.pair_full * (n > 0.5 ? 2.0 * n - 1.0 : 0.0)) * (half ? c.pair_half : 1.0) +
                    (slices > 1 ? c.split + slices * c.per_slice + partial_mb / c.tbps : 0.0);
         const int full = (int)((n - 1e-9) / c.most);  // times that a compute unit is filled up, then the rest
         const int rest = (int)std::ceil(n - full * c.most - 1e-9);
