@@ -19,12 +19,6 @@ int row_blocks(int M)
     return M <= 32 ? 1 : M <= 64 ? 2 : M <= 96 ? 3 : 4;
 }
 
-// Wavefronts per workgroup: eight (two per SIMD) where their activation rings fit the LDS, else four.
-int waves_of(int tmb)
-{
-    return tmb <= 2 ? 8 : 4;
-}
-
 template <int TMB, int NB, int WAVES, int DEPTH = 2>
 hipError_t launch_one(const mid::Args &a, hipStream_t stream)
 {
@@ -55,7 +49,6 @@ bool mid_supported(const Problem &p)
 void mid_make_plan(const Problem &p, MidPlan &plan)
 {
     const int tmb = row_blocks(p.M);
-    const int waves = waves_of(tmb);
     const int total = p.K / mid::kStageK;
     // four row blocks leave registers for two n-blocks only; three have room for four, which gained on layers of 160-256
     // such tiles only (4096x22016 at M = 77 29.4 us; 34.6 with two, 33.7 on the big-tile kernel) and lost 40 % elsewhere
@@ -72,9 +65,9 @@ void mid_make_plan(const Problem &p, MidPlan &plan)
     int split = plan.split_k;
     if (split <= 0) {
         // one workgroup per compute unit (their activation rings fill its LDS: workgroups beyond 256 wait for a
-        // second round); every wavefront should keep at least two stages
+        // second round); a slice keeps at least eight stages, or sixteen up to 64 rows
         split = 256 / tiles_n;
-        const int max_split = total / (2 * waves);
+        const int max_split = total / (tmb <= 2 ? 16 : 8);
         if (split > max_split)
             split = max_split;
         if (split < 1)
@@ -121,13 +114,16 @@ hipError_t launch_mid(const Problem &p, const MidPlan &plan, void *workspace, hi
         if (tmb == 1)
             return launch_one<1, 4, 8>(a, stream);
         if (tmb == 2)
-            return launch_one<2, 4, 8>(a, stream);
+            return launch_one<2, 4, 4, 3>(a, stream);
         return hipErrorInvalidValue;  // refused by mid_make_plan
     }
     if (tmb == 1)
         return launch_one<1, 2, 8>(a, stream);
+    // 33-64 rows: four wavefronts on the pinned loop against eight, two per SIMD, on the plain one.  M = 40 and 64:
+    // 4096x12288 15.6 us -> 14.0, 15.9 -> 15.3; 4096x22016 22.4 -> 21.2, 23.5 -> 21.9; 11008x4096 15.9 -> 15.0, 18.1 -> 17.0;
+    // 8192x10240 23.7 -> 22.1, 26.5 -> 26.0; 28672x8192 43.3 -> 43.4, 47.5 -> 46.8.
     if (tmb == 2)
-        return launch_one<2, 2, 8>(a, stream);
+        return launch_one<2, 2, 4, 3>(a, stream);
     // 65-96 rows: three row blocks leave LDS for a third stage of activations.  With four blocks as above 96 rows:
     // 8192x10240 at M = 77 39.3 us -> 31.0, 8192x8192 31.3 -> 25.0.
     if (tmb == 3)

@@ -14,8 +14,9 @@
 //     to the wavefront alone: `s_waitcnt vmcnt(n)` is all the synchronisation the loop needs.  16-byte chunks are
 //     XOR-swizzled by row so that the 32-row operand reads are free of bank conflicts;
 //   * weights are prefetched two stages ahead in three register sets (the DMA of the next stage is issued
-//     before them, so waiting for it does not wait for them), which covers the HBM latency with two wavefronts
-//     per SIMD;
+//     before them, so waiting for it does not wait for them).  From 33 to 96 rows one wavefront per SIMD runs a loop
+//     whose order is pinned around its MFMAs, with the activations two stages ahead as well; else two (above 96 rows
+//     one) per SIMD cover for each other on a plain loop;
 //   * partial sums meet in LDS (wavefronts, fixed order), then - if K is split across workgroups - in scratch,
 //     where the last workgroup to arrive adds the slices in slice order (Section 3.1's reduction, without
 //     floating point atomics).
@@ -152,8 +153,9 @@ __device__ __forceinline__ uint32_t scale_pair(const uint32_t &sc, int)
 // TMB: 32-row blocks (M <= 32 * TMB).  NB: 32-column n-blocks per wavefront (2 or 4; n-block t <-> column
 // NB * (lane % 32) + t of the tile).  WAVES: wavefronts per workgroup, each with its own share of the K slice.
 // DEPTH: stages in a wavefront's ring of activations: two, or three in the pinned loop of one wavefront per SIMD, which
-// 65-96 rows run.  There the MFMAs of 24 a stage take 0.49 us with all loads taken out and 0.7-0.8 with them (8192x10240:
-// 20.7 us without loads, 23.4 without activations' DMA, 30.6 in full): the latency of loads one and a half stages old.
+// 33-96 rows run.  At 65-96 rows a stage's 24 MFMAs and their vector work take 0.49 us with all loads taken out and
+// 0.7-0.8 with them (8192x10240 at M = 77: 20.7 us without loads, 23.4 without the activations' DMA, 30.6 in full): what a
+// compute unit gets through its load path, 60-70 KB per us, sets the pace - a fourth stage in the ring gained nothing.
 template <int TMB, int NB, int WAVES, int DEPTH>
 __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
 {
@@ -165,8 +167,8 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
     constexpr int NX = ROWS / 8;      // DMA instructions per stage: 8 rows x 128 bytes each
     constexpr int NWL = 6;            // vector memory instructions of one stage of weights (4 + scales + zeros)
     constexpr int LW = DEPTH * XBUF;  // LDS bytes of one wavefront: its ring
-    static_assert(DEPTH == 2 || DEPTH == 3, "the loop's buffer indices");
-    static_assert(2 * NX + 2 * NWL < 64, "vmcnt counts to 63");
+    static_assert(DEPTH == 2 || DEPTH == 3, "bodies of the loop");
+    static_assert(NX + 2 * NWL < 64, "vmcnt counts to 63");
 
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_last;
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
         }
     };
 
-    StageRegs<NB> r0, r1, r2;
+    StageRegs<NB> regs[3];
     if constexpr (DEPTH == 2) {
         // ---- the loop: x(i+1) and w(i+2) are issued, in that order, before stage i is consumed.  The vector memory
         //      counter retires in order, so waiting until only NX + 2*NWL instructions are outstanding leaves exactly
@@ -299,6 +301,7 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
             // fed the MFMAs above), this keeps the compiler from moving them
             asm volatile("" ::: "memory");
         };
+        StageRegs<NB> &r0 = regs[0], &r1 = regs[1], &r2 = regs[2];
         issue_w(ws0, r0);
         asm volatile("" ::: "memory");
         issue_x(ws0, 0);
@@ -322,10 +325,11 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
     } else {
         // ---- one wavefront per SIMD: nobody else's MFMAs run while this one issues loads, waits or dequantises.  The
         //      order is pinned instead: every MFMA is followed by a share of what the ones after it need - a load of
-        //      stage i+2 (first half of a stage), a piece of the next word's dequantisation, the next step's LDS reads.
-        //      Before its last step a stage waits for the next one: only x(i+2) and w(i+2) stay in flight, and the
-        //      last step prepares the first operands of stage i+1.  Buffer and registers of stage i+2 are those of
+        //      stage i+DEPTH-1 (first half of a stage), a piece of the next word's dequantisation, the next step's LDS reads.
+        //      Before its last step a stage waits for the next one: only stages i+2 .. i+DEPTH-1 stay in flight, and the
+        //      last step prepares the first operands of stage i+1.  Buffer and registers of stage i+DEPTH-1 are those of
         //      stage i-1, whose last read fed MFMAs above. ----
+        constexpr int IN_FLIGHT = (DEPTH - 2) * (NX + NWL);
         half8_t av[2][TMB];
         uint32_t nz[NB], ss[NB];
         half8_t b;
@@ -338,9 +342,12 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
         auto read_a = [&](int buf, int s, int i) {
             av[s & 1][i] = *reinterpret_cast<const half8_t *>(ring + (size_t)buf * XBUF + (aoff ^ (uint32_t)(s << 5)) + i * 4096);
         };
-        auto body = [&](int st, const StageRegs<NB> &cur, StageRegs<NB> &nxt, StageRegs<NB> &nxt2, int buf) {
-            const int bufn = (buf + 1) % 3, bufn2 = (buf + 2) % 3;
-            const int sc = min(st + 2, s1 - 1);
+        auto body = [&](int st, auto slot) {
+            constexpr int buf = decltype(slot)::value;
+            constexpr int bufn = (buf + 1) % DEPTH, bufl = (buf + DEPTH - 1) % DEPTH;
+            const StageRegs<NB> &cur = regs[buf];
+            StageRegs<NB> &nxt = regs[bufn], &ahead = regs[bufl];
+            const int sc = min(st + DEPTH - 1, s1 - 1);
             const char *xb = reinterpret_cast<const char *>(a.x + (size_t)sc * kStageK);
             const uint32_t *wrow = a.qweight + (size_t)sc * 8 * N;
             const uint32_t grp = __umulhi((uint32_t)sc, a.group_mul) + (uint32_t)sc * a.group_one;
@@ -351,18 +358,18 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
             auto load = [&](int q) {
                 if (q < NX)
                     __builtin_amdgcn_global_load_lds((global_ptr_t *)(xb + at_use(voff_x[q < NX ? q : 0])),
-                                                     (lds_ptr_t *)(ring + (size_t)bufn2 * XBUF + q * 1024), 16, 0, 0);
+                                                     (lds_ptr_t *)(ring + (size_t)bufl * XBUF + q * 1024), 16, 0, 0);
                 else if (q < NX + 4)
-                    load_global(nxt2.w[(q - NX) & 3], voff_w, wrow + (size_t)(2 * (q - NX)) * N);
+                    load_global(ahead.w[(q - NX) & 3], voff_w, wrow + (size_t)(2 * (q - NX)) * N);
                 else if (q == NX + 4)
-                    load_global(nxt2.sc, voff_s, srow);
+                    load_global(ahead.sc, voff_s, srow);
                 else if (q == NX + 5)
-                    load_global(nxt2.zb, voff_z, zrow);
+                    load_global(ahead.zb, voff_z, zrow);
             };
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 if (s == 3)
-                    arrived(nxt, std::integral_constant<int, NX + NWL>());
+                    arrived(nxt, std::integral_constant<int, IN_FLIGHT>());
 #pragma unroll
                 for (int t = 0; t < NB; ++t) {
                     const int s2 = t + 1 < NB ? s : (s + 1) & 3, t2 = t + 1 < NB ? t + 1 : 0;
@@ -404,42 +411,42 @@ __global__ __launch_bounds__(64 * WAVES) void mid_kernel(const Args a)
                 }
             }
         };
-        issue_w(ws0, r0);
-        asm volatile("" ::: "memory");
-        issue_x(ws0, 0);
-        asm volatile("" ::: "memory");
-        issue_x(ws0 + 1, 1);
-        asm volatile("" ::: "memory");
-        issue_w(ws0 + 1, r1);
-        arrived(r0, std::integral_constant<int, NX + NWL>());
+#pragma unroll
+        for (int d = 0; d < DEPTH - 1; ++d) {
+            issue_x(ws0 + d, d);
+            asm volatile("" ::: "memory");
+            issue_w(ws0 + d, regs[d]);
+            asm volatile("" ::: "memory");
+        }
+        arrived(regs[0], std::integral_constant<int, IN_FLIGHT>());
 #pragma unroll
         for (int i = 0; i < TMB; ++i)
             read_a(0, 0, i);
 #pragma unroll
         for (int t = 0; t < NB; ++t)
-            group(r0, t);
-        b = dequant_word(r0.w[0][0], magic, nz[0], ss[0]);
+            group(regs[0], t);
+        b = dequant_word(regs[0].w[0][0], magic, nz[0], ss[0]);
         int st = ws0;
-        for (int i = 3; i <= share; i += 3) {
-            body(st, r0, r1, r2, 0);
-            body(st + 1, r1, r2, r0, 1);
-            body(st + 2, r2, r0, r1, 2);
-            st += 3;
+        for (int i = DEPTH; i <= share; i += DEPTH) {
+            body(st, std::integral_constant<int, 0>());
+            body(st + 1, std::integral_constant<int, 1>());
+            body(st + 2, std::integral_constant<int, 2>());
+            st += DEPTH;
         }
-        const int rest = share % 3;
+        const int rest = share % DEPTH;
         if (rest >= 1)
-            body(st, r0, r1, r2, 0);
-        if (rest == 2)
-            body(st + 1, r1, r2, r0, 1);
+            body(st, std::integral_constant<int, 0>());
+        if (rest >= 2)
+            body(st + 1, std::integral_constant<int, 1>());
     }
 
     // ---- wavefronts meet in LDS (the rings are reused: every DMA has landed first), fixed order ----
     // The last bodies prefetched stages that nobody consumes: their registers stay reserved until those loads
     // have landed (naming them here keeps the compiler from handing them to the code below while a load that
     // it cannot see is still on its way).
-    arrived(r0, std::integral_constant<int, 0>());
-    arrived(r1, std::integral_constant<int, 0>());
-    arrived(r2, std::integral_constant<int, 0>());
+#pragma unroll
+    for (StageRegs<NB> &r : regs)
+        arrived(r, std::integral_constant<int, 0>());
     __syncthreads();
     float *red = reinterpret_cast<float *>(smem);
     constexpr int AT = ROWS * COLS;  // floats of one wavefront's tile
