@@ -325,7 +325,7 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
         if (ring_supported(p)) {
             r.ring = true;
             if (plan && plan->kernel == 4) {
-                r.skinny.cols_per_wg = plan->tile == 32 || plan->tile == 96 ? plan->tile : r.mid.cols_per_wg;
+                r.skinny.cols_per_wg = ring_width(p, plan->tile, r.mid.split_k) ? plan->tile : r.mid.cols_per_wg;
                 r.skinny.split_k = r.mid.split_k;
             }
             skinny_make_plan(p, r.skinny);

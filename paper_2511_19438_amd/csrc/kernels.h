@@ -98,6 +98,9 @@ struct SkinnyPlan {
 bool skinny_supported(const Problem &p);
 // Whether the problem has the variant on a ring of LDS slots: 32 rows at most, K a multiple of 128.
 bool ring_supported(const Problem &p);
+// Whether a workgroup of that variant may own `cols` columns: the widths that it exists in, and with K slices those that
+// leave every column tile an arrival counter.
+bool ring_width(const Problem &p, int cols, int split_k);
 void skinny_make_plan(const Problem &p, SkinnyPlan &plan);
 // Whether the plan has a form without scratch for its K slices, plan.serial.
 bool skinny_scratch_optional(const Problem &p, const SkinnyPlan &plan);

@@ -215,6 +215,12 @@ bool ring_supported(const Problem &p)
     return skinny_supported(p) && p.M <= 32 && p.K % skinny::kUnitK == 0;
 }
 
+bool ring_width(const Problem &p, int cols, int split_k)
+{
+    // (skinny_supported leaves widths of 64 and more a counter for every tile; 32 columns have one up to N = 2097152)
+    return (cols == 32 || cols == 64 || cols == 96 || cols == 128) && (split_k <= 1 || ceil_div(p.N, cols) <= kMaxColumnTiles);
+}
+
 namespace {
 
 // Slots that two slices need: one for every pair of outputs.
@@ -263,6 +269,8 @@ void ring_make_plan(const Problem &p, SkinnyPlan &plan)
         for (int asked = any_split ? 1 : plan.split_k; asked <= (any_split ? 16 : plan.split_k); ++asked) {
             const int ups = ceil_div(units, asked < units ? asked : units);
             const int split = ceil_div(units, ups);
+            if (!ring_width(p, cols, split))
+                continue;
             if (any_split && asked > 1 &&
                 (split != asked || tiles * split > 256 || ups < 8 ||
                  (long long)split * p.M * p.N * (long long)sizeof(float) > (long long)(GPTQ_STATIC_SCRATCH_BYTES - kCounterBytes)))
@@ -287,13 +295,14 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
     const int rows = 16 * row_blocks(launch_m);
     const int total_units = ceil_div(p.K, skinny::kUnitK);
     const int asked = plan.cols_per_wg;
+    const bool any_width = !ring_width(p, asked, plan.split_k);
     // 256 columns, from groups of 128 k on: on request, above 32 rows, and up to 16 rows beyond 65536 columns, wider than any
     // layer measured; in the widest of those the ring is ahead (8192x57344: M = 16 53 us, 48; level at two to four rows).
     const bool wide = p.group_size >= skinny::kUnitK &&
-                      (asked == 256 || (asked != 32 && asked != 64 && asked != 96 && asked != 128 &&
-                                        (rows > 32 ? ceil_div(p.N, 256) >= 192 : rows == 16 && p.N > 65536)));
+                      (asked == 256 ||
+                       (any_width && (rows > 32 ? ceil_div(p.N, 256) >= 192 : rows == 16 && p.N > 65536)));
     if (ring_supported(p) && !wide) {
-        if (asked != 32 && asked != 64 && asked != 96 && asked != 128)
+        if (any_width)
             plan.cols_per_wg = 0;
         ring_make_plan(p, plan);
         return;

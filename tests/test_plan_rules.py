@@ -143,3 +143,22 @@ def test_act_order_on_a_shallow_k(B):
                                 (2048, 768, 16384), (8, 256, 57344)]] == [16] * 7
     assert [flags(*s) for s in [(1024, 256, 4096), (256, 256, 16384), (2048, 256, 40960), (1024, 544, 16384), (2048, 544, 40960)]] == [0] * 5
     assert B.gptq_w4a16_plan_query(2048, 256, 40960, 32, True, B.Plan(kernel=2, flags=16)).flags == 16  # still on request
+
+
+def test_column_tiles_of_sliced_plans_have_an_arrival_counter_each(B):
+    """65536 counters; a width of 32 columns, asked for or chosen, would have more tiles beyond 2097152 columns."""
+    for M in (2, 16, 24, 32):
+        for N in (2097152, 2097160, 2097168, 3000000, 4194304):
+            for plan in (dict(kernel=3, tile=32), dict(kernel=4, tile=32), dict(kernel=3), dict(kernel=4)):
+                for split in (0, 1, 2):
+                    pl = B.gptq_w4a16_plan_query(M, 256, N, 128, False, B.Plan(split_k=split, **plan))
+                    assert split == 0 or pl.split_k == split
+                    assert pl.split_k == 1 or -(-N // pl.tile) <= 65536, (M, N, plan, pl.tile)
+    # what can be had is taken as asked: the last width with a counter for every tile, and any width without slices
+    assert B.gptq_w4a16_plan_query(2, 256, 2097152, 128, False, B.Plan(kernel=3, tile=32, split_k=2)).tile == 32
+    assert B.gptq_w4a16_plan_query(2, 256, 2097160, 128, False, B.Plan(kernel=3, tile=32, split_k=1)).tile == 32
+    # beyond it the width is chosen, as for any other that does not exist
+    for M in (2, 24):
+        for kernel in (3, 4):
+            asked, auto = (B.gptq_w4a16_plan_query(M, 256, 2097160, 128, False, B.Plan(kernel=kernel, tile=t, split_k=2)) for t in (32, 0))
+            assert kernel == 4 or fields(asked) == fields(auto)
