@@ -313,8 +313,9 @@ __global__ __launch_bounds__(64 * WAVES) void ring_kernel(const Args a)
                 }
                 get += Slot::BYTES;
                 get = get == (uint32_t)(DEPTH * Slot::BYTES) ? 0u : get;
-                // the reads of this slot are done (their values fed the MFMAs above): the next turn may fill it again
-                asm volatile("" ::: "memory");
+                // The next turn fills this slot again: its reads have to be done.  Not all of them have been used: with
+                // groups of 32 the scales of the last step belong to multiply-adds that the compiler moves behind this point.
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
             }
         }

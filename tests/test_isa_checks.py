@@ -4,7 +4,8 @@ compiler's back (CPU only: hipcc cross-compiles to assembly, nothing runs).
 Two kernels issue loads as inline assembly and wait for them by hand, because the compiler's own counter
 bookkeeping cost too much there: the mid-batch kernel (global loads of the weight stages, retired by one
 `s_waitcnt vmcnt(n)` per stage) and the big-tile kernel (LDS reads of the A operands, retired by
-`s_waitcnt lgkmcnt(n)`).  The compiler does not know that the destination registers of such a load are still
+`s_waitcnt lgkmcnt(n)`).  A third, the small-batch kernel on its ring, has its LDS slots refilled by DMA that the compiler
+does not see.  The compiler does not know that the destination registers of such a load are still
 pending: if it copied, reused or overwrote them between the load and the wait that retires it, a result would be
 wrong only now and then.  Memory operations of one kind retire in order, so a linear scan in layout order can tell.
 """
@@ -94,15 +95,35 @@ def check_pending(lines, is_tracked, is_counted, wait_re, what):
     return problems
 
 
+def check_refills(lines, what):
+    """Scans `lines` twice, as above, for LDS reads that may still be on their way when a DMA to LDS is issued."""
+    problems = []
+    queue = []
+    for trip in range(2):
+        for t in lines:
+            op = t.split()[0]
+            if op == "s_waitcnt":
+                m = re.search(r"lgkmcnt\((\d+)\)", t)
+                if m:
+                    n = int(m.group(1))
+                    queue = queue[len(queue) - n:] if n else []
+            elif op.startswith(("ds_", "s_load", "s_buffer_load")):
+                queue.append(t)
+            elif re.match(r"(global|buffer)_load\w*_lds", op) or (op.startswith("buffer_load") and " lds" in t):
+                problems += [f"{what}: '{t}' while '{r}' is in flight" for r in queue if r.startswith("ds_read")]
+    return problems
+
+
 @pytest.fixture(scope="module")
 def asm_files():
     if not os.path.exists(B.HIPCC):
         pytest.skip("no hipcc")
     tmp = tempfile.mkdtemp(prefix="gptq_isa_")
     jobs = [("mid.hip", [])] + [("prefill_tile.hip", [f"-DGPTQ_PREFILL_TILE={t}"]) for t in B.PREFILL_TILES]
+    jobs += [("ring.hip", [f"-DGPTQ_RING_GPU={g}"]) for g in B.RING_GROUPS]
     with ThreadPoolExecutor(max_workers=5) as pool:
         files = list(pool.map(lambda j: compile_to_asm(j[0], j[1], tmp), jobs))
-    return {"mid": files[0], "prefill": files[1:]}
+    return {"mid": files[0], "prefill": files[1:1 + len(B.PREFILL_TILES)], "ring": files[1 + len(B.PREFILL_TILES):]}
 
 
 def test_mid_batch_kernel_leaves_registers_of_pending_weight_loads_alone(asm_files):
@@ -132,6 +153,28 @@ def test_big_tile_kernel_leaves_registers_of_pending_lds_reads_alone(asm_files):
             problems = check_pending(lines, tracked, counted, wait, name)
             assert not problems, "\n".join(problems[:10])
     assert seen >= 4
+
+
+def test_ring_kernel_refills_a_slot_only_after_its_reads(asm_files):
+    """A turn of the loop lets DMA into the slot that the turn before has read, scales and zero points included.  (None of
+    its loads in inline assembly has a destination register: there are none in flight to leave alone.)"""
+    seen = 0
+    for path in asm_files["ring"]:
+        for name, lines in kernels(path).items():
+            if "ring_kernel" not in name:
+                continue
+            seen += 1
+            assert sum(t.startswith("global_load_lds") for t in lines) >= 6 and sum(t.startswith("ds_read") for t in lines) >= 8
+            problems = check_refills(lines, name)
+            assert not problems, "\n".join(problems[:10])
+    assert seen >= 150
+
+
+def test_the_refill_checker_flags_a_read_that_nothing_waits_for():
+    loop = ["ds_read_b128 v[0:3], v8", "ds_read_b32 v4, v9", "s_waitcnt lgkmcnt(0)", "global_load_lds_dwordx4 v10, s[4:5]"]
+    assert check_refills(loop, "good") == []
+    assert len(check_refills(loop[:2] + ["s_waitcnt lgkmcnt(1)"] + loop[3:], "late")) >= 1
+    assert len(check_refills(loop[:2] + loop[3:], "never")) >= 1
 
 
 def test_the_checker_itself_flags_a_planted_violation():
