@@ -326,7 +326,8 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
             r.ring = true;
             if (plan && plan->kernel == 4) {
                 r.skinny.cols_per_wg = ring_width(p, plan->tile, r.mid.split_k) ? plan->tile : r.mid.cols_per_wg;
-                r.skinny.split_k = r.mid.split_k;
+                // (slices of the mid-batch kernel's own choice are made for its own widths)
+                r.skinny.split_k = plan->split_k > 0 || r.skinny.cols_per_wg == r.mid.cols_per_wg ? r.mid.split_k : 0;
             }
             skinny_make_plan(p, r.skinny);
         }

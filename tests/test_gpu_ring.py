@@ -70,6 +70,17 @@ def test_the_result_does_not_depend_on_the_scratch(B, M, K, N, group):
         assert np.array_equal(bits(run_gemm(B, case, group)), bits(sliced))
 
 
+@pytest.mark.parametrize("kernel,tile", [(4, 0), (4, 32), (4, 64), (4, 96), (4, 128), (3, 32), (3, 96)])
+def test_nor_does_it_under_a_plan_that_leaves_the_slices_open(B, kernel, tile):
+    """(In slices made for wider tiles this layer's 32- and 96-column ones would be more workgroups than compute units.)"""
+    M, K, N, group = 24, 8192, 4096, 128
+    plan = B.Plan(kernel=kernel, tile=tile)
+    assert B.gptq_w4a16_plan_query(M, K, N, group, False, plan).split_k > 1
+    case, sliced = check(B, M, K, N, group, plan)
+    with workspace(B, COUNTERS):
+        assert np.array_equal(bits(run_gemm(B, case, group, plan)), bits(sliced))
+
+
 def test_rows_of_other_batches_do_not_matter(B):
     """Row blocks are padded with rows that repeat, and infinities stay in their own row."""
     case = workloads.make_case(32, 1024, 264, 128, seed=5)

@@ -162,3 +162,22 @@ def test_column_tiles_of_sliced_plans_have_an_arrival_counter_each(B):
         for kernel in (3, 4):
             asked, auto = (B.gptq_w4a16_plan_query(M, 256, 2097160, 128, False, B.Plan(kernel=kernel, tile=t, split_k=2)) for t in (32, 0))
             assert kernel == 4 or fields(asked) == fields(auto)
+
+
+def test_automatic_slices_of_the_ring_have_a_compute_unit_each(B):
+    """Eight wavefronts add the sums of an automatic slice up, as they do where there is no scratch for the slices: whatever
+    width a plan names, under either kernel's id.  A number of slices that a plan names is its own."""
+    rng = random.Random(17)
+    sliced = 0
+    for _ in range(1500):
+        group = rng.choice([32, 64, 128])
+        M, K, N = rng.randint(1, 32), 128 * rng.randint(8, 224), 8 * rng.randint(64, 2048)
+        kernel, tile = rng.choice([3, 4]), rng.choice([0, 32, 64, 96, 128])
+        pl = B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(kernel=kernel, tile=tile))
+        if pl.kernel not in (3, 4) or pl.tile == 256:
+            continue  # (a format or a width of other kernels)
+        assert pl.split_k == 1 or pl.split_k * -(-N // pl.tile) <= 256, (M, K, N, group, kernel, tile, pl.tile, pl.split_k)
+        sliced += pl.split_k > 1
+    assert sliced > 300
+    pl = B.gptq_w4a16_plan_query(24, 8192, 4096, 128, False, B.Plan(kernel=4, tile=32, split_k=4))
+    assert (pl.kernel, pl.tile, pl.split_k) == (4, 32, 4)
