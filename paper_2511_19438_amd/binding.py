@@ -15,12 +15,13 @@ from typing import Optional
 
 import torch
 
+from .build import native_call_path
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libgptq_w4a16.so")
-NATIVE_CALL_PATH = os.path.join(_HERE, "lib", "_native_call.so")
 
 _lib = None
-_native_gemm = None  # csrc/native_call.cpp: tensors to the C ABI in one call
+_native_gemm = None  # csrc/native_call.cpp: tensors to the C ABI in one call; None before load() and where there is none
 _addresses = {}      # of the entry points that it calls
 
 
@@ -48,11 +49,10 @@ def load() -> ctypes.CDLL:
     global _lib, _native_gemm
     if _lib is not None:
         return _lib
-    for path in (LIB_PATH, NATIVE_CALL_PATH):
-        if not os.path.exists(path):
-            raise FileNotFoundError(
-                f"{path} is missing: the HIP library must be built first "
-                "(python -m paper_2511_19438_amd.build); there is no CPU fallback")
+    if not os.path.exists(LIB_PATH):
+        raise FileNotFoundError(
+            f"{LIB_PATH} is missing: the HIP library must be built first "
+            "(python -m paper_2511_19438_amd.build); there is no CPU fallback")
     lib = ctypes.CDLL(LIB_PATH)
     vp, ci = ctypes.c_void_p, ctypes.c_int
     lib.gptq_w4a16_gemm.argtypes = [vp, vp, vp, vp, vp, vp, ci, ci, ci, ci, vp]
@@ -87,14 +87,25 @@ def load() -> ctypes.CDLL:
     lib.gptq_w4a16_issue_probe.restype = ci
     lib.gptq_w4a16_version.argtypes = []
     lib.gptq_w4a16_version.restype = ci
-    spec = importlib.util.spec_from_file_location("_native_call", NATIVE_CALL_PATH)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
     for name in ("gptq_w4a16_gemm", "gptq_w4a16_gemm_static", "gptq_w4a16_gemm_prepared"):
         _addresses[name] = ctypes.cast(getattr(lib, name), vp).value
-    _native_gemm = module.gemm
+    _native_gemm = _load_native_call(native_call_path())
     _lib = lib
     return lib
+
+
+def _load_native_call(path):
+    """gemm() of the extension module at `path`; None if it was not built for this torch and Python or cannot be loaded, and
+    calls are marshalled below."""
+    if not os.path.exists(path):
+        return None
+    try:
+        spec = importlib.util.spec_from_file_location("_native_call", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        return module.gemm
+    except (ImportError, OSError):
+        return None
 
 
 def strerror(code: int) -> str:
@@ -151,8 +162,7 @@ def gptq_w4a16_gemm_static(x, qweight, qzeros, scales, g_idx, out, group_size: i
 def gptq_w4a16_gemm(x, qweight, qzeros, scales, g_idx, out, group_size: int, plan: Optional[Plan] = None,
                     _static: bool = False):
     """out[M, N] = x[M, K] @ W (see the header).  Shapes are taken from the tensors; `out` is overwritten."""
-    lib = _lib or load()
-    if plan is None:
+    if plan is None and _native_gemm is not None:
         name = "gptq_w4a16_gemm_static" if _static else "gptq_w4a16_gemm"
         rc = _native_gemm(_addresses[name], x, qweight, qzeros, scales, g_idx, out, group_size)
         if rc == 0:
@@ -167,6 +177,7 @@ def gptq_w4a16_gemm(x, qweight, qzeros, scales, g_idx, out, group_size: int, pla
     M = shape[0]
     if out.shape != (M, N):
         raise ValueError(f"out must be [{M}, {N}], got {tuple(out.shape)}")
+    lib = _lib or load()
     args = (_ptr(x, torch.float16, "x"), _ptr(qweight, torch.int32, "qweight"), _ptr(qzeros, torch.int32, "qzeros"),
             _ptr(scales, torch.float16, "scales"), _ptr(g_idx, torch.int32, "g_idx"), _ptr(out, torch.float16, "out"),
             M, K, N, int(group_size), _stream())
@@ -198,8 +209,7 @@ def gptq_w4a16_act_order_prepare(qweight, g_idx, qweight_sorted, perm, group_siz
 
 def gptq_w4a16_gemm_prepared(x, qweight_sorted, qzeros, scales, perm, out, group_size: int):
     """The act-order GEMM on a repacked checkpoint: out = x[:, perm] @ W_sorted."""
-    lib = _lib or load()
-    if perm is not None:
+    if perm is not None and _native_gemm is not None:
         rc = _native_gemm(_addresses["gptq_w4a16_gemm_prepared"], x, qweight_sorted, qzeros, scales, perm, out, group_size)
         if rc == 0:
             return out
@@ -211,7 +221,7 @@ def gptq_w4a16_gemm_prepared(x, qweight_sorted, qzeros, scales, perm, out, group
     M = x.shape[0]
     if tuple(out.shape) != (M, N):
         raise ValueError(f"out must be [{M}, {N}], got {tuple(out.shape)}")
-    rc = lib.gptq_w4a16_gemm_prepared(
+    rc = load().gptq_w4a16_gemm_prepared(
         _ptr(x, torch.float16, "x"), _ptr(qweight_sorted, torch.int32, "qweight_sorted"),
         _ptr(qzeros, torch.int32, "qzeros"), _ptr(scales, torch.float16, "scales"), _ptr(perm, torch.int32, "perm"),
         _ptr(out, torch.float16, "out"), M, K, N, int(group_size), _stream())

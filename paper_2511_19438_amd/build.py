@@ -8,9 +8,11 @@ and one per tile shape of the MFMA kernel) that compile in parallel; objects go 
 """
 from __future__ import annotations
 
+import glob
 import os
 import subprocess
 import sys
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -19,7 +21,6 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libgptq_w4a16.so")
-NATIVE_CALL_PATH = os.path.join(LIB_DIR, "_native_call.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -59,26 +60,44 @@ def _compile(unit, extra_flags):
     return unit, proc
 
 
-def build_native_call() -> str:
-    """Compile the binding's CPython extension module (host code, against the installed torch).  Returns its path."""
+def native_call_path() -> str:
+    """The binding's extension module as built for the running torch and Python, which no other may load."""
     import sysconfig
 
     import torch
-    from torch.utils import cpp_extension
 
-    rocm = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"
-    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include")]
-    for path in cpp_extension.include_paths():
-        cmd += ["-isystem", path]
-    cmd += [os.path.join(CSRC, "native_call.cpp"), "-o", NATIVE_CALL_PATH,
-            "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
-    proc = subprocess.run(cmd, capture_output=True, text=True)
+    return os.path.join(LIB_DIR, f"_native_call.torch-{torch.__version__}.{sysconfig.get_config_var('SOABI')}.so")
+
+
+def build_native_call():
+    """Compile the binding's CPython extension module (host code, against the installed torch).  Returns its path, or None
+    with a warning where that cannot be done (no torch, one without GPU support, no compiler): the binding does without."""
+    for old in glob.glob(os.path.join(glob.escape(LIB_DIR), "_native_call*.so")):
+        os.remove(old)
+    try:
+        import sysconfig
+
+        import torch
+        from torch.utils import cpp_extension
+
+        path = native_call_path()
+        rocm = os.path.dirname(os.path.dirname(HIPCC)) if os.path.isabs(HIPCC) else "/opt/rocm"
+        torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+               "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include")]
+        for include in cpp_extension.include_paths():
+            cmd += ["-isystem", include]
+        cmd += [os.path.join(CSRC, "native_call.cpp"), "-o", path,
+                "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+        proc = subprocess.run(cmd, capture_output=True, text=True)
+    except (ImportError, OSError) as e:
+        warnings.warn(f"native_call.cpp was not built: {e}")
+        return None
     if proc.returncode != 0:
-        raise RuntimeError("native_call.cpp: " + (proc.stdout + proc.stderr)[-4000:])
-    return NATIVE_CALL_PATH
+        warnings.warn("native_call.cpp was not built: " + (proc.stdout + proc.stderr)[-4000:])
+        return None
+    return path
 
 
 def build(verbose: bool = False, jobs: int = 8, extra_flags=()) -> str:
