@@ -102,8 +102,9 @@ GPTQ_API int gptq_w4a16_gemm(const void *x, const void *qweight, const void *qze
  * GPTQ_STATIC_SCRATCH_EXCEEDED and enqueues nothing (needs are
  * 256 KiB + 4 * slices * M * N bytes where the plan splits K, which it does only while the output is small; the
  * largest need among the Llama-7B/70B layer shapes for M up to 2048 is 32.3 MiB, at 1024 x 11008 x 4096; the slices of
- * the big-tile kernel and of act-order problems are chosen to fit the block).  The first call on a
- * device also enqueues one small kernel on `stream` that clears the arrival counters.  All calls on one GPU share
+ * the big-tile kernel and of act-order problems are chosen to fit the block).  Behind the block lie 4 MiB more, in
+ * which two slices of the small-batch kernel exchange their sums.  Both are zero from the start: no call, the first one
+ * included, enqueues anything but the kernels of its product.  All calls on one GPU share
  * the block: calls that overlap in time on one GPU (different streams) race, as do a call here and a graph replay
  * that uses it.
  */

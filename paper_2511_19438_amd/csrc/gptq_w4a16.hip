@@ -44,17 +44,10 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kSl
 
 namespace {
 
-__global__ void clear_words_kernel(unsigned *p, unsigned n)
-{
-    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n)
-        p[i] = 0u;
-}
-
-// The current device's static scratch.  The first call on a device looks the address up and clears the arrival counters
-// at its front and the slots at its end with small kernels on `stream` (kernels, not memsets: the call may be under stream
-// capture).  No allocation.
-int static_scratch_ptr(hipStream_t stream, Scratch *out)
+// The current device's static scratch; the first call on a device looks its address up.  No allocation, and nothing to
+// clear: the array has static storage, so that the arrival counters at its front and the slots at its end are zero when the
+// code object is loaded, and every launch leaves them zero.
+int static_scratch_ptr(Scratch *out)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
@@ -63,14 +56,6 @@ int static_scratch_ptr(hipStream_t stream, Scratch *out)
     if (!g_static_ptr[dev]) {
         void *ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr)
-            return GPTQ_HIP_ERROR;
-        const unsigned words = (unsigned)(decode_counter_bytes(0) / sizeof(unsigned));
-        hipLaunchKernelGGL(clear_words_kernel, dim3((words + 255) / 256), dim3(256), 0, stream,
-                           static_cast<unsigned *>(ptr), words);
-        const unsigned slot_words = (unsigned)(kSlotBytes / sizeof(unsigned));
-        hipLaunchKernelGGL(clear_words_kernel, dim3((slot_words + 255) / 256), dim3(256), 0, stream,
-                           reinterpret_cast<unsigned *>(static_cast<unsigned char *>(ptr) + kStaticScratchBytes), slot_words);
-        if (hipGetLastError() != hipSuccess)
             return GPTQ_HIP_ERROR;
         g_static_ptr[dev] = ptr;
     }
@@ -507,7 +492,7 @@ int gptq_w4a16_gemm_static(const void *x, const void *qweight, const void *qzero
             return GPTQ_STATIC_SCRATCH_EXCEEDED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     Scratch scratch;
-    const int wrc = static_scratch_ptr(st, &scratch);
+    const int wrc = static_scratch_ptr(&scratch);
     if (wrc != GPTQ_OK)
         return wrc;
     return launch_resolved(p, r, scratch, st);

@@ -83,3 +83,60 @@ def test_static_rejects_a_problem_beyond_its_block(B):
     assert rc == -6
     assert "static" in B.strerror(rc)
     torch.cuda.synchronize()
+
+
+# In a process of its own, since it is about the first static call; device memory is dirty when the library is loaded.
+FIRST_CALL_CAPTURED = """
+import ctypes, re
+import torch
+from paper_2511_19438_amd import binding as B
+
+dirty = [torch.full((1 << 30,), 0xA5, dtype=torch.uint8, device="cuda") for _ in range(8)]
+torch.cuda.synchronize()
+del dirty
+torch.cuda.empty_cache()
+B.load()
+torch.manual_seed(1)
+K, N, group = 11008, 4096, 128
+qw = torch.randint(-2 ** 31, 2 ** 31, (K // 8, N), dtype=torch.int32, device="cuda")
+qz = torch.randint(-2 ** 31, 2 ** 31, (K // group, N // 8), dtype=torch.int32, device="cuda")
+sc = torch.full((K // group, N), 0.01, dtype=torch.float16, device="cuda")
+xs = [torch.randn(M, K, device="cuda").half() for M in (1, 8)]  # arrival counters; slots of two slices
+assert [B.gptq_w4a16_plan_query(len(x), K, N, group).split_k > 1 for x in xs] == [True, True]
+assert B.gptq_w4a16_plan_query(8, K, N, group).split_k == 2
+outs = [torch.empty(len(x), N, dtype=torch.float16, device="cuda") for x in xs]
+
+
+def static():
+    for x, out in zip(xs, outs):
+        B.gptq_w4a16_gemm_static(x, qw, qz, sc, None, out, group)
+
+
+graph = torch.cuda.CUDAGraph(keep_graph=True)
+with torch.cuda.graph(graph):
+    static()
+hip = ctypes.CDLL(re.search(r"\\S*/libamdhip64\\S*", open("/proc/self/maps").read()).group(0))
+count = ctypes.c_size_t(0)
+assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+graph.instantiate()
+wants = [B.gptq_w4a16_gemm(x, qw, qz, sc, None, torch.empty_like(out), group) for x, out in zip(xs, outs)]
+assert all(bool(w.isfinite().all()) and bool(w.any()) for w in wants)
+for run in (static, graph.replay, graph.replay, static, graph.replay):
+    for out in outs:
+        out.fill_(float("nan"))
+    run()
+    torch.cuda.synchronize()
+    assert all(torch.equal(out, want) for out, want in zip(outs, wants))
+print("nodes", count.value)
+"""
+
+
+def test_the_first_static_call_captured_records_nothing_else(B):
+    import os
+    import subprocess
+    import sys
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    proc = subprocess.run([sys.executable, "-c", FIRST_CALL_CAPTURED], cwd=root, capture_output=True, text=True, timeout=100)
+    assert proc.returncode == 0, proc.stderr[-2000:]
+    assert proc.stdout.split()[-2:] == ["nodes", "2"], proc.stdout
