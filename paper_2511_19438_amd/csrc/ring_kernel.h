@@ -30,7 +30,9 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 // One DMA instruction: lane l's 16 (or 4) bytes land at lds + 16 l (4 l).  The compiler does not know that LDS changes;
-// the memory clobbers here and at the waits keep its LDS reads where they stand.
+// the memory clobbers here and at the waits keep its LDS reads where they stand.  Nor does it know of m0, a reserved register
+// that a clobber list may not name: nothing else in this kernel may use it (no LDS-DMA builtin beside these), which a check
+// of the compiled code sees to.
 template <bool STREAM>
 __device__ __forceinline__ void dma_16(uint32_t lds, uint32_t byte_off, const char *base)
 {

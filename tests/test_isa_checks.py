@@ -170,6 +170,19 @@ def test_ring_kernel_refills_a_slot_only_after_its_reads(asm_files):
     assert seen >= 150
 
 
+def test_ring_kernel_has_m0_to_itself(asm_files):
+    """The DMA's LDS address goes through m0, in inline assembly that cannot tell the compiler so: it may not use m0 itself."""
+    for path in asm_files["ring"]:
+        for name, lines in kernels(path).items():
+            if "ring_kernel" not in name:
+                continue
+            in_asm = False
+            for t in lines:
+                in_asm = t.startswith(";;#ASMSTART") or (in_asm and not t.startswith(";;#ASMEND"))
+                assert in_asm or not re.search(r"\bm0\b", t), f"{name}: {t}"
+            assert sum("m0" in t for t in lines) >= 6
+
+
 def test_the_refill_checker_flags_a_read_that_nothing_waits_for():
     loop = ["ds_read_b128 v[0:3], v8", "ds_read_b32 v4, v9", "s_waitcnt lgkmcnt(0)", "global_load_lds_dwordx4 v10, s[4:5]"]
     assert check_refills(loop, "good") == []
