@@ -71,12 +71,15 @@ struct RingSlot {
 // TM: 16-row blocks.  LX: as above; rows that are not loaded repeat loaded ones, their outputs are not stored.
 // NF, NH: a lane's columns, NF times four (64 columns of the tile each) and NH times two (32 columns).
 // WAVES: eight wavefronts split the K slice, or four where there are more workgroups than compute units (ring_waves).
+// Registers: two wavefronts share a SIMD, those of one workgroup or of two.  Unbounded, the compiler gave the instances of
+// groups of 32, 17-32 rows and four wavefronts 280 (96 columns) and 356 (128), one workgroup to a compute unit; bounded it
+// finds room for the same loop in 188 and 234 (8192x57344, groups of 32, 128 columns, M = 24: 106.5 us -> 72.7).
 // SERIAL: no scratch for the K slices.  A workgroup walks all slices of its tile one after the other and adds their sums
 // in registers, in slice order: the bits of the sliced launch, whose tile may be any (an output's sum does not depend on
 // it).  For 64 columns and eight wavefronts only.
 template <int TM, int LX, int NF, int NH, int WAVES, int GPU, int DEPTH, bool STREAM,
           bool SERIAL = false>
-__global__ __launch_bounds__(64 * WAVES) void ring_kernel(const Args a)
+__global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
 {
     static_assert(DEPTH == 2 || DEPTH == 3, "the waits below");
     static_assert(!SERIAL || (WAVES == 8 && NF == 1 && NH == 0), "a thread keeps one quad of the tile");

@@ -183,6 +183,19 @@ def test_ring_kernel_has_m0_to_itself(asm_files):
             assert sum("m0" in t for t in lines) >= 6
 
 
+def test_ring_kernels_registers_let_two_wavefronts_share_a_simd(asm_files):
+    """Eight wavefronts of a workgroup, or two workgroups of four, as the plan's estimate takes it: 256 registers each, none spilled."""
+    seen = 0
+    for path in asm_files["ring"]:
+        for entry in re.findall(r"^  - \.agpr_count:.*?(?=^  - |^amdhsa)", open(path).read(), re.S | re.M):
+            if "ring_kernel" not in entry:
+                continue
+            seen += 1
+            field = lambda name: int(re.search(rf"\.{name}:\s+(\d+)", entry).group(1))  # noqa: E731
+            assert field("vgpr_count") <= 256 and field("vgpr_spill_count") == 0 and field("private_segment_fixed_size") == 0, entry
+    assert seen >= 150
+
+
 def test_the_refill_checker_flags_a_read_that_nothing_waits_for():
     loop = ["ds_read_b128 v[0:3], v8", "ds_read_b32 v4, v9", "s_waitcnt lgkmcnt(0)", "global_load_lds_dwordx4 v10, s[4:5]"]
     assert check_refills(loop, "good") == []
