@@ -230,10 +230,12 @@ size_t ring_slot_bytes(const Problem &p)
 }
 
 // Microseconds that a launch of ring_kernel takes, fitted to 11 k measured plans of 160 random layers (K 1024-28672, N
-// 1024-57344, groups of 128, 2-32 rows, weights from HBM): 6 % off on average, and the plan it picks 0.8 % behind the
-// best one.  A fixed part, the bytes at HBM speed, the units that one wavefront walks - more where workgroups share a
-// compute unit -, the sum over the wavefronts, and the exchange: two slices swap their sums (exchange.h), more go
-// through scratch.
+// 1024-57344, groups of 128, 2-32 rows, weights from HBM).  A fixed part, the bytes at HBM speed, the units that one
+// wavefront walks - more where workgroups share a compute unit -, the sum over the wavefronts, and the exchange: two
+// slices swap their sums (exchange.h), more go through scratch, at a price for each of them.
+// Checked, and that price set, on 33 k more plans of 590 layers with groups of 32, 64 and 128: the plan that it picks is
+// 0.7 % behind the best one (0.97 % without the price, at worst 24: 9472x1792 at M = 2 in ten slices of 96 columns 8.5 us, in
+// two of 32 7.3).  Factors on the units of groups of 64 and 32, 1.1 and 1.2, changed that by less than 0.1 % and are left out.
 float ring_estimate(const Problem &p, int cols, int split, int units_per_slice)
 {
     static const float unit[4][4] = {{0.57f, 0.65f, 0.85f, 0.95f}, {0.90f, 0.92f, 1.20f, 1.24f},
@@ -249,7 +251,7 @@ float ring_estimate(const Problem &p, int cols, int split, int units_per_slice)
     if (split == 2 && ring_slot_bytes(p) <= kSlotBytes)
         us += 0.7f + 0.004f * (float)tiles;
     else if (split > 1)
-        us += 2.2f + 5.8e-5f * m * (float)(cols * split) + 1.96e-6f * m * n * (float)split;
+        us += 1.6f + 0.1f * (float)split + 4.5e-5f * m * (float)(cols * split) + 1.96e-6f * m * n * (float)split;
     return us;
 }
 
