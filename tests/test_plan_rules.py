@@ -189,3 +189,12 @@ def test_small_batches_on_deep_narrow_layers(B):
                         (21888, 2464, 128), (9344, 1792, 32), (25728, 1792, 128), (14336, 1456, 64), (23552, 1792, 128)]:
         pl = B.gptq_w4a16_plan_query(2, K, N, group)
         assert pl.kernel == 3 and pl.tile <= 64, (K, N, group, pl.tile, pl.split_k)
+
+
+def test_small_tiles_of_small_groups(B):
+    """The plan of the big-tile kernel with groups of 32 where it measured 8-15 % ahead of the one that another pace of two
+    wavefront groups would give."""
+    plan = lambda M, K, N: (lambda pl: (pl.kernel, pl.tile, pl.split_k))(B.gptq_w4a16_plan_query(M, K, N, 32))  # noqa: E731
+    for problem, want in {(202, 7200, 2040): (5, 4), (174, 2496, 15488): (8, 2), (158, 2976, 10880): (5, 1), (378, 2112, 9064): (3, 1),
+                          (558, 2368, 1352): (5, 2), (424, 5056, 1408): (5, 3), (678, 4480, 2048): (5, 4), (357, 3200, 10496): (3, 1)}.items():
+        assert plan(*problem) == (2, *want), problem
