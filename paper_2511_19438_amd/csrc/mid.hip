@@ -34,6 +34,18 @@ hipError_t launch_one(const mid::Args &a, hipStream_t stream)
     return hipGetLastError();
 }
 
+// 33-64 rows on 128-column tiles: whether four wavefronts on the pinned loop are faster than eight, two per SIMD, on the
+// plain one.  They are on slices of up to 96 stages; deeper ones are bound by the load path, which eight keep fuller, and
+// slices of less than 32 leave too little between the prologue and the exchange.  Eight wavefronts against four, unsplit,
+// M = 33 / 48 / 64:  2048x28672 17.8 / 18.1 / 18.6 us, 16.3 / 16.7 / 17.3; 6144x57344 level; 8192x28672 43.8 / 44.8 / 46.3,
+// 45.8 / 46.0 / 47.0; 8192x57344 87.1 / 88.2 / 90.5, 94.5 / 92.2 / 93.0.  In slices:  16 stages 28672x1024 26.3 / 32.4 / 38.6,
+// 29.5 / 32.4 / 37.4 and 16384x2048 22.6 / 25.9 / 29.7, 24.9 / 27.6 / 31.1; 28 to 30 level; 64 stages 16384x8192
+// 33.9 / 35.6 / 37.8, 32.8 / 34.6 / 37.4; 112 stages 28672x8192 2-5 % for eight.
+bool pinned_on_wide_tiles(const MidPlan &plan)
+{
+    return plan.stages_per_slice <= 96 && (plan.split_k == 1 || plan.stages_per_slice >= 32);
+}
+
 }  // namespace
 
 bool mid_supported(const Problem &p)
@@ -114,14 +126,13 @@ hipError_t launch_mid(const Problem &p, const MidPlan &plan, void *workspace, hi
         if (tmb == 1)
             return launch_one<1, 4, 8>(a, stream);
         if (tmb == 2)
-            return launch_one<2, 4, 4, 3>(a, stream);
+            return pinned_on_wide_tiles(plan) ? launch_one<2, 4, 4, 3>(a, stream) : launch_one<2, 4, 8>(a, stream);
         return hipErrorInvalidValue;  // refused by mid_make_plan
     }
     if (tmb == 1)
         return launch_one<1, 2, 8>(a, stream);
     // 33-64 rows: four wavefronts on the pinned loop against eight, two per SIMD, on the plain one.  M = 40 and 64:
-    // 4096x12288 15.6 us -> 14.0, 15.9 -> 15.3; 4096x22016 22.4 -> 21.2, 23.5 -> 21.9; 11008x4096 15.9 -> 15.0, 18.1 -> 17.0;
-    // 8192x10240 23.7 -> 22.1, 26.5 -> 26.0; 28672x8192 43.3 -> 43.4, 47.5 -> 46.8.
+    // 4096x12288 15.6 us -> 14.0, 15.9 -> 15.3; 11008x4096 15.9 -> 15.0, 18.1 -> 17.0; 8192x10240 23.7 -> 22.1, 26.5 -> 26.0.
     if (tmb == 2)
         return launch_one<2, 2, 4, 3>(a, stream);
     // 65-96 rows: three row blocks leave LDS for a third stage of activations.  With four blocks as above 96 rows:

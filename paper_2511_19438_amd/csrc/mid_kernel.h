@@ -15,8 +15,8 @@
 //     XOR-swizzled by row so that the 32-row operand reads are free of bank conflicts;
 //   * weights are prefetched two stages ahead in three register sets (the DMA of the next stage is issued
 //     before them, so waiting for it does not wait for them).  From 33 to 96 rows one wavefront per SIMD runs a loop
-//     whose order is pinned around its MFMAs, with the activations two stages ahead as well; else two (above 96 rows
-//     one) per SIMD cover for each other on a plain loop;
+//     whose order is pinned around its MFMAs, with the activations two stages ahead as well; else (and on wide tiles of
+//     deep or short slices) two, above 96 rows one, per SIMD cover for each other on a plain loop;
 //   * partial sums meet in LDS (wavefronts, fixed order), then - if K is split across workgroups - in scratch,
 //     where the last workgroup to arrive adds the slices in slice order (Section 3.1's reduction, without
 //     floating point atomics).

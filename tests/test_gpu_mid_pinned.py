@@ -19,7 +19,10 @@ def B():
 # four wavefronts share K / 64 stages: none, one, two, three (a whole turn of the ring) to eight each, uneven shares
 @pytest.mark.parametrize("M,K,N,group,split", [(65, 64, 8, 64, 1), (96, 256, 72, 64, 1), (66, 576, 136, 192, 1), (95, 768, 64, 128, 1),
                                                (80, 1088, 200, 64, 1), (77, 1920, 264, 128, 1), (96, 2048, 520, 256, 3),
-                                               (33, 64, 8, 64, 1), (64, 576, 72, 192, 1), (63, 768, 136, 128, 1), (40, 1088, 200, 64, 1)])
+                                               (33, 64, 8, 64, 1), (64, 576, 72, 192, 1), (63, 768, 136, 128, 1), (40, 1088, 200, 64, 1),
+                                               (33, 6144, 136, 128, 1), (50, 6208, 136, 64, 1), (64, 8192, 8, 128, 1),
+                                               (64, 4096, 264, 128, 2), (33, 3968, 136, 128, 2), (48, 1984, 200, 64, 2)])
+# (and stages of a slice on both sides of where 128-column tiles take eight wavefronts on the plain loop)
 @pytest.mark.parametrize("tile", [64, 128])
 def test_pinned_loop_matches_the_oracle(B, M, K, N, group, split, tile):
     case = workloads.make_case(M, K, N, group, seed=K + M)
