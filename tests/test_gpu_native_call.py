@@ -78,3 +78,48 @@ def test_status_codes_and_transforms(B):
     assert torch.equal(side, t["out"])
     with pytest.raises(B.GptqError):
         B.gptq_w4a16_gemm(t["x"], t["qweight"], t["qzeros"], t["scales"], None, t["out"], -GROUP)
+
+
+def test_plain_calls_take_the_module(B, monkeypatch):
+    native = B._native_gemm
+    assert native is not None
+    codes = []
+    monkeypatch.setattr(B, "_native_gemm", lambda *a: codes.append(native(*a)) or codes[-1])
+    t = tensors()
+    call(B, t)
+    call(B, t, static=True)
+    call(B, dict(t, x=t["x"].as_subclass(Sub)))
+    assert codes == [0, 0, None]
+
+
+@pytest.mark.parametrize("static", [False, True])
+def test_the_module_enqueues_on_the_current_stream(B, static):
+    """What the call reads is there late in its stream, and only for a while."""
+    t = tensors()
+    call(B, t, static)
+    torch.cuda.synchronize()
+    want, x = t["out"].clone(), t["x"].clone()
+    big = torch.randn(4096, 4096, device="cuda")
+    side = torch.cuda.Stream()
+    t["x"].zero_()
+    t["out"].zero_()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(20):
+            torch.mm(big, big)  # tens of milliseconds ahead of the copy
+        t["x"].copy_(x)
+        call(B, t, static)
+        t["x"].zero_()
+    torch.cuda.synchronize()
+    assert torch.equal(t["out"], want)  # (on the default stream it would have read zeros)
+    graph = torch.cuda.CUDAGraph()
+    t["x"].copy_(x)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        call(B, t, static)
+    for _ in range(3):
+        t["out"].zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(t["out"], want)  # (on another stream it would not be in the graph)

@@ -24,7 +24,12 @@ CASES = [
     (2, 1024, 264, True, dict(kernel=1, split_k=2)),
     (8, 4096, 1024, False, dict(kernel=3, tile=64, split_k=4)),
     (24, 2048, 520, False, dict(kernel=3, tile=64, split_k=3)),
-    (16, 4096, 4096, False, dict()),                              # small-batch kernel, automatic plan (4 slices)
+    (16, 4096, 4096, False, dict()),                              # small-batch kernel, automatic plan: two slices that swap their sums
+    (2, 4096, 520, False, dict(kernel=3, tile=32, split_k=2)),    # the same swap on every width and row count of the ring
+    (9, 2048, 1024, False, dict(kernel=3, tile=96, split_k=2)),
+    (20, 2048, 264, False, dict(kernel=3, tile=64, split_k=2), 64),
+    (32, 4096, 1032, False, dict(kernel=3, tile=128, split_k=2), 32),
+    (8, 4096, 2056, False, dict(kernel=3, tile=32, split_k=4)),   # more slices of the ring: through scratch
     (48, 4096, 1024, False, dict(kernel=3, tile=64, split_k=2)),
     (64, 4096, 1024, False, dict(kernel=2, tile=5, split_k=8)),
     (56, 4096, 1024, False, dict(kernel=4, tile=64, split_k=4)),

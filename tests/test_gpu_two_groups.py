@@ -5,6 +5,7 @@ import torch
 
 import oracle
 from paper_2511_19438_amd import workloads
+from tests.test_gpu_scratch import COUNTERS, workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -24,3 +25,28 @@ def test_two_groups_match_the_oracle(tile, M, K, N, group, split):
     ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group)
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - ref) <= 2e-2 * np.maximum(1.0, np.abs(ref)))
     assert torch.equal(out.view(torch.int16), again.view(torch.int16))
+
+
+# automatic slices of both tiles, the plain variant and the one with a group row per half stage (small groups or a width of 8
+# mod 32), sixteen to 26 stages to a slice, a last half stage and a short last slice
+@pytest.mark.parametrize("tile", [3, 5])
+@pytest.mark.parametrize("M,K,N,group", [(257, 8192, 544, 128), (129, 6144, 288, 64), (130, 8192, 1032, 128), (200, 8224, 264, 32), (300, 8192, 1024, 32)])
+def test_two_groups_give_the_bits_of_the_form_without_scratch(tile, M, K, N, group):
+    from paper_2511_19438_amd import binding as B
+
+    plan = B.Plan(kernel=2, tile=tile)
+    split = B.gptq_w4a16_plan_query(M, K, N, group, False, plan).split_k
+    stages = -(-K // 64)
+    per_slice = -(-stages // split)
+    tiles = -(-M // (128 if tile == 3 else 64)) * -(-N // 128)
+    assert split > 1 and per_slice >= 16 and -(-tiles // 8) * split <= 32, "two groups"
+    case = workloads.make_case(M, K, N, group, seed=M)
+    dev = {k: torch.from_numpy(case[k]).cuda() for k in ("x", "qweight", "qzeros", "scales")}
+    sliced, walked = (torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    B.gptq_w4a16_gemm(dev["x"], dev["qweight"], dev["qzeros"], dev["scales"], None, sliced, group, plan)
+    with workspace(B, COUNTERS):
+        B.gptq_w4a16_gemm(dev["x"], dev["qweight"], dev["qzeros"], dev["scales"], None, walked, group, plan)
+        torch.cuda.synchronize()
+    assert torch.equal(sliced.view(torch.int16), walked.view(torch.int16))
+    ref = oracle.gemm_ref(case["x"], case["qweight"], case["qzeros"], case["scales"], None, group)
+    assert np.all(np.abs(sliced.cpu().numpy().astype(np.float64) - ref) <= 2e-2 * np.maximum(1.0, np.abs(ref)))
