@@ -133,7 +133,8 @@ typedef struct gptq_w4a16_plan {
                         but 256x256); 0 auto */
     int tile;        /* vector kernel: columns per workgroup (16, 32, 64, 128 or 256);
                         small-batch MFMA kernel: columns per workgroup (32, 64, 96 or 128 - 64 alone above 32 rows or
-                        if K % 128 != 0 -, or 256 from groups of 128 on; anything else = auto);
+                        if K % 128 != 0, 32 with K slices up to N = 2097152 -, or 256 from groups of 128 on; anything
+                        else = auto);
                         mid-batch MFMA kernel: columns per workgroup (64 or 128, up to 32 rows also 32 or 96; anything
                         else = auto; more than 64 rows always use 64);
                         MFMA kernel: tile id = rows x columns per workgroup (wavefront grid):
@@ -239,8 +240,8 @@ GPTQ_API int gptq_w4a16_unpack(const void *qweight, void *q_out, const void *qze
  * captured graph.  Growth is refused (GPTQ_WORKSPACE_TOO_SMALL, nothing enqueued) while `stream` is being
  * captured, since it allocates and clears memory: make one eager call of every problem a graph will hold
  * before capturing it, or use gptq_w4a16_gemm_static.
- * Some automatic plans can do without the scratch of their slices: act-order problems, the small-batch kernel with
- * groups of 64 or 32 where K is no multiple of 128, and the big-tile kernel.  Where it cannot be had, as above or on a workspace that
+ * Some automatic plans can do without the scratch of their slices: act-order problems, the small-batch kernel up to
+ * 32 rows (but for its 256-column workgroups), and the big-tile kernel.  Where it cannot be had, as above or on a workspace that
  * is too small, every workgroup walks the slices itself, one after the other, and adds them in the same order: the
  * result is the same, the call is slower by up to as many times as it has slices, and a graph that captured it
  * stays so.  Such a call needs no scratch from 17 rows on, and up to 16 rows what the vector kernel takes for the

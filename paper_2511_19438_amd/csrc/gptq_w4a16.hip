@@ -368,7 +368,7 @@ size_t required_scratch(const Problem &p, const gptq_w4a16_plan_t *request)
     return scratch_bytes(p, resolve(p, &vector));
 }
 
-// Act-order problems, the big-tile kernel and the small-batch kernel where K ends inside a unit do not fail where the
+// Act-order problems, the big-tile kernel and the small-batch kernel (up to 32 rows, all widths but 256) do not fail where the
 // scratch of their K slices cannot be had - a workspace of the caller's that is too small, growth under capture, the
 // static block: every workgroup then walks the slices itself, in the same order, so that the result does not depend on
 // the scratch.  (How many slices pay is a matter of measurement and may change; which calls a workspace serves may

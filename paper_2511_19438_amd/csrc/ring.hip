@@ -16,7 +16,7 @@ constexpr int kGpu = GPTQ_RING_GPU;
 template <int TM, int LX, int NF, int NH, int WAVES, bool STREAM, bool SERIAL = false>
 hipError_t launch_one(const Args &a, hipStream_t stream)
 {
-    // Slots: what measured best.  32 and 64 columns three, 96 and more two (4096x22016 in 96 columns, M = 8: 11.7, 12.1).
+    // Slots: what measured best.  32 columns three, 64 and more two (4096x22016 in 96 columns, M = 8: 11.7 us, 12.1 with three).
     constexpr int COLS = 64 * NF + 32 * NH;
     constexpr int DEPTH = COLS == 32 ? 3 : 2;
     auto kernel = ring_kernel<TM, LX, NF, NH, WAVES, kGpu, DEPTH, STREAM, SERIAL>;

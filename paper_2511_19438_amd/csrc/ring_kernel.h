@@ -15,7 +15,7 @@
 //   * Packed words, activations, scales and zero points all travel global -> LDS by DMA, in whole pieces: 1 KB of
 //     adjacent words, 8 rows x 128 bytes of x, one instruction for the scales and zero points of a group.  The loads of a
 //     64-k stage are LW + LX + 1 instructions (3 for 32 columns and 8 rows) where registers took 16 per 128 k, and no
-//     register waits for a load: one s_waitcnt per stage is all the bookkeeping, and no barrier stands in the loop.
+//     register waits for a load: a stage waits once for its loads, once for its LDS reads, and no barrier stands in the loop.
 //   * The ring is short (two or three stages).  Longer ones measured slower at every size (4096x4096, M = 8, 32
 //     columns: three stages 5.3 us, four 5.5, five 5.7, six 6.0).
 // The arithmetic is skinny_kernel's: B operand = exact q - z, scaled per group in fp32.

@@ -298,8 +298,11 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
     const int total_units = ceil_div(p.K, skinny::kUnitK);
     const int asked = plan.cols_per_wg;
     const bool any_width = !ring_width(p, asked, plan.split_k);
-    // 256 columns, from groups of 128 k on: on request, above 32 rows, and up to 16 rows beyond 65536 columns, wider than any
-    // layer measured; in the widest of those the ring is ahead (8192x57344: M = 16 53 us, 48; level at two to four rows).
+    // 256 columns, from groups of 128 k on: on request, above 32 rows, and up to 16 rows beyond 65536 columns.  The last as it
+    // was before there was the ring, whose unsplit workgroups are ahead there as well (128 columns: 4096x98304 at M = 2 and 16
+    // 44.8 us, 38.1 and 49.0, 39.3; 8192x131072 104, 106 and 126, 107; 96 columns: 4096x66560 30.9, 27.3 and 38.7, 30.5; behind
+    // on 4096x131072 at M = 2 56.6, 62.4 and 1024x196608 at M = 16 23.4, 24.6): what gemm_static refuses for its partial sums
+    // stays refused.  Up to 65536 columns the ring (8192x57344: M = 16 53 us, 48; level at two to four rows).
     const bool wide = p.group_size >= skinny::kUnitK &&
                       (asked == 256 ||
                        (any_width && (rows > 32 ? ceil_div(p.N, 256) >= 192 : rows == 16 && p.N > 65536)));

@@ -121,7 +121,7 @@ struct UnitRegs {                // GPU: quantisation groups per unit (1: groups
 // paired alike - one byte permute takes k and k + 1 of two columns - so the arithmetic needs no permutes of the entries;
 // the products go back to pairs of one column's k with one permute each.  20 vector operations per word WHATEVER M IS, and
 // the activations in their natural order (entries of one column: 24, and four permutes per activation operand; 4096x11008
-// at M = 8 13.2 us -> 12.0, 28672x2048 with groups of 64 at M = 64 42.9 -> 33.0), where the vector kernel paid for its
+// at M = 8 11.95 us -> 10.8, 28672x2048 with groups of 64 at M = 64 42.9 -> 33.0), where the vector kernel paid for its
 // lookups and for two operations per weight and row on top (40.5 us), and the big-tile kernel's general path fetched
 // every scale and zero point from global memory (M = 512 422 us, here 135).  Bound by vector issue, two 128-bit LDS reads
 // per word and, from 33 rows on, the latency of the activation loads.  More than 64 rows are row tiles of one grid.
