@@ -1,7 +1,7 @@
 // fp16 MFMA kernels for the W4A16 GPTQ matrix multiply at large batch (prefill), gfx950.
 //
 // This is the one place where the path is a real dense contraction, so it runs on the matrix
-// cores (v_mfma_f32_32x32x16_f16, fp32 accumulation).  The paper's kernel (Opt4GPTQ, Section 3)
+// cores (fp32 accumulation).  The paper's kernel (Opt4GPTQ, Section 3)
 // uses one vector kernel for every batch size; what carries over is its pipeline order: stage the
 // operands on chip with wide loads (Section 3.2), dequantise with packed half arithmetic
 // (Section 3.3), accumulate on chip and commit each output once (Section 3.1).
@@ -13,10 +13,17 @@
 //     NBUF-2 stages ahead of the MFMAs.  One s_waitcnt vmcnt(n) + s_barrier per stage publishes the
 //     oldest batch in flight; loads complete in order, so "at most n outstanding" means "the batch
 //     issued NBUF-2 stages ago has landed".
-//   * A operand (activations): 16-byte chunks are XOR-swizzled by row so that the 32-row operand
+//   * v_mfma_f32_16x16x32_f16.  What bounds large products is the power that the matrix pipe draws (the clock falls to 1.65
+//     GHz under it), and this form draws less for the same product than 32x32x16, whose accumulators pass twice as often: an
+//     MFMA-only loop on N(0,1) activations and dequantised weights 1.92 PFLOP/s against 1.69, with two vector instructions
+//     beside each 32 k operations 1.77 against 1.59.  Blocks of 16 rows also pad a ragged batch less.  One step with the
+//     inline-assembly DMA and LDS reads below (through the builtin the compiler emptied the pipeline of loads once per
+//     stage, in front of its first LDS read): 2048 rows through the four 8192-wide layers 2960 -> 2668 us, 512 rows through
+//     the four 4096-wide ones 254 -> 230, 333x2752x6888 with groups of 32 31.5 -> 29.5.
+//   * A operand (activations): 16-byte chunks are XOR-swizzled by row so that the 16-row operand
 //     reads (ds_read_b128) are bank-conflict free on the 64-bank LDS.
 //   * B operand (weights): a packed qweight word holds eight consecutive k of ONE column, which is
-//     exactly what one lane of the 32x32x16 MFMA B operand holds.  Each lane reads its word(s) from
+//     exactly what one lane of the MFMA's B operand holds.  Each lane reads its word(s) from
 //     the LDS copy and dequantises them in registers into the four VGPRs of the operand:
 //     v_perm_b32 + v_and_or_b32 build the pair (1024 + q_even, 64 + q_odd), a packed add of
 //     (-(1024 + z), -(64 + z)) gives the exact integer differences and a packed multiply by the scale
@@ -24,8 +31,9 @@
 //   * Waves of a workgroup split the N extent of the tile where possible, so every weight is
 //     dequantised by exactly one wave of the workgroup.
 //   * The instruction order of a k step is pinned with scheduling barriers: every MFMA is followed by
-//     a few instructions of the NEXT k step's LDS reads and dequantisation, which issue in the shadow
-//     of that MFMA (one wave per SIMD: nothing else would hide their latency or keep the pipe fed).
+//     a few instructions of the NEXT k step's LDS reads and dequantisation (one vector instruction per MFMA on a
+//     256-row tile), which issue in the shadow of that MFMA (one wave per SIMD: nothing else would hide their latency or
+//     keep the pipe fed).
 //   * Lane j of an n-block owns TN adjacent columns (n-block t <-> column base + TN*j + t), so the
 //     weight reads are TN dwords wide and the output stores are TN halves wide.
 //   * Workgroup ids are remapped so that the tiles resident on one XCD (ids congruent mod 8) are
@@ -36,13 +44,14 @@
 // sizes that are odd multiples of 32, a K that ends half-way through a stage, and an N that is no multiple of 32.
 //
 // prefill_general_kernel serves the remaining cases (g_idx, group sizes that are not a multiple of
-// 32) with the same operand layout but plain register staging; it is about correctness.
+// 32) with 32x32x16 MFMAs and plain register staging; it is about correctness.
 #pragma once
 
 #include <type_traits>
 
 #include "exchange.h"
 #include "kernels.h"
+#include "lds_dma.h"
 
 namespace gptq {
 namespace prefill {
@@ -76,8 +85,6 @@ struct Args {
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_ptr_t;
-typedef __attribute__((address_space(1))) const void global_ptr_t;
 
 __device__ __forceinline__ half2_t as_half2(uint32_t v)
 {
@@ -113,19 +120,10 @@ __device__ __forceinline__ uint32_t dequant_pair(uint32_t w, const PairMagic &k,
     return __builtin_bit_cast(uint32_t, v);
 }
 
-// The same in two halves, so that independent work can sit between the add and the multiply (a packed
-// multiply that consumes the result of the packed add right before it costs a wait state).
-template <int P>
-__device__ __forceinline__ uint32_t dequant_pair_begin(uint32_t w, const PairMagic &k, uint32_t nz)
+// The first step of the same on its own: byte `pair` of w in the low byte of both halves.
+__device__ __forceinline__ uint32_t spread_pair(uint32_t w, int pair)
 {
-    const uint32_t spread = __builtin_amdgcn_perm(0u, w, 0x0c000c00u | P | (P << 16));
-    const half2_t v = as_half2((spread & k.mask) | k.bias) + as_half2(nz);
-    return __builtin_bit_cast(uint32_t, v);
-}
-__device__ __forceinline__ uint32_t dequant_pair_end(uint32_t diff, uint32_t ss)
-{
-    const half2_t v = as_half2(diff) * as_half2(ss);
-    return __builtin_bit_cast(uint32_t, v);
+    return __builtin_amdgcn_perm(0u, w, 0x0c000c00u | pair | (pair << 16));
 }
 
 __device__ __forceinline__ u32x4_t dequant_word(uint32_t w, const PairMagic &k, const uint32_t nz[4],
@@ -137,6 +135,19 @@ __device__ __forceinline__ u32x4_t dequant_word(uint32_t w, const PairMagic &k, 
     r[2] = dequant_pair<2>(w, k, nz[2], ss[2]);
     r[3] = dequant_pair<3>(w, k, nz[3], ss[3]);
     return r;
+}
+
+// body(integral_constant<int, 0>) ... body(integral_constant<int, COUNT - 1>): a loop whose counter is a constant in the body
+// (longer ones than the compiler agrees to unroll would keep their register arrays in scratch memory).
+template <int FIRST, int COUNT, typename Body>
+__device__ __forceinline__ void static_for(Body &&body)
+{
+    if constexpr (COUNT == 1) {
+        body(std::integral_constant<int, FIRST>());
+    } else if constexpr (COUNT > 1) {
+        static_for<FIRST, COUNT / 2>(body);
+        static_for<FIRST + COUNT / 2, COUNT - COUNT / 2>(body);
+    }
 }
 
 // XCD-aware tile order: workgroup ids congruent mod 8 run on one XCD; give each XCD a contiguous range
@@ -182,6 +193,31 @@ __device__ __forceinline__ void store_tile(const float16_t (&acc)[TM][TN], half_
                 } else {
                     *dst = (half_t)acc[i][0][r];
                 }
+            }
+        }
+    }
+}
+
+// One fp16 rounding per output, TN adjacent columns per store.  Lane (lj, kg) holds, for 16-row block i and
+// accumulator register r, row 4*kg + r of the block and column lj of n-block t.
+template <int TM, int TN>
+__device__ __forceinline__ void store_blocks(const float4_t (&acc)[TM][TN], half_t *out, int row0, int col0, bool col_ok, int kg,
+                                             int M, int N)
+{
+    if (!col_ok)
+        return;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = row0 + i * 16 + 4 * kg + r;
+            if (m < M) {
+                half_t *dst = out + (size_t)m * N + col0;
+                if (TN == 4)
+                    *reinterpret_cast<half4_t *>(dst) = half4_t{(half_t)acc[i][0][r], (half_t)acc[i][1 % TN][r],
+                                                                (half_t)acc[i][2 % TN][r], (half_t)acc[i][3 % TN][r]};
+                else
+                    *reinterpret_cast<half2_t *>(dst) = half2_t{(half_t)acc[i][0][r], (half_t)acc[i][1 % TN][r]};
             }
         }
     }
@@ -324,19 +360,19 @@ template <int BM, int BN, int WM, int WN, int BK, int NBUF, bool HALF = false, i
 __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefill_pipelined_kernel(const Args a)
 {
     static_assert(KW == 1 || (KW == 2 && BM * BN <= 128 * 256), "two wavefronts per SIMD have 256 registers each");
-    static_assert(!HALF || BK == 64, "two 32-k halves");
     static_assert(!SERIAL || (KW == 1 && BM * BN <= 64 * 128), "32 accumulators, their sum and a half's");
     static_assert(WM * WN == 4, "four wavefronts per workgroup");
-    static_assert(BK == 32 || BK == 64, "stage of 32 or 64 k");
+    static_assert(BK == 64, "stage of 64 k");
     static_assert(NBUF >= 3, "ring of at least three stage buffers");
     using L = StageLayout<BM, BN, BK, HALF>;
-    constexpr int GROUPS = HALF ? 2 : 1;  // rows of scales / zero points per stage
     constexpr int WAVE_M = BM / WM;
     constexpr int WAVE_N = BN / WN;
-    constexpr int TM = WAVE_M / 32;
-    constexpr int TN = WAVE_N / 32;
-    static_assert(TM >= 1 && (TN == 1 || TN == 2 || TN == 4), "wave tile: 32-row blocks by 32/64/128 columns");
-    constexpr int KSTEPS = BK / 16;                         // MFMA k steps per stage (2 or 4)
+    constexpr int TM = WAVE_M / 16;
+    constexpr int TN = WAVE_N / 16;
+    static_assert(TM >= 4 && (TN == 2 || TN == 4), "wave tile: 16-row blocks by 32/64 columns");
+    constexpr int KSTEPS = 2;                               // MFMA k steps per stage
+    constexpr int RING_A = TM == 6 ? 6 : 8;                 // A operands in registers: in use or on their way
+    static_assert(KSTEPS * TM % RING_A == 0, "an operand's register is the same in every stage");
     constexpr int CH = BK / 8;                              // 16-byte chunks per A row
     constexpr int RPB = 16 / CH;                            // A rows per 256-byte bank row
     constexpr int A_CHUNKS = BM * CH / kThreads;            // DMA instructions per thread for the A tile
@@ -356,8 +392,8 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keep it in a scalar register
     const int wm = wave / WN;
     const int wn = wave % WN;
-    const int lj = lane & 31;
-    const int kh = lane >> 5;
+    const int lj = lane & 15;  // row of a 16-row block (A operand), column of a 16-column block (B operand, result)
+    const int kg = lane >> 4;  // packed row inside a 32-k step
 
     int tile_m, tile_n, tile_id, slice;
     if (!tile_of_workgroup(a, tile_m, tile_n, tile_id, slice))
@@ -370,17 +406,15 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     const int col_local = wn * WAVE_N + TN * lj;  // first of this lane's TN columns inside the tile
     const int col_raw = n0 + col_local;
     const bool col_ok = col_raw < N;
-    float16_t acc[TM][TN];
+    float4_t acc[TM][TN];
     const int groups = SERIAL ? a.serial_kw : KW;
-    float16_t total[SERIAL ? TM : 1][SERIAL ? TN : 1], half_sum[SERIAL ? TM : 1][SERIAL ? TN : 1];
+    float4_t total[SERIAL ? TM : 1][SERIAL ? TN : 1], half_sum[SERIAL ? TM : 1][SERIAL ? TN : 1];
     if (SERIAL) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int t = 0; t < TN; ++t)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    total[i][t][r] = half_sum[i][t][r] = 0.f;
+                total[i][t] = half_sum[i][t] = float4_t{0.f, 0.f, 0.f, 0.f};
     }
     int group = kgroup;  // SERIAL: the groups of every slice, one after the other
     for (;;) {           // (a single pass unless SERIAL; the body, up to the sums, is not indented)
@@ -396,9 +430,7 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int t = 0; t < TN; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-                acc[i][t][r] = 0.f;
+            acc[i][t] = float4_t{0.f, 0.f, 0.f, 0.f};
 
     // ---- global sources of this thread's DMA slots, as 32-bit byte offsets from bases that are uniform over
     //      the workgroup (scalar registers).  Loads never branch: rows past M and columns past N are clamped
@@ -460,34 +492,26 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     int ld_stage = first;
     int ld_in_group = HALF ? (first_half + s_half) % stages_per_group : first % stages_per_group;
     int z_in_group = HALF ? (first_half + z_half) % stages_per_group : 0;
-    const char *a_cur = a_base + (HALF ? (size_t)first_half * 64 : (size_t)first * BK * 2);
-    const size_t b_step = (size_t)(BK / 8) * N * 4;  // bytes between the packed rows of consecutive stages
-    const char *b_cur = b_base + (HALF ? (size_t)first_half * (b_step / 2) : (size_t)first * b_step);
+    const char *a_cur = uniform(a_base + (HALF ? (size_t)first_half * 64 : (size_t)first * BK * 2));
+    const uint32_t b_step = (uint32_t)(BK / 8) * N * 4u;  // bytes between the packed rows of consecutive stages
+    const char *b_cur = uniform(b_base + (HALF ? (size_t)first_half * (b_step / 2) : (size_t)first * b_step));
     const char *sz_cur = sz_src + (size_t)((HALF ? first_half + s_half : first) / stages_per_group) * sz_stride;
     const char *z_cur = z_src + (size_t)((first_half + z_half) / stages_per_group) * z_stride;  // HALF
-    auto stage_base = [&](int ring) { return smem + (size_t)ring * L::BYTES; };
+    const uint32_t smem_base = __builtin_amdgcn_readfirstlane(
+        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem);
     // piece `p` (0 .. LOADS_PER_STAGE-1) of the loads of stage `ld_stage` into ring slot `ring`
     auto issue_piece = [&](int p, int ring) {
-        unsigned char *base = stage_base(ring);
-        if (p < A_CHUNKS) {  // the wave's 64 lanes fill 64 consecutive 16-byte slots
-            __builtin_amdgcn_global_load_lds((global_ptr_t *)(a_cur + a_off[p]),
-                                             (lds_ptr_t *)(base + (size_t)(p * kThreads + wave * 64) * 16), 16, 0, 0);
-        } else if (p < A_CHUNKS + B_CHUNKS) {
-            const int j = p - A_CHUNKS;
-            __builtin_amdgcn_global_load_lds((global_ptr_t *)(b_cur + b_off[j]),
-                                             (lds_ptr_t *)(base + L::A_BYTES + (size_t)(j * kThreads + wave * 64) * 16),
-                                             16, 0, 0);
-        } else if (HALF && p == LOADS_PER_STAGE - 1) {
-            __builtin_amdgcn_global_load_lds((global_ptr_t *)z_cur,
-                                             (lds_ptr_t *)(base + L::A_BYTES + L::B_BYTES + L::SCALE_BYTES), 4, 0, 0);
-        } else if (HALF) {
-            __builtin_amdgcn_global_load_lds((global_ptr_t *)sz_cur,
-                                             (lds_ptr_t *)(base + L::A_BYTES + L::B_BYTES + s_part * 256), 4, 0, 0);
-        } else {
-            // all four waves write the same bytes: keeps the per-wave count of outstanding loads identical
-            __builtin_amdgcn_global_load_lds((global_ptr_t *)sz_cur, (lds_ptr_t *)(base + L::A_BYTES + L::B_BYTES),
-                                             16, 0, 0);
-        }
+        const uint32_t base = smem_base + (uint32_t)ring * (uint32_t)L::BYTES;
+        if (p < A_CHUNKS)  // the wave's 64 lanes fill 64 consecutive 16-byte slots
+            dma_16(base + (uint32_t)(p * kThreads + wave * 64) * 16u, a_off[p], a_cur);
+        else if (p < A_CHUNKS + B_CHUNKS)
+            dma_16(base + L::A_BYTES + (uint32_t)((p - A_CHUNKS) * kThreads + wave * 64) * 16u, b_off[p - A_CHUNKS], b_cur);
+        else if (HALF && p == LOADS_PER_STAGE - 1)
+            dma_4(base + L::A_BYTES + L::B_BYTES + L::SCALE_BYTES, z_cur);
+        else if (HALF)
+            dma_4(base + L::A_BYTES + L::B_BYTES + s_part * 256u, sz_cur);
+        else  // all four waves write the same bytes: keeps the per-wave count of outstanding loads identical
+            dma_16(base + L::A_BYTES + L::B_BYTES, sz_cur);
     };
     auto advance_load_stage = [&]() {
         // past the end the last stage is refetched: uniform counts, no branch in the loads
@@ -497,7 +521,7 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
             // one half less into a last stage that K ends half-way through; a group may be a single half
             const bool into_tail = k_tail && ld_stage == all_stages - 1;
             a_cur += more ? (into_tail ? BK : BK * 2) : 0;
-            b_cur += more ? (into_tail ? b_step / 2 : b_step) : (size_t)0;
+            b_cur = uniform(b_cur + (more ? (into_tail ? b_step / 2 : b_step) : 0u));
             ld_in_group += more ? (into_tail ? 1 : 2) : 0;
             z_in_group += more ? (into_tail ? 1 : 2) : 0;
 #pragma unroll
@@ -512,7 +536,7 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
             return;
         }
         a_cur += more ? BK * 2 : 0;
-        b_cur += more ? b_step : (size_t)0;
+        b_cur += more ? b_step : 0u;
         ld_in_group += more;
         const bool wrap = ld_in_group == stages_per_group;
         ld_in_group = wrap ? 0 : ld_in_group;
@@ -538,149 +562,170 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     };
 
     // ---- operand registers ----
-    half8_t afr[2][TM];  // A operands of two consecutive k steps
-    u32x4_t bfr[2][TN];  // B operands (bits of 4 half2 each)
-    uint32_t w_cur[KSTEPS][TN], w_nxt[KSTEPS][TN];  // packed words of this lane: stage in use / the next one
-    uint32_t nz_cur[GROUPS][TN], ss_cur[GROUPS][TN], nz_nxt[GROUPS][TN], ss_nxt[GROUPS][TN];
+    half8_t afr[RING_A];            // A operands, one after the other: operand q of a stage (k step q / TM, block q % TM)
+    u32x4_t bfr[2][TN];             // B operands (bits of 4 half2 each) of two consecutive k steps
+    typedef uint32_t words_t __attribute__((ext_vector_type(TN)));
+    typedef uint32_t words_half_t __attribute__((ext_vector_type(2)));
+    typedef std::conditional_t<TN == 4, words_half_t, uint32_t> scales_t;  // two in each word
+    words_t words[KSTEPS];          // packed words of this lane: of each k step, the ones to be dequantised next
+    scales_t raw_s;                 // scales and zero word of the group to be used next
+    uint32_t raw_z;
+    uint32_t nz[TN], ss[TN];        // the same, of the group in use, as operands of the packed arithmetic
     const PairMagic magic;
 
-    // A operand of 32-row block i at k step kk: row wm*WAVE_M + 32 i + lj, chunk (2 kk + kh) ^ swizzle(row).
-    // The swizzle does not depend on i (32 rows are a whole number of swizzle periods), so the byte offset is
-    // a per-lane value per k step plus i * 32 rows: the reads of one k step share ONE address register (the
+    // A operand of 16-row block i at k step kk: row wm*WAVE_M + 16 i + lj, chunk (4 kk + kg) ^ swizzle(row).
+    // The swizzle does not depend on i (16 rows are a whole number of swizzle periods), so the byte offset is
+    // a per-lane value per k step plus i * 16 rows: the reads of one k step share ONE address register (the
     // stage buffer's base added once per k step) and differ in the instruction's immediate offset.
+    static_assert(RPB == 2 && CH == 8, "sixteen rows, eight chunks: one period of the swizzle");
     uint32_t a_lane_off[KSTEPS];
 #pragma unroll
     for (int kk = 0; kk < KSTEPS; ++kk) {
         const int row = wm * WAVE_M + lj;
-        a_lane_off[kk] = (uint32_t)(row * (BK * 2) + (((2 * kk + kh) ^ ((row / RPB) & (CH - 1))) * 16));
+        a_lane_off[kk] = smem_base + (uint32_t)(row * (BK * 2) + (((4 * kk + kg) ^ ((row / RPB) & (CH - 1))) * 16));
     }
-    // The reads are issued as inline asm and waited for by hand (`wait_afrag`): the compiler's own counter
+    // The LDS reads of the loop are issued as inline asm and waited for by hand: the compiler's own counter
     // bookkeeping loses track of the order of LDS operations across the loop's back edge and falls back to
     // waiting for ALL outstanding LDS reads - including the one issued a few cycles earlier - before the first
     // use of every operand, which stalls the matrix pipe for an LDS round trip several times per k step.
-    const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    auto read_afrag = [&](int ring, int kk, int i, half8_t &dst) {
-        const uint32_t addr = smem_base + a_lane_off[kk] + (uint32_t)ring * (uint32_t)L::BYTES;
-#define GPTQ_READ_A(I) \
-    case I: asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"((I) * 32 * BK * 2)); break;
-        switch (i) {  // (the immediate offset must be a constant expression: one case per 32-row block)
-            GPTQ_READ_A(0) GPTQ_READ_A(1) GPTQ_READ_A(2) GPTQ_READ_A(3)
-            GPTQ_READ_A(4) GPTQ_READ_A(5) GPTQ_READ_A(6) GPTQ_READ_A(7)
-        }
-#undef GPTQ_READ_A
+    auto read_afrag = [&](int ring, auto operand, half8_t &dst) {  // operand (number in its stage) of the stage in `ring`
+        constexpr int Q = decltype(operand)::value, KK = Q / TM, I = Q % TM;
+        const uint32_t addr = a_lane_off[KK] + (uint32_t)ring * (uint32_t)L::BYTES;
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(I * 16 * BK * 2));
     };
-    // Before the first use of operand i of a k step: LDS reads return in order, and the reads issued after
-    // operand i's are the rest of its own k step (TM-1-i) and those of the current k step issued so far
-    // (one per slot in the first TM slots).  Reads the compiler issues in between only make this stricter.
+    // this lane's packed words of k step KK, and the scales and the zero word of the KK-th group of a stage
+    const uint32_t w_lane_off = smem_base + (uint32_t)(kg * BN + col_local) * 4u;
+    const uint32_t s_lane_off = smem_base + (uint32_t)col_local * 2u;
+    const uint32_t z_lane_off = smem_base + (uint32_t)(col_local >> 3) * 4u;
+    auto read_words = [&](int ring, auto step, words_t &dst) {
+        const uint32_t addr = w_lane_off + (uint32_t)ring * (uint32_t)L::BYTES;
+        constexpr int OFF = L::A_BYTES + decltype(step)::value * 4 * BN * 4;
+        if (TN == 4)
+            asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+        else
+            asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+    };
+    auto read_group = [&](int ring, auto number, scales_t &scales, uint32_t &zeros) {
+        constexpr int G = decltype(number)::value, SZ = L::A_BYTES + L::B_BYTES;
+        const uint32_t s_addr = s_lane_off + (uint32_t)ring * (uint32_t)L::BYTES;
+        const uint32_t z_addr = z_lane_off + (uint32_t)ring * (uint32_t)L::BYTES;
+        if (TN == 4)
+            asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(scales) : "v"(s_addr), "n"(SZ + G * BN * 2));
+        else
+            asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(scales) : "v"(s_addr), "n"(SZ + G * BN * 2));
+        asm volatile("ds_read_b32 %0, %1 offset:%2"
+                     : "=v"(zeros)
+                     : "v"(z_addr), "n"(SZ + (HALF ? L::SCALE_BYTES + G * (BN / 8) * 4 : BN * 2)));
+    };
+    // When they are read: the A operand RING_A - 1 ahead with every operand's first MFMA, the words (and the group) that
+    // are dequantised in the next k step after operand READ_AFTER of this one.
+    constexpr int READ_AFTER = TM - 4;
+    auto reads_words = [](int group) { return group % TM == READ_AFTER; };
+    auto word_reads = [](int group) { return HALF || group < TM ? 3 : 1; };
+    // Before the first use of operand q of a stage: LDS reads return in order, so what may be outstanding is what has been
+    // issued after its own read - the RING_A - 2 operands that follow and the words read in between.
     // (The operand is an in/out of the wait, so that the MFMA that consumes it cannot be moved above it.)
-    auto wait_afrag = [&](int i, half8_t &frag) {
-#define GPTQ_WAIT_A(I)                                                                                              \
-    case I:                                                                                                         \
-        asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(frag) : "n"(TM - 1 - (I) + (((I) * TN < TM) ? (I) * TN : TM))); \
-        break;
-        switch (i) {
-            GPTQ_WAIT_A(0) GPTQ_WAIT_A(1) GPTQ_WAIT_A(2) GPTQ_WAIT_A(3)
-            GPTQ_WAIT_A(4) GPTQ_WAIT_A(5) GPTQ_WAIT_A(6) GPTQ_WAIT_A(7)
-        }
-#undef GPTQ_WAIT_A
+    auto wait_afrag = [&](auto operand, half8_t &frag) {
+        constexpr int Q = decltype(operand)::value;
+        constexpr int COUNT = [=] {
+            int n = RING_A - 2;
+            for (int g = Q - (RING_A - 1); g < Q; ++g) {
+                const int group = (g + KSTEPS * TM) % (KSTEPS * TM);
+                if (reads_words(group))
+                    n += word_reads(group);
+            }
+            return n;
+        }();
+        static_assert(COUNT < 16, "lgkmcnt is a 4-bit counter");
+        asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(frag) : "n"(COUNT));
     };
-    // this lane's packed words, scales and zero points of a whole stage
-    auto read_weights = [&](int ring, uint32_t (&w)[KSTEPS][TN], uint32_t (&nz)[GROUPS][TN],
-                            uint32_t (&ss)[GROUPS][TN]) {
-        const unsigned char *base = stage_base(ring) + L::A_BYTES;
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk) {
-            const unsigned char *src = base + ((size_t)(2 * kk + kh) * BN + col_local) * 4;
-            if (TN == 4) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(src);
-                w[kk][0] = v.x;
-                w[kk][1 % TN] = v.y;
-                w[kk][2 % TN] = v.z;
-                w[kk][3 % TN] = v.w;
-            } else if (TN == 2) {
-                const uint2 v = *reinterpret_cast<const uint2 *>(src);
-                w[kk][0] = v.x;
-                w[kk][1 % TN] = v.y;
-            } else {
-                w[kk][0] = *reinterpret_cast<const uint32_t *>(src);
-            }
+    // The same for the words (and the group), behind the first MFMA of a k step: the operands read since may be outstanding.
+    auto wait_words = [&](words_t &w) { asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(w) : "n"(TM - 1 - READ_AFTER)); };
+    auto wait_group = [&](scales_t &scales, uint32_t &zeros) { asm volatile("" : "+v"(scales), "+v"(zeros)); };
+    const int z_shift = 4 * (col_local & 7);
+    auto unpack_scale = [&](int t) {
+        uint32_t pair;
+        if constexpr (TN == 4)
+            pair = raw_s[t / 2];
+        else
+            pair = raw_s;
+        ss[t] = __builtin_amdgcn_perm(0u, pair, t & 1 ? 0x03020302u : 0x01000100u);
+    };
+    auto unpack_zero = [&](int t) { nz[t] = neg_bias(raw_z >> (z_shift + 4 * t) & 15u); };
+
+    // The vector work that prepares the B operands of a k step, as a list of small operations: `GROUP_OPS` that
+    // unpack a new group's scales and zero points, then sixteen per packed word - spread, mask and bias, subtract the
+    // zero point, scale, each for the four pairs of the word before the next, so that no operation follows the one it
+    // depends on.
+    constexpr int GROUP_OPS = 2 * TN;
+    auto prepare_op = [&](int o, bool new_group, int kk, u32x4_t (&b)[TN]) {
+        if (new_group && o < GROUP_OPS) {
+            if (o & 1)
+                unpack_zero(o / 2);
+            else
+                unpack_scale(o / 2);
+            return;
         }
-        const unsigned char *sz = base + L::B_BYTES;
-#pragma unroll
-        for (int g = 0; g < GROUPS; ++g) {
-            const unsigned char *zw = HALF ? sz + L::SCALE_BYTES + (g * (BN / 8) + (col_local >> 3)) * 4
-                                           : sz + BN * 2 + (col_local >> 3) * 4;
-            const uint32_t zword = *reinterpret_cast<const uint32_t *>(zw);
-#pragma unroll
-            for (int t = 0; t < TN; ++t) {
-                const uint32_t sb = *reinterpret_cast<const uint16_t *>(sz + (g * BN + col_local + t) * 2);
-                ss[g][t] = sb | (sb << 16);
-                nz[g][t] = neg_bias((zword >> (4 * ((col_local + t) & 7))) & 15u);
-            }
+        const int d = o - (new_group ? GROUP_OPS : 0);
+        const int t = d >> 4, pair = d & 3;
+        switch (d >> 2 & 3) {
+        case 0: b[t][pair] = spread_pair(words[kk][t], pair); break;
+        case 1: b[t][pair] = (b[t][pair] & magic.mask) | magic.bias; break;
+        case 2: b[t][pair] = __builtin_bit_cast(uint32_t, as_half2(b[t][pair]) + as_half2(nz[t])); break;
+        default: b[t][pair] = __builtin_bit_cast(uint32_t, as_half2(b[t][pair]) * as_half2(ss[t])); break;
         }
     };
 
     // One k step, in exactly this instruction order (a scheduling barrier closes every slot): ONE MFMA, then
-    // its share of the work for the NEXT k step - an LDS read of an A operand (first TM slots), dequantisation
-    // of weight pairs, and whatever `extra` adds (loads for a later stage, weight reads for the next one).
-    // An MFMA occupies the matrix pipe for 8 passes but the wave can issue other instructions right behind it,
+    // its share of the work for the NEXT k step - the LDS read of the A operand RING_A - 1 ahead (once per operand),
+    // preparation of the B operands, and whatever `extra` adds (loads for a later stage).
+    // An MFMA occupies the matrix pipe for 4 passes but the wave can issue other instructions right behind it,
     // so a handful of them per MFMA run in its shadow; several MFMAs back to back followed by a block of
     // vector work would leave the pipe idle during the block.
     constexpr int SLOTS = TM * TN;  // MFMAs per k step
-    constexpr int PAIRS = 4 * TN;   // half2 results to produce per k step
-    auto kstep = [&](auto parity, int next_ring, int next_kk, const uint32_t (&nw)[TN], const uint32_t (&nnz)[TN],
-                     const uint32_t (&nss)[TN], auto &&extra) {
-        constexpr int CUR = std::decay_t<decltype(parity)>::value, NXT = CUR ^ 1;
-        uint32_t pending[(PAIRS + SLOTS - 1) / SLOTS] = {};
-#pragma unroll
-        for (int m = 0; m < SLOTS; ++m) {
-            const int i = m / TN, t = m % TN;
+    auto multiply = [&](float4_t &c, const half8_t &x, const u32x4_t &w) {
+        // 256 accumulators fill one half of a wavefront's registers.  Left to itself the compiler keeps some of them in the
+        // other half and swaps them in and out (288 moves per stage); the assembly says where they are.  It hides the MFMA
+        // from the compiler's hazard checks: the B operands are complete three MFMAs before their use, the results are
+        // first read after the wait states behind the loop.
+        if constexpr (TM * TN == 64)
+            asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(x), "v"(w));
+        else
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, __builtin_bit_cast(half8_t, w), c, 0, 0, 0);
+    };
+    auto kstep = [&](auto step, int ring, int ring_next, auto &&extra) {
+        constexpr int KK = decltype(step)::value, NXT = KK ^ 1;
+        constexpr bool NEW_GROUP = HALF || NXT == 0;  // the k step being prepared brings a row of scales
+        constexpr int OPS = 16 * TN + (NEW_GROUP ? GROUP_OPS : 0);
+        static_for<0, SLOTS>([&](auto slot) {
+            constexpr int m = decltype(slot)::value, i = m / TN, t = m % TN, q = KK * TM + i;
             if (t == 0)
-                wait_afrag(i, afr[CUR][i]);
-            acc[i][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(afr[CUR][i], __builtin_bit_cast(half8_t, bfr[CUR][t]),
-                                                               acc[i][t], 0, 0, 0);
-            if (m < TM)
-                read_afrag(next_ring, next_kk, m, afr[NXT][m]);
-            // pairs [m * PAIRS / SLOTS, (m + 1) * PAIRS / SLOTS) belong to this slot: their conversion and
-            // zero-point subtraction happen here, the multiply by the scale one slot later (the last slot
-            // finishes its own), so no multiply directly follows the add it depends on
-            constexpr int PPS = (PAIRS + SLOTS - 1) / SLOTS;
-            uint32_t now[PPS];
-#pragma unroll
-            for (int pair = m * PAIRS / SLOTS; pair < (m + 1) * PAIRS / SLOTS; ++pair) {
-                const int pt = pair >> 2;
-                uint32_t r;
-                switch (pair & 3) {
-                case 0: r = dequant_pair_begin<0>(nw[pt], magic, nnz[pt]); break;
-                case 1: r = dequant_pair_begin<1>(nw[pt], magic, nnz[pt]); break;
-                case 2: r = dequant_pair_begin<2>(nw[pt], magic, nnz[pt]); break;
-                default: r = dequant_pair_begin<3>(nw[pt], magic, nnz[pt]); break;
-                }
-                now[pair - m * PAIRS / SLOTS] = r;
+                wait_afrag(std::integral_constant<int, q>(), afr[q % RING_A]);
+            multiply(acc[i][t], afr[q % RING_A], bfr[KK][t]);
+            if (m == 0) {
+                wait_words(words[NXT]);
+                if (NEW_GROUP)
+                    wait_group(raw_s, raw_z);
             }
-            if (m > 0) {
-#pragma unroll
-                for (int pair = (m - 1) * PAIRS / SLOTS; pair < m * PAIRS / SLOTS; ++pair) {
-                    const int pt = pair >> 2;
-                    bfr[NXT][pt][pair & 3] = dequant_pair_end(pending[pair - (m - 1) * PAIRS / SLOTS], nss[pt]);
-                }
+            if (t == 0) {
+                constexpr int ahead = q + RING_A - 1;
+                read_afrag(ahead < KSTEPS * TM ? ring : ring_next, std::integral_constant<int, ahead % (KSTEPS * TM)>(),
+                           afr[ahead % RING_A]);
             }
 #pragma unroll
-            for (int q = 0; q < PPS; ++q)
-                pending[q] = now[q];
-            if (m == SLOTS - 1) {
-#pragma unroll
-                for (int pair = m * PAIRS / SLOTS; pair < (m + 1) * PAIRS / SLOTS; ++pair) {
-                    const int pt = pair >> 2;
-                    bfr[NXT][pt][pair & 3] = dequant_pair_end(pending[pair - m * PAIRS / SLOTS], nss[pt]);
-                }
+            for (int o = m * OPS / SLOTS; o < (m + 1) * OPS / SLOTS; ++o)
+                prepare_op(o, NEW_GROUP, NXT, bfr[NXT]);
+            if (t == TN - 1 && reads_words(q)) {
+                read_words(ring_next, step, words[KK]);
+                if (HALF || KK == 0)
+                    read_group(ring_next, step, raw_s, raw_z);
             }
             extra(m);
             __builtin_amdgcn_sched_barrier(0);
-        }
+        });
     };
-    using P0 = std::integral_constant<int, 0>;
-    using P1 = std::integral_constant<int, 1>;
+    using Step0 = std::integral_constant<int, 0>;
+    using Step1 = std::integral_constant<int, 1>;
     auto nothing = [](int) {};
 
     // ---- prologue: put NBUF-1 stages in flight, publish the first two, load the first operands ----
@@ -694,20 +739,27 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     publish();
     if (HALF && (tail_stage == 0 || tail_stage == 1))
         clear_repeated_half(tail_stage);
-    read_weights(0, w_cur, nz_cur, ss_cur);
+    read_words(0, Step0{}, words[0]);
+    read_group(0, Step0{}, raw_s, raw_z);
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(words[0]), "+v"(raw_s), "+v"(raw_z));
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-        read_afrag(0, 0, i, afr[0][i]);
-#pragma unroll
-    for (int t = 0; t < TN; ++t) {
-        bfr[0][t][0] = dequant_pair<0>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
-        bfr[0][t][1] = dequant_pair<1>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
-        bfr[0][t][2] = dequant_pair<2>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
-        bfr[0][t][3] = dequant_pair<3>(w_cur[0][t], magic, nz_cur[0][t], ss_cur[0][t]);
-    }
+    for (int o = 0; o < GROUP_OPS + 16 * TN; ++o)
+        prepare_op(o, true, 0, bfr[0]);
+    // (in the order of the loop: the waits count on it)
+    static_for<0, RING_A - 1>([&](auto operand) {
+        constexpr int q = decltype(operand)::value, issued_in = q - (RING_A - 1) + KSTEPS * TM;
+        read_afrag(0, operand, afr[q]);
+        if (issued_in >= TM && reads_words(issued_in)) {
+            read_words(0, Step1{}, words[1]);
+            if (HALF)
+                read_group(0, Step1{}, raw_s, raw_z);
+        }
+    });
+    static_assert(RING_A - 1 >= TM - READ_AFTER, "the words of k step 1 are read");
 
     // Invariant at the top of stage s: stages s and s+1 are in LDS and visible, every wave has left stage s-1,
-    // and the operands of k step 0 of stage s sit in afr[0] / bfr[0].
+    // the B operands of its k step 0 sit in bfr[0], the words of its k step 1 in words[1], and its first RING_A - 1 A
+    // operands are on their way.
     int ring = 0;  // s % NBUF
     for (int s = 0; s < stages; ++s) {
         const int ring_next = ring + 1 == NBUF ? 0 : ring + 1;
@@ -721,37 +773,9 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
                 if (m * PIECES_PER_SLOT + q < LOADS_PER_STAGE)
                     issue_piece(m * PIECES_PER_SLOT + q, ring_free);
         };
-        auto fetch_next_weights = [&](int m) {
-            if (m == SLOTS - 1)
-                read_weights(ring_next, w_nxt, nz_nxt, ss_nxt);
-        };
-        if (KSTEPS == 4) {
-            constexpr int G2 = GROUPS - 1;  // the second half's row where the halves have their own
-            kstep(P0{}, ring, 1, w_cur[1], nz_cur[0], ss_cur[0], issue_loads);
-            kstep(P1{}, ring, 2, w_cur[2 % KSTEPS], nz_cur[G2], ss_cur[G2], nothing);
-            kstep(P0{}, ring, 3, w_cur[3 % KSTEPS], nz_cur[G2], ss_cur[G2], fetch_next_weights);
-            kstep(P1{}, ring_next, 0, w_nxt[0], nz_nxt[0], ss_nxt[0], nothing);
-        } else {
-            auto both = [&](int m) {
-                issue_loads(m);
-                fetch_next_weights(m);
-            };
-            kstep(P0{}, ring, 1, w_cur[1], nz_cur[0], ss_cur[0], both);
-            kstep(P1{}, ring_next, 0, w_nxt[0], nz_nxt[0], ss_nxt[0], nothing);
-        }
+        kstep(Step0{}, ring, ring_next, issue_loads);
+        kstep(Step1{}, ring, ring_next, nothing);
         advance_load_stage();
-#pragma unroll
-        for (int kk = 0; kk < KSTEPS; ++kk)
-#pragma unroll
-            for (int t = 0; t < TN; ++t)
-                w_cur[kk][t] = w_nxt[kk][t];
-#pragma unroll
-        for (int g = 0; g < GROUPS; ++g)
-#pragma unroll
-            for (int t = 0; t < TN; ++t) {
-                nz_cur[g][t] = nz_nxt[g][t];
-                ss_cur[g][t] = ss_nxt[g][t];
-            }
         publish();  // stage s+2 has landed; everyone is done with stage s
         if (HALF && s + 2 == tail_stage)
             clear_repeated_half(ring_next + 1 == NBUF ? 0 : ring_next + 1);
@@ -763,10 +787,16 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     // issued for the stage after the last one, whose destination registers stay reserved until here (named as
     // in/outs after the wait: the compiler knows nothing of the inline-asm reads in flight and could otherwise
     // reuse the registers of these dead values while a read is still due to land in them)
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_nop 15" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-        asm volatile("" : "+v"(afr[0][i]), "+v"(afr[1][i]));
+    for (int q = 0; q < RING_A; ++q)
+        asm volatile("" : "+v"(afr[q]));
+    asm volatile("" : "+v"(words[0]), "+v"(words[1]), "+v"(raw_s), "+v"(raw_z));
+    if constexpr (TM * TN == 64)  // (no sum is read before the wait states that end the asm above)
+        static_for<0, TM * TN>([&](auto n) {
+            float4_t &c = acc[decltype(n)::value / TN][decltype(n)::value % TN];
+            asm volatile("" : "+a"(c));
+        });
 
     if (SERIAL) {
         if (group + 1 < groups) {
@@ -802,43 +832,34 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     if (KW > 1) {
         // the second group's sums go to the first through LDS (the rings are done with: every DMA has landed),
         // four values per access, [value / 4][thread]
-        static_assert(KW == 1 || TM * TN * 16 * kThreads * 4 <= KW * NBUF * L::BYTES, "the sums fit the rings");
+        static_assert(KW == 1 || TM * TN * 4 * kThreads * 4 <= KW * NBUF * L::BYTES, "the sums fit the rings");
         __syncthreads();
         float4_t *sums = reinterpret_cast<float4_t *>(smem_all) + tid;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int t = 0; t < TN; ++t)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (kgroup == 1)
-                        sums[((i * TN + t) * 4 + q) * kThreads] = float4_t{acc[i][t][4 * q], acc[i][t][4 * q + 1],
-                                                                          acc[i][t][4 * q + 2], acc[i][t][4 * q + 3]};
+                if (kgroup == 1)
+                    sums[(i * TN + t) * kThreads] = acc[i][t];
         __syncthreads();
         if (kgroup == 0) {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4_t v = sums[((i * TN + t) * 4 + q) * kThreads];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            acc[i][t][4 * q + r] += v[r];
-                    }
+                    acc[i][t] += sums[(i * TN + t) * kThreads];
         }
     }
     if (!SERIAL && a.split_k > 1) {
-        constexpr int ACC = TM * TN * 16;
+        constexpr int ACC = TM * TN * 4;
         float flat[ACC];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int t = 0; t < TN; ++t)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    flat[(i * TN + t) * 16 + r] = acc[i][t][r];
+                for (int r = 0; r < 4; ++r)
+                    flat[(i * TN + t) * 4 + r] = acc[i][t][r];
         if (!combine_slices<ACC>(flat, a, slice, tile_id, tid, kgroup == 0))
             return;
 #pragma unroll
@@ -846,11 +867,11 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
 #pragma unroll
             for (int t = 0; t < TN; ++t)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    acc[i][t][r] = flat[(i * TN + t) * 16 + r];
+                for (int r = 0; r < 4; ++r)
+                    acc[i][t][r] = flat[(i * TN + t) * 4 + r];
     }
     if (kgroup == 0)
-        store_tile<TM, TN>(acc, a.out, m0 + wm * WAVE_M, col_raw, col_ok, kh, M, N);
+        store_blocks<TM, TN>(acc, a.out, m0 + wm * WAVE_M, col_raw, col_ok, kg, M, N);
 }
 
 // =====================================================================================================

@@ -21,6 +21,7 @@
 // The arithmetic is skinny_kernel's: B operand = exact q - z, scaled per group in fp32.
 #pragma once
 
+#include "lds_dma.h"
 #include "skinny_kernel.h"
 
 namespace gptq {
@@ -28,30 +29,6 @@ namespace skinny {
 
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-// One DMA instruction: lane l's 16 (or 4) bytes land at lds + 16 l (4 l).  The compiler does not know that LDS changes;
-// the memory clobbers here and at the waits keep its LDS reads where they stand.  Nor does it know of m0, a reserved register
-// that a clobber list may not name: nothing else in this kernel may use it (no LDS-DMA builtin beside these), which a check
-// of the compiled code sees to.
-template <bool STREAM>
-__device__ __forceinline__ void dma_16(uint32_t lds, uint32_t byte_off, const char *base)
-{
-    if (STREAM)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(byte_off), "s"(base)
-                     : "memory");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(byte_off), "s"(base)
-                     : "memory");
-}
-__device__ __forceinline__ void dma_4(uint32_t lds, const char *src)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(src) : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 
 constexpr int kStageK = 64;  // k per ring slot: two MFMA steps
 constexpr int kUnitStages = kUnitK / kStageK;
@@ -181,7 +158,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
         }
 #pragma unroll
         for (int q = 0; q < LX; ++q)
-            dma_16<false>(put + Slot::W_BYTES + q * 1024, off_x[q], x_next);
+            dma_16(put + Slot::W_BYTES + q * 1024, off_x[q], x_next);
         w_next += w_step;
         x_next += kStageK * 2;
         put += Slot::BYTES;

@@ -155,6 +155,50 @@ def test_big_tile_kernel_leaves_registers_of_pending_lds_reads_alone(asm_files):
     assert seen >= 4
 
 
+def check_mfma_wait_states(lines, what, valu_to_mfma=2, mfma_to_other=11):
+    """MFMAs in inline assembly are unknown to the compiler's hazard checks: a vector instruction's result needs two wait
+    states before an MFMA reads it, a sum of four passes eleven before anything but an MFMA touches it."""
+    problems = []
+    written, summed, now = {}, {}, 0
+    for trip in range(2):
+        for t in lines:
+            if t.startswith(";;#"):
+                continue
+            op, _, rest = t.partition(" ")
+            sums = {int(r) for m in re.finditer(r"\ba\[(\d+):(\d+)\]", rest) for r in range(int(m.group(1)), int(m.group(2)) + 1)}
+            sums |= {int(m) for m in re.findall(r"\ba(\d+)\b", rest)}
+            if op.startswith("v_mfma"):
+                problems += [f"{what}: '{t}' {now - written[r]} after the write of v{r}"
+                             for r in vregs(rest) if now - written.get(r, -99) <= valu_to_mfma]
+                summed.update({r: now for r in sums})
+            else:
+                problems += [f"{what}: '{t}' {now - summed[r]} after the MFMA of a{r}"
+                             for r in sums if now - summed.get(r, -99) <= mfma_to_other]
+                if op.startswith("v_"):
+                    written.update({r: now for r in vregs(rest.split(",")[0])})
+            now += int(rest) + 1 if op == "s_nop" else 1
+    return problems
+
+
+def test_big_tile_kernel_leaves_wait_states_around_its_mfmas(asm_files):
+    seen = 0
+    for path in asm_files["prefill"]:
+        for name, lines in kernels(path).items():
+            if "prefill_pipelined_kernelILi256ELi256" in name:
+                seen += 1
+                assert sum(t.startswith("v_mfma") and " a[" in t for t in lines) >= 128
+                problems = check_mfma_wait_states(lines, name)
+                assert not problems, "\n".join(problems[:10])
+    assert seen == 2
+
+
+def test_the_wait_state_checker_flags_what_it_should():
+    mfma = "v_mfma_f32_16x16x32_f16 a[0:3], v[4:7], v[8:11], a[0:3]"
+    assert check_mfma_wait_states(["v_perm_b32 v9, v1, v2, v3", "s_nop 1", mfma, "s_nop 15", "v_accvgpr_read_b32 v1, a2"], "good") == []
+    assert len(check_mfma_wait_states(["v_perm_b32 v9, v1, v2, v3", mfma, "s_nop 15"], "early operand")) >= 1
+    assert len(check_mfma_wait_states([mfma, "s_nop 3", "v_accvgpr_read_b32 v1, a2", "s_nop 15"], "early result")) >= 1
+
+
 def test_ring_kernel_refills_a_slot_only_after_its_reads(asm_files):
     """A turn of the loop lets DMA into the slot that the turn before has read, scales and zero points included.  (None of
     its loads in inline assembly has a destination register: there are none in flight to leave alone.)"""
@@ -170,11 +214,12 @@ def test_ring_kernel_refills_a_slot_only_after_its_reads(asm_files):
     assert seen >= 150
 
 
-def test_ring_kernel_has_m0_to_itself(asm_files):
+@pytest.mark.parametrize("files, kernel", [("ring", "ring_kernel"), ("prefill", "prefill_pipelined_kernel")])
+def test_kernels_with_inline_dma_have_m0_to_themselves(asm_files, files, kernel):
     """The DMA's LDS address goes through m0, in inline assembly that cannot tell the compiler so: it may not use m0 itself."""
-    for path in asm_files["ring"]:
+    for path in asm_files[files]:
         for name, lines in kernels(path).items():
-            if "ring_kernel" not in name:
+            if kernel not in name:
                 continue
             in_asm = False
             for t in lines:
