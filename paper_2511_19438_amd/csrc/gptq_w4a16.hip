@@ -228,6 +228,29 @@ bool mid_batch_by_default(const Problem &p)
     return tiles64 <= 256 && (tiles64 >= 128 || p.K >= 8192);
 }
 
+// Whether the small-batch kernel on its ring of LDS slots, which has overtaken the mid-batch kernel on small batches, runs in
+// its place, with widths and slices of its own unless a plan says kernel 4.
+bool ring_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
+{
+    if (!ring_supported(p))
+        return false;
+    // Up to 32 rows: 170 random layers at 17-32 rows 1-35 % faster, 2 % slower on one; 4096x22016 at M = 32 19.6 us -> 15.7,
+    // 28672x8192 40.5 -> 34.1.
+    if (p.M <= 32)
+        return true;
+    // 33-48 rows: 145 random layers 1.31 times as fast on average, 4-7 % slower on four (shallow ones and 11904x2104).
+    // (A plan that names kernel 4 gets the ring with a width that automatic plans have there, else the mid-batch kernel.)
+    if (plan && plan->kernel == 4)
+        return ring_width(p, plan->tile, plan->split_k);
+    if (p.M <= kRingWideMaxM)
+        return true;
+    // 49-64 rows, in 32 columns: ahead on every layer of one round of workgroups up to this depth and on narrow ones of any
+    // (100 random layers: 5-79 %, K 2048-4096 30 % and more; 5632x7552 at M = 64 17.6 us -> 16.7, 13312x1280 at M = 56
+    // 16.1 -> 11.2), level or behind on deeper ones (6144x4576 14.4, 15.8; 8960x4864 17.2, 21.3) and with more tiles
+    // (1792x8832 7.8, 9.0; 3456x10256 14.8, 19.9).
+    return p.N <= 2048 || (p.N <= 8192 && p.K <= 5632);
+}
+
 // Act-order as stored: whether the lookup variant (64x64 tiles, each with its own table) is the better one against the
 // kernels without it.  It is everywhere but where a shallow K leaves many tiles little to do, against the big-tile kernel's
 // general path: 256x256x4096 9 us against 20, 512x256x4096 15, 20, but 1024x256x4096 26, 21 and 2048x256x40960 458, 272;
@@ -304,16 +327,15 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
         r.mid.cols_per_wg = plan ? plan->tile : 0;
         r.mid.split_k = plan ? plan->split_k : 0;
         mid_make_plan(p, r.mid);
-        // Up to 32 rows the small-batch kernel on its ring of LDS slots has overtaken the mid-batch kernel and runs in its
-        // place (170 random layers at 17-32 rows: 1-35 % faster, 2 % slower on one; 4096x22016 at M = 32 19.6 us -> 15.7,
-        // 28672x8192 40.5 -> 34.1), with widths and slices of its own unless a plan says kernel 4.
-        if (ring_supported(p)) {
+        if (ring_in_place_of_mid(p, plan)) {
             r.ring = true;
             if (plan && plan->kernel == 4) {
                 r.skinny.cols_per_wg = ring_width(p, plan->tile, r.mid.split_k) ? plan->tile : r.mid.cols_per_wg;
                 // (slices of the mid-batch kernel's own choice are made for its own widths)
                 r.skinny.split_k = plan->split_k > 0 || r.skinny.cols_per_wg == r.mid.cols_per_wg ? r.mid.split_k : 0;
             }
+            if (p.M > kRingWideMaxM)
+                r.skinny.cols_per_wg = 32;
             skinny_make_plan(p, r.skinny);
         }
     } else {

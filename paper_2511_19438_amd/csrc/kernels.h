@@ -96,10 +96,13 @@ struct SkinnyPlan {
     bool serial;          // every workgroup walks all slices one after the other: no scratch, the same bits
 };
 bool skinny_supported(const Problem &p);
-// Whether the problem has the variant on a ring of LDS slots: 32 rows at most, K a multiple of 128.
+// Whether the problem has the variant on a ring of LDS slots: K a multiple of 128; up to 32 rows all groups of the
+// small-batch kernel, up to 64 those of 64 and more.
+constexpr int kRingMaxM = 64;
+constexpr int kRingWideMaxM = 48;  // beyond: 32 columns alone
 bool ring_supported(const Problem &p);
-// Whether a workgroup of that variant may own `cols` columns: the widths that it exists in, and with K slices those that
-// leave every column tile an arrival counter.
+// Whether a workgroup of that variant may own `cols` columns: the widths that it exists in at the problem's rows, and with K
+// slices those that leave every column tile an arrival counter.
 bool ring_width(const Problem &p, int cols, int split_k);
 void skinny_make_plan(const Problem &p, SkinnyPlan &plan);
 // Whether the plan has a form without scratch for its K slices, plan.serial.

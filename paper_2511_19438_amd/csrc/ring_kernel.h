@@ -1,4 +1,4 @@
-// Small-batch MFMA kernel on a ring of LDS slots (2 <= M <= 32, no g_idx, K a multiple of 128), gfx950.
+// Small-batch MFMA kernel on a ring of LDS slots (2 <= M <= 48, on narrow layers 64; no g_idx, K a multiple of 128), gfx950.
 //
 // A layer of 4-25 MB takes 3-6 us to read, launch included; what a small batch costs above that is the price of everything
 // around the packed words.  Measured on the variant that loads both operands straight into registers (skinny_kernel.h,
@@ -19,6 +19,13 @@
 //   * The ring is short (two or three stages).  Longer ones measured slower at every size (4096x4096, M = 8, 32
 //     columns: three stages 5.3 us, four 5.5, five 5.7, six 6.0).
 // The arithmetic is skinny_kernel's: B operand = exact q - z, scaled per group in fp32.
+//
+// 33-48 rows: a third row block.  The mid-batch kernel, which served them, pads to 64 rows with one wavefront per SIMD; here
+// two share it, and nothing but the rows' own activations is loaded or multiplied.  us at M = 40, mid-batch -> ring:
+// 4096x12288 14.0 -> 12.7, 4096x4096 10.6 -> 7.4, 4096x22016 21.9 -> 17.2, 11008x4096 15.8 -> 14.2, 8192x10240 22.9 -> 20.0,
+// 8192x8192 19.0 -> 16.9, 8192x57344 86.9 -> 76.4, 28672x8192 46.4 -> 40.8.  128 columns do not fit 256 registers then.  A
+// fourth block (49-64 rows) leaves room in the LDS for eight wavefronts of 32 columns only and pays where those are one
+// unsplit round (4096x4096 at M = 64: 12.0 -> 9.3); in 64 columns it was level with the mid-batch kernel or behind it.
 #pragma once
 
 #include "lds_dma.h"
@@ -53,13 +60,13 @@ struct RingSlot {
 // finds room for the same loop in 188 and 234 (8192x57344, groups of 32, 128 columns, M = 24: 106.5 us -> 72.7).
 // SERIAL: no scratch for the K slices.  A workgroup walks all slices of its tile one after the other and adds their sums
 // in registers, in slice order: the bits of the sliced launch, whose tile may be any (an output's sum does not depend on
-// it).  For 64 columns and eight wavefronts only.
+// it).  For eight wavefronts of 64 columns, or 32 where the rows have no other width (kSerialCols).
 template <int TM, int LX, int NF, int NH, int WAVES, int GPU, int DEPTH, bool STREAM,
           bool SERIAL = false>
 __global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
 {
     static_assert(DEPTH == 2 || DEPTH == 3, "the waits below");
-    static_assert(!SERIAL || (WAVES == 8 && NF == 1 && NH == 0), "a thread keeps one quad of the tile");
+    static_assert(!SERIAL || (WAVES == 8 && NF + NH == 1), "one serial width, see there");
     constexpr int kThreads = 64 * WAVES;
     constexpr int ROWS = 16 * TM;
     constexpr int NT = 4 * NF + 2 * NH;
@@ -71,6 +78,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
     constexpr int LOADS0 = LW + LX + LS, LOADS1 = LW + LX + (GPU > 1 ? LS : 0);
     constexpr int XROWS = 8 * LX;
     constexpr int QUADS = COLS / 4;
+    constexpr int PER_THREAD = (ROWS * QUADS + kThreads - 1) / kThreads;  // quads of the tile that a thread adds up
     static_assert(XROWS <= ROWS && XROWS > ROWS - 16, "every row block has rows of its own");
 
     extern __shared__ __align__(16) unsigned char smem[];
@@ -87,7 +95,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
         tile -= slice * a.tiles_n;
     }
     const int N = a.N;
-    float4_t total = {0.f, 0.f, 0.f, 0.f};  // SERIAL: quad tid of the tile, over the slices so far
+    float4_t total[SERIAL ? PER_THREAD : 1];  // SERIAL: the thread's quads of the tile, over the slices so far
+#pragma unroll
+    for (float4_t &t : total)
+        t = float4_t{0.f, 0.f, 0.f, 0.f};
     for (;;) {  // (a single pass unless SERIAL; the body, up to the sums over the wavefronts, is not indented)
     const int u0 = slice * a.units_per_slice;
     const int u1 = min(u0 + a.units_per_slice, a.total_units);
@@ -319,7 +330,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
                 *reinterpret_cast<f32x2_t *>(row + NF * kCols + 2 * cq) = f32x2_t{acc[i][4 * NF][r], acc[i][4 * NF + 1][r]};
         }
     __syncthreads();
-    for (int e = tid; e < a.M * QUADS; e += kThreads) {
+    auto add_up = [&](int e, float4_t &sum) {
         const int m = e / QUADS;
         const int col = (e - m * QUADS) * 4;
         const int n = tile * COLS + col;
@@ -328,11 +339,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
         for (int w = 1; w < WAVES; ++w)
             s += *reinterpret_cast<const float4_t *>(red + ((size_t)w * ROWS + m) * COLS + col);
         if (SERIAL) {
-            total += s;
-            s = total;
+            sum += s;
+            s = sum;
         }
         if (n >= N || (SERIAL && slice + 1 < a.serial_slices))
-            continue;
+            return;
         if (a.split_k == 1) {
             *reinterpret_cast<half4_t *>(a.out + (size_t)m * N + n) =
                 half4_t{(half_t)s[0], (half_t)s[1], (half_t)s[2], (half_t)s[3]};
@@ -352,6 +363,15 @@ __global__ __launch_bounds__(64 * WAVES, 2) void ring_kernel(const Args a)
             __hip_atomic_store(dst + 1, __builtin_bit_cast(unsigned long long, f32x2_t{s[2], s[3]}), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
+    };
+    if constexpr (SERIAL) {
+#pragma unroll
+        for (int j = 0; j < PER_THREAD; ++j)
+            if (tid + j * kThreads < a.M * QUADS)
+                add_up(tid + j * kThreads, total[j]);
+    } else {
+        for (int e = tid; e < a.M * QUADS; e += kThreads)
+            add_up(e, total[0]);
     }
 
     if (!SERIAL || ++slice >= a.serial_slices)

@@ -212,13 +212,23 @@ bool skinny_supported(const Problem &p)
 
 bool ring_supported(const Problem &p)
 {
-    return skinny_supported(p) && p.M <= 32 && p.K % skinny::kUnitK == 0;
+    if (p.K % skinny::kUnitK != 0)
+        return false;
+    if (p.M > 32 && p.M <= kRingMaxM && p.group_size == 64) {  // (from there on under the mid-batch kernel's id alone)
+        Problem few = p;
+        few.M = 32;
+        return skinny_supported(few);
+    }
+    return skinny_supported(p) && p.M <= kRingMaxM;
 }
 
 bool ring_width(const Problem &p, int cols, int split_k)
 {
+    if (p.M > kRingWideMaxM && cols != 32)
+        return false;
     // (skinny_supported leaves widths of 64 and more a counter for every tile; 32 columns have one up to N = 2097152)
-    return (cols == 32 || cols == 64 || cols == 96 || cols == 128) && (split_k <= 1 || ceil_div(p.N, cols) <= kMaxColumnTiles);
+    return (cols == 32 || cols == 64 || cols == 96 || (cols == 128 && p.M <= 32)) &&
+           (split_k <= 1 || ceil_div(p.N, cols) <= kMaxColumnTiles);
 }
 
 namespace {
@@ -236,11 +246,12 @@ size_t ring_slot_bytes(const Problem &p)
 // Checked, and that price set, on 33 k more plans of 590 layers with groups of 32, 64 and 128: the plan that it picks is
 // 0.7 % behind the best one (0.97 % without the price, at worst 24: 9472x1792 at M = 2 in ten slices of 96 columns 8.5 us, in
 // two of 32 7.3).  Factors on the units of groups of 64 and 32, 1.1 and 1.2, changed that by less than 0.1 % and are left out.
+// 33-64 rows: the units alone, on 1100 plans of 245 layers with groups of 64 and 128.
 float ring_estimate(const Problem &p, int cols, int split, int units_per_slice)
 {
-    static const float unit[4][4] = {{0.57f, 0.65f, 0.85f, 0.95f}, {0.90f, 0.92f, 1.20f, 1.24f},
-                                     {1.27f, 1.29f, 1.72f, 1.80f}, {1.65f, 1.65f, 2.21f, 2.23f}};
-    const int rows = p.M <= 8 ? 0 : p.M <= 16 ? 1 : p.M <= 24 ? 2 : 3;
+    static const float unit[4][8] = {{0.57f, 0.65f, 0.85f, 0.95f, 1.18f, 1.39f, 1.43f, 1.59f}, {0.90f, 0.92f, 1.20f, 1.24f, 1.71f, 1.93f},
+                                     {1.27f, 1.29f, 1.72f, 1.80f, 2.34f, 2.64f}, {1.65f, 1.65f, 2.21f, 2.23f, 0.f, 0.f}};
+    const int rows = p.M <= 48 ? (p.M - 1) / 8 : p.M <= 56 ? 6 : 7;
     const int tiles = ceil_div(p.N, cols);
     const int waves = skinny::ring_waves(tiles * split);
     const float rounds = (float)ceil_div(tiles * split, 256);
@@ -303,10 +314,11 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
     // 44.8 us, 38.1 and 49.0, 39.3; 8192x131072 104, 106 and 126, 107; 96 columns: 4096x66560 30.9, 27.3 and 38.7, 30.5; behind
     // on 4096x131072 at M = 2 56.6, 62.4 and 1024x196608 at M = 16 23.4, 24.6): what gemm_static refuses for its partial sums
     // stays refused.  Up to 65536 columns the ring (8192x57344: M = 16 53 us, 48; level at two to four rows).
+    const bool ring = ring_supported(p) && (!any_width || p.M <= kRingWideMaxM);
     const bool wide = p.group_size >= skinny::kUnitK &&
                       (asked == 256 ||
-                       (any_width && (rows > 32 ? ceil_div(p.N, 256) >= 192 : rows == 16 && p.N > 65536)));
-    if (ring_supported(p) && !wide) {
+                       (any_width && (rows > 32 ? !ring && ceil_div(p.N, 256) >= 192 : rows == 16 && p.N > 65536)));
+    if (ring && !wide) {
         if (any_width)
             plan.cols_per_wg = 0;
         ring_make_plan(p, plan);
@@ -365,7 +377,7 @@ void skinny_make_plan(const Problem &p, SkinnyPlan &plan)
 
 bool skinny_scratch_optional(const Problem &p, const SkinnyPlan &plan)
 {
-    return plan.cols_per_wg != 256 && p.M <= 32;
+    return plan.cols_per_wg != 256 && (p.M <= 32 || (ring_supported(p) && ring_width(p, plan.cols_per_wg, plan.split_k)));
 }
 
 size_t skinny_workspace_bytes(const Problem &p, const SkinnyPlan &plan)
@@ -382,6 +394,7 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
 {
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const int wn = plan.cols_per_wg / skinny::kCols;
+    const bool ring = ring_supported(p) && ring_width(p, plan.cols_per_wg, plan.split_k);
     for (int m0 = 0; m0 < p.M; m0 += kRowsPerLaunch) {
         skinny::Args a;
         a.x = p.x + (size_t)m0 * p.K;
@@ -414,11 +427,11 @@ hipError_t launch_skinny(const Problem &p, const SkinnyPlan &plan, void *workspa
         const int gpu = p.group_size >= skinny::kUnitK ? 1 : skinny::kUnitK / p.group_size;
         const bool tail = p.K % skinny::kUnitK != 0;
         hipError_t err;
-        if (wn != 4 && tm <= 2 && !tail) {
-            if (plan.serial && plan.split_k > 1) {  // (64 columns whatever the sliced plan has)
+        if (ring || (wn != 4 && tm <= 2 && !tail)) {  // (or the rest of a batch of more than 64 rows)
+            if (plan.serial && plan.split_k > 1) {  // (columns of its own whatever the sliced plan has)
                 a.serial_slices = plan.split_k;
                 a.split_k = 1;
-                a.tiles_n = ceil_div(p.N, skinny::kCols);
+                a.tiles_n = ceil_div(p.N, a.M > kRingWideMaxM ? 32 : skinny::kCols);
             } else if (plan.split_k == 2 && ring_slot_bytes(p) <= kSlotBytes) {
                 a.slots = static_cast<unsigned long long *>(slots);
             }

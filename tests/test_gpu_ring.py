@@ -40,6 +40,32 @@ def test_edges(B, tile, M, K, N, group, split_k):
     check(B, M, K, N, group, plan)
 
 
+# three row blocks in every width that they have, four in 32 columns: rows on both sides of every change of the loads
+@pytest.mark.parametrize("M,K,N,group,split_k,tiles", [
+    (33, 128, 8, 128, 1, (32, 64, 96)), (40, 1152, 328, 384, 2, (32, 64, 96)), (41, 2176, 104, 128, 3, (32, 64, 96)),
+    (48, 1280, 264, 128, 1, (32, 64, 96)), (49, 1152, 136, 128, 2, (32,)), (56, 1280, 72, 256, 1, (32,)), (57, 2176, 104, 128, 3, (32,)),
+    (64, 1024, 328, 128, 1, (32,))])
+def test_more_than_two_row_blocks(B, M, K, N, group, split_k, tiles):
+    for tile in tiles:
+        plan = B.Plan(kernel=3, tile=tile, split_k=split_k)
+        resolved = B.gptq_w4a16_plan_query(M, K, N, group, False, plan)
+        assert (resolved.kernel, resolved.tile, resolved.split_k) == (3, tile, split_k)
+        check(B, M, K, N, group, plan)
+
+
+# in the mid-batch kernel's place, with the slices in parallel or without scratch for them
+@pytest.mark.parametrize("M,K,N,group,sliced", [(33, 4096, 1032, 64, True), (40, 11008, 520, 128, True), (48, 8192, 264, 64, True),
+                                                (48, 640, 257 * 96 + 8, 128, False), (56, 5120, 520, 64, True), (64, 8192, 264, 128, True),
+                                                (49, 640, 8192, 128, False)])
+def test_up_to_64_rows_under_the_mid_batch_kernels_id(B, M, K, N, group, sliced):
+    resolved = B.gptq_w4a16_plan_query(M, K, N, group)
+    assert resolved.kernel == 4 and (resolved.split_k > 1) == sliced and resolved.tile <= (96 if M <= 48 else 32)
+    case, got = check(B, M, K, N, group, None)
+    assert np.array_equal(bits(run_gemm(B, case, group, resolved)), bits(got))
+    with workspace(B, COUNTERS):
+        assert np.array_equal(bits(run_gemm(B, case, group)), bits(got))
+
+
 # more workgroups than compute units: four wavefronts each
 @pytest.mark.parametrize("M,tile,group", [(3, 32, 128), (12, 32, 32), (20, 32, 128), (32, 32, 64), (8, 64, 128), (32, 64, 128)])
 def test_four_wavefronts(B, M, tile, group):
