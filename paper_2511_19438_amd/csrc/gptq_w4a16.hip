@@ -251,6 +251,24 @@ bool ring_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
     return p.N <= 2048 || (p.N <= 8192 && p.K <= 5632);
 }
 
+// Whether the big-tile kernel, which has overtaken the mid-batch kernel beyond 64 rows on most layers since its workgroups may
+// have 80, 96 and 112 rows, runs in its place: a plan under the mid-batch kernel's id with a tile of the other's.  Mid-batch
+// against big-tile on 150 layers that mid_batch_by_default names: mid-batch ahead on shallow ones with a round of unsplit
+// workgroups (80x2176x8320 10.7 us, 13.8; 96x4096x12288 19.2, 20.8; but 104x1792x14912 13.9, 13.0 and 65x4992x8832 20.5, 18.7)
+// and, by 1 % on average, up to 80 rows on narrow ones in slices (72x25984x1984 23.1, 26.4; 80x28544x3520 35.8, 33.0); behind
+// by 5-60 % elsewhere (77x8192x10240 30.1, 25.6; 100x28672x8192 72, 60; 112x11008x4096 26.2, 22.7; 128x8192x8192 32.4, 27.9).
+bool big_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
+{
+    if (p.M <= 64 || !prefill_pipelined(p))
+        return false;
+    if (plan && plan->kernel == 4)
+        return plan->tile == 3 || plan->tile == 5 || plan->tile == 8;
+    const int tiles64 = (p.N + 63) / 64;
+    if (tiles64 > 128 && p.K <= 4736 && p.M <= 96)
+        return false;
+    return !(tiles64 <= 64 && tiles64 > 16 && p.M <= 80);
+}
+
 // Act-order as stored: whether the lookup variant (64x64 tiles, each with its own table) is the better one against the
 // kernels without it.  It is everywhere but where a shallow K leaves many tiles little to do, against the big-tile kernel's
 // general path: 256x256x4096 9 us against 20, 512x256x4096 15, 20, but 1024x256x4096 26, 21 and 2048x256x40960 458, 272;
@@ -268,6 +286,7 @@ struct Resolved {
     int kernel;  // 1 vector, 2 big-tile MFMA, 3 small-batch MFMA, 4 mid-batch streaming MFMA
     bool act;    // the act-order lookup variant of the small-batch kernel (plan in `skinny`) runs in its place
     bool ring;   // the small-batch kernel (plan in `skinny`) runs in the mid-batch kernel's place
+    bool big;    // the big-tile kernel (plan in `prefill`) does
     DecodePlan decode;
     SkinnyPlan skinny;
     MidPlan mid;
@@ -337,6 +356,11 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
             if (p.M > kRingWideMaxM)
                 r.skinny.cols_per_wg = 32;
             skinny_make_plan(p, r.skinny);
+        } else if (big_in_place_of_mid(p, plan)) {
+            r.big = true;
+            r.prefill.tile = plan ? plan->tile : 0;
+            r.prefill.split_k = plan ? plan->split_k : 0;
+            prefill_make_plan(p, r.prefill);
         }
     } else {
         r.prefill.tile = plan ? plan->tile : 0;
@@ -355,7 +379,7 @@ size_t scratch_bytes(const Problem &p, const Resolved &r)
         bytes = decode_workspace_bytes(p, r.decode);
     else if (r.kernel == 3 || r.ring)
         bytes = skinny_workspace_bytes(p, r.skinny);
-    else if (r.kernel == 4)
+    else if (r.kernel == 4 && !r.big)
         bytes = mid_workspace_bytes(p, r.mid);
     else
         bytes = prefill_workspace_bytes(p, r.prefill);  // 0 unless K is split
@@ -372,7 +396,7 @@ int launch_resolved(const Problem &p, const Resolved &r, const Scratch &scratch,
         err = launch_decode(p, r.decode, ws, stream);
     else if (r.kernel == 3 || r.ring)
         err = launch_skinny(p, r.skinny, ws, scratch.slots, stream);
-    else if (r.kernel == 4)
+    else if (r.kernel == 4 && !r.big)
         err = launch_mid(p, r.mid, ws, stream);
     else
         err = launch_prefill(p, r.prefill, ws, stream);
@@ -401,7 +425,7 @@ bool fall_back(const Problem &p, const gptq_w4a16_plan_t *request, Resolved &r)
         return false;
     if (r.act || ((r.kernel == 3 || r.ring) && skinny_scratch_optional(p, r.skinny)))
         r.skinny.serial = true;
-    else if (r.kernel == 2 && r.prefill.split_k > 1)
+    else if ((r.kernel == 2 || r.big) && r.prefill.split_k > 1)
         r.prefill.serial = true;
     else
         return false;
@@ -560,7 +584,7 @@ int gptq_w4a16_plan_query(int M, int K, int N, int group_size, int act_order, co
     } else if (r.kernel == 3 || r.ring) {
         out.split_k = r.skinny.split_k;
         out.tile = r.skinny.cols_per_wg;
-    } else if (r.kernel == 4) {
+    } else if (r.kernel == 4 && !r.big) {
         out.split_k = r.mid.split_k;
         out.tile = r.mid.cols_per_wg;
     } else {

@@ -134,7 +134,7 @@ hipError_t launch_mid(const Problem &p, const MidPlan &plan, void *workspace, hi
 struct PrefillPlan {
     int tile;     // tile configuration id (1-based), 0 = auto
     int split_k;  // K slices (pipelined kernel only), 0 = auto
-    int rows;     // filled in: rows of tile 8's workgroups, 96 or 128
+    int rows;     // filled in: rows of a workgroup
     bool serial;  // every workgroup walks all slices one after the other: no scratch, the same bits (tile 5 in any case)
 };
 bool prefill_supported(const Problem &p);

@@ -14,6 +14,11 @@ template <> hipError_t launch_tile<3>(const Args &, int, int, hipStream_t);
 template <> hipError_t launch_tile<5>(const Args &, int, int, hipStream_t);
 template <> hipError_t launch_tile<8>(const Args &, int, int, hipStream_t);
 template <> hipError_t launch_tile<9>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<10>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<11>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<12>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<13>(const Args &, int, int, hipStream_t);
+template <> hipError_t launch_tile<14>(const Args &, int, int, hipStream_t);
 }  // namespace prefill
 
 namespace {
@@ -23,8 +28,8 @@ struct TileShape {
     bool may_split;  // K slices pay only where a thread holds few accumulators (the combine moves them all)
 };
 // by tile id (1, 3, 5, 8: see the plan documentation in the public header; the other ids up to 10 belonged to
-// layouts that measurement retired - 2x2 wavefront grids, 32-k stages, a 32-row tile - and are refused; tile 8 runs
-// with 96 rows where that fits the batch better)
+// layouts that measurement retired - 2x2 wavefront grids, 32-k stages, a 32-row tile - and are refused; tiles 5 and 8 run
+// with other rows where those fit the batch better, see row_choice)
 constexpr TileShape kTiles[11] = {{0, 0, false},   {256, 256, false}, {0, 0, false}, {128, 128, true},
                                   {0, 0, false},   {64, 128, true},   {0, 0, false}, {0, 0, false},
                                   {128, 256, true}, {0, 0, false},    {0, 0, false}};
@@ -32,10 +37,28 @@ constexpr int kNumTiles = 10;
 constexpr int kComputeUnits = 256;
 constexpr size_t kCounterBytes = 256 * 1024;  // same fixed counter area as the other kernels
 constexpr int kMaxSplit = 32;
+// Rows that the workgroups of tiles 5 and 8 may have; the first is the tile's own.
+constexpr int kRows[2][4] = {{64, 80, 96, 112}, {128, 112, 96, 80}};
 
 int ceil_div_i(int a, int b)
 {
     return (a + b - 1) / b;
+}
+
+// Rows number `i` of a workgroup of tile `t`, 0 if they are not for the problem: another number than the tile's own has to pad
+// the batch less - or, on tile 5, as little, which makes fewer and larger tiles; in the HALF variant from three of 96 rows on -
+// so that the scratch of slices is bounded by that of the tile's own rows.
+// us, the tiles' own rows -> these: M = 77 8192x10240 30.1 -> 25.6 (80x128), 8192x57344 97.0 -> 92.0 (80x256), 28672x8192
+// 61.7 -> 54.2 (80x128); 88x1664x25448 25.0 -> 18.4 (96x128); 100x4096x22016 39.5 -> 30.8 (112x128); 333x2752x6888 with groups
+// of 32 31.9 -> 25.1 (96x128, unsplit; the others in two slices and more); 266x8448x28344 237 -> 179.
+int row_choice(const Problem &p, int t, int i, bool half)
+{
+    const int own = kTiles[t].bm;
+    if (t != 5 && t != 8)
+        return i == 0 ? own : 0;
+    const int rows = kRows[t == 8][i];
+    const int padded = ceil_div_i(p.M, rows) * rows, padded_own = ceil_div_i(p.M, own) * own;
+    return i == 0 || padded < padded_own || (t == 5 && padded == padded_own && (!half || p.M > 192)) ? rows : 0;
 }
 
 // Workgroups of tile 8 (`rows` x 256) with `split` K slices (as many as whole stages make of them).
@@ -63,9 +86,9 @@ int k_groups_of_tile8(const Problem &p, int rows, int split)
 // M = 512 32.9 -> 28.0 us, at M = 100 29.3 -> 24.9 (in four slices of 16 stages 16.1 -> 15.3), 28672x4096 at M = 100
 // 183 -> 138; 128x128 tile, 4096x12288 at M = 256 61.2 -> 43.4, 11008x4096 at M = 512 147 -> 99.  Two groups fill the chip
 // without the partial sums of two slices in scratch: 4096x4096 at M = 256 20.7 us in four slices -> 19.5 in two.
-int k_groups_of_small_tile(const Problem &p, int t, int split)
+int k_groups_of_small_tile(const Problem &p, int t, int rows, int split)
 {
-    const int tiles = ceil_div_i(p.M, kTiles[t].bm) * ceil_div_i(p.N, kTiles[t].bn);
+    const int tiles = ceil_div_i(p.M, rows) * ceil_div_i(p.N, kTiles[t].bn);
     const int stages = ceil_div_i(p.K, 64);
     const int sps = ceil_div_i(stages, split < 1 ? 1 : split);
     return ceil_div_i(tiles, 8) * ceil_div_i(stages, sps) <= kComputeUnits / 8 && sps >= 16 ? 2 : 1;
@@ -73,80 +96,68 @@ int k_groups_of_small_tile(const Problem &p, int t, int split)
 
 int k_groups(const Problem &p, int t, int rows, int split)
 {
-    return t == 8 ? k_groups_of_tile8(p, rows, split) : t == 3 || t == 5 ? k_groups_of_small_tile(p, t, split) : 1;
+    return t == 8 ? k_groups_of_tile8(p, rows, split) : t == 3 || t == 5 ? k_groups_of_small_tile(p, t, rows, split) : 1;
 }
 
-// Estimated duration (microseconds) of the pipelined kernel with tile `t` and `split` K slices.  A workgroup walks its
-// stages at a pace set by instruction issue and latency: alone on a compute unit it leaves most of it idle, and
-// co-resident workgroups slow each other down by less than their number.  What counts is the busiest compute unit of the
-// busiest XCD: a tile's slices share an XCD and the tiles are dealt out in eight equal ranges (tile_of_workgroup), so 50
+// Estimated duration (microseconds) of the pipelined kernel with tile `t`, `rows` rows to a workgroup and `split` K slices.  A
+// workgroup walks its stages at a pace set by instruction issue and latency: alone on a compute unit it leaves most of it
+// idle, and co-resident workgroups slow each other down by less than their number.  What counts is the busiest compute unit of
+// the busiest XCD: a tile's slices share an XCD and the tiles are dealt out in eight equal ranges (tile_of_workgroup), so 50
 // tiles in five slices are 35 workgroups on 32 compute units there, not 250 on 256 (28160x2432 at M = 385: 136 us; 94 in
 // six slices of fewer tiles).  The slices' exchange costs a fixed part, a part per slice that the last arriver of a tile
-// reads, and the traffic of all partial tiles.  Constants: least squares over 3.9 k measured plans of 160 random problems
-// (M 33-1100, K 1024-28672, N 1024-57344; 6-8 % rms), whose picks are 1.4 % behind the best of every problem on
-// average, 25 % at worst (the model before, without the XCDs: 7.7 %, 45 %).
-struct SmallTilePace {
-    double resident[3];  // one stage with that many workgroups on a compute unit
+// reads, and the traffic of all partial tiles.  Constants: least squares over 2.0 k measured plans of 110 random problems (M
+// 65-1100, K 1024-28672, N 1024-57344, a fifth of them with groups of 32; 4-8 % rms), whose picks are 0.6 % behind the best of
+// every problem on average, 10 % at worst.  Tile 1 and the pairs of tile 8, whose pace is that of a full chip under sustained
+// load, keep the ratio that 1.9 k problems of M 129-2048 had given (777x8192x57344 814 -> 744 us, 129x8192x57344 210 -> 187).
+struct Pace {
+    int tile, rows;
+    double resident[3];  // one stage with that many workgroups of one wavefront group on a compute unit
     int most;            // workgroups that fit one
-    double fixed, split, per_slice, tbps, half;  // half: the HALF variant's stages take this much longer
-    // Two wavefront groups: a pair of stages with up to half of the compute units busy, what it takes longer with all of
-    // them, and the sum of the groups' results.  (64x128 tile, 28672x4096 unsplit: 138 us on 64 and 128 units, 166 on 256;
-    // 128x128: 237 and 241 on 32 and 128 units, 1.22-1.28 a pair on 256.)
-    // pair_half: `half` of such stages.  On 277 random problems with groups of 32 (M 65-700, K 1024-16384, N 512-16384) the
-    // plan is 0.71 % behind the best one with 1.22 for both tiles, 0.74 to 0.88 % with 1.18 to 1.32 for the 128x128 tile,
-    // 0.73 to 0.84 % with 1.17 to 1.27 for the other.
-    double pair, pair_full, pair_fixed, pair_half;
+    double fixed;
+    // Two wavefront groups: a pair of stages with up to half of the compute units busy, what it takes longer with all of them.
+    double pair, pair_full, pair_fixed;
+    double split, per_slice, per_mb;
 };
-constexpr SmallTilePace kPace64x128 = {{0.41, 0.635, 0.925}, 3, 5.3, 1.65, 0.48, 6.3, 1.22, 0.59, 0.13, 0.5, 1.22};
-constexpr SmallTilePace kPace128x128 = {{0.825, 1.12, 0.0}, 2, 2.3, 2.55, 1.03, 4.8, 1.18, 1.05, 0.2, 3.0, 1.22};
+constexpr Pace kPaces[] = {
+    {5, 64, {0.385, 0.574, 0.860}, 3, 4.3, 0.567, 0.070, 4.25, 1.0, 0.60, 0.105},
+    {5, 80, {0.414, 0.669, 0.0}, 2, 5.0, 0.664, 0.097, 5.1, 0.2, 0.83, 0.200},
+    {5, 96, {0.412, 0.705, 0.0}, 2, 5.1, 0.698, 0.102, 5.2, 0.2, 0.90, 0.180},
+    {5, 112, {0.397, 0.757, 0.0}, 2, 5.1, 0.761, 0.095, 5.4, 0.5, 0.93, 0.180},
+    {3, 128, {0.580, 1.014, 0.0}, 2, 4.4, 1.019, 0.090, 4.4, 1.1, 1.00, 0.140},
+    {8, 80, {0.650, 1.060, 0.0}, 2, 5.2, 1.057, 0.282, 5.9, 2.1, 1.38, 0.075},
+    {8, 96, {0.800, 1.280, 0.0}, 2, 5.2, 1.162, 0.344, 5.4, 2.4, 1.64, 0.080},
+    {8, 112, {0.840, 1.370, 0.0}, 2, 5.2, 1.229, 0.361, 6.0, 2.5, 1.82, 0.082},
+    {8, 128, {0.920, 1.500, 0.0}, 2, 5.2, 1.267, 0.354, 6.5, 2.4, 1.79, 0.086}};
 
 double estimate_us(const Problem &p, int t, int rows, int split, bool half)
 {
-    const TileShape &ts = kTiles[t];  // (rows: of tile 8, 96 or 128)
-    const int bm = t == 8 ? rows : ts.bm;
-    const int tiles = ceil_div_i(p.M, bm) * ceil_div_i(p.N, ts.bn);
+    const int bn = kTiles[t].bn;
+    const int tiles = ceil_div_i(p.M, rows) * ceil_div_i(p.N, bn);
     const int stages = ceil_div_i(p.K, 64);
     const int sps = ceil_div_i(stages, split);
     const int slices = ceil_div_i(stages, sps);
     const int wgs = tiles * slices;
     const double n = ceil_div_i(tiles, 8) * slices / 32.0;  // workgroups per compute unit of the busiest XCD
-    const double partial_mb = wgs * (double)bm * ts.bn * sizeof(float) / 1e6;
-    if (t == 3 || t == 5) {
-        const SmallTilePace &c = t == 5 ? kPace64x128 : kPace128x128;
-        if (k_groups_of_small_tile(p, t, split) == 2)
-            return c.fixed + c.pair_fixed + ceil_div_i(sps, 2) * (c.pair + c.pair_full * (n > 0.5 ? 2.0 * n - 1.0 : 0.0)) * (half ? c.pair_half : 1.0) +
-                   (slices > 1 ? c.split + slices * c.per_slice + partial_mb / c.tbps : 0.0);
-        const int full = (int)((n - 1e-9) / c.most);  // times that a compute unit is filled up, then the rest
-        const int rest = (int)std::ceil(n - full * c.most - 1e-9);
-        const double stage = full * c.resident[c.most - 1] + (rest > 0 ? c.resident[rest - 1] : 0.0);
-        return c.fixed + sps * stage * (half ? c.half : 1.0) +
-               (slices > 1 ? c.split + slices * c.per_slice + partial_mb / c.tbps : 0.0);
+    if (t == 1)  // one workgroup per compute unit, whole rounds
+        return std::ceil(n - 1e-9) * (sps * 1.30 * (half ? 1.16 : 1.0) + 9.9);
+    // tile 8 in more workgroups than compute units and K slices: the exchange is not worth it
+    if (t == 8 && slices > 1 && wgs > kComputeUnits)
+        return 1e30;
+    const Pace *c = kPaces;
+    while (c->tile != t || c->rows != rows)
+        ++c;
+    const double exchange =
+        slices > 1 ? c->split + slices * c->per_slice + wgs * (double)rows * bn * sizeof(float) / 1e6 * c->per_mb : 0.0;
+    const int groups = k_groups(p, t, rows, split);
+    const double stage_scale = !half ? 1.0 : t == 5 ? (groups == 1 ? 1.25 : 1.22) : t == 3 ? 1.2 : 1.15;  // of the HALF variant
+    if (groups == 2) {
+        const double full = n <= 0.5 ? 0.0 : n >= 1.0 ? 1.0 : 2.0 * n - 1.0;
+        return c->pair_fixed + ceil_div_i(sps, 2) * (c->pair + c->pair_full * full) * stage_scale * (n > 1.0 ? 2.0 : 1.0) + exchange;
     }
-    if (t == 8) {
-        // more workgroups than compute units and K slices: the exchange is not worth it
-        if (slices > 1 && wgs > kComputeUnits)
-            return 1e30;
-        // (96 rows: three quarters of the MFMAs and all of the dequantisation)
-        const double scale = (rows == 96 ? 0.89 : 1.0) * (half ? 1.16 : 1.0);
-        const double exchange =
-            slices > 1 ? 3.2 + slices * (bm * ts.bn * sizeof(float) / 79e3) + partial_mb / 4.9 : 0.0;
-        if (k_groups_of_tile8(p, rows, split) == 2) {
-            // a pair of stages takes 1.4 us with up to 160 workgroups on the chip, 1.75 with one on every compute unit
-            const double on_chip = n * kComputeUnits;
-            const double pace = on_chip <= 160 ? 1.4 : 1.4 + (on_chip - 160) * (0.35 / 96.0);
-            return 5.2 + ceil_div_i(sps, 2) * pace * scale * (n > 1.0 ? 2.0 : 1.0) + exchange;
-        }
-        const int full = (int)((n - 1e-9) / 2.0);  // two workgroups per compute unit, then the rest
-        const double rest = n - 2.0 * full;
-        const double stage = full * 1.6 + (rest > 1.0 + 1e-9 ? 1.6 : rest > 1e-9 ? 0.98 : 0.0);
-        return 5.2 + sps * stage * scale + 1.5 * full + exchange;
-    }
-    // 256x256: one workgroup per compute unit, whole rounds.  The pace is that of a full chip under sustained load: a
-    // stage takes 1.22 us with half of the units busy, 1.38 with one round of all, 1.43-1.55 over several rounds, and the
-    // tile is a candidate where they are busy (1.9 k random problems with M 129-2048, against the fitted 1.286: picks 0.7 %
-    // behind the best tile instead of 1.1, 19 % at worst instead of 34; 777x8192x57344 814 -> 744 us, 129x8192x57344
-    // 210 -> 187, 777x4096x12288 95 -> 87).
-    return std::ceil(n - 1e-9) * (sps * 1.39 * (half ? 1.16 : 1.0) + 9.9);
+    const int full = (int)((n - 1e-9) / c->most);  // times that a compute unit is filled up, then the rest
+    const int rest = (int)std::ceil(n - full * c->most - 1e-9);
+    const double stage = full * c->resident[c->most - 1] + (rest > 0 ? c->resident[rest - 1] : 0.0);
+    return c->fixed + sps * stage * stage_scale + (t == 8 ? 1.5 * full : 0.0) + exchange;
 }
 
 int mode_of(const Problem &p)
@@ -182,7 +193,7 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     if (!prefill_pipelined(p)) {
         plan.tile = 3;  // the general modes exist for one tile shape only, without a K split
         plan.split_k = 1;
-        plan.rows = 0;
+        plan.rows = kTiles[3].bm;
         return;
     }
     const bool tile_given = prefill_tile_exists(plan.tile);
@@ -191,9 +202,7 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     // (combined through scratch in slice order) shorten the walk.  Cheapest (tile, split) by the estimate.
     const bool half = mode_of(p) == prefill::kGroupPerHalf;
     double best = 0.0;
-    int best_tile = 3, best_split = 1, best_rows = 128;
-    // tile 8 with 96 rows is a candidate where it pads the batch less (65-96 rows, 129-192, ...)
-    const bool try96 = ceil_div_i(p.M, 96) * 96 < ceil_div_i(p.M, 128) * 128;
+    int best_tile = 3, best_split = 1, best_rows = kTiles[3].bm;
     const int stages = ceil_div_i(p.K, 64);
     for (int t = 1; t <= kNumTiles; ++t) {
         if (kTiles[t].bm == 0 || (tile_given && t != plan.tile))
@@ -212,7 +221,10 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
             PrefillPlan candidate = {t, slices, 0, false};
             if (!split_given && slices > 1 && prefill_workspace_bytes(p, candidate) > GPTQ_STATIC_SCRATCH_BYTES)
                 continue;
-            for (int rows = 128; rows >= (t == 8 && try96 ? 96 : 128); rows -= 32) {
+            for (int i = 0; i < 4; ++i) {
+                const int rows = row_choice(p, t, i, half);
+                if (rows == 0)
+                    continue;
                 const double us = estimate_us(p, t, rows, split, half);
                 if (best == 0.0 || us < best - 1e-9) {
                     best = us;
@@ -226,7 +238,11 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     if (best == 0.0) {  // a requested split beyond what the loop offers
         best_tile = tile_given ? plan.tile : 3;
         best_split = split_given ? plan.split_k : 1;
-        best_rows = try96 ? 96 : 128;
+        best_rows = kTiles[best_tile].bm;
+        for (int i = 1; i < 4; ++i)
+            if (row_choice(p, best_tile, i, half) > 0 && ceil_div_i(p.M, row_choice(p, best_tile, i, half)) * row_choice(p, best_tile, i, half) <
+                                                       ceil_div_i(p.M, best_rows) * best_rows)
+                best_rows = row_choice(p, best_tile, i, half);
     }
     plan.rows = best_rows;
     plan.tile = best_tile;
@@ -238,7 +254,7 @@ size_t prefill_workspace_bytes(const Problem &p, const PrefillPlan &plan)
     if (plan.split_k <= 1 || plan.serial || !prefill_tile_exists(plan.tile))
         return 0;
     const TileShape &ts = kTiles[plan.tile];
-    // (tile 8 runs with 96 rows only where they cover no more rows in all)
+    // (other rows than the tile's own cover no more in all)
     const size_t tiles = (size_t)ceil_div_i(p.M, ts.bm) * ceil_div_i(p.N, ts.bn);
     return kCounterBytes + (size_t)plan.split_k * tiles * ts.bm * ts.bn * sizeof(float);
 }
@@ -263,7 +279,7 @@ hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *works
     a.serial_kw = 1;
     a.counters = reinterpret_cast<unsigned *>(workspace);
     a.partial = workspace ? reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) + kCounterBytes) : nullptr;
-    if (a.split_k > 1 && (size_t)ceil_div_i(p.M, plan.tile == 8 ? plan.rows : kTiles[plan.tile].bm) *
+    if (a.split_k > 1 && (size_t)ceil_div_i(p.M, plan.rows) *
                                ceil_div_i(p.N, kTiles[plan.tile].bn) >
                              kCounterBytes / sizeof(unsigned))
         a.split_k = 1;  // more tiles than arrival counters: such a problem needs no split anyway
@@ -279,8 +295,16 @@ hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *works
     switch (plan.tile) {
     case 1: return prefill::launch_tile<1>(a, mode, 1, stream);
     case 3: return prefill::launch_tile<3>(a, mode, kw, stream);
-    case 5: return prefill::launch_tile<5>(a, mode, kw, stream);
-    case 8: return plan.rows == 96 ? prefill::launch_tile<9>(a, mode, kw, stream) : prefill::launch_tile<8>(a, mode, kw, stream);
+    case 5:
+        return plan.rows == 112  ? prefill::launch_tile<14>(a, mode, kw, stream)
+               : plan.rows == 96 ? prefill::launch_tile<13>(a, mode, kw, stream)
+               : plan.rows == 80 ? prefill::launch_tile<12>(a, mode, kw, stream)
+                                 : prefill::launch_tile<5>(a, mode, kw, stream);
+    case 8:
+        return plan.rows == 112  ? prefill::launch_tile<11>(a, mode, kw, stream)
+               : plan.rows == 96 ? prefill::launch_tile<9>(a, mode, kw, stream)
+               : plan.rows == 80 ? prefill::launch_tile<10>(a, mode, kw, stream)
+                                 : prefill::launch_tile<8>(a, mode, kw, stream);
     default: return hipErrorInvalidValue;
     }
 }

@@ -371,11 +371,15 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     constexpr int TN = WAVE_N / 16;
     static_assert(TM >= 4 && (TN == 2 || TN == 4), "wave tile: 16-row blocks by 32/64 columns");
     constexpr int KSTEPS = 2;                               // MFMA k steps per stage
-    constexpr int RING_A = TM == 6 ? 6 : 8;                 // A operands in registers: in use or on their way
+    // A operands in registers, in use or on their way: a divisor of a stage's, enough of them to hide an LDS read
+    constexpr int RING_A = TM < 5 || TM > 7 ? 8 : TM > 5 || TN == 4 ? TM : 2 * TM;
     static_assert(KSTEPS * TM % RING_A == 0, "an operand's register is the same in every stage");
     constexpr int CH = BK / 8;                              // 16-byte chunks per A row
     constexpr int RPB = 16 / CH;                            // A rows per 256-byte bank row
-    constexpr int A_CHUNKS = BM * CH / kThreads;            // DMA instructions per thread for the A tile
+    // DMA instructions per thread for the A tile; in the last of 80 and 112 rows' two wavefronts repeat the other two's pieces
+    constexpr int A_CHUNKS = (BM * CH + kThreads - 1) / kThreads;
+    constexpr int A_REPEAT = A_CHUNKS * kThreads - BM * CH;
+    static_assert(A_REPEAT == 0 || A_REPEAT == kThreads / 2, "whole wavefronts repeat");
     constexpr int B_CHUNKS = (BK / 8) * BN / 4 / kThreads;  // ... for the packed weights
     static_assert(A_CHUNKS >= 1 && B_CHUNKS >= 1, "tile too small for 256 threads");
     static_assert(BN / 8 + BN / 32 <= 64, "scales and zero points of a stage must fit one wave-wide DMA");
@@ -440,7 +444,8 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     uint32_t a_off[A_CHUNKS];
 #pragma unroll
     for (int j = 0; j < A_CHUNKS; ++j) {
-        const int slot = tid + j * kThreads;
+        int slot = tid + j * kThreads;
+        slot -= slot >= BM * CH ? A_REPEAT : 0;
         const int row = slot / CH;
         const int ch = (slot % CH) ^ ((row / RPB) & (CH - 1));
         a_off[j] = (uint32_t)((min(m0 + row, M - 1) - m0) * K + ch * 8) * 2u;
@@ -502,9 +507,10 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     // piece `p` (0 .. LOADS_PER_STAGE-1) of the loads of stage `ld_stage` into ring slot `ring`
     auto issue_piece = [&](int p, int ring) {
         const uint32_t base = smem_base + (uint32_t)ring * (uint32_t)L::BYTES;
-        if (p < A_CHUNKS)  // the wave's 64 lanes fill 64 consecutive 16-byte slots
-            dma_16(base + (uint32_t)(p * kThreads + wave * 64) * 16u, a_off[p], a_cur);
-        else if (p < A_CHUNKS + B_CHUNKS)
+        if (p < A_CHUNKS) {  // the wave's 64 lanes fill 64 consecutive 16-byte slots
+            const int slot = p * kThreads + wave * 64;
+            dma_16(base + (uint32_t)(slot - (slot >= BM * CH ? A_REPEAT : 0)) * 16u, a_off[p], a_cur);
+        } else if (p < A_CHUNKS + B_CHUNKS)
             dma_16(base + L::A_BYTES + (uint32_t)((p - A_CHUNKS) * kThreads + wave * 64) * 16u, b_off[p - A_CHUNKS], b_cur);
         else if (HALF && p == LOADS_PER_STAGE - 1)
             dma_4(base + L::A_BYTES + L::B_BYTES + L::SCALE_BYTES, z_cur);

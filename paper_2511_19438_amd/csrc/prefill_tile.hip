@@ -3,7 +3,7 @@
 #include "prefill_kernel.h"
 
 #ifndef GPTQ_PREFILL_TILE
-#error "compile with -DGPTQ_PREFILL_TILE=<1|3|5|8|9>"
+#error "compile with -DGPTQ_PREFILL_TILE=<1|3|5|8|9|10|11|12|13|14>"
 #endif
 
 namespace gptq {
@@ -14,17 +14,30 @@ hipError_t launch_tile(const Args &a, int mode, int kw, hipStream_t stream);
 
 namespace {
 
-// rows x columns per workgroup, wavefront grid, k per stage, stage buffers in the LDS ring
+// rows x columns per workgroup, wavefront grid, k per stage, stage buffers in the LDS ring - of one wavefront group, and of
+// each of two
 #if GPTQ_PREFILL_TILE == 1
-constexpr int BM = 256, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3;
+constexpr int BM = 256, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3, NBUF2 = 0;
 #elif GPTQ_PREFILL_TILE == 3
-constexpr int BM = 128, BN = 128, WM = 2, WN = 2, BK = 64, NBUF = 3;
+constexpr int BM = 128, BN = 128, WM = 2, WN = 2, BK = 64, NBUF = 3, NBUF2 = 3;
 #elif GPTQ_PREFILL_TILE == 5
-constexpr int BM = 64, BN = 128, WM = 1, WN = 4, BK = 64, NBUF = 4;
+constexpr int BM = 64, BN = 128, WM = 1, WN = 4, BK = 64, NBUF = 4, NBUF2 = 4;
 #elif GPTQ_PREFILL_TILE == 8
-constexpr int BM = 128, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3;
-#elif GPTQ_PREFILL_TILE == 9  // tile 8 where 96 rows fit the batch better
-constexpr int BM = 96, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3;
+constexpr int BM = 128, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3, NBUF2 = 3;
+// tile 8 where other rows fit the batch better
+#elif GPTQ_PREFILL_TILE == 9
+constexpr int BM = 96, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3, NBUF2 = 3;
+#elif GPTQ_PREFILL_TILE == 10
+constexpr int BM = 80, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 4, NBUF2 = 4;
+#elif GPTQ_PREFILL_TILE == 11
+constexpr int BM = 112, BN = 256, WM = 1, WN = 4, BK = 64, NBUF = 3, NBUF2 = 3;
+// tile 5 where they do
+#elif GPTQ_PREFILL_TILE == 12
+constexpr int BM = 80, BN = 128, WM = 1, WN = 4, BK = 64, NBUF = 4, NBUF2 = 5;
+#elif GPTQ_PREFILL_TILE == 13
+constexpr int BM = 96, BN = 128, WM = 1, WN = 4, BK = 64, NBUF = 4, NBUF2 = 4;
+#elif GPTQ_PREFILL_TILE == 14
+constexpr int BM = 112, BN = 128, WM = 1, WN = 4, BK = 64, NBUF = 4, NBUF2 = 4;
 #else
 #error "unknown tile id"
 #endif
@@ -61,11 +74,11 @@ hipError_t launch_tile<GPTQ_PREFILL_TILE>(const Args &a, int mode, int kw, hipSt
 {
 #if GPTQ_PREFILL_TILE != 1
     if (kw == 2 && mode == kGroupPerStage)
-        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, false, 2>, a,
-                      2 * (size_t)NBUF * StageLayout<BM, BN, BK, false>::BYTES, true, stream, 2);
+        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF2, false, 2>, a,
+                      2 * (size_t)NBUF2 * StageLayout<BM, BN, BK, false>::BYTES, true, stream, 2);
     if (kw == 2 && mode == kGroupPerHalf)
-        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF, true, 2>, a,
-                      2 * (size_t)NBUF * StageLayout<BM, BN, BK, true>::BYTES, true, stream, 2);
+        return launch(prefill_pipelined_kernel<BM, BN, WM, WN, BK, NBUF2, true, 2>, a,
+                      2 * (size_t)NBUF2 * StageLayout<BM, BN, BK, true>::BYTES, true, stream, 2);
 #endif
     if (kw != 1)
         return hipErrorInvalidValue;
