@@ -78,7 +78,7 @@ enum gptq_status {
  * (and 17-32 or 65-128 rows on the layer shapes where it measured faster) a mid-batch MFMA
  * kernel in which every wavefront streams its own share of the K slice (no g_idx, K and
  * group_size multiples of 64; up to 48 rows, and up to 64 on narrow layers, the small-batch kernel runs in its place, under
- * its id, if K % 128 == 0, from 65 rows on the big-tile kernel where it measured faster, likewise), larger M the big-tile fp16 MFMA kernel (with K slices where
+ * its id, if K % 128 == 0, from 49 rows on the big-tile kernel where it measured faster, likewise), larger M the big-tile fp16 MFMA kernel (with K slices where
  * the output tiles alone would not fill the chip).
  * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in
  * a table of all groups in LDS (as long as that fits: up to 606 groups, 630 at up to 384 rows; not large batches of a K under 640); plan
@@ -138,7 +138,7 @@ typedef struct gptq_w4a16_plan {
                         or 256 from groups of 128 on; anything else = auto);
                         mid-batch MFMA kernel: columns per workgroup (64 or 128; anything else = auto; more than 64 rows
                         always use 64), or those of the small-batch kernel in its place: 32 and 96 up to 48 rows, where
-                        64 is its too, 32 up to 64 (K % 128 == 0); above 64 rows 3, 5 and 8 are tiles of the big-tile
+                        64 is its too, 32 up to 64 (K % 128 == 0); above 48 rows 3, 5 and 8 are tiles of the big-tile
                         kernel in its place;
                         MFMA kernel: tile id = rows x columns per workgroup (wavefront grid):
                         1 256x256 (1x4), 3 128x128 (2x2), 5 64x128 (1x4), 8 128x256 (1x4, two workgroups

@@ -257,12 +257,20 @@ bool ring_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
 // workgroups (80x2176x8320 10.7 us, 13.8; 96x4096x12288 19.2, 20.8; but 104x1792x14912 13.9, 13.0 and 65x4992x8832 20.5, 18.7)
 // and, by 1 % on average, up to 80 rows on narrow ones in slices (72x25984x1984 23.1, 26.4; 80x28544x3520 35.8, 33.0); behind
 // by 5-60 % elsewhere (77x8192x10240 30.1, 25.6; 100x28672x8192 72, 60; 112x11008x4096 26.2, 22.7; 128x8192x8192 32.4, 27.9).
-bool big_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
+// 49-64 rows, where the ring does not serve: as the estimates of both have it, that of the big-tile kernel 3 % ahead, or 8 % of
+// 128-column tiles, whose estimate is high on one round of shallow ones (134 layers: 8 % faster on average, 64x8192x10240 26.8,
+// 23.1; 60x1280x35968 23.2, 15.9; 56x25856x8320 69.8, 50.2).
+bool big_in_place_of_mid(const Problem &p, const MidPlan &mid, const gptq_w4a16_plan_t *plan)
 {
-    if (p.M <= 64 || !prefill_pipelined(p))
+    if (p.M <= 48 || !prefill_pipelined(p))
         return false;
     if (plan && plan->kernel == 4)
         return plan->tile == 3 || plan->tile == 5 || plan->tile == 8;
+    if (p.M <= 64) {
+        PrefillPlan big = {};
+        prefill_make_plan(p, big);
+        return prefill_estimate_us(p, big) < (mid.cols_per_wg == 64 ? 0.97 : 0.92) * mid_estimate_us(p, mid);
+    }
     const int tiles64 = (p.N + 63) / 64;
     if (tiles64 > 128 && p.K <= 4736 && p.M <= 96)
         return false;
@@ -356,7 +364,7 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
             if (p.M > kRingWideMaxM)
                 r.skinny.cols_per_wg = 32;
             skinny_make_plan(p, r.skinny);
-        } else if (big_in_place_of_mid(p, plan)) {
+        } else if (big_in_place_of_mid(p, r.mid, plan)) {
             r.big = true;
             r.prefill.tile = plan ? plan->tile : 0;
             r.prefill.split_k = plan ? plan->split_k : 0;

@@ -127,6 +127,8 @@ struct MidPlan {
 };
 bool mid_supported(const Problem &p);
 void mid_make_plan(const Problem &p, MidPlan &plan);
+// Estimated duration (microseconds) of a plan at 49-64 rows.
+double mid_estimate_us(const Problem &p, const MidPlan &plan);
 size_t mid_workspace_bytes(const Problem &p, const MidPlan &plan);
 hipError_t launch_mid(const Problem &p, const MidPlan &plan, void *workspace, hipStream_t stream);
 
@@ -142,6 +144,8 @@ bool prefill_supported(const Problem &p);
 bool prefill_pipelined(const Problem &p);
 bool prefill_tile_exists(int tile);  // the tile ids a plan may name
 void prefill_make_plan(const Problem &p, PrefillPlan &plan);
+// Estimated duration (microseconds) of a plan of the pipelined kernel.
+double prefill_estimate_us(const Problem &p, const PrefillPlan &plan);
 // Scratch of a plan with split_k > 1 (counter area first, as for the other kernels); 0 without a split.
 size_t prefill_workspace_bytes(const Problem &p, const PrefillPlan &plan);
 hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *workspace, hipStream_t stream);

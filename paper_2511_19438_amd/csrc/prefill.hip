@@ -249,6 +249,11 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     plan.split_k = best_split;
 }
 
+double prefill_estimate_us(const Problem &p, const PrefillPlan &plan)
+{
+    return estimate_us(p, plan.tile, plan.rows, plan.split_k, mode_of(p) == prefill::kGroupPerHalf);
+}
+
 size_t prefill_workspace_bytes(const Problem &p, const PrefillPlan &plan)
 {
     if (plan.split_k <= 1 || plan.serial || !prefill_tile_exists(plan.tile))

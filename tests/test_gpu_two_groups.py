@@ -76,7 +76,7 @@ def test_rows_that_fit_the_batch(tile, M, K, N, group, split):
 
 
 # the big-tile kernel in the mid-batch kernel's place, and plans that a query gave: the same bits, also without scratch
-@pytest.mark.parametrize("M,K,N,group", [(100, 11008, 520, 128), (77, 8192, 8192, 128), (65, 9216, 704, 64)])
+@pytest.mark.parametrize("M,K,N,group", [(100, 11008, 520, 128), (77, 8192, 8192, 128), (65, 9216, 704, 64), (64, 8192, 10240, 128)])
 def test_in_the_mid_batch_kernels_place(M, K, N, group):
     from paper_2511_19438_amd import binding as B
 
