@@ -1,6 +1,6 @@
 // Mid-batch streaming MFMA kernel for the W4A16 GPTQ matrix multiply (32 < M <= 128 per launch), gfx950.
 //
-// Between the small-batch kernel (up to 32 rows: one or two 16-row MFMA operands per weight) and the big-tile
+// Between the small-batch kernel (few 16-row MFMA operands per weight) and the big-tile
 // kernel (hundreds of rows per tile) the weights still have to be streamed once at HBM speed, but every packed
 // word now feeds enough MFMAs that instruction issue, not memory, sets the pace of a wavefront.  This kernel
 // therefore makes each wavefront an independent stream processor with nothing shared and no workgroup barrier
