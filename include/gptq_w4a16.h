@@ -243,8 +243,8 @@ GPTQ_API int gptq_w4a16_unpack(const void *qweight, void *q_out, const void *qze
  * captured graph.  Growth is refused (GPTQ_WORKSPACE_TOO_SMALL, nothing enqueued) while `stream` is being
  * captured, since it allocates and clears memory: make one eager call of every problem a graph will hold
  * before capturing it, or use gptq_w4a16_gemm_static.
- * Some automatic plans can do without the scratch of their slices: act-order problems, the small-batch kernel up to
- * 32 rows (but for its 256-column workgroups), and the big-tile kernel.  Where it cannot be had, as above or on a workspace that
+ * Some automatic plans can do without the scratch of their slices: act-order problems, the small-batch kernel (but
+ * for its 256-column workgroups), and the big-tile kernel, under their own ids and the mid-batch kernel's.  Where it cannot be had, as above or on a workspace that
  * is too small, every workgroup walks the slices itself, one after the other, and adds them in the same order: the
  * result is the same, the call is slower by up to as many times as it has slices, and a graph that captured it
  * stays so.  Such a call needs no scratch from 17 rows on, and up to 16 rows what the vector kernel takes for the

@@ -142,12 +142,11 @@ int acquire_workspace(size_t bytes, hipStream_t stream, Scratch *out)
 
 // Default kernel by batch size, from measurement on Llama-shaped layers.  A single row is streamed fastest
 // by the vector kernel.  From two rows on the small-batch MFMA kernel wins: its time is nearly flat up to 16
-// rows and grows slowly to 32, where the vector kernel pays for every weight once per batch row.  From 33 to
-// 64 rows the mid-batch streaming kernel is the fastest on every Llama shape measured (10-40 % ahead of the
-// big-tile kernel with K slices); it also takes 17-32 rows on wide or very deep layers (3-17 % ahead of the
-// small-batch kernel, 2-12 % behind it on narrow ones) and 65-128 rows where its 64-column tiles give between half
-// and all of the compute units one workgroup each, or K is deep (1-24 % ahead of the big-tile kernel; 3-18 %
-// behind it on 4096x4096 and on layers whose tiles make a second, partly filled round).
+// rows and grows slowly to 32, where the vector kernel pays for every weight once per batch row.  The mid-batch
+// streaming kernel's id stands for 33 to 64 rows, 17-32 rows on wide or very deep layers, and 65-128 rows where its
+// 64-column tiles give between half and all of the compute units one workgroup each, or K is deep; where the
+// small-batch or the big-tile kernel has overtaken it since, that one runs under the id (ring_in_place_of_mid,
+// big_in_place_of_mid).
 constexpr int kVectorMaxM = 1;
 constexpr int kSmallBatchAutoMaxM = 32;
 // Formats that the small-batch kernel does not take (groups of 96, ...): the vector kernel up to eight rows, then the
@@ -422,7 +421,7 @@ size_t required_scratch(const Problem &p, const gptq_w4a16_plan_t *request)
     return scratch_bytes(p, resolve(p, &vector));
 }
 
-// Act-order problems, the big-tile kernel and the small-batch kernel (up to 32 rows, all widths but 256) do not fail where the
+// Act-order problems, the big-tile kernel and the small-batch kernel (all widths but 256 where it runs on its ring, and up to 32 rows else) do not fail where the
 // scratch of their K slices cannot be had - a workspace of the caller's that is too small, growth under capture, the
 // static block: every workgroup then walks the slices itself, in the same order, so that the result does not depend on
 // the scratch.  (How many slices pay is a matter of measurement and may change; which calls a workspace serves may

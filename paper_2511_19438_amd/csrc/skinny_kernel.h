@@ -13,7 +13,7 @@
 //     column 4*(lane%16) + t;
 //   * every weight is read once and dequantised once, whatever M is: 2 vector ALU operations per weight
 //     instead of 1.2 + M/2 in the vector kernel.
-// ring_kernel.h has the variant that serves plain formats up to 32 rows.  This one serves what does not fit its slots:
+// ring_kernel.h has the variant that serves plain formats up to 48 rows, narrow layers up to 64.  This one serves what does not fit its slots:
 // g_idx (template ACT), a K that ends inside a 128-k unit (TAIL), 256-column workgroups for very wide layers (WN = 4), and
 // 33 to 64 rows per launch (TM = 4, by explicit plan).
 #pragma once
