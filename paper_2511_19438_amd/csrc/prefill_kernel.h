@@ -628,8 +628,25 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
     constexpr int READ_AFTER = TM - 4;
     auto reads_words = [](int group) { return group % TM == READ_AFTER; };
     auto word_reads = [](int group) { return HALF || group < TM ? 3 : 1; };
+    // The prologue issues the first RING_A - 1 operands in this order, too, but of the words in between those of k step 1 alone:
+    // it has waited for the others before.
+    auto in_prologue = [](int operand) { return operand + KSTEPS * TM - (RING_A - 1); };  // the group that issues it in the loop
+    // LDS reads behind that of operand Q, in the first stage, where its wait stands
+    auto behind_in_first_stage = [=](int operand) {
+        int behind = -1;
+        for (int q = 0; q < RING_A - 1 + operand; ++q) {
+            const bool prologue = q < RING_A - 1;
+            const int group = prologue ? in_prologue(q) : q - (RING_A - 1);
+            behind = q == operand ? 0 : behind + (behind >= 0);
+            if (behind >= 0 && reads_words(group) && (!prologue || group >= TM))
+                behind += word_reads(group);
+        }
+        return behind;
+    };
     // Before the first use of operand q of a stage: LDS reads return in order, so what may be outstanding is what has been
-    // issued after its own read - the RING_A - 2 operands that follow and the words read in between.
+    // issued after its own read - the RING_A - 2 operands that follow and the words read in between, but for those that the
+    // prologue leaves out (one wait serves the first stage and the others: on 80x128, whose ring is two k steps long,
+    // operand 0 waits for the words and the group behind it as well).
     // (The operand is an in/out of the wait, so that the MFMA that consumes it cannot be moved above it.)
     auto wait_afrag = [&](auto operand, half8_t &frag) {
         constexpr int Q = decltype(operand)::value;
@@ -637,11 +654,12 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
             int n = RING_A - 2;
             for (int g = Q - (RING_A - 1); g < Q; ++g) {
                 const int group = (g + KSTEPS * TM) % (KSTEPS * TM);
-                if (reads_words(group))
+                if (reads_words(group) && (g >= 0 || group >= TM))
                     n += word_reads(group);
             }
             return n;
         }();
+        static_assert(COUNT <= behind_in_first_stage(Q), "a wait that the first stage meets with too few reads in flight is none");
         static_assert(COUNT < 16, "lgkmcnt is a 4-bit counter");
         asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(frag) : "n"(COUNT));
     };
@@ -753,7 +771,7 @@ __global__ __launch_bounds__(kThreads * KW, (kWavesPerSimd<BM, BN>)) void prefil
         prepare_op(o, true, 0, bfr[0]);
     // (in the order of the loop: the waits count on it)
     static_for<0, RING_A - 1>([&](auto operand) {
-        constexpr int q = decltype(operand)::value, issued_in = q - (RING_A - 1) + KSTEPS * TM;
+        constexpr int q = decltype(operand)::value, issued_in = in_prologue(q);
         read_afrag(0, operand, afr[q]);
         if (issued_in >= TM && reads_words(issued_in)) {
             read_words(0, Step1{}, words[1]);

@@ -7,7 +7,7 @@ bookkeeping cost too much there: the mid-batch kernel (global loads of the weigh
 `s_waitcnt lgkmcnt(n)`).  A third, the small-batch kernel on its ring, has its LDS slots refilled by DMA that the compiler
 does not see.  The compiler does not know that the destination registers of such a load are still
 pending: if it copied, reused or overwrote them between the load and the wait that retires it, a result would be
-wrong only now and then.  Memory operations of one kind retire in order, so a linear scan in layout order can tell.
+wrong only now and then.  Memory operations of one kind retire in order, so a walk along the paths of the code can tell.
 """
 import os
 import re
@@ -30,8 +30,8 @@ def compile_to_asm(src, defines, out_dir):
     return out
 
 
-def kernels(path):
-    """{kernel name: instruction lines (labels, directives and comments removed; asm markers kept)}"""
+def kernels(path, labels=False):
+    """{kernel name: instruction lines (directives and comments removed, labels too unless asked for; asm markers kept)}"""
     text = open(path).read()
     out = {}
     for m in re.finditer(r"^(_Z\w+):.*?\n(.*?)\.end_amdhsa_kernel", text, re.S | re.M):
@@ -42,7 +42,11 @@ def kernels(path):
                 lines.append(t)
                 continue
             t = t.split(";")[0].strip()
-            if not t or t.startswith(".") or t.endswith(":"):
+            if t.endswith(":"):
+                if labels:
+                    lines.append(t)
+                continue
+            if not t or t.startswith("."):
                 continue
             lines.append(t)
         out[m.group(1)] = lines
@@ -59,59 +63,113 @@ def vregs(operand):
     return out
 
 
-def check_pending(lines, is_tracked, is_counted, wait_re, what):
-    """Scans `lines` twice (the second pass stands for the loop's next trip and for the code after it): an
-    instruction for which is_tracked(op, in_asm) holds puts its destination registers in flight; instructions for
+def blocks(lines):
+    """The basic blocks of a kernel's lines: [[(instruction, in inline assembly?)], [numbers of the blocks that may follow]]."""
+    out, labels, in_asm = [[[], []]], {}, False
+    for t in lines:
+        if t.startswith(";;#ASM"):
+            in_asm = t.startswith(";;#ASMSTART")
+        elif t.endswith(":"):
+            out.append([[], []])
+            labels[t[:-1]] = len(out) - 1
+        else:
+            assert not t.startswith(("s_setpc", "s_swappc", "s_call", "s_cbranch_i_fork", "s_cbranch_g_fork")), t
+            out[-1][0].append((t, in_asm))
+            if t.startswith(("s_branch", "s_cbranch", "s_endpgm")):
+                out.append([[], []])
+    for number, (code, successors) in enumerate(out):
+        last = code[-1][0].split() if code else [""]
+        if last[0].startswith(("s_branch", "s_cbranch")):
+            successors.append(labels[last[1]])
+        if last[0] not in ("s_branch", "s_endpgm") and number + 1 < len(out):
+            successors.append(number + 1)
+    return out
+
+
+def walk(lines, step, without=()):
+    """Follows every path through `lines` but those over the edges `without` (from one block to another).  What is in flight - {operation: how many behind it in the queue at least} - is
+    handed to step(in_flight, instruction, in_asm), which changes it; where paths meet, an operation is in flight if it is on
+    any of them, with the fewest behind it.  Step is called until nothing changes, and sees the weakest case of each place."""
+    code = blocks(lines)
+    entry = {0: {}}
+    todo = [0]
+    while todo:
+        number = todo.pop()
+        state = dict(entry[number])
+        for t, in_asm in code[number][0]:
+            step(state, t, in_asm)
+        for nxt in code[number][1]:
+            if (number, nxt) in without:
+                continue
+            known = entry.get(nxt)
+            met = dict(state) if known is None else dict(known)
+            if known is not None:
+                for op, behind in state.items():
+                    met[op] = min(behind, met.get(op, behind))
+            if met != known:
+                entry[nxt] = met
+                if nxt not in todo:
+                    todo.append(nxt)
+
+
+def queue_up(state, op, counted=True):
+    """`op` is issued; one that may overtake others (a scalar load) is no place in the queue for those before it."""
+    if counted:
+        for other in state:
+            state[other] = min(state[other] + 1, 64)
+    state[op] = 0
+
+
+def retire(state, n):
+    """A wait for at most n in flight: an operation with n or more behind it is done - one with fewer may not be."""
+    for op in [op for op, behind in state.items() if behind >= n]:
+        del state[op]
+
+
+def check_pending(lines, is_tracked, is_counted, wait_re, what, without=()):
+    """An instruction for which is_tracked(op, in_asm) holds puts its destination registers in flight; instructions for
     which is_counted(op) holds take a place in the in-order queue; `wait_re` extracts n from the waits.  No other
-    instruction may name a register in flight."""
-    problems = []
-    queue = []  # [dest regs or None, text]
-    in_asm = False
-    for trip in range(2):
-        for t in lines:
-            if t.startswith(";;#ASMSTART"):
-                in_asm = True
-                continue
-            if t.startswith(";;#ASMEND"):
-                in_asm = False
-                continue
-            op = t.split()[0]
-            m = wait_re.search(t) if op == "s_waitcnt" else None
-            if op == "s_waitcnt":
-                if m:
-                    n = int(m.group(1))
-                    queue = queue[len(queue) - n:] if n else []
-                continue
-            if op == "s_endpgm":
-                queue = []
-                continue
-            named = vregs(t.split(None, 1)[1]) if " " in t else set()
-            for dest, text in queue:
-                if dest and dest & named and not (is_tracked(op, in_asm) and text == t):
-                    problems.append(f"{what}: '{t}' names v{sorted(dest & named)} while '{text}' is in flight")
-            if is_counted(op):
-                dest = vregs(t.split(None, 1)[1].split(",")[0]) if is_tracked(op, in_asm) else None
-                queue.append([dest, t])
-    return problems
+    instruction may name a register in flight, on any path."""
+    problems = set()
+
+    def step(state, t, in_asm):
+        op = t.split()[0]
+        if op == "s_waitcnt":
+            m = wait_re.search(t)
+            if m:
+                retire(state, int(m.group(1)))
+            return
+        rest = t.partition(" ")[2]
+        own, sources = frozenset(vregs(rest.split(",")[0])), vregs(rest.partition(",")[2])
+        tracked = is_tracked(op, in_asm)
+        for text, dest in state:
+            # (a load of the same registers as a whole lands behind the one in flight: the queue is in order)
+            if dest & sources or (dest & own and not (tracked and dest == own)):
+                problems.add(f"{what}: '{t}' names v{sorted(dest & (own | sources))} while '{text}' is in flight")
+        if is_counted(op):
+            queue_up(state, (t, own if tracked else frozenset()), not op.startswith("s_"))
+
+    walk(lines, step, without)
+    return sorted(problems)
 
 
 def check_refills(lines, what):
-    """Scans `lines` twice, as above, for LDS reads that may still be on their way when a DMA to LDS is issued."""
-    problems = []
-    queue = []
-    for trip in range(2):
-        for t in lines:
-            op = t.split()[0]
-            if op == "s_waitcnt":
-                m = re.search(r"lgkmcnt\((\d+)\)", t)
-                if m:
-                    n = int(m.group(1))
-                    queue = queue[len(queue) - n:] if n else []
-            elif op.startswith(("ds_", "s_load", "s_buffer_load")):
-                queue.append(t)
-            elif re.match(r"(global|buffer)_load\w*_lds", op) or (op.startswith("buffer_load") and " lds" in t):
-                problems += [f"{what}: '{t}' while '{r}' is in flight" for r in queue if r.startswith("ds_read")]
-    return problems
+    """LDS reads that may still be on their way, on some path, when a DMA to LDS is issued."""
+    problems = set()
+
+    def step(state, t, in_asm):
+        op = t.split()[0]
+        if op == "s_waitcnt":
+            m = re.search(r"lgkmcnt\((\d+)\)", t)
+            if m:
+                retire(state, int(m.group(1)))
+        elif op.startswith(("ds_", "s_load", "s_buffer_load")):
+            queue_up(state, t, op.startswith("ds_"))
+        elif re.match(r"(global|buffer)_load\w*_lds", op) or (op.startswith("buffer_load") and " lds" in t):
+            problems.update(f"{what}: '{t}' while '{r}' is in flight" for r in state if r.startswith("ds_read"))
+
+    walk(lines, step)
+    return sorted(problems)
 
 
 @pytest.fixture(scope="module")
@@ -127,7 +185,7 @@ def asm_files():
 
 
 def test_mid_batch_kernel_leaves_registers_of_pending_weight_loads_alone(asm_files):
-    ks = {k: v for k, v in kernels(asm_files["mid"]).items() if "mid_kernel" in k}
+    ks = {k: v for k, v in kernels(asm_files["mid"], labels=True).items() if "mid_kernel" in k}
     assert len(ks) >= 5
     wait = re.compile(r"vmcnt\((\d+)\)")
     for name, lines in ks.items():
@@ -136,15 +194,23 @@ def test_mid_batch_kernel_leaves_registers_of_pending_weight_loads_alone(asm_fil
         n_asm = sum(1 for i, t in enumerate(lines) if t.startswith("global_load_dword") and i and
                     lines[i - 1].startswith(";;#ASMSTART"))
         assert n_asm >= 18, f"{name}: expected the loop's weight loads as inline assembly, found {n_asm}"
-        problems = check_pending(lines, tracked, counted, wait, name)
-        assert not problems, "\n".join(problems[:10])
+        # Behind the loop stand the bodies of a first and of a second remaining stage: nobody runs the second without the first.
+        code = blocks(lines)
+        rest = [i for i, (block, _) in enumerate(code) if sum(in_asm and t.startswith("global_load_dword") for t, in_asm in block) == 6]
+        assert len(rest) == 2, name
+        first_left_out = {(i, n) for i, (_, nxt) in enumerate(code) if rest[0] in nxt for n in nxt if n != rest[0]}
+        second_run = {(i, rest[1]) for i, (_, nxt) in enumerate(code) if rest[1] in nxt}
+        assert first_left_out and second_run
+        for without in (first_left_out, second_run):
+            problems = check_pending(lines, tracked, counted, wait, name, without)
+            assert not problems, "\n".join(problems[:10])
 
 
 def test_big_tile_kernel_leaves_registers_of_pending_lds_reads_alone(asm_files):
     wait = re.compile(r"lgkmcnt\((\d+)\)")
     seen = 0
     for path in asm_files["prefill"]:
-        for name, lines in kernels(path).items():
+        for name, lines in kernels(path, labels=True).items():
             if "prefill_pipelined_kernel" not in name:
                 continue
             seen += 1
@@ -152,7 +218,7 @@ def test_big_tile_kernel_leaves_registers_of_pending_lds_reads_alone(asm_files):
             counted = lambda op: op.startswith("ds_") or op.startswith("s_load") or op.startswith("s_buffer_load")  # noqa: E731
             problems = check_pending(lines, tracked, counted, wait, name)
             assert not problems, "\n".join(problems[:10])
-    assert seen >= 4
+    assert seen >= 40
 
 
 def check_mfma_wait_states(lines, what, valu_to_mfma=2, mfma_to_other=11):
@@ -204,7 +270,7 @@ def test_ring_kernel_refills_a_slot_only_after_its_reads(asm_files):
     its loads in inline assembly has a destination register: there are none in flight to leave alone.)"""
     seen = 0
     for path in asm_files["ring"]:
-        for name, lines in kernels(path).items():
+        for name, lines in kernels(path, labels=True).items():
             if "ring_kernel" not in name:
                 continue
             seen += 1
@@ -268,3 +334,40 @@ def test_the_checker_itself_flags_a_planted_violation():
     late_wait = list(good)
     late_wait[6] = "s_waitcnt vmcnt(2)"       # a wait that does not retire the load
     assert len(check_pending(late_wait, tracked, counted, wait, "late wait")) >= 1
+
+
+def lds_problems(lines):
+    return check_pending(lines, lambda op, in_asm: in_asm and op.startswith("ds_read"),
+                         lambda op: op.startswith(("ds_", "s_load")), re.compile(r"lgkmcnt\((\d+)\)"), "planted")
+
+
+def asm(text):
+    return [";;#ASMSTART", text, ";;#ASMEND"]
+
+
+def test_the_checker_flags_a_wait_for_more_reads_than_are_in_flight():
+    """As many as the loop has in flight at this place, but fewer have been issued on the way into it: a wait for nothing."""
+    reads = asm("ds_read_b128 v[0:3], v40") + asm("ds_read_b128 v[4:7], v40")
+    use = ["v_mfma_f32_16x16x32_f16 v[8:11], v[0:3], v[12:15], v[8:11]"]
+    assert lds_problems(reads + asm("s_waitcnt lgkmcnt(1)") + use) == []
+    for n in (2, 3, 12):
+        assert lds_problems(reads + asm(f"s_waitcnt lgkmcnt({n})") + use) != [], n
+    dma = "global_load_lds_dwordx4 v10, s[4:5]"
+    assert check_refills(reads + ["s_waitcnt lgkmcnt(0)", dma], "good") == []
+    assert check_refills(reads + ["s_waitcnt lgkmcnt(3)", dma], "none") != []
+
+
+def test_the_checker_follows_branches():
+    """A wait in a block that a path jumps over, a loop's next turn, and what only one of two ways leaves in flight."""
+    read, use = asm("ds_read_b128 v[0:3], v40"), ["v_add_u32 v8, v1, v9"]
+    skipped = read + ["s_cbranch_scc1 .LBB0_1", "s_waitcnt lgkmcnt(0)", ".LBB0_1:"] + use + ["s_endpgm"]
+    assert lds_problems(skipped) != []
+    assert lds_problems(read + ["s_branch .LBB0_1"] + use + [".LBB0_1:", "s_waitcnt lgkmcnt(0)"] + use + ["s_endpgm"]) == []
+    loop = ["s_waitcnt lgkmcnt(0)", ".LBB0_1:"] + use + read + ["s_cbranch_scc1 .LBB0_1", "s_waitcnt lgkmcnt(0)", "s_endpgm"]
+    assert lds_problems(loop) != []
+    assert lds_problems(loop[:-3] + ["s_waitcnt lgkmcnt(0)"] + loop[-3:]) == []
+    # the fewest reads behind the one in flight count, not those of the longer way
+    joined = read + ["s_cbranch_scc1 .LBB0_1"] + asm("ds_read_b32 v20, v40") + [".LBB0_1:"] + asm("s_waitcnt lgkmcnt(1)") + use
+    assert lds_problems(joined) != []
+    # a scalar load may overtake the reads before it: it makes no place in the queue
+    assert lds_problems(read + ["s_load_dword s4, s[0:1], 0x0"] + asm("s_waitcnt lgkmcnt(1)") + use) != []
