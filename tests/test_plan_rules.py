@@ -198,3 +198,14 @@ def test_small_tiles_of_small_groups(B):
     for problem, want in {(202, 7200, 2040): (5, 4), (174, 2496, 15488): (8, 2), (158, 2976, 10880): (5, 1), (378, 2112, 9064): (3, 1),
                           (558, 2368, 1352): (5, 2), (424, 5056, 1408): (5, 3), (678, 4480, 2048): (5, 4), (357, 3200, 10496): (3, 1)}.items():
         assert plan(*problem) == (2, *want), problem
+
+
+def test_slices_asked_for_up_to_128_rows_leave_the_largest_tile_out(B):
+    """256x256 has no rows for them; a plan that names it still gets it, and one under the mid-batch kernel's id, which has no
+    such tile, resolves to itself."""
+    for M, K, N, group, split in [(128, 8192, 8192, 128, 8), (113, 2432, 14080, 128, 4), (69, 3040, 5888, 32, 8), (31, 2944, 1536, 128, 16)]:
+        for kernel in (0, 2, 4):
+            pl = B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(kernel=kernel, split_k=split))
+            assert pl.tile != 1, (M, K, N, kernel)
+            assert fields(B.gptq_w4a16_plan_query(M, K, N, group, False, pl)) == fields(pl), (M, K, N, kernel)
+        assert B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(kernel=2, tile=1, split_k=split)).tile == 1
