@@ -227,8 +227,19 @@ bool mid_batch_by_default(const Problem &p)
     return tiles64 <= 256 && (tiles64 >= 128 || p.K >= 8192);
 }
 
+// Whether a plan settles which of the kernels under the mid-batch kernel's id runs: by the id, or by a tile that one of them has
+// at these rows.
+bool names_kernel_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
+{
+    if (!plan || plan->kernel == 4)
+        return plan != nullptr;
+    const int t = plan->tile;
+    return t == 64 || (t == 128 && p.M <= 64) || (ring_supported(p) && ring_width(p, t, plan->split_k)) ||
+           (p.M > 48 && prefill_pipelined(p) && (t == 3 || t == 5 || t == 8));
+}
+
 // Whether the small-batch kernel on its ring of LDS slots, which has overtaken the mid-batch kernel on small batches, runs in
-// its place, with widths and slices of its own unless a plan says kernel 4.
+// its place, with widths and slices of its own where a plan leaves them open.
 bool ring_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
 {
     if (!ring_supported(p))
@@ -238,8 +249,8 @@ bool ring_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
     if (p.M <= 32)
         return true;
     // 33-48 rows: 145 random layers 1.31 times as fast on average, 4-7 % slower on four (shallow ones and 11904x2104).
-    // (A plan that names kernel 4 gets the ring with a width that automatic plans have there, else the mid-batch kernel.)
-    if (plan && plan->kernel == 4)
+    // (A plan that names one of the kernels gets the ring with a width that automatic plans have there, else the mid-batch kernel.)
+    if (names_kernel_of_mid(p, plan))
         return ring_width(p, plan->tile, plan->split_k);
     if (p.M <= kRingWideMaxM)
         return true;
@@ -263,10 +274,11 @@ bool big_in_place_of_mid(const Problem &p, const MidPlan &mid, const gptq_w4a16_
 {
     if (p.M <= 48 || !prefill_pipelined(p))
         return false;
-    if (plan && plan->kernel == 4)
+    if (names_kernel_of_mid(p, plan))
         return plan->tile == 3 || plan->tile == 5 || plan->tile == 8;
     if (p.M <= 64) {
         PrefillPlan big = {};
+        big.split_k = plan ? plan->split_k : 0;
         prefill_make_plan(p, big);
         return prefill_estimate_us(p, big) < (mid.cols_per_wg == 64 ? 0.97 : 0.92) * mid_estimate_us(p, mid);
     }
@@ -355,10 +367,11 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
         mid_make_plan(p, r.mid);
         if (ring_in_place_of_mid(p, plan)) {
             r.ring = true;
-            if (plan && plan->kernel == 4) {
-                r.skinny.cols_per_wg = ring_width(p, plan->tile, r.mid.split_k) ? plan->tile : r.mid.cols_per_wg;
+            if (plan) {
+                const bool named = plan->kernel == 4;
+                r.skinny.cols_per_wg = ring_width(p, plan->tile, r.mid.split_k) ? plan->tile : named ? r.mid.cols_per_wg : 0;
                 // (slices of the mid-batch kernel's own choice are made for its own widths)
-                r.skinny.split_k = plan->split_k > 0 || r.skinny.cols_per_wg == r.mid.cols_per_wg ? r.mid.split_k : 0;
+                r.skinny.split_k = plan->split_k > 0 || (named && r.skinny.cols_per_wg == r.mid.cols_per_wg) ? r.mid.split_k : 0;
             }
             if (p.M > kRingWideMaxM)
                 r.skinny.cols_per_wg = 32;

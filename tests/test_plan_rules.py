@@ -209,3 +209,24 @@ def test_slices_asked_for_up_to_128_rows_leave_the_largest_tile_out(B):
             assert pl.tile != 1, (M, K, N, kernel)
             assert fields(B.gptq_w4a16_plan_query(M, K, N, group, False, pl)) == fields(pl), (M, K, N, kernel)
         assert B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(kernel=2, tile=1, split_k=split)).tile == 1
+
+
+def test_slices_and_tiles_asked_for_without_a_kernel(B):
+    """A plan that leaves the kernel open gets the slices and the tile that it names all the same, whichever kernel runs under
+    the mid-batch kernel's id (its own, the ring up to 64 rows, the big-tile kernel from 49 on), and resolves to itself."""
+    kernels = set()
+    for M, K, N, group in [(24, 4096, 22016, 128), (24, 28672, 8192, 64), (32, 8192, 57344, 128), (33, 8192, 1024, 64), (40, 11008, 4096, 128),
+                           (48, 8192, 1024, 128), (48, 4032, 4096, 64), (56, 8192, 1024, 128), (56, 11008, 4096, 128), (64, 8192, 10240, 128),
+                           (64, 4096, 4096, 128), (64, 24960, 17344, 128), (77, 8192, 10240, 128), (100, 11008, 4096, 64), (128, 8192, 8192, 128)]:
+        assert B.gptq_w4a16_plan_query(M, K, N, group).kernel == 4
+        for split in (1, 2, 3, 4, 5, 8):
+            asked = B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(split_k=split))
+            assert asked.kernel == 4 and asked.split_k == split, (M, K, N, split, fields(asked))
+            assert fields(B.gptq_w4a16_plan_query(M, K, N, group, False, asked)) == fields(asked), (M, K, N, split)
+            kernels.add(asked.tile)
+        for tile in (32, 64, 96, 128, 3, 5, 8):
+            named, asked = (B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(kernel=k, tile=tile, split_k=2)) for k in (4, 0))
+            if named.tile == tile:  # (a tile that one of the kernels has at these rows)
+                assert fields(asked) == fields(named), (M, K, N, tile, fields(asked), fields(named))
+                assert B.gptq_w4a16_plan_query(M, K, N, group, False, B.Plan(tile=tile)).tile == tile, (M, K, N, tile)
+    assert kernels >= {32, 64, 128, 5, 8}
