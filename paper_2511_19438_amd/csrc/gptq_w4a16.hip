@@ -270,22 +270,27 @@ bool ring_in_place_of_mid(const Problem &p, const gptq_w4a16_plan_t *plan)
 // 49-64 rows, where the ring does not serve: as the estimates of both have it, that of the big-tile kernel 3 % ahead, or 8 % of
 // 128-column tiles, whose estimate is high on one round of shallow ones (134 layers: 8 % faster on average, 64x8192x10240 26.8,
 // 23.1; 60x1280x35968 23.2, 15.9; 56x25856x8320 69.8, 50.2).
-bool big_in_place_of_mid(const Problem &p, const MidPlan &mid, const gptq_w4a16_plan_t *plan)
+// (`big`: its plan, with what `plan` leaves open filled in)
+bool big_in_place_of_mid(const Problem &p, const MidPlan &mid, const gptq_w4a16_plan_t *plan, PrefillPlan &big)
 {
     if (p.M <= 48 || !prefill_pipelined(p))
         return false;
-    if (names_kernel_of_mid(p, plan))
-        return plan->tile == 3 || plan->tile == 5 || plan->tile == 8;
-    if (p.M <= 64) {
-        PrefillPlan big = {};
-        big.split_k = plan ? plan->split_k : 0;
+    big.tile = 0;
+    big.split_k = plan ? plan->split_k : 0;
+    if (names_kernel_of_mid(p, plan)) {
+        big.tile = plan->tile;
+        if (plan->tile != 3 && plan->tile != 5 && plan->tile != 8)
+            return false;
+    } else if (p.M > 64) {
+        const int tiles64 = (p.N + 63) / 64;
+        if ((tiles64 > 128 && p.K <= 4736 && p.M <= 96) || (tiles64 <= 64 && tiles64 > 16 && p.M <= 80))
+            return false;
+    } else {
         prefill_make_plan(p, big);
         return prefill_estimate_us(p, big) < (mid.cols_per_wg == 64 ? 0.97 : 0.92) * mid_estimate_us(p, mid);
     }
-    const int tiles64 = (p.N + 63) / 64;
-    if (tiles64 > 128 && p.K <= 4736 && p.M <= 96)
-        return false;
-    return !(tiles64 <= 64 && tiles64 > 16 && p.M <= 80);
+    prefill_make_plan(p, big);
+    return true;
 }
 
 // Act-order as stored: whether the lookup variant (64x64 tiles, each with its own table) is the better one against the
@@ -376,11 +381,8 @@ Resolved resolve(const Problem &p, const gptq_w4a16_plan_t *plan)
             if (p.M > kRingWideMaxM)
                 r.skinny.cols_per_wg = 32;
             skinny_make_plan(p, r.skinny);
-        } else if (big_in_place_of_mid(p, r.mid, plan)) {
-            r.big = true;
-            r.prefill.tile = plan ? plan->tile : 0;
-            r.prefill.split_k = plan ? plan->split_k : 0;
-            prefill_make_plan(p, r.prefill);
+        } else {
+            r.big = big_in_place_of_mid(p, r.mid, plan, r.prefill);
         }
     } else {
         r.prefill.tile = plan ? plan->tile : 0;

@@ -2,8 +2,6 @@
 #include "gptq_w4a16.h"
 #include "prefill_kernel.h"
 
-#include <cmath>
-
 namespace gptq {
 
 namespace prefill {
@@ -61,13 +59,27 @@ int row_choice(const Problem &p, int t, int i, bool half)
     return i == 0 || padded < padded_own || (t == 5 && padded == padded_own && (!half || p.M > 192)) ? rows : 0;
 }
 
-// Workgroups of tile 8 (`rows` x 256) with `split` K slices (as many as whole stages make of them).
-int workgroups_of_tile8(const Problem &p, int rows, int split, int *stages_per_slice)
+// The output tiles of a tile shape, and how many of them the busiest XCD has (tile_of_workgroup).
+struct Grid {
+    int tiles, per_xcd;
+};
+
+Grid grid_of(const Problem &p, int t, int rows)
+{
+    const int tiles = ceil_div_i(p.M, rows) * ceil_div_i(p.N, kTiles[t].bn);
+    return {tiles, ceil_div_i(tiles, 8)};
+}
+
+// K slices: how many, as whole stages make of `split`, and the stages of each.
+struct Slices {
+    int count, stages;
+};
+
+Slices slices_of(const Problem &p, int split)
 {
     const int stages = ceil_div_i(p.K, 64);
-    const int sps = ceil_div_i(stages, split < 1 ? 1 : split);
-    *stages_per_slice = sps;
-    return ceil_div_i(p.M, rows) * ceil_div_i(p.N, 256) * ceil_div_i(stages, sps);
+    const int each = ceil_div_i(stages, split < 1 ? 1 : split);
+    return {ceil_div_i(stages, each), each};
 }
 
 // Wavefront groups that share a tile of 128x256, each with half of the K slice: two where that gives every compute
@@ -75,10 +87,9 @@ int workgroups_of_tile8(const Problem &p, int rows, int split, int *stages_per_s
 // in two slices 266 -> 226; M = 128, 8192x57344 152 -> 126).  With more workgroups than compute units two of them
 // meet there anyway (4096x22016 at M = 512, 344 workgroups: 104 us with one group, 114 with two), and slices of a few
 // stages do not earn the sum through LDS (4096x4096 at M = 256, eight stages: 34.2, 35.3).
-int k_groups_of_tile8(const Problem &p, int rows, int split)
+int k_groups_of_tile8(const Grid &grid, const Slices &slices)
 {
-    int sps;
-    return workgroups_of_tile8(p, rows, split, &sps) <= kComputeUnits && sps > 8 ? 2 : 1;
+    return grid.tiles * slices.count <= kComputeUnits && slices.stages > 8 ? 2 : 1;
 }
 
 // The same for the 128x128 and 64x128 tiles, where no compute unit of the busiest XCD has more than one workgroup (the
@@ -86,20 +97,17 @@ int k_groups_of_tile8(const Problem &p, int rows, int split)
 // M = 512 32.9 -> 28.0 us, at M = 100 29.3 -> 24.9 (in four slices of 16 stages 16.1 -> 15.3), 28672x4096 at M = 100
 // 183 -> 138; 128x128 tile, 4096x12288 at M = 256 61.2 -> 43.4, 11008x4096 at M = 512 147 -> 99.  Two groups fill the chip
 // without the partial sums of two slices in scratch: 4096x4096 at M = 256 20.7 us in four slices -> 19.5 in two.
-int k_groups_of_small_tile(const Problem &p, int t, int rows, int split)
+int k_groups_of_small_tile(const Grid &grid, const Slices &slices)
 {
-    const int tiles = ceil_div_i(p.M, rows) * ceil_div_i(p.N, kTiles[t].bn);
-    const int stages = ceil_div_i(p.K, 64);
-    const int sps = ceil_div_i(stages, split < 1 ? 1 : split);
-    return ceil_div_i(tiles, 8) * ceil_div_i(stages, sps) <= kComputeUnits / 8 && sps >= 16 ? 2 : 1;
+    return grid.per_xcd * slices.count <= kComputeUnits / 8 && slices.stages >= 16 ? 2 : 1;
 }
 
-int k_groups(const Problem &p, int t, int rows, int split)
+int k_groups(int t, const Grid &grid, const Slices &slices)
 {
-    return t == 8 ? k_groups_of_tile8(p, rows, split) : t == 3 || t == 5 ? k_groups_of_small_tile(p, t, rows, split) : 1;
+    return t == 8 ? k_groups_of_tile8(grid, slices) : t == 3 || t == 5 ? k_groups_of_small_tile(grid, slices) : 1;
 }
 
-// Estimated duration (microseconds) of the pipelined kernel with tile `t`, `rows` rows to a workgroup and `split` K slices.  A
+// Estimated duration (microseconds) of the pipelined kernel with tile `t`, the rows to a workgroup of `c`, and K slices.  A
 // workgroup walks its stages at a pace set by instruction issue and latency: alone on a compute unit it leaves most of it
 // idle, and co-resident workgroups slow each other down by less than their number.  What counts is the busiest compute unit of
 // the busiest XCD: a tile's slices share an XCD and the tiles are dealt out in eight equal ranges (tile_of_workgroup), so 50
@@ -119,6 +127,7 @@ struct Pace {
     double split, per_slice, per_mb;
 };
 constexpr Pace kPaces[] = {
+    {1, 256, {}, 1, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0},  // (has a formula of its own)
     {5, 64, {0.385, 0.574, 0.860}, 3, 4.3, 0.567, 0.070, 4.25, 1.0, 0.60, 0.105},
     {5, 80, {0.414, 0.669, 0.0}, 2, 5.0, 0.664, 0.097, 5.1, 0.2, 0.83, 0.200},
     {5, 96, {0.412, 0.705, 0.0}, 2, 5.1, 0.698, 0.102, 5.2, 0.2, 0.90, 0.180},
@@ -129,35 +138,42 @@ constexpr Pace kPaces[] = {
     {8, 112, {0.840, 1.370, 0.0}, 2, 5.2, 1.229, 0.361, 6.0, 2.5, 1.82, 0.082},
     {8, 128, {0.920, 1.500, 0.0}, 2, 5.2, 1.267, 0.354, 6.5, 2.4, 1.79, 0.086}};
 
-double estimate_us(const Problem &p, int t, int rows, int split, bool half)
+const Pace &pace_of(int t, int rows)
 {
-    const int bn = kTiles[t].bn;
-    const int tiles = ceil_div_i(p.M, rows) * ceil_div_i(p.N, bn);
-    const int stages = ceil_div_i(p.K, 64);
-    const int sps = ceil_div_i(stages, split);
-    const int slices = ceil_div_i(stages, sps);
-    const int wgs = tiles * slices;
-    const double n = ceil_div_i(tiles, 8) * slices / 32.0;  // workgroups per compute unit of the busiest XCD
-    if (t == 1)  // one workgroup per compute unit, whole rounds
-        return std::ceil(n - 1e-9) * (sps * 1.30 * (half ? 1.16 : 1.0) + 9.9);
-    // tile 8 in more workgroups than compute units and K slices: the exchange is not worth it
-    if (t == 8 && slices > 1 && wgs > kComputeUnits)
-        return 1e30;
     const Pace *c = kPaces;
     while (c->tile != t || c->rows != rows)
         ++c;
+    return *c;
+}
+
+double estimate_us(int t, const Pace &c, const Grid &grid, const Slices &slices, bool half)
+{
+    const int wgs = grid.tiles * slices.count;
+    const int busiest = grid.per_xcd * slices.count;  // workgroups of the busiest XCD, which has 32 compute units
+    if (t == 1)  // one workgroup per compute unit, whole rounds
+        return ceil_div_i(busiest, 32) * (slices.stages * 1.30 * (half ? 1.16 : 1.0) + 9.9);
+    // tile 8 in more workgroups than compute units and K slices: the exchange is not worth it
+    if (t == 8 && slices.count > 1 && wgs > kComputeUnits)
+        return 1e30;
     const double exchange =
-        slices > 1 ? c->split + slices * c->per_slice + wgs * (double)rows * bn * sizeof(float) / 1e6 * c->per_mb : 0.0;
-    const int groups = k_groups(p, t, rows, split);
+        slices.count > 1 ? c.split + slices.count * c.per_slice + wgs * (double)c.rows * kTiles[t].bn * sizeof(float) / 1e6 * c.per_mb : 0.0;
+    const int groups = k_groups(t, grid, slices);
     const double stage_scale = !half ? 1.0 : t == 5 ? (groups == 1 ? 1.25 : 1.22) : t == 3 ? 1.2 : 1.15;  // of the HALF variant
     if (groups == 2) {
-        const double full = n <= 0.5 ? 0.0 : n >= 1.0 ? 1.0 : 2.0 * n - 1.0;
-        return c->pair_fixed + ceil_div_i(sps, 2) * (c->pair + c->pair_full * full) * stage_scale * (n > 1.0 ? 2.0 : 1.0) + exchange;
+        const double full = busiest <= 16 ? 0.0 : busiest >= 32 ? 1.0 : busiest / 16.0 - 1.0;
+        return c.pair_fixed + ceil_div_i(slices.stages, 2) * (c.pair + c.pair_full * full) * stage_scale * (busiest > 32 ? 2.0 : 1.0) + exchange;
     }
-    const int full = (int)((n - 1e-9) / c->most);  // times that a compute unit is filled up, then the rest
-    const int rest = (int)std::ceil(n - full * c->most - 1e-9);
-    const double stage = full * c->resident[c->most - 1] + (rest > 0 ? c->resident[rest - 1] : 0.0);
-    return c->fixed + sps * stage * stage_scale + (t == 8 ? 1.5 * full : 0.0) + exchange;
+    const int full = (busiest - 1) / (32 * c.most);  // times that a compute unit is filled up, then the rest
+    const int rest = ceil_div_i(busiest - 32 * c.most * full, 32);
+    const double stage = full * c.resident[c.most - 1] + (rest > 0 ? c.resident[rest - 1] : 0.0);
+    return c.fixed + slices.stages * stage * stage_scale + (t == 8 ? 1.5 * full : 0.0) + exchange;
+}
+
+// Partial sums of one K slice, whatever the rows to a workgroup (other rows than the tile's own cover no more in all).
+size_t partial_bytes(const Problem &p, int t)
+{
+    const TileShape &ts = kTiles[t];
+    return (size_t)ceil_div_i(p.M, ts.bm) * ceil_div_i(p.N, ts.bn) * ts.bm * ts.bn * sizeof(float);
 }
 
 int mode_of(const Problem &p)
@@ -204,6 +220,15 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
     double best = 0.0;
     int best_tile = 3, best_split = 1, best_rows = kTiles[3].bm;
     const int stages = ceil_div_i(p.K, 64);
+    Slices offered[kMaxSplit];
+    int offers = 0;
+    for (int split = 1; split <= kMaxSplit && split <= stages / 2 + (stages < 2); ++split) {
+        if (split_given && split != (plan.split_k < stages ? plan.split_k : stages))
+            continue;
+        const Slices slices = slices_of(p, split);
+        if (offers == 0 || slices.count != offered[offers - 1].count)
+            offered[offers++] = slices;
+    }
     for (int t = 1; t <= kNumTiles; ++t) {
         if (kTiles[t].bm == 0 || (tile_given && t != plan.tile))
             continue;
@@ -211,30 +236,31 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
         // exchange: 128x8192x8192 in eight 68 us, on the 64x128 tile 34; 113x2432x14080 in four 44, 26; 95x3072x632 in sixteen 74, 16)
         if (t == 1 && !tile_given && p.M <= 128)
             continue;
-        int last_slices = 0;
-        for (int split = 1; split <= kMaxSplit && split <= stages / 2 + (stages < 2); ++split) {
-            if (split_given && split != (plan.split_k < stages ? plan.split_k : stages))
+        const Pace *paces[4];
+        Grid grids[4];
+        int candidates = 0;
+        for (int i = 0; i < 4; ++i) {
+            const int rows = row_choice(p, t, i, half);
+            if (rows == 0)
                 continue;
-            if (!split_given && split > 1 && !kTiles[t].may_split)
+            paces[candidates] = &pace_of(t, rows);
+            grids[candidates++] = grid_of(p, t, rows);
+        }
+        const size_t slice_bytes = partial_bytes(p, t);
+        for (int o = 0; o < offers; ++o) {
+            const Slices slices = offered[o];
+            if (!split_given && slices.count > 1 && !kTiles[t].may_split)
                 break;
-            const int slices = ceil_div_i(stages, ceil_div_i(stages, split));
-            if (slices == last_slices)
-                continue;
-            last_slices = slices;
             // (automatic slices stay within the static scratch block, so that gptq_w4a16_gemm_static runs the same plan)
-            PrefillPlan candidate = {t, slices, 0, false};
-            if (!split_given && slices > 1 && prefill_workspace_bytes(p, candidate) > GPTQ_STATIC_SCRATCH_BYTES)
-                continue;
-            for (int i = 0; i < 4; ++i) {
-                const int rows = row_choice(p, t, i, half);
-                if (rows == 0)
-                    continue;
-                const double us = estimate_us(p, t, rows, split, half);
+            if (!split_given && slices.count > 1 && kCounterBytes + slices.count * slice_bytes > GPTQ_STATIC_SCRATCH_BYTES)
+                break;
+            for (int i = 0; i < candidates; ++i) {
+                const double us = estimate_us(t, *paces[i], grids[i], slices, half);
                 if (best == 0.0 || us < best - 1e-9) {
                     best = us;
                     best_tile = t;
-                    best_split = slices;
-                    best_rows = rows;
+                    best_split = slices.count;
+                    best_rows = paces[i]->rows;
                 }
             }
         }
@@ -255,17 +281,15 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
 
 double prefill_estimate_us(const Problem &p, const PrefillPlan &plan)
 {
-    return estimate_us(p, plan.tile, plan.rows, plan.split_k, mode_of(p) == prefill::kGroupPerHalf);
+    return estimate_us(plan.tile, pace_of(plan.tile, plan.rows), grid_of(p, plan.tile, plan.rows), slices_of(p, plan.split_k),
+                       mode_of(p) == prefill::kGroupPerHalf);
 }
 
 size_t prefill_workspace_bytes(const Problem &p, const PrefillPlan &plan)
 {
     if (plan.split_k <= 1 || plan.serial || !prefill_tile_exists(plan.tile))
         return 0;
-    const TileShape &ts = kTiles[plan.tile];
-    // (other rows than the tile's own cover no more in all)
-    const size_t tiles = (size_t)ceil_div_i(p.M, ts.bm) * ceil_div_i(p.N, ts.bn);
-    return kCounterBytes + (size_t)plan.split_k * tiles * ts.bm * ts.bn * sizeof(float);
+    return kCounterBytes + plan.split_k * partial_bytes(p, plan.tile);
 }
 
 hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *workspace, hipStream_t stream)
@@ -296,11 +320,11 @@ hipError_t launch_prefill(const Problem &p, const PrefillPlan &plan, void *works
     if (plan.serial) {
         a.split_k = 1;
         a.serial_slices = plan.split_k;
-        a.serial_kw = k_groups(p, plan.tile, plan.rows, plan.split_k);
+        a.serial_kw = k_groups(plan.tile, grid_of(p, plan.tile, plan.rows), slices_of(p, plan.split_k));
         return prefill::launch_tile<5>(a, mode, 1, stream);
     }
     const bool pipelined = mode == prefill::kGroupPerStage || mode == prefill::kGroupPerHalf;
-    const int kw = pipelined ? k_groups(p, plan.tile, plan.rows, plan.split_k) : 1;
+    const int kw = pipelined ? k_groups(plan.tile, grid_of(p, plan.tile, plan.rows), slices_of(p, plan.split_k)) : 1;
     switch (plan.tile) {
     case 1: return prefill::launch_tile<1>(a, mode, 1, stream);
     case 3: return prefill::launch_tile<3>(a, mode, kw, stream);
