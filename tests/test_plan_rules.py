@@ -239,17 +239,16 @@ def test_planning_stays_short_where_several_kernels_are_weighed(B):
     there: a lone call waits for that on the host.  In units of the ring's search for 32 rows: 2.4 (searching twice, and every
     estimate from the problem's sizes on, it was 13)."""
     lib, out = B.load(), B.Plan()
-
-    def microseconds(M, K, N, request=None):
-        call = lambda: lib.gptq_w4a16_plan_query(M, K, N, 128, 0, request, ctypes.byref(out))  # noqa: E731
-        best = 1e9
-        for _ in range(60):
+    named = B.Plan(kernel=4, tile=64)  # (names everything: a call without a search)
+    calls = [(100, 8192, 10240, ctypes.byref(named)), (32, 4096, 4096, None), (56, 8192, 10240, None), (64, 24960, 17344, None), (77, 8192, 10240, None)]
+    best = [1e9] * len(calls)
+    for attempt in range(2000):  # (in turn, the shortest of each: whatever else the machine does; more turns where that did not do)
+        for i, (M, K, N, request) in enumerate(calls):
             start = time.perf_counter()
             for _ in range(100):
-                call()
-            best = min(best, time.perf_counter() - start)
-        return best * 1e4
-
-    call_alone = microseconds(100, 8192, 10240, ctypes.byref(B.Plan(kernel=4, tile=64)))  # (names everything: no search)
-    ring = microseconds(32, 4096, 4096) - call_alone
-    assert max(microseconds(*s) - call_alone for s in [(56, 8192, 10240), (64, 24960, 17344), (77, 8192, 10240)]) <= 5 * ring
+                lib.gptq_w4a16_plan_query(M, K, N, 128, 0, request, ctypes.byref(out))
+            best[i] = min(best[i], time.perf_counter() - start)
+        alone, ring, *searches = best
+        if attempt >= 40 and max(searches) - alone <= 5 * (ring - alone):
+            return
+    raise AssertionError([b * 1e4 for b in best])
