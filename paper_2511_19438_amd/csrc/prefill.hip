@@ -43,20 +43,36 @@ int ceil_div_i(int a, int b)
     return (a + b - 1) / b;
 }
 
+// Rows of the batch, and those that only fill up the last workgroups.
+int padded(const Problem &p, int rows)
+{
+    return ceil_div_i(p.M, rows) * rows;
+}
+
 // Rows number `i` of a workgroup of tile `t`, 0 if they are not for the problem: another number than the tile's own has to pad
-// the batch less - or, on tile 5, as little, which makes fewer and larger tiles; in the HALF variant from three of 96 rows on -
-// so that the scratch of slices is bounded by that of the tile's own rows.
+// the batch less - or, on tile 5, as little, which makes fewer and larger tiles -, so that the scratch of slices is bounded by
+// that of the tile's own rows.
 // us, the tiles' own rows -> these: M = 77 8192x10240 30.1 -> 25.6 (80x128), 8192x57344 97.0 -> 92.0 (80x256), 28672x8192
 // 61.7 -> 54.2 (80x128); 88x1664x25448 25.0 -> 18.4 (96x128); 100x4096x22016 39.5 -> 30.8 (112x128); 333x2752x6888 with groups
-// of 32 31.9 -> 25.1 (96x128, unsplit; the others in two slices and more); 266x8448x28344 237 -> 179.
-int row_choice(const Problem &p, int t, int i, bool half)
+// of 32 31.9 -> 25.1 (96x128, unsplit; the others in two slices and more); 266x8448x28344 237 -> 175.
+int row_choice(const Problem &p, int t, int i)
 {
     const int own = kTiles[t].bm;
     if (t != 5 && t != 8)
         return i == 0 ? own : 0;
     const int rows = kRows[t == 8][i];
-    const int padded = ceil_div_i(p.M, rows) * rows, padded_own = ceil_div_i(p.M, own) * own;
-    return i == 0 || padded < padded_own || (t == 5 && padded == padded_own && (!half || p.M > 192)) ? rows : 0;
+    return i == 0 || padded(p, rows) < padded(p, own) || (t == 5 && padded(p, rows) == padded(p, own)) ? rows : 0;
+}
+
+// What the estimate of rows that pad as little as the tile's own has to be multiplied with before it may choose them: the HALF
+// variant on two of 96 rows (129-192 rows) is estimated about 10 % low against the 96x256 tile.  150 layers with groups of 32
+// to 128 whose plan the 96 rows change at 129-192 rows: 41 are 8 % ahead by the estimate, all of them 7 % and more by the
+// clock (174x2496x15488 with groups of 32 30.0 -> 24.7 us, 161x1984x13680 27.1 -> 20.6, 190x1344x13704 18.6 -> 15.4); 24 of the
+// others lose 2-7 % (161x2912x48552 70.3, 75.7; 176x1024x47464 28.6, 30.3).  With the factor, 150 other layers whose plan the
+// 96 rows change: 1.16 times as fast (geometric mean), 4 % at least.
+double tie_factor(const Problem &p, int t, int rows, bool half)
+{
+    return half && p.M <= 192 && rows != kTiles[t].bm && padded(p, rows) == padded(p, kTiles[t].bm) ? 1.08 : 1.0;
 }
 
 // The output tiles of a tile shape, and how many of them the busiest XCD has (tile_of_workgroup).
@@ -238,11 +254,13 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
             continue;
         const Pace *paces[4];
         Grid grids[4];
+        double factors[4];
         int candidates = 0;
         for (int i = 0; i < 4; ++i) {
-            const int rows = row_choice(p, t, i, half);
+            const int rows = row_choice(p, t, i);
             if (rows == 0)
                 continue;
+            factors[candidates] = tie_factor(p, t, rows, half);
             paces[candidates] = &pace_of(t, rows);
             grids[candidates++] = grid_of(p, t, rows);
         }
@@ -255,7 +273,7 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
             if (!split_given && slices.count > 1 && kCounterBytes + slices.count * slice_bytes > GPTQ_STATIC_SCRATCH_BYTES)
                 break;
             for (int i = 0; i < candidates; ++i) {
-                const double us = estimate_us(t, *paces[i], grids[i], slices, half);
+                const double us = factors[i] * estimate_us(t, *paces[i], grids[i], slices, half);
                 if (best == 0.0 || us < best - 1e-9) {
                     best = us;
                     best_tile = t;
@@ -269,10 +287,11 @@ void prefill_make_plan(const Problem &p, PrefillPlan &plan)
         best_tile = tile_given ? plan.tile : 3;
         best_split = split_given ? plan.split_k : 1;
         best_rows = kTiles[best_tile].bm;
-        for (int i = 1; i < 4; ++i)
-            if (row_choice(p, best_tile, i, half) > 0 && ceil_div_i(p.M, row_choice(p, best_tile, i, half)) * row_choice(p, best_tile, i, half) <
-                                                       ceil_div_i(p.M, best_rows) * best_rows)
-                best_rows = row_choice(p, best_tile, i, half);
+        for (int i = 1; i < 4; ++i) {
+            const int rows = row_choice(p, best_tile, i);
+            if (rows > 0 && padded(p, rows) < padded(p, best_rows))
+                best_rows = rows;
+        }
     }
     plan.rows = best_rows;
     plan.tile = best_tile;

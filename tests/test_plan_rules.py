@@ -195,9 +195,10 @@ def test_small_batches_on_deep_narrow_layers(B):
 
 def test_small_tiles_of_small_groups(B):
     """The plan of the big-tile kernel with groups of 32 where it measured 8-15 % ahead of the one that another pace of two
-    wavefront groups would give."""
+    wavefront groups would give.  (174x2496x15488: 128x256 in two slices 30.0 us, which was ahead of the tiles there were then;
+    two of 96x128 unsplit 24.7.)"""
     plan = lambda M, K, N: (lambda pl: (pl.kernel, pl.tile, pl.split_k))(B.gptq_w4a16_plan_query(M, K, N, 32))  # noqa: E731
-    for problem, want in {(202, 7200, 2040): (5, 4), (174, 2496, 15488): (8, 2), (158, 2976, 10880): (5, 1), (378, 2112, 9064): (3, 1),
+    for problem, want in {(202, 7200, 2040): (5, 4), (174, 2496, 15488): (5, 1), (158, 2976, 10880): (5, 1), (378, 2112, 9064): (3, 1),
                           (558, 2368, 1352): (5, 2), (424, 5056, 1408): (5, 3), (678, 4480, 2048): (5, 4), (357, 3200, 10496): (3, 1)}.items():
         assert plan(*problem) == (2, *want), problem
 
