@@ -118,7 +118,7 @@ def test_default_dispatch_by_batch_size(lib):
     q = binding.gptq_w4a16_plan_query
     assert [q(M, 4096, 4096, 128).kernel for M in (1, 2, 3, 16, 32, 33, 64, 65, 128, 129, 2048)] == \
         [1, 3, 3, 3, 3, 4, 4, 2, 2, 2, 2]
-    # the mid-batch streaming kernel: 33-64 rows everywhere, 17-32 rows on wide or very deep layers, 65-128 rows
+    # the mid-batch streaming kernel's id: 33-64 rows everywhere, 17-32 rows on wide or very deep layers, 65-128 rows
     # where its 64-column tiles give half to all of the compute units a workgroup or K is deep
     assert [q(M, 4096, 22016, 128).kernel for M in (16, 17, 32, 33, 64, 65, 128)] == [3, 4, 4, 4, 4, 2, 2]
     assert [q(M, 4096, 12288, 128).kernel for M in (16, 17, 64, 65, 128, 129)] == [3, 4, 4, 4, 4, 2]

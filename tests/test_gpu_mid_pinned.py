@@ -22,6 +22,7 @@ def B():
                                                (33, 64, 8, 64, 1), (64, 576, 72, 192, 1), (63, 768, 136, 128, 1), (40, 1088, 200, 64, 1),
                                                (33, 6144, 136, 128, 1), (50, 6208, 136, 64, 1), (64, 8192, 8, 128, 1),
                                                (64, 4096, 264, 128, 2), (33, 3968, 136, 128, 2), (48, 1984, 200, 64, 2)])
+# (at 33-48 rows 64 columns of whole 128 k are the ring's: 33x6144 and 33x3968 run it, their 128 columns the pinned loop)
 # (and stages of a slice on both sides of where 128-column tiles take eight wavefronts on the plain loop)
 @pytest.mark.parametrize("tile", [64, 128])
 def test_pinned_loop_matches_the_oracle(B, M, K, N, group, split, tile):

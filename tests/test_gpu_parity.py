@@ -314,6 +314,7 @@ def test_small_batch_request_falls_back_when_unsupported(B):
 
 
 # ------------------------------------------------------------------ GEMM, mid-batch streaming MFMA kernel
+# (up to 32 rows, and in 64 columns up to 48, the ring runs in its place where K is a multiple of 128)
 
 MID_SHAPES = [
     # (K, N, group): several column tiles with a ragged last one; stage counts that are not multiples of three or of

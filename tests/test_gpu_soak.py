@@ -35,13 +35,22 @@ CASES = [
     (56, 4096, 1024, False, dict(kernel=4, tile=64, split_k=4)),
     (120, 2048, 544, False, dict(kernel=4, split_k=3)),
     (100, 2048, 544, False, dict(kernel=2, tile=3, split_k=2)),
-    (64, 4096, 4096, False, dict()),                              # mid-batch kernel, automatic plan with K slices
+    (64, 4096, 4096, False, dict()),                              # the ring on four row blocks, automatic plan with K slices
+    (40, 11008, 520, False, dict()),                              # ... on three, many slices
+    (77, 8192, 8192, False, dict()),                              # the big-tile kernel in the mid-batch kernel's place
     (8, 4096, 1024, True, dict()),                                # act-order lookups: one row tile
     (200, 4096, 520, True, dict()),                               # several: a counter per row and column tile
     (120, 2560, 520, False, dict(kernel=2, tile=8, split_k=2)),   # two wavefront groups, half of the threads exchange
     (96, 2560, 520, False, dict(kernel=2, tile=8, split_k=2)),    # the same on 96 rows
     (40, 4256, 136, False, dict(), 32),                           # big-tile kernel with a group row per half stage
     (70, 4256, 520, False, dict(kernel=2, tile=8, split_k=3), 32),
+    # the other rows to a workgroup, whose accumulators travel in batches of their own: 80, 96 and 112 of 128 columns, 80 and 112 of 256
+    (80, 3392, 5216, False, dict(kernel=2, tile=5), 64),
+    (96, 3904, 5152, False, dict(kernel=2, tile=5), 64),
+    (95, 1728, 5936, False, dict(kernel=2, tile=5), 96),
+    (97, 2912, 8464, False, dict(kernel=2, tile=5), 32),
+    (80, 1920, 520, False, dict(kernel=2, tile=8, split_k=3)),
+    (112, 1536, 520, False, dict(kernel=2, tile=8, split_k=2), 64),
 ]
 ROUNDS = 1500
 BUDGET_S = 25.0

@@ -52,19 +52,41 @@ def test_two_groups_give_the_bits_of_the_form_without_scratch(tile, M, K, N, gro
     assert np.all(np.abs(sliced.cpu().numpy().astype(np.float64) - ref) <= 2e-2 * np.maximum(1.0, np.abs(ref)))
 
 
-# other rows to a workgroup than the tile's own, where they pad less: 80, 96 and 112 rows of both widths, one group and two, whole
-# and half stages, a last half stage, rows on both sides of a tile's edge, with and without scratch for the slices
-@pytest.mark.parametrize("tile,M,K,N,group,split", [(5, 65, 1024, 136, 128, 1), (5, 80, 704, 1032, 64, 2), (5, 81, 1088, 288, 64, 1), (5, 96, 2112, 264, 32, 2),
-                                                    (5, 97, 640, 520, 128, 1), (5, 112, 1056, 136, 32, 1), (5, 333, 2112, 128, 64, 2),
-                                                    (8, 77, 1024, 264, 128, 1), (8, 80, 1120, 520, 32, 2), (8, 65, 512, 256, 128, 1),
-                                                    (8, 112, 2112, 288, 64, 2), (8, 97, 1056, 40, 32, 1), (8, 222, 448, 544, 64, 1)])
-def test_rows_that_fit_the_batch(tile, M, K, N, group, split):
+# Rows to a workgroup other than the tile's own, where they pad less (the first seven: the tile's own, which the estimate keeps on
+# narrow layers): tile, M, K, N, group, slices (0: as the plan has it), then the rows and the wavefront groups that the plan has for
+# it.  80, 96 and 112 rows of both widths, one group and two, whole and half stages - a check on the CPU holds the list to that -,
+# a last half stage, one row tile and several, rows on both sides of a tile's edge.
+ROWS_THAT_FIT = [
+    (5, 65, 1024, 136, 128, 1, 64, 2), (5, 80, 704, 1032, 64, 2, 64, 1), (5, 81, 1088, 288, 64, 1, 64, 2),
+    (5, 96, 2112, 264, 32, 2, 64, 2), (5, 97, 640, 520, 128, 1, 64, 1), (5, 112, 1056, 136, 32, 1, 64, 2),
+    (5, 333, 2112, 128, 64, 2, 64, 2), (8, 77, 1024, 264, 128, 1, 80, 2), (8, 80, 1120, 520, 32, 2, 80, 2),
+    (8, 65, 512, 256, 128, 1, 80, 1), (8, 112, 2112, 288, 64, 2, 112, 2), (8, 97, 1056, 40, 32, 1, 112, 2),
+    (8, 222, 448, 544, 64, 1, 80, 1), (5, 65, 2112, 8416, 64, 0, 80, 1), (5, 80, 3392, 5216, 64, 0, 80, 2),
+    (5, 66, 1696, 5136, 32, 0, 80, 1), (5, 79, 2912, 5216, 32, 0, 80, 2), (5, 160, 384, 10912, 128, 0, 80, 1),
+    (5, 129, 320, 10968, 160, 0, 80, 1), (5, 80, 1024, 17152, 64, 0, 80, 2), (5, 81, 2432, 8288, 64, 0, 96, 1),
+    (5, 96, 3904, 5152, 64, 0, 96, 2), (5, 95, 1728, 5936, 96, 0, 96, 1), (5, 96, 2016, 8480, 96, 0, 96, 2),
+    (5, 192, 1024, 11032, 32, 0, 96, 2), (5, 161, 384, 11424, 128, 0, 96, 1), (5, 333, 2752, 6888, 32, 0, 96, 2),
+    (5, 82, 992, 16424, 32, 0, 96, 2), (5, 97, 2496, 8640, 64, 0, 112, 1), (5, 112, 2944, 8384, 128, 0, 112, 2),
+    (5, 111, 2080, 8504, 160, 0, 112, 1), (5, 97, 2912, 8464, 32, 0, 112, 2), (5, 66, 384, 16576, 128, 0, 112, 1),
+    (5, 65, 320, 16568, 160, 0, 112, 1), (5, 224, 1024, 8224, 64, 0, 80, 2), (8, 65, 1152, 32, 64, 0, 80, 1),
+    (8, 80, 1920, 32, 128, 0, 80, 2), (8, 79, 960, 40, 160, 0, 80, 1), (8, 65, 2240, 40, 160, 0, 80, 2),
+    (8, 160, 576, 320, 64, 0, 80, 2), (8, 96, 1152, 32, 128, 2, 96, 2), (8, 96, 448, 32, 64, 0, 96, 1),
+    (8, 90, 1408, 32, 128, 0, 96, 2), (8, 95, 1344, 56, 96, 0, 96, 1), (8, 81, 1248, 56, 32, 0, 96, 2),
+    (8, 192, 1344, 264, 96, 0, 80, 1), (8, 190, 384, 32, 128, 3, 80, 1), (8, 97, 1344, 256, 64, 0, 112, 1),
+    (8, 112, 1536, 32, 64, 0, 112, 2), (8, 100, 1312, 264, 32, 0, 112, 1), (8, 111, 1280, 40, 32, 0, 112, 2),
+    (8, 224, 512, 264, 128, 0, 80, 1),
+]
+
+
+@pytest.mark.parametrize("tile,M,K,N,group,split,rows,groups", ROWS_THAT_FIT)
+def test_rows_that_fit_the_batch(tile, M, K, N, group, split, rows, groups):
     from paper_2511_19438_amd import binding as B
 
     case = workloads.make_case(M, K, N, group, seed=K + M)
     dev = {k: torch.from_numpy(case[k]).cuda() for k in ("x", "qweight", "qzeros", "scales")}
     plan = B.Plan(kernel=2, tile=tile, split_k=split)
-    assert B.gptq_w4a16_plan_query(M, K, N, group, False, plan).split_k == split
+    slices = B.gptq_w4a16_plan_query(M, K, N, group, False, plan).split_k
+    assert split in (0, slices)
     dev["x"][M - 1, K - 1] = float("inf")  # reaches its own row alone
     out, again = (torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
     for o in (out, again):
@@ -73,6 +95,12 @@ def test_rows_that_fit_the_batch(tile, M, K, N, group, split):
     assert np.all(np.abs(out[:M - 1].cpu().numpy().astype(np.float64) - ref) <= 2e-2 * np.maximum(1.0, np.abs(ref)))
     assert not np.isfinite(out[M - 1].float().cpu().numpy()).any()
     assert torch.equal(out.view(torch.int16), again.view(torch.int16))
+    if split == 0 and slices > 1:  # the same without scratch for the slices
+        with workspace(B, COUNTERS):
+            B.gptq_w4a16_gemm(dev["x"], dev["qweight"], dev["qzeros"], dev["scales"], None, again, group, plan)
+            torch.cuda.synchronize()
+        finite = out[:M - 1].view(torch.int16), again[:M - 1].view(torch.int16)
+        assert torch.equal(*finite) and not np.isfinite(again[M - 1].float().cpu().numpy()).any()
 
 
 # the big-tile kernel in the mid-batch kernel's place, and plans that a query gave: the same bits, also without scratch

@@ -108,9 +108,9 @@ def test_big_tile_half_stage_groups(B, tile, M, K, N, group, split_k):
     assert np.array_equal(first.view(np.uint16), run_gemm(B, case, group, plan).view(np.uint16))
 
 
-# ---- 128x256 tile: 96 rows where they fit the batch better, two wavefront groups per workgroup that halve its K slice ----
+# ---- 128x256 tile: 80 and 96 rows where they fit the batch better, two wavefront groups per workgroup that halve its K slice ----
 
-@pytest.mark.parametrize("M", [70, 96, 128, 130, 192])  # 96 rows; 96; 128; two tiles of 96, ragged and full
+@pytest.mark.parametrize("M", [70, 96, 128, 130, 192])  # 80 rows; 96; 128; two tiles of 80; three
 @pytest.mark.parametrize("K,N,group,split_k", [
     (512, 264, 128, 1),    # eight stages: one group
     (576, 264, 64, 1),     # nine: five and four
@@ -179,7 +179,8 @@ def test_an_infinity_survives_the_exchange_of_k_slices(B, kernel, tile, M, group
 
 @pytest.mark.parametrize("M,K,tile,split_k", [(40, 1280, 64, 3), (24, 1280, 128, 1), (64, 704, 64, 1), (90, 1344, 64, 2), (48, 2048, 0, 0)])
 def test_an_infinity_counts_once_where_wavefronts_have_uneven_shares(B, M, K, tile, split_k):
-    """Mid-batch kernel: a wavefront with fewer stages than the others goes through its last bodies without a stage."""
+    """Mid-batch kernel, and the ring in its place (40 and 24 rows): a wavefront with fewer stages than the others goes through
+    its last bodies without a stage."""
     N, group = 136, 64
     case = workloads.make_case(M, K, N, group, seed=M)
     plan = B.Plan(kernel=4, tile=tile, split_k=split_k)

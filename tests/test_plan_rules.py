@@ -1,6 +1,8 @@
 """Host logic of the automatic plans (no device is touched)."""
 import ctypes
+import os
 import random
+import subprocess
 import time
 
 import pytest
@@ -10,7 +12,7 @@ import pytest
 def B():
     from paper_2511_19438_amd import build
 
-    if not __import__("os").path.exists(build.LIB_PATH):
+    if not os.path.exists(build.LIB_PATH):
         build.build()
     from paper_2511_19438_amd import binding
 
@@ -253,3 +255,45 @@ def test_planning_stays_short_where_several_kernels_are_weighed(B):
         if attempt >= 40 and max(searches) - alone <= 5 * (ring - alone):
             return
     raise AssertionError([b * 1e4 for b in best])
+
+
+PLANNER = r"""
+#include "prefill.hip"
+namespace gptq {
+namespace prefill {
+#define NO_DEVICE(tile) template <> hipError_t launch_tile<tile>(const Args &, int, int, hipStream_t) { return hipErrorNoDevice; }
+%s
+}  // namespace prefill
+}  // namespace gptq
+extern "C" __attribute__((visibility("default"))) void plan(int M, int K, int N, int group, int tile, int split, int *out)
+{
+    gptq::Problem p = {};
+    p.M = M, p.K = K, p.N = N, p.group_size = group;
+    gptq::PrefillPlan plan = {tile, split, 0, false};
+    gptq::prefill_make_plan(p, plan);
+    out[0] = plan.rows;
+    out[1] = gptq::k_groups(plan.tile, gptq::grid_of(p, plan.tile, plan.rows), gptq::slices_of(p, plan.split_k));
+    out[2] = gptq::mode_of(p) == gptq::prefill::kGroupPerHalf;
+}
+"""
+
+
+def test_the_problems_of_the_gpu_tests_get_the_rows_that_they_are_for(tmp_path):
+    """The rows to a workgroup and the wavefront groups are no part of a plan query: the host code of the big-tile kernel on its own."""
+    from paper_2511_19438_amd import build
+    from tests.test_gpu_two_groups import ROWS_THAT_FIT
+
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no hipcc")
+    source, lib = tmp_path / "planner.hip", tmp_path / "planner.so"
+    source.write_text(PLANNER % "\n".join(f"NO_DEVICE({t})" for t in build.PREFILL_TILES))
+    flags = [f for f in build.COMMON if f != "-fvisibility=hidden"]
+    proc = subprocess.run([build.HIPCC, *flags, "--cuda-host-only", "-shared", str(source), "-o", str(lib)], capture_output=True, text=True)
+    assert proc.returncode == 0, proc.stderr[-2000:]
+    plan, out = ctypes.CDLL(str(lib)).plan, (ctypes.c_int * 3)()
+    seen = set()
+    for tile, M, K, N, group, split, rows, groups in ROWS_THAT_FIT:
+        plan(M, K, N, group, tile, split, out)
+        assert tuple(out)[:2] == (rows, groups), (tile, M, K, N, group, split)
+        seen.add((tile, rows, groups, bool(out[2])))
+    assert seen >= {(t, r, g, h) for t in (5, 8) for r in (80, 96, 112) for g in (1, 2) for h in (False, True)}
