@@ -74,12 +74,13 @@ enum gptq_status {
  * MFMA kernel with the same split-K decomposition (when the format allows: no g_idx,
  * group_size % 128 == 0 or 64 / 32; otherwise the vector kernel up to M = 8, or 16 on deep
  * narrow layers, which also keeps up to four rows where it measured faster with a K that is
- * no multiple of 128), 33 <= M <= 64
- * (and 17-32 or 65-128 rows on the layer shapes where it measured faster) a mid-batch MFMA
- * kernel in which every wavefront streams its own share of the K slice (no g_idx, K and
- * group_size multiples of 64; up to 48 rows, and up to 64 on narrow layers, the small-batch kernel runs in its place, under
- * its id, if K % 128 == 0, from 49 rows on the big-tile kernel where it measured faster, likewise), larger M the big-tile fp16 MFMA kernel (with K slices where
- * the output tiles alone would not fill the chip).
+ * no multiple of 128), larger M the big-tile fp16 MFMA kernel (with K slices where the output
+ * tiles alone would not fill the chip).  Between them stands the id of a mid-batch MFMA kernel in
+ * which every wavefront streams its own share of the K slice (no g_idx, K and group_size multiples
+ * of 64): 33 <= M <= 64, 17-32 rows on wide or deep layers, 65-128 rows on many layers.  Under it
+ * the small-batch kernel runs up to 48 rows, and up to 64 on narrow layers, if K % 128 == 0, the
+ * big-tile kernel from 49 rows on where it measured faster and always above 96, the mid-batch
+ * kernel itself elsewhere.
  * With g_idx, M >= 2 and K % 32 == 0 run a variant of the small-batch kernel that looks every k up in
  * a table of all groups in LDS (as long as that fits: up to 606 groups, 630 at up to 384 rows; not large batches of a K under 640); plan
  * queries report it as kernel 1 (M <= 16) or 2 with 64-column tiles and the flag GPTQ_ACT_LOOKUP, and such
@@ -129,7 +130,8 @@ typedef struct gptq_w4a16_plan {
                         3 small-batch MFMA kernel (M <= 128, processed 64 rows at a time; no g_idx,
                         group_size % 128 == 0, or 64 or 32 with M <= 32; else falls back),
                         4 mid-batch streaming MFMA kernel (M <= 128; no g_idx, K % 64 == 0, group_size % 64 == 0;
-                        else falls back) */
+                        else falls back).  With 0 the number of slices and the tile below hold for the kernel that
+                        the library chooses, a tile that it does not have counting as auto */
     int split_k;     /* number of K slices (all four kernels; the big-tile kernel splits by itself on every tile
                         but 256x256); 0 auto */
     int tile;        /* vector kernel: columns per workgroup (16, 32, 64, 128 or 256);
@@ -247,7 +249,8 @@ GPTQ_API int gptq_w4a16_unpack(const void *qweight, void *q_out, const void *qze
  * for its 256-column workgroups), and the big-tile kernel, under their own ids and the mid-batch kernel's.  Where it cannot be had, as above or on a workspace that
  * is too small, every workgroup walks the slices itself, one after the other, and adds them in the same order: the
  * result is the same, the call is slower by up to as many times as it has slices, and a graph that captured it
- * stays so.  Such a call needs no scratch from 17 rows on, and up to 16 rows what the vector kernel takes for the
+ * stays so (77 rows of 8192 x 10240: three slices 26 us, walked 60; this and other calls of 49-128 rows made no slices
+ * before the big-tile kernel ran under the mid-batch kernel's id, and took 30 us on any workspace).  Such a call needs no scratch from 17 rows on, and up to 16 rows what the vector kernel takes for the
  * problem.  A number of slices that an explicit plan names is never given up.  A graph replay and an eager call that use different
  * blocks do not share arrival counters; two pieces of work that share one block must not overlap in time.
  * gptq_w4a16_set_workspace() hands over caller-owned device memory (256-byte aligned, at least

@@ -16,7 +16,7 @@
 //   * v_mfma_f32_16x16x32_f16.  What bounds large products is the power that the matrix pipe draws (the clock falls to 1.65
 //     GHz under it), and this form draws less for the same product than 32x32x16, whose accumulators pass twice as often: an
 //     MFMA-only loop on N(0,1) activations and dequantised weights 1.92 PFLOP/s against 1.69, with two vector instructions
-//     beside each 32 k operations 1.77 against 1.59.  Blocks of 16 rows also pad a ragged batch less.  One step with the
+//     beside each 32 k operations 1.77 against 1.59 (a probe of both forms; probe.hip's has the 32x32x16 form alone).  Blocks of 16 rows also pad a ragged batch less.  One step with the
 //     inline-assembly DMA and LDS reads below (through the builtin the compiler emptied the pipeline of loads once per
 //     stage, in front of its first LDS read): 2048 rows through the four 8192-wide layers 2960 -> 2668 us, 512 rows through
 //     the four 4096-wide ones 254 -> 230, 333x2752x6888 with groups of 32 31.5 -> 29.5.
